@@ -1003,21 +1003,6 @@ __global__ __launch_bounds__(32 * (D / 16)) void combine_kernel(const AttnParams
     dst[1] = ow.u[1];
 }
 
-// Compute units of the current device (each host thread remembers the last device it asked about).
-int device_compute_units(int *device = nullptr) {
-    static thread_local int cached_dev = -1, cached_cus = 0;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (dev != cached_dev) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        cached_cus = cus;
-        cached_dev = dev;
-    }
-    if (device != nullptr) *device = dev;
-    return cached_cus;
-}
-
 template <int D>
 int64_t workspace_bytes_for(int cus) { return int64_t(2) * cus * slot_floats<D>() * int64_t(sizeof(float)); }
 
@@ -1028,7 +1013,7 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     static std::atomic<uint64_t> attr_set{0};
     const void *kern = reinterpret_cast<const void *>(&attention_kernel<D, NB>);
     int dev = 0;
-    const int cus = device_compute_units(&dev);
+    const int cus = lp::device_compute_units(&dev);
     const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
     if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
         hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Tile<D, NB>::kBytes);
@@ -1092,7 +1077,7 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 extern "C" int64_t lp_attention_workspace_size(int32_t head_dim) {
     if (head_dim != 64 && head_dim != 128) return LP_ERR_UNSUPPORTED;
-    const int cus = device_compute_units();
+    const int cus = lp::device_compute_units();
     if (cus <= 0) return LP_ERR_HIP;
     return head_dim == 128 ? workspace_bytes_for<128>(cus) : workspace_bytes_for<64>(cus);
 }
@@ -1214,7 +1199,7 @@ extern "C" int lp_attention_static(const void *q, const void *k, const void *v, 
                                    float scale, void *stream) {
     const int chk = attention_check(q, k, v, o, 1, n_tokens, heads, head_dim, 0, stride_tok, stride_head, nullptr, 0);
     if (chk != LP_OK) return chk == kNothingToDo ? LP_OK : chk;
-    const int cus = device_compute_units();
+    const int cus = lp::device_compute_units();
     if (cus <= 0) return LP_ERR_HIP;
     // the slots of every compute unit must fit the fixed array
     const int64_t need = head_dim == 128 ? workspace_bytes_for<128>(cus) : workspace_bytes_for<64>(cus);

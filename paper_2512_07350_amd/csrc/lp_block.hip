@@ -9,20 +9,24 @@
 // The paper leaves the block's internals open (Sec. 5.1: 30 DiT blocks whose atomic units are
 // the patches of Sec. 3.1); the form taken is stated in include/lp.h.
 //
-// The product is computed TRANSPOSED, C^T[feature, token] = W . X^T with bf16 MFMA 32x32x16
+// The product is computed TRANSPOSED, C^T[feature, token] = W . X^T with bf16 MFMA 16x16x32
 // (A = rows of W, B = rows of x, both k-contiguous, both streamed global -> LDS without
-// passing through registers): in the accumulator layout a lane then holds 64 features of ONE
-// token, so the sum of squares of a head is an in-lane sum plus one exchange with the other
-// half-wave, and the two elements of a rotary pair sit in neighbouring registers.
+// passing through registers): in the accumulator layout a lane then holds, for ONE token, four
+// consecutive features of every 16-feature block, so the sum of squares of a head is an in-lane
+// sum plus two exchanges inside the wavefront, and the two elements of a rotary pair sit in
+// neighbouring registers.  16x16x32 and not 32x32x16: the part is limited by power, and a loop of
+// nothing but products on N(0,1) operands sustains 2077 TFLOP/s with the former, 1837 with the
+// latter (2480 and 2460 on zeros).
 //
-// Work decomposition.  A workgroup (8 wavefronts, two per SIMD) owns 256 features x 256
-// tokens; a wavefront 128 features (one head of 128, or two of 64) x 64 tokens: 4 x 2 MFMA
-// blocks, 128 accumulator registers, 6 LDS operand reads per 8 products.  k advances in tiles
-// of 64 through two LDS stages (W tile + x tile, 64 KB per stage).
+// Work decomposition.  A workgroup owns a tile of features x tokens (struct Tiling: the sizes, how
+// its wavefronts share it, and the LDS stages); k advances in tiles of 64.  Which tiling a
+// call runs, and how the tiles that do not fill a round of the compute units are cut, is chosen
+// from the sizes in pick_plan.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
 #include <cmath>
+#include <type_traits>
 
 #include "lp_internal.h"
 
@@ -30,7 +34,6 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -38,16 +41,9 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 #define LP_LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
 
-constexpr int kTF = 256;                 // features per workgroup
-constexpr int kTT = 256;                 // tokens per workgroup
 constexpr int kBK = 64;                  // k per LDS stage
 constexpr int kRowBytes = kBK * 2;       // one tile row: 64 bf16
-constexpr int kTileBytes = 256 * kRowBytes;      // W tile or x tile: 32 KB
-constexpr int kStageBytes = 2 * kTileBytes;      // W tile then x tile
-constexpr int kStagesG = 2;
-constexpr int kLdsBytes = kStagesG * kStageBytes;
-constexpr int kThreadsG = 512;
-constexpr int kPanel = 4;                // token tiles per panel of the tile order
+constexpr int kPanel = 8;                // token tiles per panel of the tile order
 constexpr int kMaxPairs = 64;            // rotary pairs per head (head_dim <= 128)
 
 // floor(n / d) for 0 <= n < 2^31 as (n * magic) >> shift (64-bit product); see make_fastdiv.
@@ -85,11 +81,10 @@ struct GemmArgs {
     const float *gain[2];        // qkv: gain_q, gain_k [heads, head_dim]
     int32_t n, d_in, d_out;
     int32_t heads;               // qkv: heads; d_out = 3 * heads * head_dim
-    int32_t n_ftiles, n_ttiles;
+    int32_t n_ftiles, n_ttiles;  // tiles of the call's tiling
+    int32_t whole;               // workgroups [0, whole) take one tile each; the tiles from there on are cut in smaller ones
     RopeArgs rope;
 };
-
-__device__ __forceinline__ float other_half(float x) { return __shfl_xor(x, 32, 64); }
 
 __device__ __forceinline__ bf16x2 to_bf16x2(float lo, float hi) {
     f32x2 f = {lo, hi};
@@ -103,7 +98,7 @@ __device__ __forceinline__ V lds_load(uint32_t addr) {
 
 // granule XOR mask of a tile row (reader and writer use the same function): with 128-byte rows
 // the 16-byte granule g of row r lives at position g ^ swz(r), which makes the ds_read_b128 of
-// 32 rows x one granule free of bank conflicts
+// 16 rows x 4 granules free of bank conflicts (SQ_LDS_BANK_CONFLICT: 1.6 % of the LDS cycles)
 __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 
 // One wave-wide global -> LDS load of 1024 bytes (see lp_attention.hip for why this is an
@@ -115,8 +110,6 @@ __device__ __forceinline__ void load_to_lds_16(__amdgpu_buffer_rsrc_t rsrc, uint
                  : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
                  : "memory", "m0");
 }
-
-__device__ __forceinline__ void wait_all_tile_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Workgroup ids are dealt round robin to the 8 XCDs; remap so that each XCD owns a contiguous
 // stretch of the tile order (see the panels in gemm_kernel) and what neighbouring tiles share
@@ -131,248 +124,385 @@ __device__ __forceinline__ uint32_t logical_workgroup(uint32_t b, uint32_t n_wg)
 // program order, and the LDS reads written between them stay between them.  The compiler does
 // not know what the statement is and adds no wait states after it: settle() stands between the
 // last product and the first vector instruction that reads an accumulator.
-__device__ __forceinline__ void mfma(f32x16 &acc, const bf16x8 &a, const bf16x8 &b) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-}
-__device__ __forceinline__ void settle(f32x16 (&acc)[4][2]) {
-    asm volatile("s_nop 15\n\ts_nop 7");
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) asm volatile("" : "+v"(acc[mb][nb]));
+__device__ __forceinline__ void mfma(f32x4 &acc, const bf16x8 &a, const bf16x8 &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
 
-// Writes 32 result rows (tokens) of 128 features, rounded to bf16, to dst + r * row_stride
-// (r < rows_valid).  A lane holds, for token `col`, features 32 mb + 8 (i / 4) + 4 half + i % 4;
-// the 8-byte pieces pass through 4 KB of the wave's LDS (64 features at a time, granules XORed
-// with the row) and leave as whole 128-byte lines.
-__device__ __forceinline__ void store_rows(uint32_t out_lds, const float (&val)[4][16], __bf16 *dst, int64_t row_stride,
-                                           int rows_valid, int lane) {
-    const int col = lane % 32, half = lane / 32;
-#pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll
-        for (int mbl = 0; mbl < 2; ++mbl)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float (&x)[16] = val[2 * pass + mbl];
-                union { u32x2 u; bf16x2 p[2]; } ow;
-                ow.p[0] = to_bf16x2(x[4 * g + 0], x[4 * g + 1]);
-                ow.p[1] = to_bf16x2(x[4 * g + 2], x[4 * g + 3]);
-                *LP_LDS_PTR(u32x2, uintptr_t(out_lds + col * 128 + 16 * ((4 * mbl + g) ^ (col & 7)) + 8 * half)) = ow.u;
-            }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = lane / 8 + 8 * j, gran = lane % 8;
-            const u32x4 u = lds_load<u32x4>(out_lds + r * 128 + 16 * (gran ^ (r & 7)));
-            if (r < rows_valid) *reinterpret_cast<u32x4 *>(dst + r * row_stride + 64 * pass + 8 * gran) = u;
-        }
+// All of this wave's LDS reads have returned and at most PENDING of its global -> LDS loads are
+// still in flight; then the workgroup's barrier.
+template <int PENDING>
+__device__ __forceinline__ void stage_barrier() {
+    static_assert(PENDING >= 0 && PENDING < 64, "vmcnt range");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PENDING) : "memory");
+}
+
+// f(integral_constant<int, I>) for I = FROM .. TO-1
+template <int FROM, int TO, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (FROM < TO) {
+        f(std::integral_constant<int, FROM>{});
+        static_for<FROM + 1, TO>(f);
     }
 }
 
-// Per-head RMS normalisation and rotary encoding of the 128 features x 32 tokens a wave holds
-// in val (layout as store_rows).  HD = 128: the 128 features are one head; HD = 64: two heads
-// (blocks 0-1 and 2-3).  gain points at the first of these features; tk is this lane's token.
-// The rotary table sits in LDS at rope_lds: float4 per pair.
-template <int HD>
-__device__ __forceinline__ void norm_rope(float (&val)[4][16], const float *gain, const RopeArgs &r, uint32_t rope_lds,
-                                          uint32_t tk, int half) {
-    // coordinates of this lane's token
-    const uint32_t t = fastdiv(tk, r.hw);
-    const uint32_t rem = tk - t * r.hw.d;
-    const uint32_t h = fastdiv(rem, r.w);
-    const float pt = float(int32_t(t) + r.off[0]), ph = float(int32_t(h) + r.off[1]),
-                pw = float(int32_t(rem - h * r.w.d) + r.off[2]);
-    constexpr int kHeads = 128 / HD, kBlocks = HD / 32;
-#pragma unroll
-    for (int hh = 0; hh < kHeads; ++hh) {
-        float ss = 0.0f;
-#pragma unroll
-        for (int b = 0; b < kBlocks; ++b)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) ss += val[hh * kBlocks + b][i] * val[hh * kBlocks + b][i];
-        ss += other_half(ss);
-        const float inv = 1.0f / sqrtf(ss * (1.0f / float(HD)) + r.eps);
-#pragma unroll
-        for (int b = 0; b < kBlocks; ++b) {
-            const int mb = hh * kBlocks + b;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                // features 32 mb + 8 g + 4 half + 0..3 of the wave's 128: two rotary pairs
-                const int f_local = 32 * b + 8 * g + 4 * half;             // inside the head
-                const float4 gn = *reinterpret_cast<const float4 *>(gain + hh * HD + f_local);
-                const float gv[4] = {gn.x, gn.y, gn.z, gn.w};
-#pragma unroll
-                for (int pr = 0; pr < 2; ++pr) {
-                    const f32x4 tb = lds_load<f32x4>(rope_lds + 16 * (f_local / 2 + pr));
-                    float turns = pt * tb.x + ph * tb.y + pw * tb.z;
-                    turns = turns - floorf(turns);
-                    const float c = __builtin_amdgcn_cosf(turns), s = __builtin_amdgcn_sinf(turns);
-                    const float a = val[mb][4 * g + 2 * pr] * inv * gv[2 * pr];
-                    const float bb = val[mb][4 * g + 2 * pr + 1] * inv * gv[2 * pr + 1];
-                    val[mb][4 * g + 2 * pr] = a * c - bb * s;
-                    val[mb][4 * g + 2 * pr + 1] = a * s + bb * c;
-                }
-            }
-        }
-    }
-}
+// The tile of one workgroup: WF x WT wavefronts, each with FB x TB blocks of 16 features x 16
+// tokens, and S LDS stages of one k-tile (W rows, then x rows).
+template <int WF_, int WT_, int FB_, int TB_, int S_>
+struct Tiling {
+    static constexpr int WF = WF_, WT = WT_, FB = FB_, TB = TB_, S = S_;
+    static constexpr int kWaves = WF * WT, kThreads = 64 * kWaves;
+    static constexpr int kF = WF * FB * 16, kT = WT * TB * 16;            // features and tokens of the tile
+    static constexpr int kWBytes = kF * kRowBytes, kStage = kWBytes + kT * kRowBytes;
+    static constexpr int kRing = S * kStage;
+    static constexpr int kOut = kWaves * 16 * FB * 32;                    // result staging, see store_tile
+    // + rotary table + sums of squares + per wave the bias and gain of its features
+    static constexpr int kEpilogue = kOut + kMaxPairs * 16 + kWaves * TB * 16 * 4 + kWaves * FB * 16 * 8;
+    static constexpr int kLds = kRing > kEpilogue ? kRing : kEpilogue;
+    static constexpr int FH = FB / 2;                                     // blocks in a lo (or hi) half of a wave's features
+    // wave-wide loads (8 rows each) per wave and stage: X = x rows and the lo halves of W, Y = the hi halves
+    static constexpr int kLoadsW = kF / 16 / kWaves, kLoadsX = kT / 8 / kWaves;
+    static constexpr int X = kLoadsX + kLoadsW, Y = kLoadsW;
+    static_assert(kWaves % 2 == 0 && kF % (16 * kWaves) == 0 && kT % (8 * kWaves) == 0 && FB % 2 == 0, "whole loads");
+};
 
-// QKV = true: the epilogue cuts the features into q | k | v sections of heads * HD, normalises
-// and rotates q and k.  QKV = false: plain y = x W^T + b.
-template <bool QKV, int HD>
-__global__ __launch_bounds__(kThreadsG) void gemm_kernel(const GemmArgs a) {
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const uint32_t lds0 = uint32_t(uintptr_t(LP_LDS_PTR(unsigned char, smem)));
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int lane = tid % 64, col = lane % 32, half = lane / 32;
-    const int fw = wave / 4, tq = wave % 4;              // feature half, token quarter of the workgroup tile
-
-    // Tiles are ordered in panels of kPanel token tiles, feature tile by feature tile inside a
-    // panel: the 32 workgroups an XCD runs at a time then cover 8 feature tiles x 4 token tiles
-    // and share their W and x rows through its L2 (12 operand tiles fetched for 32 products).
-    const uint32_t lw = logical_workgroup(blockIdx.x, gridDim.x);
-    const int panel_tiles = kPanel * a.n_ftiles;
-    const int panel = int(lw) / panel_tiles, in_panel = int(lw) - panel * panel_tiles;
-    const int panel_h = min(kPanel, a.n_ttiles - panel * kPanel);
-    const int ftile = in_panel / panel_h, ttile = panel * kPanel + in_panel - ftile * panel_h;
-    const int f0 = ftile * kTF, t0 = ttile * kTT;
+// acc[f][t] += W[f0 + ..] . x[t0 + ..]^T over all of k.
+//
+// What bounds it.  A k-tile is kStage bytes arriving in LDS against 2 kF kT 64 flop.  With a stage
+// held until all its operands have been read and its successor sent for only then, a load had
+// one tile's products to arrive in and did not make it (1131 TFLOP/s at 13230 x 5120 -> 15360; 1460
+// without the loads).  Here a wave takes a stage's operands into registers half a tile ahead of
+// their products, in two phases: while the products of the lo halves of its features run it reads
+// the hi halves, while those of the hi halves run it reads the next tile's x and lo operands.
+// Each half of a stage is refilled as soon as the barrier after its read has passed, so a load has one
+// and a half tiles' products to arrive in and no wait ever drains the queue.  A barrier stands
+// PRE products into its phase: the waves meet with products still in the pipeline.
+// 1131 -> 1380 TFLOP/s (32x32x16 products: 1312; 256 x 256 tile, same box); matrix pipeline busy
+// 76 % of the cycles, at a clock that the power limit holds to 1.65 GHz.
+template <typename C>
+__device__ __forceinline__ void product(uint32_t lds0, const GemmArgs &a, int f0, int t0, int wave, int lane,
+                                        f32x4 (&acc)[C::FB][C::TB]) {
+    constexpr int FB = C::FB, TB = C::TB, FH = C::FH, S = C::S, W = C::kWaves;
+    const int col = lane % 16, quad = lane / 16;
+    const int fw = wave / C::WT, tw = wave % C::WT;
 
     // raw buffers over the rows this tile can touch (rows past the end read as zeros)
-    const int64_t w_rows = min(int64_t(kTF), int64_t(a.d_out) - f0), x_rows = min(int64_t(kTT), int64_t(a.n) - t0);
+    const int64_t w_rows = min(int64_t(C::kF), int64_t(a.d_out) - f0), x_rows = min(int64_t(C::kT), int64_t(a.n) - t0);
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<__bf16 *>(a.w + int64_t(f0) * a.d_in), 0, int(w_rows * a.d_in * 2), 0x00020000);
     const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<__bf16 *>(a.x + int64_t(t0) * a.d_in), 0, int(x_rows * a.d_in * 2), 0x00020000);
 
-    // this lane's part of the tile traffic: 4 wave-wide loads per operand tile and stage
-    uint32_t voff[4], ld_dst[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int instr = wave + 8 * i;                  // 32 instructions of 8 rows per operand tile
-        const int row = instr * 8 + lane / 8, gran = lane % 8;
-        ld_dst[i] = instr * 1024;
-        voff[i] = uint32_t(row) * uint32_t(a.d_in * 2) + 16 * (gran ^ swz(row));
-    }
-    auto issue = [&](int kt, uint32_t stage_off) {
-        const uint32_t soff = uint32_t(kt) * kRowBytes;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + stage_off + ld_dst[i]);
-            load_to_lds_16(w_rsrc, dst, voff[i], soff);
-            load_to_lds_16(x_rsrc, dst + kTileBytes, voff[i], soff);
-        }
+    // A wave-wide load moves a group of 8 rows x 128 bytes.  All of a wave's groups have the parity of the
+    // wave, so one swizzled lane offset serves them all; the group and the k-tile are scalar offsets.
+    const uint32_t row_bytes = uint32_t(a.d_in) * 2;
+    const uint32_t voff = uint32_t(lane / 8) * row_bytes + 16 * ((lane % 8) ^ swz((wave & 1) * 8 + lane / 8));
+    constexpr int kHalfGroups = FH * 2;                  // groups in the lo (or hi) half of a wave row's features
+    auto lo_group = [&](int i) { const int g = wave + i * W; return (g / kHalfGroups) * 2 * kHalfGroups + g % kHalfGroups; };
+    auto load = [&](const __amdgpu_buffer_rsrc_t &rsrc, int group, int kt, uint32_t lds) {
+        load_to_lds_16(rsrc, __builtin_amdgcn_readfirstlane(lds0 + lds + group * 1024), voff,
+                       __builtin_amdgcn_readfirstlane(uint32_t(kt) * kRowBytes + uint32_t(group) * 8 * row_bytes));
     };
+    auto load_x = [&](int i, int kt, uint32_t stage) {
+        if (i < C::kLoadsX) load(x_rsrc, wave + i * W, kt, stage + C::kWBytes);
+        else load(w_rsrc, lo_group(i - C::kLoadsX), kt, stage);
+    };
+    auto load_y = [&](int i, int kt, uint32_t stage) { load(w_rsrc, lo_group(i) + kHalfGroups, kt, stage); };
 
-    // LDS operand addresses in stage 0: A = W rows (4 blocks of 32 features), B = x rows (2 blocks of 32 tokens)
-    uint32_t a_addr[4], b_addr[2];
+    // operand addresses of the two k-steps of 32 in the stage being read
+    uint32_t w_addr[2], x_addr[2];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-        const int row = fw * 128 + mb * 32 + col;
-        a_addr[mb] = lds0 + row * kRowBytes + 16 * (half ^ swz(row));       // granule 2 s + half is (2 s) ^ ... below
+    for (int s = 0; s < 2; ++s) {
+        w_addr[s] = lds0 + (fw * FB * 16 + col) * kRowBytes + 16 * ((4 * s + quad) ^ swz(col));
+        x_addr[s] = lds0 + C::kWBytes + (tw * TB * 16 + col) * kRowBytes + 16 * ((4 * s + quad) ^ swz(col));
     }
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const int row = tq * 64 + nb * 32 + col;
-        b_addr[nb] = lds0 + kTileBytes + row * kRowBytes + 16 * (half ^ swz(row));
-    }
+    bf16x8 lo[FH][2], hi[FH][2], xop[TB][2];
+    auto read_lo = [&](int m, int s) { lo[m][s] = lds_load<bf16x8>(w_addr[s] + m * 16 * kRowBytes); };
+    auto read_hi = [&](int m, int s) { hi[m][s] = lds_load<bf16x8>(w_addr[s] + (FH + m) * 16 * kRowBytes); };
+    auto read_x = [&](int t, int s) { xop[t][s] = lds_load<bf16x8>(x_addr[s] + t * 16 * kRowBytes); };
 
-    f32x16 acc[4][2];
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
+    for (int f = 0; f < FB; ++f)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[mb][nb][i] = 0.0f;
+        for (int t = 0; t < TB; ++t) acc[f][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
     const int n_kt = a.d_in / kBK;
-    issue(0, 0);
-    for (int kt = 0; kt < n_kt; ++kt) {
-        const uint32_t stage = (kt & 1) * kStageBytes;
-        wait_all_tile_loads();
-        __syncthreads();          // stage kt has landed for everyone; everyone has left the other stage
-        if (kt + 1 < n_kt) issue(kt + 1, kStageBytes - stage);
-        // Operands of k-step s+1 are fetched from LDS while the products of step s run: two
-        // register sets, one fetch after each of the first six products of a step.  The products
-        // are assembly statements so that this order stands (left to the scheduler, an operand is
-        // fetched right before its two products and the wave sits out the LDS latency every time);
-        // LDS reads keep their place between such statements.
-        // granule (2 s + half) ^ swz(row) = (half ^ swz(row)) ^ (2 s): a step flips bits 1-2 of the granule index
-        bf16x8 aop[2][4], bop[2][2];
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) bop[0][nb] = lds_load<bf16x8>(b_addr[nb] + stage);
+    for (int p = 0; p < S; ++p) {
+        if (p < n_kt) {
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) aop[0][mb] = lds_load<bf16x8>(a_addr[mb] + stage);
+            for (int i = 0; i < C::X; ++i) load_x(i, p, p * C::kStage);
 #pragma unroll
-        for (int s = 0; s < kBK / 16; ++s) {
-            const int cur = s & 1, nxt = cur ^ 1;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int mb = i / 2, nb = i % 2;
-                mfma(acc[mb][nb], aop[cur][mb], bop[cur][nb]);
-                if (s + 1 < kBK / 16) {
-                    if (i < 2) bop[nxt][i] = lds_load<bf16x8>((b_addr[i] + stage) ^ uint32_t(32 * (s + 1)));
-                    else if (i < 6) aop[nxt][i - 2] = lds_load<bf16x8>((a_addr[i - 2] + stage) ^ uint32_t(32 * (s + 1)));
-                }
-            }
+            for (int i = 0; i < C::Y; ++i) load_y(i, p, p * C::kStage);
         }
     }
-    settle(acc);
+    if (n_kt >= S) stage_barrier<C::Y + (S - 1) * (C::X + C::Y)>();     // the first tile's X group has landed
+    else stage_barrier<0>();
+#pragma unroll
+    for (int m = 0; m < FH; ++m) read_lo(m, 0);
+#pragma unroll
+    for (int t = 0; t < TB; ++t) read_x(t, 0);
 
-    // ---- epilogue; the tile ring is free once every wave has left it
-    __syncthreads();
-    const uint32_t out_lds = lds0 + wave * 4096;
-    const uint32_t rope_lds = lds0 + 8 * 4096;
-    if (QKV) {
-        if (tid < kMaxPairs)
-            *LP_LDS_PTR(f32x4, uintptr_t(rope_lds + 16 * tid)) =
-                f32x4{a.rope.turns[tid][0], a.rope.turns[tid][1], a.rope.turns[tid][2], 0.0f};
-        __syncthreads();
-    }
-    const int fbase = f0 + fw * 128;                     // first of this wave's 128 features
-    if (fbase >= a.d_out) return;
-    int section = 0, f_in_section = fbase;
-    if (QKV) {
-        const int dm = a.heads * HD;
-        section = fbase / dm;
-        f_in_section = fbase - section * dm;
-    }
+    constexpr int PK = FH * TB;                          // products per k-step of a phase
+    constexpr int PRE = PK >= 4 ? 3 * PK / 4 : PK / 2;   // products before a phase's barrier
+    static_assert(PRE >= 1 && PRE < PK, "the lo operands are read between the barrier and the k-step's end");
+    uint32_t cur = 0;                                    // stage of tile kt
+    // LEFT = tiles after this one, as far as the code depends on it: with LEFT = S there is also a tile
+    // to send for (kt + S); below that everything that is left is already under way.
+    auto tile = [&](int kt, auto left_c) {
+        constexpr int LEFT = decltype(left_c)::value;
+        constexpr bool REFILL = LEFT >= S;
+        constexpr int AHEAD = REFILL ? S - 1 : LEFT;     // later tiles whose loads are under way
+        // products in an order in which neighbours share an operand
+        auto tcol = [](int m, int i) constexpr { return (m & 1) ? TB - 1 - i % TB : i % TB; };
+        // ---- phase 1: lo x x; meanwhile the rest of this tile's x and lo operands, then hi
+        static_for<0, 2 * PK>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, s = i / PK, m = (i % PK) / TB, t = tcol(m, i);
+            if constexpr (i == PRE) stage_barrier<AHEAD *(C::X + C::Y)>();
+            mfma(acc[m][t], lo[m][s], xop[t][s]);
+            if constexpr (i < PRE) {
+                static_for<i *(FH + TB) / PRE, (i + 1) * (FH + TB) / PRE>([&](auto rc) {
+                    constexpr int r = decltype(rc)::value;
+                    if constexpr (r < FH) read_lo(r, 1);
+                    else read_x(r - FH, 1);
+                });
+            } else {
+                constexpr int j = i - PRE, rest = 2 * PK - PRE;
+                if constexpr (j < PK)
+                    static_for<j * 2 * FH / PK, (j + 1) * 2 * FH / PK>([&](auto rc) {
+                        constexpr int r = decltype(rc)::value;
+                        read_hi(r % FH, r / FH);
+                    });
+                if constexpr (REFILL)
+                    static_for<j * C::X / rest, (j + 1) * C::X / rest>([&](auto rc) { load_x(decltype(rc)::value, kt + S, cur); });
+            }
+        });
+        // ---- phase 2: hi x x; meanwhile the first k-step of the next tile's lo and x operands
+        const uint32_t nxt = cur + C::kStage == C::kRing ? 0u : cur + C::kStage;
+        const uint32_t delta = nxt - cur;
+        static_for<0, 2 * PK>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, s = i / PK, m = (i % PK) / TB, t = tcol(m, i);
+            if constexpr (i == PRE && LEFT > 0) stage_barrier<(AHEAD - 1) * (C::X + C::Y) + C::Y + (REFILL ? C::X : 0)>();
+            mfma(acc[FH + m][t], hi[m][s], xop[t][s]);
+            if constexpr (LEFT > 0) {
+                if constexpr (i == 0) {
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const int tok_first = t0 + tq * 64 + nb * 32;    // first token of this 32-token block
-        if (tok_first >= a.n) break;
-        float val[4][16];
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float bv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (a.bias != nullptr) {
-                    const int f = fbase + 32 * mb + 8 * g + 4 * half;
-                    if (f + 3 < a.d_out) {
-                        const float4 b4 = *reinterpret_cast<const float4 *>(a.bias + f);
-                        bv[0] = b4.x; bv[1] = b4.y; bv[2] = b4.z; bv[3] = b4.w;
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) if (f + e < a.d_out) bv[e] = a.bias[f + e];
-                    }
+                    for (int q = 0; q < 2; ++q) { w_addr[q] += delta; x_addr[q] += delta; }
                 }
+                if constexpr (i >= PRE && i < PK) {
+                    constexpr int j = i - PRE, slots = PK - PRE;
+                    static_for<j * FH / slots, (j + 1) * FH / slots>([&](auto rc) { read_lo(decltype(rc)::value, 0); });
+                }
+                if constexpr (i >= PK && i < 2 * PK) {   // the first k-step's x operands have had their last product
+                    constexpr int j = i - PK, slots = PK > TB ? PK / 2 : PK;
+                    if constexpr (j < slots)
+                        static_for<j * TB / slots, (j + 1) * TB / slots>([&](auto rc) { read_x(decltype(rc)::value, 0); });
+                }
+                if constexpr (REFILL && i >= PRE) {
+                    constexpr int j = i - PRE, rest = 2 * PK - PRE;
+                    static_for<j * C::Y / rest, (j + 1) * C::Y / rest>([&](auto rc) { load_y(decltype(rc)::value, kt + S, cur); });
+                }
+            }
+        });
+        cur = nxt;
+    };
+    int kt = 0;
+    for (; kt + S < n_kt; ++kt) tile(kt, std::integral_constant<int, S>{});
+    static_for<0, S>([&](auto lc) {
+        constexpr int LEFT = S - 1 - decltype(lc)::value;
+        if (kt + LEFT == n_kt - 1) tile(kt++, std::integral_constant<int, LEFT>{});
+    });
+    // products become readable by vector instructions
+    asm volatile("s_nop 15\n\ts_nop 7");
 #pragma unroll
-                for (int e = 0; e < 4; ++e) val[mb][4 * g + e] = acc[mb][nb][4 * g + e] + bv[e];
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int t = 0; t < TB; ++t) asm volatile("" : "+v"(acc[f][t]));
+}
+
+// Per-head RMS normalisation and rotary encoding, in place, of the features a wave holds in acc
+// (those of one section of q or k): block f, token block t, element i of lane (col, quad) is
+// feature 16 f + 4 quad + i of token 16 t + col.  sum_sq(t, h) is the sum of squares over the
+// h-th head's features; gain_lds holds the gains of the wave's features; in_head is the first one's
+// place in its head.  The rotary table sits in LDS at rope_lds, float4 per pair.
+template <int HD, typename C, typename F>
+__device__ __forceinline__ void norm_rope(f32x4 (&acc)[C::FB][C::TB], F &&sum_sq, uint32_t gain_lds, int in_head,
+                                          const RopeArgs &r, uint32_t rope_lds, int tok_first, int n, int col, int quad) {
+    constexpr int kHeads = C::FB * 16 > HD ? C::FB * 16 / HD : 1, kBlocks = C::FB / kHeads;
+    float pt[C::TB], ph[C::TB], pw[C::TB];               // coordinates of this lane's tokens
+#pragma unroll
+    for (int t = 0; t < C::TB; ++t) {
+        const uint32_t tk = uint32_t(min(tok_first + 16 * t + col, n - 1));
+        const uint32_t ct = fastdiv(tk, r.hw), rem = tk - ct * r.hw.d, ch = fastdiv(rem, r.w);
+        pt[t] = float(int32_t(ct) + r.off[0]);
+        ph[t] = float(int32_t(ch) + r.off[1]);
+        pw[t] = float(int32_t(rem - ch * r.w.d) + r.off[2]);
+    }
+#pragma unroll
+    for (int hh = 0; hh < kHeads; ++hh) {
+        float inv[C::TB];
+#pragma unroll
+        for (int t = 0; t < C::TB; ++t) inv[t] = 1.0f / sqrtf(sum_sq(t, hh) * (1.0f / float(HD)) + r.eps);
+#pragma unroll
+        for (int b = 0; b < kBlocks; ++b) {
+            const int f = hh * kBlocks + b;
+            const f32x4 gn = lds_load<f32x4>(gain_lds + 4 * (16 * f + 4 * quad));
+            const int pair = ((in_head + 16 * f + 4 * quad) % HD) / 2;
+#pragma unroll
+            for (int pr = 0; pr < 2; ++pr) {
+                const f32x4 tb = lds_load<f32x4>(rope_lds + 16 * (pair + pr));
+#pragma unroll
+                for (int t = 0; t < C::TB; ++t) {
+                    float turns = pt[t] * tb.x + ph[t] * tb.y + pw[t] * tb.z;
+                    turns = turns - floorf(turns);
+                    const float c = __builtin_amdgcn_cosf(turns), s = __builtin_amdgcn_sinf(turns);
+                    const float x = acc[f][t][2 * pr] * inv[t] * gn[2 * pr], y = acc[f][t][2 * pr + 1] * inv[t] * gn[2 * pr + 1];
+                    acc[f][t][2 * pr] = x * c - y * s;
+                    acc[f][t][2 * pr + 1] = x * s + y * c;
+                }
             }
         }
-        __bf16 *dst;
-        int64_t row_stride;
-        if (QKV) {
-            if (section < 2) norm_rope<HD>(val, a.gain[section] + f_in_section, a.rope, rope_lds, uint32_t(min(tok_first + col, a.n - 1)), half);
-            row_stride = int64_t(a.heads) * HD;
-            dst = a.out[section] + int64_t(tok_first) * row_stride + f_in_section;
-        } else {
-            row_stride = a.d_out;
-            dst = a.out[0] + int64_t(tok_first) * row_stride + fbase;
+    }
+}
+
+// Writes a wave's results, rounded to bf16, to dst + token * row_stride + feature: 16 tokens at
+// a time pass through the wave's own LDS (16-byte granules XORed with the row) and leave as
+// whole 128-byte lines.
+template <typename C>
+__device__ __forceinline__ void store_tile(uint32_t out_lds, const f32x4 (&acc)[C::FB][C::TB], __bf16 *dst, int64_t row_stride,
+                                           int tokens_valid, int lane) {
+    constexpr int kGran = C::FB * 2, kRow = kGran * 16;  // granules and bytes of a staged row
+    const int col = lane % 16, quad = lane / 16;
+#pragma unroll
+    for (int t = 0; t < C::TB; ++t) {
+        if (16 * t >= tokens_valid) break;
+#pragma unroll
+        for (int f = 0; f < C::FB; ++f) {
+            union { u32x2 u; bf16x2 p[2]; } ow;
+            ow.p[0] = to_bf16x2(acc[f][t][0], acc[f][t][1]);
+            ow.p[1] = to_bf16x2(acc[f][t][2], acc[f][t][3]);
+            *LP_LDS_PTR(u32x2, uintptr_t(out_lds + col * kRow + 16 * ((2 * f + quad / 2) ^ (col % kGran)) + 8 * (quad % 2))) = ow.u;
         }
-        store_rows(out_lds, val, dst, row_stride, a.n - tok_first, lane);
+#pragma unroll
+        for (int j = 0; j < 16 * kGran / 64; ++j) {
+            const int r = (lane + 64 * j) / kGran, g = lane % kGran;
+            const u32x4 u = lds_load<u32x4>(out_lds + r * kRow + 16 * (g ^ (r % kGran)));
+            if (16 * t + r < tokens_valid) *reinterpret_cast<u32x4 *>(dst + int64_t(16 * t + r) * row_stride + 8 * g) = u;
+        }
+    }
+}
+
+// One tile from its first load to its last store.  QKV = true: the epilogue cuts the features into
+// q | k | v sections of heads * HD, normalises and rotates q and k.  QKV = false: plain y = x W^T + b.
+template <bool QKV, int HD, typename C>
+__device__ __forceinline__ void run_tile(uint32_t lds0, const GemmArgs &a, int f0, int t0) {
+    constexpr int FB = C::FB, TB = C::TB;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int lane = tid % 64, col = lane % 16, quad = lane / 16;
+    const int fbase = f0 + (wave / C::WT) * FB * 16;     // first of this wave's features
+    const bool live = fbase < a.d_out;                   // d_out is a multiple of FB * 16: all of them or none
+    const int dm = QKV ? a.heads * HD : a.d_out;
+    const int section = QKV ? min(fbase / dm, 2) : 0, f_in_section = fbase - section * dm;
+    // what the epilogue needs from memory is fetched before the product starts: two features' bias
+    // and gain per lane, one pair's rotary turns per thread
+    const int f_pre = min(2 * lane, FB * 16 - 2);
+    f32x2 bias_pre = {0.0f, 0.0f}, gain_pre = {0.0f, 0.0f};
+    f32x4 turns_pre = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (live && a.bias != nullptr) bias_pre = *reinterpret_cast<const f32x2 *>(a.bias + fbase + f_pre);
+    if (QKV) {
+        if (live && section < 2) gain_pre = *reinterpret_cast<const f32x2 *>(a.gain[section] + f_in_section + f_pre);
+        const float *tp = a.rope.turns[tid % kMaxPairs];
+        turns_pre = f32x4{tp[0], tp[1], tp[2], 0.0f};
+    }
+    f32x4 acc[FB][TB];
+    product<C>(lds0, a, f0, t0, wave, lane, acc);
+
+    stage_barrier<0>();                                  // the ring is free: every wave has read its last operand
+    const uint32_t out_lds = lds0 + wave * (16 * FB * 32), rope_lds = lds0 + C::kOut, ss_lds = rope_lds + kMaxPairs * 16;
+    const uint32_t bias_lds = ss_lds + C::kWaves * TB * 16 * 4 + wave * FB * 16 * 8, gain_lds = bias_lds + FB * 16 * 4;
+    *LP_LDS_PTR(f32x2, uintptr_t(bias_lds + 4 * f_pre)) = bias_pre;
+#pragma unroll
+    for (int f = 0; f < FB; ++f) {
+        const f32x4 b4 = lds_load<f32x4>(bias_lds + 4 * (16 * f + 4 * quad));
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[f][t][i] += b4[i];
+    }
+    const int tok_first = t0 + (wave % C::WT) * TB * 16;
+    if (QKV) {
+        // sums of squares over the features of a head that this wave holds
+        constexpr int kHeads = FB * 16 > HD ? FB * 16 / HD : 1, kSharing = FB * 16 < HD ? HD / (FB * 16) : 1;
+        float ss[TB][kHeads];
+#pragma unroll
+        for (int t = 0; t < TB; ++t)
+#pragma unroll
+            for (int hh = 0; hh < kHeads; ++hh) {
+                float s = 0.0f;
+#pragma unroll
+                for (int b = 0; b < FB / kHeads; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) s += acc[hh * (FB / kHeads) + b][t][i] * acc[hh * (FB / kHeads) + b][t][i];
+                s += __shfl_xor(s, 16, 64);
+                ss[t][hh] = s + __shfl_xor(s, 32, 64);
+            }
+        if (tid < kMaxPairs) *LP_LDS_PTR(f32x4, uintptr_t(rope_lds + 16 * tid)) = turns_pre;
+        *LP_LDS_PTR(f32x2, uintptr_t(gain_lds + 4 * f_pre)) = gain_pre;
+        if (kSharing > 1 && quad == 0) {
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+                *LP_LDS_PTR(float, uintptr_t(ss_lds + 4 * (wave * TB * 16 + t * 16 + col))) = ss[t][0];
+        }
+        __syncthreads();
+        if (!live) return;
+        if (kSharing > 1) {                              // the head's other features are with the neighbouring wave rows
+            const int first = (wave / (C::WT * kSharing)) * (C::WT * kSharing) + wave % C::WT;
+#pragma unroll
+            for (int t = 0; t < TB; ++t) {
+                float s = 0.0f;
+#pragma unroll
+                for (int q = 0; q < kSharing; ++q)
+                    s += lds_load<float>(ss_lds + 4 * ((first + q * C::WT) * TB * 16 + t * 16 + col));
+                ss[t][0] = s;
+            }
+        }
+        if (section < 2)
+            norm_rope<HD, C>(acc, [&](int t, int hh) { return ss[t][hh]; }, gain_lds, f_in_section % HD, a.rope, rope_lds, tok_first,
+                             a.n, col, quad);
+    } else if (!live) {
+        return;
+    }
+    store_tile<C>(out_lds, acc, a.out[section] + int64_t(tok_first) * dm + f_in_section, dm, a.n - tok_first, lane);
+}
+
+// Workgroups [0, whole) take one tile of tiling P each; every later tile is cut into tiles of R.
+// P's tiles are ordered in panels of kPanel token tiles, feature tile by feature tile inside a
+// panel: the workgroups an XCD runs at a time share their W and x rows through its L2.
+template <bool QKV, int HD, typename P, typename R>
+__global__ __launch_bounds__(P::kThreads, 2) void gemm_kernel(const GemmArgs a) {
+    static_assert(P::kThreads == R::kThreads && P::kF % R::kF == 0 && P::kT % R::kT == 0, "R cuts P");
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const uint32_t lds0 = uint32_t(uintptr_t(LP_LDS_PTR(unsigned char, smem)));
+    constexpr int kCutF = P::kF / R::kF, kCut = kCutF * (P::kT / R::kT);
+    const bool cut = std::is_same<P, R>::value ? false : int(blockIdx.x) >= a.whole;
+    int tile, part = 0;
+    if (!cut) {
+        tile = int(logical_workgroup(blockIdx.x, std::is_same<P, R>::value ? gridDim.x : uint32_t(a.whole)));
+    } else {
+        const int j = int(logical_workgroup(blockIdx.x - uint32_t(a.whole), gridDim.x - uint32_t(a.whole)));
+        tile = a.whole + j / kCut;
+        part = j % kCut;
+    }
+    const int panel_tiles = kPanel * a.n_ftiles;
+    const int panel = tile / panel_tiles, in_panel = tile - panel * panel_tiles;
+    const int panel_h = min(kPanel, a.n_ttiles - panel * kPanel);
+    const int ftile = in_panel / panel_h, ttile = panel * kPanel + in_panel - ftile * panel_h;
+    const int f0 = ftile * P::kF, t0 = ttile * P::kT;
+    if (!cut) {
+        run_tile<QKV, HD, P>(lds0, a, f0, t0);
+    } else {
+        const int fr = f0 + (part % kCutF) * R::kF, tr = t0 + (part / kCutF) * R::kT;
+        if (fr < a.d_out && tr < a.n) run_tile<QKV, HD, R>(lds0, a, fr, tr);
     }
 }
 
@@ -461,10 +591,76 @@ int make_rope_args(const lp_rope *rope, int64_t n, int32_t head_dim, float eps, 
     return LP_OK;
 }
 
-template <bool QKV, int HD>
-int launch_gemm(GemmArgs a, hipStream_t stream) {
+using Tile256x256 = Tiling<2, 4, 8, 4, 2>;
+using Tile256x128 = Tiling<2, 4, 8, 2, 3>;
+using Tile128x128 = Tiling<2, 4, 4, 2, 4>;
+using Tile128x64 = Tiling<4, 2, 2, 2, 5>;
+using Tile64x64 = Tiling<2, 2, 2, 2, 5>;
+
+// How a call is cut.  A round is one tile on every compute unit (two of the smallest).  Measured per
+// round and k-tile of 64, in us (4096 .. 1024 tokens and features so that one round is full or half
+// full, d_in 1536 and 5120): `part` with at most half of the compute units busy, `full` with all of
+// them, where the power limit lowers the clock; `once` is what a tile costs besides (first loads, stores).
+struct TileCost {
+    int f, t, per_cu;
+    float part, full, once;
+};
+constexpr TileCost kTileCost[] = {
+    {256, 256, 1, 1.01f, 1.41f, 5.0f}, {256, 128, 1, 0.58f, 0.80f, 3.5f}, {128, 128, 1, 0.35f, 0.445f, 2.5f},
+    {128, 64, 1, 0.27f, 0.307f, 0.4f}, {64, 64, 2, 0.19f, 0.36f, 0.4f},
+};
+constexpr int kCutNone = -1;
+
+// us for `tiles` tiles of one kind over n_kt k-tiles
+float tiles_cost(const TileCost &c, int64_t tiles, int n_kt, int cus) {
+    const int64_t slots = int64_t(cus) * c.per_cu, rounds = tiles / slots, rest = tiles - rounds * slots;
+    float us = float(rounds) * (c.full * float(n_kt) + c.once);
+    if (rest > 0) {
+        const float u = float(rest) / float(slots);
+        const float per = u <= 0.5f ? c.part : c.part + (u - 0.5f) * 2.0f * (c.full - c.part);
+        us += per * float(n_kt) + c.once;
+    }
+    return us;
+}
+
+struct Plan {
+    int tile, cut;       // indexes of kTileCost; cut = kCutNone: every tile is taken whole
+    int64_t whole;       // tiles taken whole
+};
+
+// Whole rounds run the largest tiling that fills them.  What is left of a last round is cut into
+// tiles that fill the chip once: 13230 x 5120 -> 5120 is 4 rounds of 256 x 256 tiles and 16 tiles
+// more, 546 us with them whole and 494 us with those 16 cut into 128 x 64; 3780 x 1536 -> 4608 (one
+// round and 14 tiles) 67 and 48 us; 2737 x 1024 -> 1024 (44 tiles) 22 us whole, 10.3 us as 176 tiles of
+// 128 x 128; 520 x 5120 -> 640 (9 tiles) 85 and 18 us as 90 tiles of 64 x 64.
+Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
+    static constexpr int kCuts[][2] = {{0, 1}, {0, 2}, {0, 3}, {2, 3}};   // the pairs compiled below
+    const int n_kt = d_in / kBK;
+    auto count = [&](int k) { return ((n + kTileCost[k].t - 1) / kTileCost[k].t) * ((d_out + kTileCost[k].f - 1) / kTileCost[k].f); };
+    Plan best{0, kCutNone, 0};
+    float best_us = 0.0f;
+    auto offer = [&](int tile, int cut, int64_t whole, float us) {
+        if (best.whole != 0 && us >= best_us) return;
+        best = Plan{tile, cut, whole};
+        best_us = us;
+    };
+    for (int k = 0; k < (small_ok ? 5 : 4); ++k) offer(k, kCutNone, count(k), tiles_cost(kTileCost[k], count(k), n_kt, cus));
+    for (const auto &p : kCuts) {
+        const TileCost &big = kTileCost[p[0]], &small = kTileCost[p[1]];
+        const int64_t tiles = count(p[0]), whole = tiles / cus * cus;
+        if (whole == 0 || whole == tiles) continue;
+        const int64_t parts = (tiles - whole) * (big.f / small.f) * (big.t / small.t);
+        offer(p[0], p[1], whole, tiles_cost(big, whole, n_kt, cus) + tiles_cost(small, parts, n_kt, cus));
+    }
+    return best;
+}
+
+template <bool QKV, int HD, typename P, typename R>
+int launch_tiles(GemmArgs a, int64_t whole, hipStream_t stream) {
+    constexpr int kLds = P::kLds > R::kLds ? P::kLds : R::kLds;
+    // the dynamic-LDS limit is an attribute of the function on a device: set once per device
     static std::atomic<uint64_t> attr_set{0};
-    const void *kern = reinterpret_cast<const void *>(&gemm_kernel<QKV, HD>);
+    const void *kern = reinterpret_cast<const void *>(&gemm_kernel<QKV, HD, P, R>);
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) {
@@ -473,18 +669,42 @@ int launch_gemm(GemmArgs a, hipStream_t stream) {
     }
     const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
     if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
-        e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
         if (e != hipSuccess) {
             lp::set_last_hip_error(int(e));
             return LP_ERR_HIP;
         }
         attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
     }
-    a.n_ftiles = (a.d_out + kTF - 1) / kTF;
-    a.n_ttiles = int32_t((a.n + kTT - 1) / kTT);
+    a.n_ftiles = (a.d_out + P::kF - 1) / P::kF;
+    a.n_ttiles = (a.n + P::kT - 1) / P::kT;
     const int64_t tiles = int64_t(a.n_ftiles) * a.n_ttiles;
-    if (tiles >= (int64_t(1) << 31)) return LP_ERR_UNSUPPORTED;
-    return lp::launch_kernel(kern, dim3(uint32_t(tiles)), dim3(kThreadsG), kLdsBytes, stream, a);
+    constexpr int64_t kCut = int64_t(P::kF / R::kF) * (P::kT / R::kT);
+    const int64_t grid = whole + (tiles - whole) * kCut;
+    if (grid >= (int64_t(1) << 31)) return LP_ERR_UNSUPPORTED;
+    a.whole = int32_t(whole);
+    return lp::launch_kernel(kern, dim3(uint32_t(grid)), dim3(P::kThreads), kLds, stream, a);
+}
+
+template <bool QKV, int HD>
+int launch_gemm(GemmArgs a, hipStream_t stream) {
+    constexpr bool kSmall = !QKV || HD <= 64;             // a head does not fit the smallest tile's features
+    const int cus = lp::device_compute_units();
+    if (cus <= 0) return LP_ERR_HIP;
+    const Plan p = pick_plan(a.n, a.d_in, a.d_out, kSmall, cus);
+    switch (p.tile * 8 + p.cut + 1) {
+        case 0 * 8 + 2: return launch_tiles<QKV, HD, Tile256x256, Tile256x128>(a, p.whole, stream);
+        case 0 * 8 + 3: return launch_tiles<QKV, HD, Tile256x256, Tile128x128>(a, p.whole, stream);
+        case 0 * 8 + 4: return launch_tiles<QKV, HD, Tile256x256, Tile128x64>(a, p.whole, stream);
+        case 2 * 8 + 4: return launch_tiles<QKV, HD, Tile128x128, Tile128x64>(a, p.whole, stream);
+        case 1 * 8: return launch_tiles<QKV, HD, Tile256x128, Tile256x128>(a, p.whole, stream);
+        case 2 * 8: return launch_tiles<QKV, HD, Tile128x128, Tile128x128>(a, p.whole, stream);
+        case 3 * 8: return launch_tiles<QKV, HD, Tile128x64, Tile128x64>(a, p.whole, stream);
+        case 4 * 8:
+            if constexpr (kSmall) return launch_tiles<QKV, HD, Tile64x64, Tile64x64>(a, p.whole, stream);
+            [[fallthrough]];
+        default: return launch_tiles<QKV, HD, Tile256x256, Tile256x256>(a, p.whole, stream);
+    }
 }
 
 // shape limits of the product: k in whole tiles, 32-bit byte offsets inside a tile's rows

@@ -40,5 +40,20 @@ inline int launch_kernel(const void *fn, dim3 grid, dim3 block, size_t lds_bytes
     }
     return LP_OK;
 }
+
+// Compute units of the current device (each host thread remembers the last device it asked about).
+inline int device_compute_units(int *device = nullptr) {
+    static thread_local int cached_dev = -1, cached_cus = 0;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (dev != cached_dev) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        cached_cus = cus;
+        cached_dev = dev;
+    }
+    if (device != nullptr) *device = dev;
+    return cached_cus;
+}
 }  // namespace lp
 #endif

@@ -63,6 +63,29 @@ def test_linear_matches_oracle(n, d_in, d_out, with_bias):
     _close(_linear(x, w, b), orc.linear(x, w, b), "linear %dx%d->%d" % (n, d_in, d_out))
 
 
+@pytest.mark.parametrize("n,d_in,d_out", [
+    (1, 64, 128), (63, 64, 128), (65, 128, 384), (129, 320, 256),     # 64 x 64 tiles; 1, 2 and 5 k-tiles (5 stages), ragged tokens
+    (2563, 64, 640),                    # 128 x 64
+    (2737, 1024, 1024),                 # 128 x 128
+    (12001, 1024, 384),                 # 128 x 128, the last tiles cut into 128 x 64
+    (4097, 512, 1536),                  # 256 x 128; one token in the last tile
+    (3783, 128, 3840),                  # 256 x 256; as many k-tiles as stages; d_out not a multiple of 256
+    (3600, 128, 4608),                  # 256 x 256, the last tiles cut into 128 x 64
+    (4097, 1024, 4608),                 # ... into 128 x 128, some of them wholly past the last token
+    (3601, 512, 6144),                  # ... into 256 x 128
+])
+def test_linear_of_every_tiling_on_sampled_tokens(n, d_in, d_out):
+    """The tilings are chosen from the sizes (named for 256 compute units).  The oracle evaluates both
+    sides of every 64-token tile edge among the first and last tiles, and random tokens; all features."""
+    x = _bits(1200 + n, (n, d_in))
+    w = _bits(1300 + n, (d_out, d_in), scale=d_in ** -0.5)
+    b = synth.normal_f32(1400 + n, (d_out,))
+    y = _linear(x, w, b)
+    assert np.all(np.isfinite(y))
+    rows = synth.sample_rows(n, 160, seed=29)
+    _close(y[rows], orc.linear(x[rows], w, b), "linear %dx%d->%d" % (n, d_in, d_out))
+
+
 def _qkv(x, w, bias, gq, gk, eps, heads, hd, grid, offset, split, base):
     import torch
     from tests import gpu_util as g
@@ -96,6 +119,31 @@ def test_qkv_projection_matches_oracle(heads, hd, grid, offset, split, base, wit
     got = _qkv(x, w, b, gq, gk, eps, heads, hd, grid, offset, split, base)
     for name, a, e in zip("qkv", got, want):
         _close(a, e, "%s heads=%d hd=%d grid=%s" % (name, heads, hd, grid))
+
+
+@pytest.mark.parametrize("heads,hd,grid", [
+    (8, 64, (3, 5, 9)),                  # 64 x 64 tiles: a head per tile row
+    (8, 128, (3, 5, 9)),                 # 128 x 64: four wavefronts share a head
+    (16, 64, (3, 13, 17)),               # 128 x 128: one head per wavefront
+    (8, 128, (3, 20, 20)),               # 128 x 128: two wavefronts share a head
+    (4, 128, (7, 23, 31)),               # 256 x 128
+    (12, 128, (9, 20, 20)),              # 256 x 256, the last tiles cut
+    (10, 128, (7, 23, 23)),              # 256 x 256 tiles that reach from one section into the next
+])
+def test_qkv_projection_of_every_tiling_on_sampled_tokens(heads, hd, grid):
+    dm, n = heads * hd, grid[0] * grid[1] * grid[2]
+    x = _bits(1500 + n, (n, dm))
+    w = _bits(1600 + n, (3 * dm, dm), scale=dm ** -0.5)
+    b = 0.5 * synth.normal_f32(1700 + n, (3 * dm,))
+    gq = 1.0 + 0.2 * synth.normal_f32(1800 + n, (heads, hd))
+    gk = 1.0 + 0.2 * synth.normal_f32(1900 + n, (heads, hd))
+    got = _qkv(x, w, b, gq, gk, 1e-6, heads, hd, grid, (0, 0, 0), None, 10000.0)
+    assert all(np.all(np.isfinite(a)) for a in got)
+    for r in synth.sample_rows(n, 64, seed=31):
+        where = (r // (grid[1] * grid[2]), r // grid[2] % grid[1], r % grid[2])
+        want = orc.qkv_block(x[r:r + 1], w, b, gq, gk, 1e-6, heads, hd, (1, 1, 1), where, None, 10000.0)
+        for name, a, e in zip("qkv", got, want):
+            _close(a[r:r + 1], e, "%s token %d" % (name, r))
 
 
 def test_qkv_projection_at_benchmark_size_sampled_tokens():
