@@ -188,6 +188,8 @@ int lp_reconstruct_guided_step_partition(const lp_plan *plan, const float *cond_
  * is launched per 256-row query tile and head, which leaves compute units idle
  * when their number does not divide the tile count.  Two calls that overlap in
  * time must not share a workspace.
+ * Short calls (a few hundred tokens, or a few heads) run a kernel of their own
+ * that needs no workspace.
  * Products run on bf16 MFMA with binary32 accumulation; q is multiplied by
  * scale*log2(e) and re-rounded to bf16 once; the softmax is binary32;
  * probabilities are rounded to bf16 before the second product and the result is

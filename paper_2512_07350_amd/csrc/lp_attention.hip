@@ -1008,21 +1008,8 @@ int64_t workspace_bytes_for(int cus) { return int64_t(2) * cus * slot_floats<D>(
 
 template <int D, int NB>
 int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hipStream_t stream) {
-    // The dynamic-LDS limit is an attribute of the function on a device: set once per device
-    // (a repeated set by a racing host thread is harmless).
-    static std::atomic<uint64_t> attr_set{0};
-    const void *kern = reinterpret_cast<const void *>(&attention_kernel<D, NB>);
     int dev = 0;
     const int cus = lp::device_compute_units(&dev);
-    const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
-    if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Tile<D, NB>::kBytes);
-        if (e != hipSuccess) {
-            lp::set_last_hip_error(int(e));
-            return LP_ERR_HIP;
-        }
-        attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
-    }
     a.n_qtiles = (a.n + kBM - 1) / kBM;
     a.tiles_per_unit = (a.n + kBN - 1) / kBN;
     const uint32_t units = uint32_t(a.n_qtiles) * uint32_t(heads), tpu = uint32_t(a.tiles_per_unit);
@@ -1034,6 +1021,7 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     a.shared_work = 0;
     a.unit_cost = tpu;
     a.shared_wgs = 0;
+    uint32_t tiles = cus > 0 ? ((units + cus - 1) / cus) * tpu : tpu;         // tiles of the busiest workgroup
     if (workspace != nullptr && cus > 0 && workspace_bytes >= workspace_bytes_for<D>(cus)) {
         // Candidate: one workgroup per compute unit takes floor(units / #CU) rounds of whole
         // units, and the units left over are shared evenly by as many workgroups as get at least
@@ -1061,9 +1049,31 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
                     a.unit_cost = tpu + kBoundaryTiles;
                     a.shared_work = shared * a.unit_cost;
                     a.shared_wgs = sharers;
+                    tiles = rounds * tpu + (shared * tpu + sharers - 1) / sharers + kBoundaryTiles;
                 }
             }
         }
+    }
+    // Short calls go to attention_short_kernel, which needs no scratch.  This kernel takes about 9 us before
+    // and after its tiles (launch, first tiles and Q, the first round, stores), 1.45 us a tile at
+    // head_dim 128 and 0.75 at 64, and 8 us for the merge kernel; attention_short_us says what the other takes.
+    // Measured, this kernel / the other: 600 tokens x 40 heads of 128 24 / 19 us, 1500 x 40 45 / 76, 1000 x 12
+    // 31 / 16, 3000 x 12 66 / 86; of 64: 2000 x 12 31 / 22, 3000 x 12 43 / 45.
+    const float long_us = 9.0f + (D == 128 ? 1.45f : 0.75f) * float(tiles) + (a.ws != nullptr ? 8.0f : 0.0f);
+    if (cus > 0 && lp::attention_short_us(a.n, heads, D, cus) < long_us)
+        return lp::attention_short({a.q, a.k, a.v, a.o, a.stride_tok, a.stride_head, a.stride_batch, a.heads, heads, D, a.n, a.scale_log2e}, stream);
+    // The dynamic-LDS limit is an attribute of the function on a device: set once per device
+    // (a repeated set by a racing host thread is harmless).
+    static std::atomic<uint64_t> attr_set{0};
+    const void *kern = reinterpret_cast<const void *>(&attention_kernel<D, NB>);
+    const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
+    if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
+        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Tile<D, NB>::kBytes);
+        if (e != hipSuccess) {
+            lp::set_last_hip_error(int(e));
+            return LP_ERR_HIP;
+        }
+        attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
     }
     int rc = lp::launch_kernel(kern, dim3(n_wg), dim3(waves_of(NB) * 64), Tile<D, NB>::kBytes, stream, a);
     if (rc != LP_OK || a.ws == nullptr) return rc;

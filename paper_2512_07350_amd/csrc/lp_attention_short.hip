@@ -1,0 +1,376 @@
+// lp_attention for short sequences and few heads.
+//
+// What bounds such a call is not the matrix pipeline but a chain: launch, first bytes of Q and K from
+// memory, one round of products after the other, results.  attention_kernel (lp_attention.hip) gives
+// a workgroup 256 query rows, so 200 tokens of 4 heads are four workgroups that walk all keys one
+// round after the other.  Here a workgroup takes 32 query rows of a head and its four wavefronts
+// share the KEYS: wavefront w takes the rounds w, w + 4, ... of 32 keys, each with its own
+// running maximum, row sum and output accumulators, and the four partial results are merged
+// through LDS at the end (m = max m_w, l = sum l_w 2^(m_w - m), O = sum O_w 2^(m_w - m) / l).  The
+// chain is a quarter as long and there are eight times as many workgroups; a wavefront's K and V
+// pass through LDS of its own, so the loop has no barrier.  The price is that a K/V row is fetched for
+// 32 query rows instead of 256, which is why long calls stay with attention_kernel: see
+// attention_short_us for where the line lies.
+//
+// Products, operand layouts and the order of keys in a round are those of attention_kernel (16x16x32
+// MFMA, S^T = K Q^T and O^T += V^T P^T, K rows permuted so that a lane's eight probabilities are eight
+// consecutive keys, V read transposed); the products are builtins here: with 32 rows a wavefront
+// needs 166 registers and two workgroups share a compute unit.
+//
+// Measured (us, attention_kernel / this): 200 tokens, 4 heads of 64: 9.9 / 4.5; 333, 3 of 128: 17.8 /
+// 6.6; 1000, 12 of 128: 32 / 16.4; 2000, 12 of 128: 43 / 42; 3000, 12 of 128: 67 / 86.  One stage per
+// wavefront, whose K half is refilled once the scores are formed and whose V half after the PV
+// product, and two workgroups per compute unit are faster than two whole stages and one workgroup
+// (1000 tokens, 12 heads of 128: 16.4 / 23.1); eight wavefronts per workgroup 20.9; 64 rows 22.8.
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+
+#include "lp_internal.h"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+#define LP_LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
+
+constexpr int kWaves = 4;                     // wavefronts of a workgroup; they share the keys
+constexpr int kQB = 2;                        // 16-row query blocks of a workgroup
+constexpr int kRows = 16 * kQB;
+constexpr float kRescaleThreshold = 8.0f;     // log2 units the running maximum may lag behind
+
+struct ShortParams {
+    const __bf16 *q, *k, *v;
+    __bf16 *o;
+    int64_t stride_tok, stride_head, stride_batch;
+    int heads;                 // heads per batch item
+    int n, n_blocks;           // tokens, and blocks of kRows of them
+    float scale_log2e;
+};
+
+template <int D>
+struct Round {
+    static constexpr int kRowBytes = D * 2, kGran = kRowBytes / 16;    // a K or V row and its 16-byte granules
+    static constexpr int kTileBytes = 32 * kRowBytes;                  // K or V of a round
+    static constexpr int kRingBytes = kWaves * 2 * kTileBytes;         // K then V, for every wavefront
+    static constexpr int kPartBytes = kRows * D * 4;                   // partial rows of a wavefront in the merge
+    static constexpr int kMergeBytes = kWaves * (kPartBytes + kRows * 8);
+    static constexpr int kLds = kRingBytes > kMergeBytes ? kRingBytes : kMergeBytes;
+    static constexpr int kRowsPerLoad = 1024 / kRowBytes, kLoads = 32 / kRowsPerLoad;   // wave-wide loads of a tile
+    // granule XOR masks as in attention_kernel: the rows that one LDS access touches lie in different banks
+    __device__ static int swz_k(int row) { return D == 128 ? (row & 3) | ((row >> 1) & 12) : ((row >> 1) & 1) | ((row >> 2) & 6); }
+    __device__ static int swz_v(int row) { return D == 128 ? 2 * ((row & 3) | ((row >> 1) & 4)) : (row & 2) | ((row >> 1) & 4); }
+};
+
+union Pack16 {
+    uint4 u;
+    bf16x8 v;
+    bf16x4 h[2];
+    bf16x2 p[4];
+};
+
+template <typename V>
+__device__ __forceinline__ V lds_load(uint32_t addr) {
+    return *LP_LDS_PTR(const V, uintptr_t(addr));
+}
+template <typename V>
+__device__ __forceinline__ void lds_store(uint32_t addr, const V &x) {
+    *LP_LDS_PTR(V, uintptr_t(addr)) = x;
+}
+
+__device__ __forceinline__ bf16x2 to_bf16x2(float lo, float hi) {
+    f32x2 f = {lo, hi};
+    return __builtin_convertvector(f, bf16x2);
+}
+
+__device__ __forceinline__ float quad_max(float x) { return lp::over_quads(x, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float quad_sum(float x) { return lp::over_quads(x, [](float a, float b) { return a + b; }); }
+
+// One wave-wide global -> LDS load of 1024 bytes (an assembly statement for the reason given in
+// lp_attention.hip); bytes outside the buffer arrive as zeros.
+__device__ __forceinline__ void load_to_lds_16(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+
+// At most PENDING of this wavefront's loads are still in flight.
+template <int PENDING>
+__device__ __forceinline__ void wait_loads() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PENDING) : "memory");
+}
+
+template <int D>
+__global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const ShortParams a) {
+    using T = Round<D>;
+    constexpr int KS = D / 32, MB = D / 16;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const uint32_t lds0 = uint32_t(uintptr_t(LP_LDS_PTR(unsigned char, smem)));
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int lane = tid % 64, col = lane % 16, quad = lane / 16;
+    const int n = a.n;
+
+    // workgroup ids are dealt round robin to the 8 XCDs: the blocks of a head go to one of them
+    const uint32_t xcd = blockIdx.x % 8, slot = blockIdx.x / 8, base = gridDim.x / 8, rem = gridDim.x % 8;
+    const uint32_t unit = xcd * base + (xcd < rem ? xcd : rem) + slot;
+    const int bh = int(unit) / a.n_blocks, q0 = (int(unit) - bh * a.n_blocks) * kRows;
+    const int item = bh / a.heads;
+    const int64_t head_off = int64_t(item) * a.stride_batch + int64_t(bh - item * a.heads) * a.stride_head;
+
+    // K and V of this head as raw buffers ending with token n-1
+    const int valid_bytes = int((int64_t(n - 1) * a.stride_tok + D) * 2);
+    const __amdgpu_buffer_rsrc_t k_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(a.k + head_off), 0, valid_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16 *>(a.v + head_off), 0, valid_bytes, 0x00020000);
+    const uint32_t tok_bytes = uint32_t(a.stride_tok * 2);
+    const uint32_t k_lds = lds0 + wave * 2 * T::kTileBytes, v_lds = k_lds + T::kTileBytes;
+    uint32_t k_voff[T::kLoads], v_voff[T::kLoads];
+#pragma unroll
+    for (int i = 0; i < T::kLoads; ++i) {
+        const int row = i * T::kRowsPerLoad + lane / T::kGran, g = lane % T::kGran;
+        k_voff[i] = uint32_t(row) * tok_bytes + 16 * (g ^ T::swz_k(row));
+        v_voff[i] = uint32_t(row) * tok_bytes + 16 * (g ^ T::swz_v(row));
+    }
+    auto issue_k = [&](int round) {
+#pragma unroll
+        for (int i = 0; i < T::kLoads; ++i)
+            load_to_lds_16(k_rsrc, __builtin_amdgcn_readfirstlane(k_lds + i * 1024), k_voff[i], uint32_t(round) * 32 * tok_bytes);
+    };
+    auto issue_v = [&](int round) {
+#pragma unroll
+        for (int i = 0; i < T::kLoads; ++i)
+            load_to_lds_16(v_rsrc, __builtin_amdgcn_readfirstlane(v_lds + i * 1024), v_voff[i], uint32_t(round) * 32 * tok_bytes);
+    };
+    const int n_rounds = (n + 31) / 32;
+    int round = wave;
+    if (round < n_rounds) {
+        issue_k(round);
+        issue_v(round);
+    }
+
+    // Q^T operands, multiplied by scale * log2(e) and rounded to bf16 again; rows past the end repeat
+    // the last one and are not stored
+    bf16x8 q[kQB][KS];
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb) {
+        const __bf16 *row = a.q + head_off + int64_t(min(q0 + qb * 16 + col, n - 1)) * a.stride_tok;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            Pack16 t;
+            t.u = *reinterpret_cast<const uint4 *>(row + kk * 32 + quad * 8);
+            const uint32_t u[4] = {t.u.x, t.u.y, t.u.z, t.u.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)       // a bf16 is the upper half of the binary32 with the same value
+                t.p[e] = to_bf16x2(__uint_as_float(u[e] << 16) * a.scale_log2e, __uint_as_float(u[e] & 0xffff0000u) * a.scale_log2e);
+            q[qb][kk] = t.v;
+        }
+    }
+
+    // LDS addresses of the K operands (rows 8 (r / 4) + r % 4, block 1 four rows later) and V^T operands
+    const int krow = 8 * (col / 4) + col % 4, vrow = 8 * quad + col / 4;
+    uint32_t k_addr[KS], v_addr[MB];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) k_addr[kk] = k_lds + krow * T::kRowBytes + 16 * ((4 * kk + quad) ^ T::swz_k(krow));
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+        v_addr[mb] = v_lds + vrow * T::kRowBytes + 8 * (col % 2) + 16 * ((2 * mb + (col % 4) / 2) ^ T::swz_v(vrow));
+
+    f32x4 acc[MB][kQB];
+    float m[kQB], l[kQB];                       // m: log2 units, common to the four lanes of a query
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb) {
+        m[qb] = -INFINITY;
+        l[qb] = 0.0f;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[mb][qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    for (bool first = true; round < n_rounds; round += kWaves, first = false) {
+        const bool more = round + kWaves < n_rounds;
+        wait_loads<T::kLoads>();                // K of this round; behind it only V
+        f32x4 s[2][kQB];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) {
+                const float c = first ? 0.0f : -m[qb];
+                s[b][qb] = f32x4{c, c, c, c};
+            }
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const bf16x8 ka = lds_load<bf16x8>(k_addr[kk] + 4 * b * T::kRowBytes);
+#pragma unroll
+                for (int qb = 0; qb < kQB; ++qb) s[b][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, q[qb][kk], s[b][qb], 0, 0, 0);
+            }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // every K operand has left LDS
+            issue_k(round + kWaves);
+        }
+        if ((round + 1) * 32 > n) {             // keys past the end: score -inf
+            const int kbase = round * 32 + 8 * quad;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const bool past = kbase + e >= n;
+#pragma unroll
+                for (int qb = 0; qb < kQB; ++qb) s[e / 4][qb][e % 4] = past ? -INFINITY : s[e / 4][qb][e % 4];
+            }
+        }
+        // the maximum is set by the first round and raised when a score exceeds it by more than the threshold
+        float mx[kQB];
+        bool raise = first;
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) {
+            mx[qb] = s[0][qb][0];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) mx[qb] = fmaxf(mx[qb], s[e / 4][qb][e % 4]);
+            raise = raise || mx[qb] > kRescaleThreshold;
+        }
+        if (__any(raise)) {
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) {
+                const float top = quad_max(mx[qb]), d = first ? top : fmaxf(top, 0.0f);
+                const float f = first ? 0.0f : __builtin_amdgcn_exp2f(-d);
+                m[qb] = first ? d : m[qb] + d;
+                l[qb] *= f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s[e / 4][qb][e % 4] -= d;
+                if (!first) {
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[mb][qb][i] *= f;
+                }
+            }
+        }
+        bf16x8 p[kQB];
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) {
+            Pack16 t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+                t.p[e] = to_bf16x2(__builtin_amdgcn_exp2f(s[e / 2][qb][(2 * e) % 4]), __builtin_amdgcn_exp2f(s[e / 2][qb][(2 * e) % 4 + 1]));
+                l[qb] = __builtin_amdgcn_fdot2_f32_bf16(t.p[e], ones, l[qb], false);     // the row sum adds the rounded probabilities
+            }
+            p[qb] = t.v;
+        }
+        if (more) wait_loads<T::kLoads>();      // V of this round; behind it only the next round's K
+        else wait_loads<0>();
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            Pack16 t;
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+                t.h[hf] = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LP_LDS_PTR(bf16x4, uintptr_t(v_addr[mb] + 4 * hf * T::kRowBytes)));
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) acc[mb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.v, p[qb], acc[mb][qb], 0, 0, 0);
+        }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // every V operand has left LDS
+            issue_v(round + kWaves);
+        }
+    }
+
+    // ---- merge: maxima and row sums through LDS, then the rows, scaled to the common maximum
+    __syncthreads();                            // every wavefront has left its ring (its loads have all landed)
+    const uint32_t ml_lds = lds0 + kWaves * T::kPartBytes;
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb) {
+        l[qb] = quad_sum(l[qb]);
+        if (quad == 0) lds_store(ml_lds + 8 * (wave * kRows + qb * 16 + col), f32x2{m[qb], l[qb]});
+    }
+    __syncthreads();
+#pragma unroll
+    for (int qb = 0; qb < kQB; ++qb) {
+        const int row = qb * 16 + col;
+        f32x2 part[kWaves];
+        float top = -INFINITY, sum = 0.0f;      // wavefront 0 always has a round, so top is finite
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            part[w] = lds_load<f32x2>(ml_lds + 8 * (w * kRows + row));
+            top = fmaxf(top, part[w].x);
+        }
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += part[w].y * __builtin_amdgcn_exp2f(part[w].x - top);
+        const float f = __builtin_amdgcn_exp2f(m[qb] - top) / sum;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            lds_store(lds0 + wave * T::kPartBytes + row * D * 4 + 16 * ((4 * mb + quad) ^ col), acc[mb][qb] * f);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kRows * D / 8 / (64 * kWaves); ++j) {       // eight consecutive d of a row per thread
+        const int c = tid + 64 * kWaves * j, row = c / (D / 8), ch = c % (D / 8);
+        f32x4 lo = {0.0f, 0.0f, 0.0f, 0.0f}, hi = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const uint32_t part = lds0 + w * T::kPartBytes + row * D * 4;
+            lo += lds_load<f32x4>(part + 16 * ((2 * ch) ^ (row % 16)));
+            hi += lds_load<f32x4>(part + 16 * ((2 * ch + 1) ^ (row % 16)));
+        }
+        Pack16 t;
+        t.p[0] = to_bf16x2(lo[0], lo[1]);
+        t.p[1] = to_bf16x2(lo[2], lo[3]);
+        t.p[2] = to_bf16x2(hi[0], hi[1]);
+        t.p[3] = to_bf16x2(hi[2], hi[3]);
+        if (q0 + row < n) *reinterpret_cast<uint4 *>(a.o + head_off + int64_t(q0 + row) * a.stride_tok + 8 * ch) = t.u;
+    }
+}
+
+template <int D>
+int launch_short(ShortParams a, int64_t groups, hipStream_t stream) {
+    // the dynamic-LDS limit is an attribute of the function on a device: set once per device
+    static std::atomic<uint64_t> attr_set{0};
+    const void *kern = reinterpret_cast<const void *>(&attention_short_kernel<D>);
+    int dev = 0;
+    lp::device_compute_units(&dev);
+    const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
+    if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
+        const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Round<D>::kLds);
+        if (e != hipSuccess) {
+            lp::set_last_hip_error(int(e));
+            return LP_ERR_HIP;
+        }
+        attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
+    }
+    return lp::launch_kernel(kern, dim3(uint32_t(groups)), dim3(kWaves * 64), Round<D>::kLds, stream, a);
+}
+
+int64_t short_groups(int64_t n, int64_t all_heads) { return all_heads * ((n + kRows - 1) / kRows); }
+
+}  // namespace
+
+namespace lp {
+
+// us: launch and first fetch, then the workgroups of a compute unit, each a quarter of the rounds long.
+// Fitted to 333 x 3 .. 3000 x 12 and 600 x 40 .. 1500 x 40 (tokens x heads) at head_dim 128 and 64; off by up to 15 %.
+float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus) {
+    const int64_t per_cu = (short_groups(n, all_heads) + cus - 1) / cus, rounds = (n + 127) / 128;
+    return 4.0f + float(per_cu) * (0.3f + (head_dim == 128 ? 0.8f : 0.37f) * float(rounds));
+}
+
+int attention_short(const AttentionCall &c, hipStream_t stream) {
+    ShortParams a;
+    a.q = static_cast<const __bf16 *>(c.q);
+    a.k = static_cast<const __bf16 *>(c.k);
+    a.v = static_cast<const __bf16 *>(c.v);
+    a.o = static_cast<__bf16 *>(c.o);
+    a.stride_tok = c.stride_tok;
+    a.stride_head = c.stride_head;
+    a.stride_batch = c.stride_batch;
+    a.heads = c.heads;
+    a.n = c.n;
+    a.n_blocks = (c.n + kRows - 1) / kRows;
+    a.scale_log2e = c.scale_log2e;
+    const int64_t groups = short_groups(c.n, c.all_heads);
+    return c.head_dim == 128 ? launch_short<128>(a, groups, stream) : launch_short<64>(a, groups, stream);
+}
+
+}  // namespace lp

@@ -41,6 +41,19 @@ inline int launch_kernel(const void *fn, dim3 grid, dim3 block, size_t lds_bytes
     return LP_OK;
 }
 
+// lp_attention's arguments after the checks.
+struct AttentionCall {
+    const void *q, *k, *v;
+    void *o;
+    int64_t stride_tok, stride_head, stride_batch;
+    int32_t heads, all_heads, head_dim;   // heads of one batch item, of all items
+    int32_t n;
+    float scale_log2e;
+};
+// The kernel for short sequences (lp_attention_short.hip) and what it is expected to take.
+int attention_short(const AttentionCall &c, hipStream_t stream);
+float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus);
+
 // Compute units of the current device (each host thread remembers the last device it asked about).
 inline int device_compute_units(int *device = nullptr) {
     static thread_local int cached_dev = -1, cached_cus = 0;
@@ -54,6 +67,17 @@ inline int device_compute_units(int *device = nullptr) {
     }
     if (device != nullptr) *device = dev;
     return cached_cus;
+}
+
+// op over the four lanes of equal lane % 16 (the four quads of a matrix instruction's column), in every
+// one of them.  The swaps exchange rows of 16 (32) lanes between two copies of x, after which one copy
+// holds the first and the other the second of each pair of rows.
+template <typename Op>
+__device__ __forceinline__ float over_quads(float x, Op &&op) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 }  // namespace lp
 #endif

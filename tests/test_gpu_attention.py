@@ -307,3 +307,46 @@ def test_scores_far_above_the_first_round(balanced, hd, profile):
     plateau = synth.bf16_bits_to_f32(v)[level == 32.0].mean(axis=0)
     assert np.max(np.abs(want[700] - plateau)) < 1e-2          # the oracle itself: the plateau's keys carry the weight
 
+
+
+# With 40 heads these lengths run the kernel of 256-row query tiles; the same lengths with few heads, and
+# everything of a few hundred tokens, run the kernel whose wavefronts share the keys.
+@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("n", [1536, 1537, 1567, 1599, 1600, 1601, 1632, 1791, 1793, 2047])
+def test_long_kernel_at_tile_and_round_edges(n, hd, balanced):
+    from tests import gpu_util as g
+    q, k, v = synth.qkv_bf16(4500 + 2 * n + hd, n, 40, hd)
+    got = g.hip_attention(q, k, v, balanced=balanced)
+    rows = synth.sample_rows(n, 48, seed=n, tile=256)
+    g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "n=%d hd=%d" % (n, hd))
+    assert np.all(np.isfinite(got))
+
+
+# the rounds of 32 keys are dealt to four wavefronts: no round, one, a ragged last one, one more than the others
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("n", [3, 30, 62, 98, 126, 130, 161, 225, 383, 385, 1151])
+def test_short_kernel_at_round_edges(n, hd):
+    from tests import gpu_util as g
+    q, k, v = synth.qkv_bf16(4700 + 2 * n + hd, n, 2, hd)
+    g.assert_attention_close(g.hip_attention(q, k, v), orc.attention(q, k, v), "n=%d hd=%d" % (n, hd))
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("profile", ["ramp", "cliff"])
+@pytest.mark.parametrize("n,heads", [(1500, 40), (3000, 12)], ids=["whole tiles", "shared tiles"])
+def test_long_kernel_scores_far_above_the_first_round(n, heads, profile, hd):
+    """test_scores_far_above_the_first_round at lengths that run the kernel of 256-row query tiles."""
+    from tests import gpu_util as g
+    rng = np.random.default_rng(4321)
+    base = np.where(rng.random((heads, hd)) < 0.5, -1.0, 1.0).astype(np.float32)
+    level = np.where(np.arange(n) < 40, 0.0, 32.0) if profile == "cliff" else np.minimum(np.floor(np.arange(n) / 32.0), 32.0)
+    qf = np.broadcast_to(base[None] * np.float32(64.0 / hd), (n, heads, hd)).copy()
+    kf = base[None] * level.astype(np.float32)[:, None, None]
+    vf = rng.standard_normal((n, heads, hd)).astype(np.float32)
+    q, k, v = (synth.f32_to_bf16_bits(a) for a in (qf, kf, vf))
+    scale = 0.125 / np.log2(np.e)
+    got = g.hip_attention(q, k, v, scale=scale)
+    rows = synth.sample_rows(n, 48, seed=7, tile=256)
+    g.assert_attention_close(got[rows], orc.attention(q, k, v, scale=scale, rows=rows), "scores far above the first round")
+    assert np.all(np.isfinite(got))
