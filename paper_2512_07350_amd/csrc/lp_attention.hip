@@ -1,23 +1,28 @@
 // lp_attention: non-causal multi-head self-attention over the patch tokens of one
 // sub-latent (supplement, proof of Theorem 1, step 3: inside a sub-latent the DiT
 // blocks attend globally over all of its positions), as a flash-style kernel for
-// gfx950: bf16 MFMA 32x32x16 for both products, binary32 online softmax, K and V
+// gfx950: bf16 MFMA 16x16x32 for both products, binary32 online softmax, K and V
 // tiles streamed global -> LDS without passing through registers.
 //
 // Work decomposition.  One workgroup = 4 wavefronts = 256 query rows of one head, one
-// wavefront per SIMD; each wavefront owns 64 query rows (two 32-column MFMA blocks) and
+// wavefront per SIMD; each wavefront owns 64 query rows (four 16-column MFMA blocks) and
 // walks all keys in rounds of 32.  Per round it forms the TRANSPOSED scores
 //     S^T[key, query] = K . Q^T            (A = K rows from LDS, B = Q in registers)
-// so that in the MFMA accumulator layout a lane holds 16 scores of ONE query: the
+// so that in the MFMA accumulator layout a lane holds 8 scores of ONE query per block: the
 // row maximum and row sum are in-lane reductions, the rescale factor of the running
 // output is a per-lane scalar, and the bf16 probabilities are already laid out as
 // the B operand of
 //     O^T[d, query] += V^T . P^T           (A = V^T, read transposed from LDS).
-// Every operand fetched from LDS feeds two products (one per 32-query block): 0.75 LDS
-// reads per matrix instruction.  The 64 rows need more than 256 registers per lane: the
-// O^T accumulators and the Q^T operands are kept in the accumulation registers (AGPRs) by
-// writing the matrix instructions as assembly statements with the register file of every
-// operand spelled out (see mfma_score / mfma_pv).
+// Every operand fetched from LDS feeds four products (one per 16-query block).  The 64 rows
+// need more than 256 registers per lane: the O^T accumulators and the Q^T operands are kept in
+// the accumulation registers (AGPRs) by writing the matrix instructions as assembly statements
+// with the register file of every operand spelled out (see mfma_score / mfma_pv).
+//
+// The products are 16x16x32 and not 32x32x16: the part is limited by power, and a loop of nothing
+// but products on N(0,1) operands sustains 2077 TFLOP/s with the former and 1837 with the latter.
+// The kernel's own step on the same schedule: 1258 TFLOP/s with 32x32x16, 1373 with 16x16x32, 1408
+// with four tiles unrolled (13230 tokens, 40 heads of 128; at head_dim 64 1068, 1065 and 1170: there the
+// vector issue slots bind, and the unrolled addresses free some).
 //
 // Details that matter for speed:
 //  * Q is multiplied by scale*log2(e) once and re-rounded to bf16, and the score
@@ -35,10 +40,10 @@
 //    r-1 share one step, and the step's vector and LDS work is cut into one small window
 //    per matrix instruction (pipeline_step), so that the one wavefront of a SIMD has its
 //    next product ready when the matrix pipeline takes it.
-//  * The key order inside a 32-key round is permuted (bits 2 and 3 of the MFMA row
-//    index swapped when K rows are read) so that the 8 probabilities a lane feeds
-//    to one MFMA belong to 8 consecutive keys; V^T operands then come from two
-//    ds_read_b64_tr_b16 (transposing LDS reads) of the row-major V tile.
+//  * The key order inside a 32-key round is permuted (MFMA row r of the round's block b is
+//    key 8 (r / 4) + 4 b + r % 4) so that the 8 probabilities a lane feeds to one MFMA
+//    belong to 8 consecutive keys; V^T operands then come from two ds_read_b64_tr_b16
+//    (transposing LDS reads) of the row-major V tile.
 //  * K/V tiles go global -> LDS with buffer_load_dwordx4 ... lds (kStages tiles
 //    resident), with XOR swizzles of the 16-byte granules chosen so that the K
 //    reads (ds_read_b128) and the V reads are free of bank conflicts.
@@ -59,7 +64,7 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -77,31 +82,34 @@ __device__ __forceinline__ void static_for(F &&f) {
 }
 
 constexpr int kBM = 256;                      // query rows per workgroup
-// A wavefront owns NB blocks of 32 query rows; the workgroup has kBM / (32 NB) wavefronts.
-constexpr int waves_of(int nb) { return kBM / (32 * nb); }
-// NB used by lp_attention: 64 query rows per wavefront (one wavefront per SIMD, four per workgroup)
-constexpr int blocks_per_wave(int /* head_dim */) { return 2; }
+constexpr int kWaves = 4;                     // wavefronts per workgroup, one per SIMD
+constexpr int kQB = kBM / (16 * kWaves);      // 16-query blocks of a wavefront: 64 rows
+// Row sums kept per query: two at head_dim 64, where two pairs of scores are added between LDS
+// fetches and the compiler would put a wait state between additions to the same one.
+constexpr int row_sums(int head_dim) { return head_dim == 64 ? 2 : 1; }
 constexpr int kBN = 64;                       // keys per LDS tile (two rounds of 32)
 constexpr int kStages = 4;                    // LDS stages: three tiles in use plus one arriving
 constexpr float kRescaleThreshold = 8.0f;     // log2 units the running max may lag behind
 constexpr uint32_t kBoundaryTiles = 4;        // what changing units costs a workgroup, in tile times
 
-template <int D, int NB>
+template <int D>
 struct Tile {
-    static constexpr int kWaves = waves_of(NB);
     static constexpr int kRowBytes = D * 2;
     static constexpr int kGran = kRowBytes / 16;            // 16-byte granules per row
     static constexpr int kTileBytes = kBN * kRowBytes;      // one K or one V tile
     static constexpr int kStageBytes = 2 * kTileBytes;      // K tile then V tile
     static constexpr int kRingBytes = kStages * kStageBytes;
-    static constexpr int kOutBytes = 4096;                  // per wave: 32 result rows of 64 d in bf16
+    static constexpr int kOutBytes = 16 * kRowBytes;        // per wave: 16 result rows in bf16
     static constexpr int kBytes = kRingBytes + kWaves * kOutBytes;
+    // Stages an LDS instruction reaches by its 16-bit offset from the first of them (power of two)
+    static constexpr int kReach = kStages * kStageBytes <= 65536 ? kStages : 2;
     static constexpr int kRowsPerInstr = 1024 / kRowBytes;  // rows one wave-wide 16-byte load covers
     static constexpr int kInstrPerTile = kBN / kRowsPerInstr;
-    static constexpr int kLoadsPerWave = 2 * kInstrPerTile / kWaves;   // K and V, per tile
-    // granule XOR masks; reader and writer use the same functions
-    __device__ static int swz_k(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
-    __device__ static int swz_v(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row & 3) >> 1); }
+    // Granule XOR masks; reader and writer use the same functions.  A K read takes, per 16 lanes, one
+    // granule of the rows 8 (r / 4) + r % 4 (+ 4): their 16 places must differ modulo the 256 bytes of
+    // the banks.  A V read takes, per 32 lanes, two granules of the rows 0-3 and 8-11 (+ 4, + 16).
+    __device__ static int swz_k(int row) { return D == 128 ? (row & 3) | ((row >> 1) & 12) : ((row >> 1) & 1) | ((row >> 2) & 6); }
+    __device__ static int swz_v(int row) { return D == 128 ? 2 * ((row & 3) | ((row >> 1) & 4)) : (row & 2) | ((row >> 1) & 4); }
 };
 
 union Pack16 {
@@ -111,9 +119,9 @@ union Pack16 {
     bf16x2 p[4];
 };
 
-__device__ __forceinline__ float other_half(float x) {
-    return __shfl_xor(x, 32, 64);   // value held by the lane 32 away
-}
+// A query's scores lie with the four lanes of equal lane % 16.
+__device__ __forceinline__ float quad_max(float x) { return lp::over_quads(x, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float quad_sum(float x) { return lp::over_quads(x, [](float a, float b) { return a + b; }); }
 
 __device__ __forceinline__ bf16x2 to_bf16x2(float lo, float hi) {
     f32x2 f = {lo, hi};
@@ -142,35 +150,30 @@ __device__ __forceinline__ int opaque(int x) {
     return x;
 }
 
+// addr += delta, here and once (the compiler would otherwise form every address of an unrolled
+// stretch anew from the first one).
+__device__ __forceinline__ void move_address(uint32_t &addr, uint32_t delta) {
+    addr += delta;
+    asm volatile("" : "+v"(addr));
+}
+
 template <typename V>
 __device__ __forceinline__ V lds_load(uint32_t addr) {
     return *LP_LDS_PTR(const V, uintptr_t(addr));
 }
 
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-__device__ __forceinline__ float max16(const f32x16 &s) {
-    float t = s[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) t = fmaxf(t, s[i]);
-    return t;
-}
-
 // What a lane needs to know to move tiles from global memory into LDS.
-template <int D, int NB>
+template <int D>
 struct Lane {
-    using T = Tile<D, NB>;
-    static constexpr int kLd = T::kInstrPerTile / T::kWaves;   // K (and V) load instructions per wave per tile
+    using T = Tile<D>;
+    static constexpr int kLd = T::kInstrPerTile / kWaves;   // K (and V) load instructions per wave per tile
     __amdgpu_buffer_rsrc_t k_rsrc, v_rsrc;   // K and V of this head as raw buffers ending with token n-1
     uint32_t k_voff[kLd], v_voff[kLd];       // byte offset of this lane's 16 bytes in tile 0
     uint32_t ld_dst[kLd];                    // LDS offset of the 1024-byte block inside a K tile (wave-uniform)
+    uint32_t ld_base[kLd];                   // lds0 + ld_dst
     uint32_t tile_bytes;                     // global byte distance between consecutive tiles
     uint32_t valid_bytes;                    // size of the K (and V) buffer of the current head: a load at or past it reads zeros and fetches nothing
-    int half;                                // lane / 32
+    int quad;                                // lane / 16
     int key_end;                             // keys at and past this index do not exist for the current segment
     int t_end;                               // one past the segment's last tile
 };
@@ -197,15 +200,24 @@ __device__ __forceinline__ void load_kv_to_lds_16(__amdgpu_buffer_rsrc_t k_rsrc,
                  : "memory", "m0", "scc");
 }
 
+// The same in two statements, one window apart: M0 for the next load (its LDS address, base + OFF), then the load.
+template <int OFF>
+__device__ __forceinline__ void set_m0(uint32_t base) {
+    asm volatile("s_add_u32 m0, %0, %1" ::"s"(base), "n"(OFF) : "memory", "m0", "scc");
+}
+__device__ __forceinline__ void load_to_lds_16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, uint32_t soff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
 // global -> LDS loads of one K/V tile into the stage at byte offset stage_off.  One
 // wave-wide instruction moves 1024 bytes.  Rows past token n-1 lie outside the buffers
 // and arrive as zeros.
-template <int D, int NB>
-__device__ __forceinline__ void issue_tile(uint32_t lds0, const Lane<D, NB> &c, int tile, uint32_t stage_off) {
-    using T = Tile<D, NB>;
+template <int D>
+__device__ __forceinline__ void issue_tile(uint32_t lds0, const Lane<D> &c, int tile, uint32_t stage_off) {
+    using T = Tile<D>;
     const uint32_t soff = uint32_t(tile) * c.tile_bytes;
 #pragma unroll
-    for (int i = 0; i < Lane<D, NB>::kLd; ++i) {
+    for (int i = 0; i < Lane<D>::kLd; ++i) {
         const uint32_t dst_k = __builtin_amdgcn_readfirstlane(lds0 + stage_off + c.ld_dst[i]);
         load_kv_to_lds_16<T::kTileBytes>(c.k_rsrc, c.v_rsrc, dst_k, c.k_voff[i], c.v_voff[i], soff);
     }
@@ -213,80 +225,78 @@ __device__ __forceinline__ void issue_tile(uint32_t lds0, const Lane<D, NB> &c, 
 
 // The I-th of a wave's kLd load statements of a tile (K block and V block), at scalar byte offset
 // soff (which takes part in the buffer's range check, like the lane's own offset).
-template <int D, int NB, int I>
-__device__ __forceinline__ void issue_tile_part(uint32_t lds0, const Lane<D, NB> &c, uint32_t soff, uint32_t stage_off) {
-    using T = Tile<D, NB>;
+template <int D, int I>
+__device__ __forceinline__ void issue_tile_part(uint32_t lds0, const Lane<D> &c, uint32_t soff, uint32_t stage_off) {
+    using T = Tile<D>;
     const uint32_t dst_k = __builtin_amdgcn_readfirstlane(lds0 + stage_off + c.ld_dst[I]);
     load_kv_to_lds_16<T::kTileBytes>(c.k_rsrc, c.v_rsrc, dst_k, c.k_voff[I], c.v_voff[I], soff);
 }
 
-// Keys past the end get score -inf.  Accumulator register i of a lane is key
-// 32*r + 16*(i/8) + 8*half + i%8.
-template <int NB>
-__device__ __forceinline__ void mask_scores(int r, int half, int n, f32x16 (&s)[NB]) {
-    const int kbase = r * 32 + half * 8;
+// Keys past the end get score -inf.  Element i of a lane's block b is key 32 r + 8 quad + 4 b + i.
+__device__ __forceinline__ void mask_scores(int r, int quad, int n, f32x4 (&s)[2][kQB]) {
+    const int kbase = r * 32 + quad * 8;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        if (kbase + 16 * (i / 8) + (i % 8) >= n) {
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) s[nb][i] = -INFINITY;
+        for (int i = 0; i < 4; ++i) {
+            const bool past = kbase + 4 * b + i >= n;
+#pragma unroll
+            for (int qb = 0; qb < kQB; ++qb) s[b][qb][i] = past ? -INFINITY : s[b][qb][i];
         }
-    }
 }
 
 // ---- the matrix instructions, with the register file of every operand chosen here.
 // A wavefront that owns 64 query rows needs more than 256 registers: the O^T accumulators
-// (D/32 * NB * 16) and the Q^T operands (NB * D/16 * 4) live in the accumulation registers
+// (D / 16 * kQB * 4) and the Q^T operands (kQB * D / 32 * 4) live in the accumulation registers
 // (AGPRs) and are touched by matrix instructions only; scores, probabilities and the LDS
 // operands live in the ordinary ones, where the vector ALU works on them.  The compiler is
 // not told what these statements are, so it neither moves operands between the two files
 // nor inserts the wait states that separate a matrix instruction's result from a vector
 // instruction reading it; settle_scores / settle_acc below do that where such a read follows.
-__device__ __forceinline__ void mfma_score_init(f32x16 &d, const bf16x8 &k, const bf16x8 &q, const f32x16 &c) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(k), "a"(q), "v"(c));
+__device__ __forceinline__ void mfma_score_init(f32x4 &d, const bf16x8 &k, const bf16x8 &q, const f32x4 &c) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %3" : "=&v"(d) : "v"(k), "a"(q), "v"(c));
 }
-__device__ __forceinline__ void mfma_score(f32x16 &d, const bf16x8 &k, const bf16x8 &q) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(k), "a"(q));
+__device__ __forceinline__ void mfma_score(f32x4 &d, const bf16x8 &k, const bf16x8 &q) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(k), "a"(q));
 }
-__device__ __forceinline__ void mfma_pv(f32x16 &acc, const bf16x8 &vt, const bf16x8 &p) {
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(vt), "v"(p));
+__device__ __forceinline__ void mfma_pv(f32x4 &acc, const bf16x8 &vt, const bf16x8 &p) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(vt), "v"(p));
 }
 
-// Ordering points for the vector work between matrix instructions.  Statements of this kind
-// keep their program order among themselves, so whatever produces x comes before this point
-// and whatever uses x afterwards comes after it; no instruction is emitted.
-__device__ __forceinline__ void pin(float &x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void pin(uint32_t &x) { asm volatile("" : "+v"(x)); }
+// The vector work between the products, likewise as assembly statements: they keep their program
+// order, so every instruction stays in the window it is written in.  (With ordering points between
+// ordinary instructions the compiler puts a wait state wherever a use directly follows such a
+// point.)  A conversion must not directly follow the exponential it reads, nor a product by
+// less than two instructions the conversion it reads; the windows keep them further apart.
+__device__ __forceinline__ void exp2_to(float &p, float s) { asm volatile("v_exp_f32 %0, %1" : "=v"(p) : "v"(s)); }
+__device__ __forceinline__ void pack_bf16(uint32_t &w, float lo, float hi) {
+    asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(w) : "v"(lo), "v"(hi));
+}
+// The row sum adds the rounded probabilities: l += 1 * lo + 1 * hi.
+__device__ __forceinline__ void add_to_row_sum(uint32_t pair, float &l) {
+    asm volatile("v_dot2c_f32_bf16 %0, %1, %2" : "+v"(l) : "s"(0x3f803f80), "v"(pair));
+}
 
 // Scores written by matrix instructions become readable by vector instructions: 16 wait
-// states cover the 8 passes of the last product plus its write-back.
-template <int NB>
-__device__ __forceinline__ void settle_scores(f32x16 (&s)[NB], bool wait) {
+// states cover the passes of the last product plus its write-back.
+__device__ __forceinline__ void settle_scores(f32x4 (&s)[2][kQB], bool wait) {
+    if (wait) asm volatile("s_nop 15");
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        if (wait) asm volatile("s_nop 15" : "+v"(s[nb]));
-        else asm volatile("" : "+v"(s[nb]));
-    }
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) asm volatile("" : "+v"(s[b][qb]));
 }
 
 // The same for the accumulators in the AGPRs (before they are rescaled or stored), and, with
 // after = true, between vector writes to them and the next matrix instruction.
-template <int D, int NB>
-__device__ __forceinline__ void settle_acc(f32x16 (&acc)[D / 32][NB], bool after) {
+template <int D>
+__device__ __forceinline__ void settle_acc(f32x4 (&acc)[D / 16][kQB], bool after) {
     if (after) asm volatile("s_nop 3");
     else asm volatile("s_nop 15\n\ts_nop 7");
 #pragma unroll
-    for (int mb = 0; mb < D / 32; ++mb)
+    for (int mb = 0; mb < D / 16; ++mb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) asm volatile("" : "+a"(acc[mb][nb]));
-}
-
-// The row sum adds the rounded probabilities.
-__device__ __forceinline__ void add_to_row_sum(uint32_t pair, float &l) {
-    union { bf16x2 p; uint32_t u; } w;
-    w.u = pair;
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    l = __builtin_amdgcn_fdot2_f32_bf16(w.p, ones, l, false);
+        for (int qb = 0; qb < kQB; ++qb) asm volatile("" : "+a"(acc[mb][qb]));
 }
 
 // Lazy running maximum.  Score accumulators start at neg_m = -m (m = running maximum, log2
@@ -294,134 +304,121 @@ __device__ __forceinline__ void add_to_row_sum(uint32_t pair, float &l) {
 // exceeds kRescaleThreshold, raise the maximum by delta and rescale what was accumulated
 // under the old one: these scores, the output accumulators, the row sums, and the
 // probabilities p_pending that have been computed but not yet multiplied into acc.
-template <int D, int NB>
-__device__ __forceinline__ void raise_maximum(const float (&lane_max)[NB], f32x16 (&s)[NB], f32x16 (&neg_m)[NB],
-                                              bf16x8 (&p_pending)[NB][2], f32x16 (&acc)[D / 32][NB], float (&l_run)[NB]) {
+template <int D>
+__device__ __forceinline__ void raise_maximum(const float (&lane_max)[kQB], f32x4 (&s)[2][kQB], f32x4 (&neg_m)[kQB],
+                                              bf16x8 (&p_pending)[kQB], f32x4 (&acc)[D / 16][kQB], float (&l_run)[kQB][row_sums(D)]) {
     bool raise = false;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) raise = raise || (lane_max[nb] > kRescaleThreshold);
+    for (int qb = 0; qb < kQB; ++qb) raise = raise || (lane_max[qb] > kRescaleThreshold);
     if (__builtin_expect(__any(raise) != 0, 0)) {     // the branch body is laid out away from the loop
-        settle_acc<D, NB>(acc, false);
+        settle_acc<D>(acc, false);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            float tmax = lane_max[nb];
-            tmax = fmaxf(tmax, other_half(tmax));
-            const float delta = fmaxf(tmax, 0.0f);           // the maximum never goes down
+        for (int qb = 0; qb < kQB; ++qb) {
+            const float delta = fmaxf(quad_max(lane_max[qb]), 0.0f);           // the maximum never goes down
             const float alpha = __builtin_amdgcn_exp2f(-delta);
-            l_run[nb] *= alpha;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                s[nb][i] -= delta;
-                neg_m[nb][i] -= delta;
+            for (int e = 0; e < row_sums(D); ++e) l_run[qb][e] *= alpha;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s[0][qb][i] -= delta;
+                s[1][qb][i] -= delta;
+                neg_m[qb][i] -= delta;
             }
 #pragma unroll
-            for (int mb = 0; mb < D / 32; ++mb)
+            for (int mb = 0; mb < D / 16; ++mb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[mb][nb][i] *= alpha;
+                for (int i = 0; i < 4; ++i) acc[mb][qb][i] *= alpha;
+            Pack16 t;
+            t.v = p_pending[qb];
+            const uint32_t w[4] = {t.u.x, t.u.y, t.u.z, t.u.w};
 #pragma unroll
-            for (int ks = 0; ks < 2; ++ks) {
-                Pack16 t;
-                t.v = p_pending[nb][ks];
-                const uint32_t w[4] = {t.u.x, t.u.y, t.u.z, t.u.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    t.p[e] = to_bf16x2(__uint_as_float(w[e] << 16) * alpha, __uint_as_float(w[e] & 0xffff0000u) * alpha);
-                p_pending[nb][ks] = t.v;
-            }
+            for (int e = 0; e < 4; ++e)
+                t.p[e] = to_bf16x2(__uint_as_float(w[e] << 16) * alpha, __uint_as_float(w[e] & 0xffff0000u) * alpha);
+            p_pending[qb] = t.v;
         }
-        settle_acc<D, NB>(acc, true);
+        settle_acc<D>(acc, true);
     }
 }
 
-// One K operand (16 bytes of a K row) from LDS: SUB selects the first or second round of
-// the tile whose operand addresses are k_addr.
-template <int D, int NB, int SUB>
-__device__ __forceinline__ bf16x8 load_k_operand(const uint32_t (&k_addr)[D / 16], int kk) {
-    return lds_load<bf16x8>(k_addr[kk] + SUB * 32 * Tile<D, NB>::kRowBytes);
+// One K operand (16 bytes of a K row) from LDS: operand g is block g % 2 of the d-step g / 2; SUB
+// selects the first or second round of the tile OFF bytes after the one k_addr points into.
+template <int D, int SUB, int OFF>
+__device__ __forceinline__ bf16x8 load_k_operand(const uint32_t (&k_addr)[D / 32], int g) {
+    return lds_load<bf16x8>(k_addr[g / 2] + OFF + (SUB * 32 + 4 * (g % 2)) * Tile<D>::kRowBytes);
 }
 
 // One V^T operand via two transposing reads.  Inside a group of 16 lanes, lane j supplies
 // the 8-byte chunk (row j/4, columns 4*(j%4)..+3) and receives column j of that 4x16 block,
-// i.e. 4 consecutive keys of one d.  Operand j covers keys 16*(j / MB).. of the round and
-// rows 32*(j % MB).. of O^T; HALF selects its first or second four keys.
-template <int D, int NB, int SUB, int HALF>
-__device__ __forceinline__ bf16x4 load_v_half(const uint32_t (&v_addr)[D / 32], int j) {
-    using T = Tile<D, NB>;
-    constexpr int MB = D / 32;
-    const uint32_t a0 = v_addr[j % MB] + (SUB * 32 + (j / MB) * 16 + HALF * 4) * T::kRowBytes;
+// i.e. 4 consecutive keys of one d.  Operand mb covers the round's 32 keys and rows 16 mb .. of
+// O^T; HALF selects the first or second four of a lane's eight keys.
+template <int D, int SUB, int HALF, int OFF>
+__device__ __forceinline__ bf16x4 load_v_half(const uint32_t (&v_addr)[D / 16], int mb) {
+    const uint32_t a0 = v_addr[mb] + OFF + (SUB * 32 + HALF * 4) * Tile<D>::kRowBytes;
     return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LP_LDS_PTR(bf16x4, uintptr_t(a0)));
 }
 
 // Everything one wavefront carries from step to step.
-template <int D, int NB>
+template <int D>
 struct Pipe {
-    bf16x8 qreg[NB][D / 16];       // Q^T operands (pre-scaled)
+    bf16x8 qreg[kQB][D / 32];      // Q^T operands (pre-scaled)
     bf16x8 opreg[D / 16];          // LDS operands: K rows before a score product, V^T blocks before a PV product
-    f32x16 acc[D / 32][NB];        // O^T accumulators
-    f32x16 neg_m[NB];              // -m in every element (m = running maximum, log2 units, common to
-                                   // both half-waves): the initial value of every score accumulator
-    float l_run[NB];               // this lane's share of the running sum
-    uint32_t k_addr[D / 16];       // LDS addresses of the K operands in the stage at k_off
-    uint32_t v_addr[D / 32];       // LDS addresses of the V operands in the stage at v_off
+    f32x4 acc[D / 16][kQB];        // O^T accumulators
+    f32x4 neg_m[kQB];              // -m in every element (m = running maximum, log2 units, common to
+                                   // the four lanes of a query): the initial value of every score accumulator
+    float l_run[kQB][row_sums(D)]; // this lane's share of the running sum
+    uint32_t k_addr[D / 32];       // LDS addresses of the K operands in the stage at k_off
+    uint32_t v_addr[D / 16];       // LDS addresses of the V operands in the stage at v_off
     uint32_t k_off, v_off;         // stage offsets k_addr / v_addr currently point into
     uint32_t tile_off;             // stage offset of tile i/2
     uint32_t issue_off;            // stage offset the next issued tile goes to
     int issue_t;                   // index of the next tile to issue
 };
 
-// Writes this wave's 32 result rows (acc scaled by `inv`, rounded to bf16) to rows
+// Writes 16 result rows of this wave (block qb of acc scaled by `inv`, rounded to bf16) to rows
 // dst + r * row_stride, r < rows_valid.  A lane holds, for query `col`, rows
-// d = 32*mb + 8*(i/4) + 4*half + i%4 of O^T, i.e. 8-byte pieces of many rows; the pieces
-// pass through the wave's own 4 KB of LDS (64 d at a time, 16-byte granules XORed with
-// the row so that both directions are conflict free) and leave as whole 128-byte lines.
-template <int D, int NB>
-__device__ __forceinline__ void store_rows(uint32_t out_lds, const f32x16 (&acc)[D / 32][NB], int nb, float inv, __bf16 *dst,
+// d = 16 mb + 4 quad + i of O^T, i.e. 8-byte pieces of many rows; the pieces pass through the
+// wave's own LDS (16-byte granules XORed with the row) and leave as whole 128-byte lines.
+template <int D>
+__device__ __forceinline__ void store_rows(uint32_t out_lds, const f32x4 (&acc)[D / 16][kQB], int qb, float inv, __bf16 *dst,
                                            int64_t row_stride, int rows_valid, int lane) {
-    const int col = lane % 32, half = lane / 32;
+    constexpr int kGran = Tile<D>::kGran;
+    const int col = lane % 16, quad = lane / 16;
 #pragma unroll
-    for (int pass = 0; pass < D / 64; ++pass) {
+    for (int mb = 0; mb < D / 16; ++mb) {
+        const f32x4 &x = acc[mb][qb];
+        union { u32x2 u; bf16x2 p[2]; } ow;
+        ow.p[0] = to_bf16x2(x[0] * inv, x[1] * inv);
+        ow.p[1] = to_bf16x2(x[2] * inv, x[3] * inv);
+        *LP_LDS_PTR(u32x2, uintptr_t(out_lds + col * Tile<D>::kRowBytes + 16 * ((2 * mb + quad / 2) ^ (col % kGran)) + 8 * (quad % 2))) = ow.u;
+    }
 #pragma unroll
-        for (int mbl = 0; mbl < 2; ++mbl)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const f32x16 &x = acc[2 * pass + mbl][nb];
-                union { u32x2 u; bf16x2 p[2]; } ow;
-                ow.p[0] = to_bf16x2(x[4 * g + 0] * inv, x[4 * g + 1] * inv);
-                ow.p[1] = to_bf16x2(x[4 * g + 2] * inv, x[4 * g + 3] * inv);
-                *LP_LDS_PTR(u32x2, uintptr_t(out_lds + col * 128 + 16 * ((4 * mbl + g) ^ (col & 7)) + 8 * half)) = ow.u;
-            }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = lane / 8 + 8 * j, gran = lane % 8;
-            const u32x4 u = lds_load<u32x4>(out_lds + r * 128 + 16 * (gran ^ (r & 7)));
-            if (r < rows_valid) *reinterpret_cast<u32x4 *>(dst + r * row_stride + 64 * pass + 8 * gran) = u;
-        }
+    for (int j = 0; j < 16 * kGran / 64; ++j) {
+        const int r = (lane + 64 * j) / kGran, g = lane % kGran;
+        const u32x4 u = lds_load<u32x4>(out_lds + r * Tile<D>::kRowBytes + 16 * (g ^ (r % kGran)));
+        if (r < rows_valid) *reinterpret_cast<u32x4 *>(dst + r * row_stride + 8 * g) = u;
     }
 }
 
-// The part of the softmax that trails the exponentials: converts the pairs [CVT_FROM, CVT_TO)
-// to packed bf16 words (and completes an operand with its fourth word), then adds the words
-// [SUM_FROM, CVT_FROM) to the row sums.  Pair k holds scores 2 k, 2 k + 1 counted across both
-// blocks: word k % 4 of operand (k % 8) / 4 of block k / 8.
-template <int NB, int CVT_TO, int CVT_FROM, int SUM_FROM>
-__device__ __forceinline__ void vector_tail(const float (&ex)[NB * 16], uint32_t (&pw)[NB][2][4], bf16x8 (&p_cur)[NB][2],
-                                            float (&l_run)[NB]) {
-    static_for<CVT_FROM, CVT_TO>([&](auto kc) {
-        constexpr int k = decltype(kc)::value, nb = k / 8, part = (k % 8) / 4, e = k % 4;
-        union { bf16x2 p; uint32_t u; } cv;
-        cv.p = to_bf16x2(ex[2 * k], ex[2 * k + 1]);
-        pw[nb][part][e] = cv.u;
-        pin(pw[nb][part][e]);
+// The part of the softmax that trails the exponentials.  Pair k holds scores 2 k, 2 k + 1 counted block
+// by block: word k % 4 of the operand of query block k / 4.  convert_pairs rounds the pairs [FROM, TO)
+// to packed bf16 words (and completes an operand with its fourth word), sum_pairs adds them to the row sums.
+template <int FROM, int TO>
+__device__ __forceinline__ void convert_pairs(const float (&ex)[kQB * 8], uint32_t (&pw)[kQB][4], bf16x8 (&p_cur)[kQB]) {
+    static_for<FROM, TO>([&](auto kc) {
+        constexpr int k = decltype(kc)::value, qb = k / 4, e = k % 4;
+        pack_bf16(pw[qb][e], ex[2 * k], ex[2 * k + 1]);
         if constexpr (e == 3) {
             Pack16 t;
-            t.u = make_uint4(pw[nb][part][0], pw[nb][part][1], pw[nb][part][2], pw[nb][part][3]);
-            p_cur[nb][part] = t.v;
+            t.u = make_uint4(pw[qb][0], pw[qb][1], pw[qb][2], pw[qb][3]);
+            p_cur[qb] = t.v;
         }
     });
-    static_for<SUM_FROM, CVT_FROM>([&](auto kc) {
+}
+template <int FROM, int TO, int SUMS>
+__device__ __forceinline__ void sum_pairs(const uint32_t (&pw)[kQB][4], float (&l_run)[kQB][SUMS]) {
+    static_for<FROM, TO>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        add_to_row_sum(pw[k / 8][(k % 8) / 4][k % 4], l_run[k / 8]);
-        pin(l_run[k / 8]);
+        add_to_row_sum(pw[k / 4][k % 4], l_run[k / 4][k % SUMS]);
     });
 }
 
@@ -447,12 +444,15 @@ __device__ __forceinline__ uint32_t next_stage(uint32_t off) {
 // the products issued for rounds that do not exist add nothing; their operands are read
 // from valid, if stale, LDS addresses.  MASK = false is for steps whose rounds i+1 lie
 // wholly inside the segment and keeps the step free of conditionals.
-template <int D, int NB, int SUB, bool MASK, bool CHECK>
-__device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D, NB> &c, int i, bool first,
-                                              Pipe<D, NB> &w, f32x16 (&s_cur)[NB], f32x16 (&s_nxt)[NB],
-                                              bf16x8 (&p_prev)[NB][2], bf16x8 (&p_cur)[NB][2]) {
-    using T = Tile<D, NB>;
-    constexpr int KS = D / 16, MB = D / 32;
+//
+// STAGE >= 0: tile i/2 lies in that LDS stage, known at compile time (the unrolled part of a segment,
+// see run_segment): operand addresses then differ between stages by an instruction's offset, and
+// by kReach stages where that does not reach.
+template <int D, int SUB, bool MASK, bool CHECK, int STAGE = -1>
+__device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, int i, bool first,
+                                              Pipe<D> &w, f32x4 (&s_cur)[2][kQB], f32x4 (&s_nxt)[2][kQB],
+                                              bf16x8 (&p_prev)[kQB], bf16x8 (&p_cur)[kQB]) {
+    using T = Tile<D>;
     // Per-tile bookkeeping is scalar and happens here; what it decides is carried out inside the
     // windows below, so that no stretch of the step is without a product to issue:
     //  * SUB == 0 opens tile t+1 (t = i/2).  Its K operands are first fetched in the PV phase, so
@@ -465,8 +465,22 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D, NB> &
     //    unless it lies past the segment and was never loaded (its probabilities are 0, and 0
     //    times whatever an unwritten stage holds need not be 0); each V operand address moves
     //    right before its first fetch of the step.
+    constexpr bool kFixed = STAGE >= 0;
+    constexpr int kKStage = (STAGE + 1) % kStages, kVStage = SUB == 0 ? (STAGE + kStages - 1) % kStages : STAGE;
+    constexpr int kKOff = kFixed ? (kKStage % T::kReach) * T::kStageBytes : 0, kVOff = kFixed ? (kVStage % T::kReach) * T::kStageBytes : 0;
+    // in the unrolled part: the step to the next kReach stages, taken by the fetch that enters them
+    constexpr uint32_t kHop = T::kReach * T::kStageBytes;
+    constexpr bool kKHop = kFixed && T::kReach < kStages && SUB == 0 && kKStage % T::kReach == 0;
+    constexpr bool kVHop = kFixed && T::kReach < kStages && SUB == 1 && STAGE % T::kReach == 0;
     uint32_t k_delta = 0, v_delta = 0, issue_soff = 0, issue_stage = 0;
-    if (SUB == 0) {
+    if (kFixed) {
+        k_delta = kKStage == 0 ? 0u - (kStages / T::kReach - 1) * kHop : kHop;
+        v_delta = STAGE == 0 ? 0u - (kStages / T::kReach - 1) * kHop : kHop;
+        if (SUB == 0) {
+            issue_soff = w.issue_t < c.t_end ? uint32_t(w.issue_t) * c.tile_bytes : c.valid_bytes;
+            ++w.issue_t;
+        }
+    } else if (SUB == 0) {
         if (!first) w.tile_off = next_stage<T::kStageBytes>(w.tile_off);
         const uint32_t nxt_off = next_stage<T::kStageBytes>(w.tile_off);
         k_delta = nxt_off - w.k_off;       // wraps; the sums do not
@@ -482,96 +496,100 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D, NB> &
         }
     }
 
-    // The step's 2 KS NB products, in KS score groups and then KS PV groups (a group is the
-    // NB products that share one LDS operand).  The wavefront is alone on its SIMD, so the
-    // matrix pipeline is busy only if the next product is issued within the 8 passes of the
-    // one before: the vector and LDS work of the step is therefore cut into one window per
-    // product -- the exponentials of round i (8 / KS per window), a conversion and a row-sum
-    // update for every second of them, the refill of the operand registers the group has just
-    // read (half a V^T operand or one K operand per window), in even steps a quarter of the next
-    // tile's loads in every second PV group, and, from four windows after the last score product
-    // to the end of the step, the per-lane maximum of round i+1's scores.
-    static_assert(NB == 2, "the windows below are laid out for two 32-row blocks per wavefront");
-    constexpr int M = 2 * KS * NB;              // products per step
-    constexpr int X = (NB * 16) / M;            // exponentials per window
-    // the maximum of round i+1's scores: from four windows after its last product (whose result
-    // has then left the pipeline) to the end of the step, both blocks in turn
-    constexpr int kMaxFrom = KS * NB + 4, kMaxWin = (M - kMaxFrom) / NB;   // windows per block
-    uint32_t pw[NB][2][4];
-    float ex[NB * 16];
-    float lane_max[NB];
+    // The step's products come in G score groups and then G PV groups (a group is the kQB products
+    // that share one LDS operand).  The wavefront is alone on its SIMD, so the matrix pipeline is
+    // busy only if the next product is issued before the one before it has passed: the vector
+    // and LDS work of the step is therefore cut into one small window per product -- the
+    // exponentials of round i, a conversion and a row-sum update for every second of them, the
+    // refill of the operand registers the group has just read (half a V^T operand or a K operand
+    // per window), in even steps the next tile's loads.  In a window the softmax work comes before the
+    // product and the LDS fetch directly after it: with the exponential between product and fetch the
+    // same instructions took 7 % longer.
+    constexpr int G = D / 16;                   // groups per phase
+    constexpr int M = 2 * G * kQB;              // products per step
+    constexpr int E = kQB * 8;                  // exponentials per step
+    constexpr int PP = row_sums(D);             // pairs of scores per group
+    static_assert(E == 4 * G * PP, "the exponentials fill the groups");
+    uint32_t pw[kQB][4];
+    float ex[E];
     Pack16 vop;
+    // The softmax work of a window: of the pairs of group g the exponentials, of those of the group before
+    // the conversions, of those of the one before that the row sums.
+    auto softmax_window = [&](auto mc) {
+        constexpr int m = decltype(mc)::value, g = m / kQB, qb = m % kQB;
+        if constexpr (PP == 2 || qb % 2 == 1) {
+            constexpr int x = PP == 1 ? 2 * g + qb / 2 : 4 * g + qb;
+            exp2_to(ex[x], s_cur[(x / 4) % 2][x / 8][x % 4]);
+        }
+        constexpr int cvt = PP * (g - 1) + qb, dot = PP * (g - 2) + qb - PP;
+        if constexpr (g > 0 && qb < PP) convert_pairs<cvt, cvt + 1>(ex, pw, p_cur);
+        if constexpr (g > 1 && qb >= PP && qb < 2 * PP) sum_pairs<dot, dot + 1, PP>(pw, w.l_run);
+    };
     static_for<0, M>([&](auto mc) {
-        constexpr int m = decltype(mc)::value, g = m / NB, nb = m % NB;
+        constexpr int m = decltype(mc)::value, g = m / kQB, qb = m % kQB;
+        softmax_window(mc);
         // Operand arrivals are checked for half a phase at a time.  In issue order the LDS queue
-        // holds, at the start of the score phase, the KS K fetches of the previous PV phase: all
-        // but the newest KS/2 cover groups 0 .. KS/2-1; by group KS/2 the newest are KS/2 groups
-        // of V fetches (2 each), so lgkmcnt(KS) covers the rest.  The PV phase mirrors this with
-        // 2 KS V fetches followed by one K fetch per group.
-        if constexpr (nb == 0 && g == 0) lds_wait<KS / 2>();
-        if constexpr (nb == 0 && g == KS / 2) lds_wait<KS>();
-        if constexpr (nb == 0 && g == KS) lds_wait<KS>();
-        if constexpr (nb == 0 && g == KS + KS / 2) lds_wait<KS / 2>();
-        if constexpr (g < KS) {
-            if constexpr (g == 0) mfma_score_init(s_nxt[nb], w.opreg[g], w.qreg[nb][g], w.neg_m[nb]);
-            else mfma_score(s_nxt[nb], w.opreg[g], w.qreg[nb][g]);
-            if constexpr (SUB == 1 && nb == 0 && g < MB) w.v_addr[g] += v_delta;
-            if constexpr (nb == 0) vop.h[0] = load_v_half<D, NB, 1 - SUB, 0>(w.v_addr, g);
-            else {
-                vop.h[1] = load_v_half<D, NB, 1 - SUB, 1>(w.v_addr, g);
+        // holds, at the start of the score phase, the G K fetches of the previous PV phase: all
+        // but the newest G/2 cover groups 0 .. G/2-1; by group G/2 the newest are G/2 groups
+        // of V fetches (2 each), so lgkmcnt(G) covers the rest.  The PV phase mirrors this with
+        // 2 G V fetches followed by one K fetch per group.
+        if constexpr (qb == 0 && g == 0) lds_wait<G / 2>();
+        if constexpr (qb == 0 && g == G / 2) lds_wait<G>();
+        if constexpr (qb == 0 && g == G) lds_wait<G>();
+        if constexpr (qb == 0 && g == G + G / 2) lds_wait<G / 2>();
+        if constexpr (g < G) {
+            if constexpr (g < 2) mfma_score_init(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][0], w.neg_m[qb]);
+            else mfma_score(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][g / 2]);
+            if constexpr (qb == 0 && (kFixed ? kVHop : SUB == 1)) move_address(w.v_addr[g], v_delta);
+            if constexpr (qb == kQB - 2) vop.h[0] = load_v_half<D, 1 - SUB, 0, kVOff>(w.v_addr, g);
+            if constexpr (qb == kQB - 1) {
+                vop.h[1] = load_v_half<D, 1 - SUB, 1, kVOff>(w.v_addr, g);
                 w.opreg[g] = vop.v;
             }
         } else {
-            constexpr int j = g - KS;
-            mfma_pv(w.acc[j % MB][nb], w.opreg[j], p_prev[nb][j / MB]);
-            if constexpr (nb == NB - 1) {
-                if constexpr (SUB == 0) w.k_addr[j] += k_delta;
-                w.opreg[j] = load_k_operand<D, NB, SUB>(w.k_addr, j);
-            } else if constexpr (SUB == 0 && nb == 0) {
-                // the tile's load statements, evenly over the PV groups
-                constexpr int kLd = Lane<D, NB>::kLd, every = KS / kLd;
-                if constexpr (j % every == 0) issue_tile_part<D, NB, j / every>(lds0, c, issue_soff, issue_stage);
+            constexpr int j = g - G;
+            mfma_pv(w.acc[j][qb], w.opreg[j], p_prev[qb]);
+            // the tile's load statements, evenly over the PV groups
+            constexpr int kLd = Lane<D>::kLd, every = G / kLd, ld = j / every;
+            if constexpr (qb == kQB - 1) {
+                if constexpr (j % 2 == 0 && (kFixed ? kKHop : SUB == 0)) move_address(w.k_addr[j / 2], k_delta);
+                w.opreg[j] = load_k_operand<D, SUB, kKOff>(w.k_addr, j);
+            } else if constexpr (SUB == 0 && j % every == 0) {
+                if constexpr (!kFixed) {
+                    if constexpr (qb == 0) issue_tile_part<D, ld>(lds0, c, issue_soff, issue_stage);
+                } else {
+                    constexpr int kDst = ((STAGE + kStages - 2) % kStages) * T::kStageBytes;
+                    if constexpr (qb == 0) set_m0<kDst>(c.ld_base[ld]);
+                    if constexpr (qb == 1) {
+                        load_to_lds_16(c.k_rsrc, c.k_voff[ld], issue_soff);
+                        set_m0<kDst + T::kTileBytes>(c.ld_base[ld]);
+                    }
+                    if constexpr (qb == 2) load_to_lds_16(c.v_rsrc, c.v_voff[ld], issue_soff);
+                }
             }
         }
-        if constexpr (SUB == 0 && m == KS * NB - 1) {
-            wait_tile_loads<0>();              // tile t+1, issued one tile ago
-            __syncthreads();
+        if constexpr (SUB == 0 && m == G * kQB - 1) {
+            // tile t+1, issued one tile ago; what is still on its way from LDS is V of tile t-1
+            asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         }
-        // exponentials x = m X .. of the round's NB * 16 scores.  A pair is converted in the
-        // window after its second exponential (a conversion must not directly follow the
-        // exponential it reads) and joins the row sum one window later.
-        static_for<m * X, (m + 1) * X>([&](auto xc) {
-            constexpr int x = decltype(xc)::value;
-            float sc = s_cur[x / 16][x % 16];
-            pin(sc);
-            ex[x] = __builtin_amdgcn_exp2f(sc);
-        });
-        vector_tail<NB, m * X / 2, (m > 0 ? (m - 1) * X / 2 : 0), (m > 1 ? (m - 2) * X / 2 : 0)>(ex, pw, p_cur, w.l_run);
-        static_for<m * X, (m + 1) * X>([&](auto xc) { pin(ex[decltype(xc)::value]); });
-        if constexpr (m == kMaxFrom - 1) {
-            settle_scores<NB>(s_nxt, false);
-            if (MASK) mask_scores<NB>(i + 1, c.half, c.key_end, s_nxt);
-        }
-        if constexpr (CHECK && m >= kMaxFrom) {
-            constexpr int wdx = m - kMaxFrom, nbm = wdx % NB, first = (16 * (wdx / NB)) / kMaxWin;
-            // three-operand maxima, written out so that no operand is first passed through a
-            // quieting v_max (the scores come from assembly statements, so the compiler cannot
-            // tell that they are ordinary numbers)
-            float mx = first == 0 ? s_nxt[nbm][0] : lane_max[nbm];
-            constexpr int lo = first == 0 ? 1 : first, hi = (16 * (wdx / NB + 1)) / kMaxWin;
-            static_for<0, (hi - lo) / 2>([&](auto rc) {
-                constexpr int r = lo + 2 * decltype(rc)::value;
-                mx = max3(mx, s_nxt[nbm][r], s_nxt[nbm][r + 1]);
-            });
-            if constexpr ((hi - lo) % 2 == 1) mx = max3(mx, s_nxt[nbm][hi - 1], s_nxt[nbm][hi - 1]);
-            lane_max[nbm] = mx;
-            pin(lane_max[nbm]);
+        if constexpr (m == G * kQB + 2 * kQB) {        // the last score product has left the pipeline
+            settle_scores(s_nxt, false);
+            if (MASK) mask_scores(i + 1, c.quad, c.key_end, s_nxt);
         }
     });
-    // what the last two windows left to convert and to add
-    vector_tail<NB, NB * 8, (M - 1) * X / 2, (M - 2) * X / 2>(ex, pw, p_cur, w.l_run);
-    vector_tail<NB, NB * 8, NB * 8, (M - 1) * X / 2>(ex, pw, p_cur, w.l_run);
-    if constexpr (CHECK) raise_maximum<D, NB>(lane_max, s_nxt, w.neg_m, p_cur, w.acc, w.l_run);
+    // what the last groups left to convert and to add
+    convert_pairs<E / 2 - PP, E / 2>(ex, pw, p_cur);
+    sum_pairs<E / 2 - 2 * PP, E / 2, PP>(pw, w.l_run);
+    if constexpr (CHECK) {                     // the repeated run only, see run_segment
+        float lane_max[kQB];
+#pragma unroll
+        for (int qb = 0; qb < kQB; ++qb) {
+            lane_max[qb] = s_nxt[0][qb][0];
+#pragma unroll
+            for (int e = 1; e < 8; ++e) lane_max[qb] = fmaxf(lane_max[qb], s_nxt[e / 4][qb][e % 4]);
+        }
+        raise_maximum<D>(lane_max, s_nxt, w.neg_m, p_cur, w.acc, w.l_run);
+    }
 }
 
 // Launch parameters.  A unit is one 256-row query tile of one head; every unit walks
@@ -670,10 +688,10 @@ __device__ __forceinline__ Segment next_segment(Walk &k, const AttnParams &a, ui
 // Points the tile traffic at a segment and sends for its first kStages-2 tiles (the
 // segment's tiles use the LDS stages in turn, from stage 0).  The caller has made sure
 // that no wave still reads the stages.
-template <int D, int NB>
+template <int D>
 __device__ __forceinline__ void start_tiles(uint32_t lds0, const AttnParams &a, const Segment &seg,
-                                            Lane<D, NB> &c, Pipe<D, NB> &w, int n, int64_t stride_tok) {
-    using T = Tile<D, NB>;
+                                            Lane<D> &c, Pipe<D> &w, int n, int64_t stride_tok) {
+    using T = Tile<D>;
     const int64_t head_off = head_offset(a, int(seg.unit) / a.n_qtiles);
     c.key_end = min(n, seg.t_stop * kBN);
     c.t_end = seg.t_stop;
@@ -690,39 +708,38 @@ __device__ __forceinline__ void start_tiles(uint32_t lds0, const AttnParams &a, 
     w.issue_t = seg.t_begin;
 #pragma unroll
     for (int t = 0; t < kStages - 2; ++t) {
-        if (w.issue_t < c.t_end) issue_tile<D, NB>(lds0, c, w.issue_t, w.issue_off);
+        if (w.issue_t < c.t_end) issue_tile<D>(lds0, c, w.issue_t, w.issue_off);
         w.issue_off += T::kStageBytes;
         ++w.issue_t;
     }
 }
 
-// Loads a segment's raw Q rows: a lane holds, for query `col`, d = 16*kk + 8*half .. +7.
-template <int D, int NB>
-__device__ __forceinline__ void load_q(const AttnParams &a, const Segment &seg, Pipe<D, NB> &w, int n,
-                                       int64_t stride_tok, int wave, int col, int half) {
+// Loads a segment's raw Q rows: a lane holds, for query `col` of a block, d = 32 kk + 8 quad .. +7.
+template <int D>
+__device__ __forceinline__ void load_q(const AttnParams &a, const Segment &seg, Pipe<D> &w, int n,
+                                       int64_t stride_tok, int wave, int col, int quad) {
     const int head = int(seg.unit) / a.n_qtiles;
     const int qtile = int(seg.unit) % a.n_qtiles;
     const __bf16 *qh = a.q + head_offset(a, head);
-    const int q0 = qtile * kBM + wave * (32 * NB);
+    const int q0 = qtile * kBM + wave * (16 * kQB);
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int qi = q0 + nb * 32 + col;
+    for (int qb = 0; qb < kQB; ++qb) {
+        const int qi = q0 + qb * 16 + col;
 #pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) {
+        for (int kk = 0; kk < D / 32; ++kk) {
             Pack16 t;
             t.u = make_uint4(0, 0, 0, 0);
-            if (qi < n) t.u = *reinterpret_cast<const uint4 *>(qh + int64_t(qi) * stride_tok + kk * 16 + half * 8);
-            w.qreg[nb][kk] = t.v;
+            if (qi < n) t.u = *reinterpret_cast<const uint4 *>(qh + int64_t(qi) * stride_tok + kk * 32 + quad * 8);
+            w.qreg[qb][kk] = t.v;
         }
     }
 }
 
-template <int D, int NB>
-__global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const AttnParams a) {
-    using T = Tile<D, NB>;
-    using L = Lane<D, NB>;
-    constexpr int KS = D / 16;        // MFMA steps along d for S^T
-    constexpr int MB = D / 32;        // 32-row blocks of O^T
+template <int D>
+__global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams a) {
+    using T = Tile<D>;
+    using L = Lane<D>;
+    constexpr int G = D / 16;         // LDS operands per phase: (block, d-step) of S^T, 16-row blocks of O^T
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const uint32_t lds0 = uint32_t(uintptr_t(LP_LDS_PTR(unsigned char, smem)));
 
@@ -730,22 +747,23 @@ __global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const Attn
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int lane_id = tid % 64;
     const int lane = lane_id;
-    const int col = lane % 32;        // MFMA column (query) / A-operand row
-    const int half = lane / 32;
+    const int col = lane % 16;        // MFMA column (query) / A-operand row
+    const int quad = lane / 16;
     const int n = a.n;
     const int64_t stride_tok = a.stride_tok;
     const int n_rounds = (n + 31) / 32;
 
     // ---- lane constants of the tile traffic
     L c;
-    c.half = half;
+    c.quad = quad;
     c.tile_bytes = uint32_t(kBN * stride_tok * 2);
 #pragma unroll
     for (int i = 0; i < L::kLd; ++i) {
-        const int instr = wave + i * T::kWaves;
+        const int instr = wave + i * kWaves;
         const int row = instr * T::kRowsPerInstr + lane / T::kGran;
         const int gran = lane % T::kGran;          // physical granule this lane fills
         c.ld_dst[i] = instr * 1024;
+        c.ld_base[i] = __builtin_amdgcn_readfirstlane(lds0 + instr * 1024);
         c.k_voff[i] = uint32_t(row * stride_tok * 2) + 16 * (gran ^ T::swz_k(row));
         c.v_voff[i] = uint32_t(row * stride_tok * 2) + 16 * (gran ^ T::swz_v(row));
     }
@@ -763,9 +781,9 @@ __global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const Attn
 
     Segment seg = next_segment(walk, a, tpu, lp, gridDim.x);
     if (!seg.valid) return;
-    Pipe<D, NB> w;
-    start_tiles<D, NB>(lds0, a, seg, c, w, n, stride_tok);
-    load_q<D, NB>(a, seg, w, n, stride_tok, wave, col, half);
+    Pipe<D> w;
+    start_tiles<D>(lds0, a, seg, c, w, n, stride_tok);
+    load_q<D>(a, seg, w, n, stride_tok, wave, col, quad);
 
     while (true) {
         const int qtile = int(seg.unit) % a.n_qtiles;
@@ -776,25 +794,25 @@ __global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const Attn
 
         // ---- Q^T operands arrive raw; multiply by scale*log2(e) and round to bf16 again
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+        for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk) {
+            for (int kk = 0; kk < D / 32; ++kk) {
                 Pack16 t;
-                t.v = w.qreg[nb][kk];
+                t.v = w.qreg[qb][kk];
                 const uint32_t u[4] = {t.u.x, t.u.y, t.u.z, t.u.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e)   // a bf16 is the upper half of the binary32 with the same value
                     t.p[e] = to_bf16x2(__uint_as_float(u[e] << 16) * a.scale_log2e,
                                        __uint_as_float(u[e] & 0xffff0000u) * a.scale_log2e);
-                w.qreg[nb][kk] = t.v;
+                w.qreg[qb][kk] = t.v;
             }
         // the Q^T operands now live in AGPRs for the whole segment (left to itself the register
         // allocator may keep them elsewhere and copy each into one shared AGPR quad right before
         // its product, overwriting the quad the product issued just before is still reading)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+        for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk) asm volatile("" : "+a"(w.qreg[nb][kk]));
+            for (int kk = 0; kk < D / 32; ++kk) asm volatile("" : "+a"(w.qreg[qb][kk]));
 
         // ---- the segment's rounds.  Run first without the running-maximum check (CHECK = false):
         // the maximum stays what the first round made it, a probability is exp2 of whatever the
@@ -806,14 +824,14 @@ __global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const Attn
         auto run_segment = [&](auto checked_c) {
         constexpr bool CHECK = decltype(checked_c)::value;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < G; ++mb)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
+            for (int qb = 0; qb < kQB; ++qb) w.acc[mb][qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int r = 0; r < 16; ++r) w.acc[mb][nb][r] = 0.0f;
+        for (int qb = 0; qb < kQB; ++qb)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) w.l_run[nb] = 0.0f;
-        settle_acc<D, NB>(w.acc, true);
+            for (int e = 0; e < row_sums(D); ++e) w.l_run[qb][e] = 0.0f;
+        settle_acc<D>(w.acc, true);
 
         // ---- LDS operand addresses in stage 0 (recomputed from an opaque copy of the lane
         // index: kept as loop invariants they would be held in registers through the pipeline)
@@ -821,70 +839,92 @@ __global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const Attn
         w.k_off = 0;
         w.v_off = 0;
         {
-            const int lane = opaque(lane_id), col = lane % 32, half = lane / 32;
-            // K operand: row = col with bits 2 and 3 swapped, so that accumulator register i
-            // of a lane is key 16*(i/8) + 8*half + i%8 of the round
-            const int krow = (col & 0x13) | ((col & 4) << 1) | ((col & 8) >> 1);
+            const int lane = opaque(lane_id), col = lane % 16, quad = lane / 16;
+            // K operand: the row of key 8 (col / 4) + col % 4 (block 1: 4 keys later), so that elements
+            // 4 b + i of a lane are the keys 8 quad .. 8 quad + 7 of the round
+            const int krow = 8 * (col / 4) + col % 4;
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-                w.k_addr[kk] = lds0 + krow * T::kRowBytes + 16 * ((2 * kk + half) ^ T::swz_k(krow));
-            const int vj = lane % 16, vg = (lane / 16) % 2;
-            const int vrow = half * 8 + vj / 4;
+            for (int kk = 0; kk < D / 32; ++kk)
+                w.k_addr[kk] = lds0 + krow * T::kRowBytes + 16 * ((4 * kk + quad) ^ T::swz_k(krow));
+            const int vrow = 8 * quad + col / 4;
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-                w.v_addr[mb] = lds0 + T::kTileBytes + vrow * T::kRowBytes + 8 * ((vj % 4) % 2) +
-                               16 * ((4 * mb + 2 * vg + (vj % 4) / 2) ^ T::swz_v(vrow));
+            for (int mb = 0; mb < G; ++mb)
+                w.v_addr[mb] = lds0 + T::kTileBytes + vrow * T::kRowBytes + 8 * (col % 2) + 16 * ((2 * mb + (col % 4) / 2) ^ T::swz_v(vrow));
         }
 
         // ---- the segment's first round fixes the initial maximum
         wait_tile_loads<0>();
         __syncthreads();
-        f32x16 s_a[NB], s_b[NB];
-        bf16x8 p_a[NB][2], p_b[NB][2];
+        f32x4 s_a[2][kQB], s_b[2][kQB];
+        bf16x8 p_a[kQB], p_b[kQB];
         {
-            f32x16 zero16;
+            f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+            asm volatile("s_nop 1" : "+v"(zero4));       // two wait states before a product may read it
 #pragma unroll
-            for (int r = 0; r < 16; ++r) zero16[r] = 0.0f;
+            for (int g = 0; g < G; ++g) w.opreg[g] = load_k_operand<D, 0, 0>(w.k_addr, g);
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk) w.opreg[kk] = load_k_operand<D, NB, 0>(w.k_addr, kk);
+            for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    if (kk == 0) mfma_score_init(s_a[nb], w.opreg[kk], w.qreg[nb][kk], zero16);
-                    else mfma_score(s_a[nb], w.opreg[kk], w.qreg[nb][kk]);
+                for (int qb = 0; qb < kQB; ++qb) {
+                    if (g < 2) mfma_score_init(s_a[g % 2][qb], w.opreg[g], w.qreg[qb][0], zero4);
+                    else mfma_score(s_a[g % 2][qb], w.opreg[g], w.qreg[qb][g / 2]);
                 }
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk) w.opreg[kk] = load_k_operand<D, NB, 1>(w.k_addr, kk);
-            settle_scores<NB>(s_a, true);
+            for (int g = 0; g < G; ++g) w.opreg[g] = load_k_operand<D, 1, 0>(w.k_addr, g);
+            settle_scores(s_a, true);
         }
-        if ((i_begin + 1) * 32 > c.key_end) mask_scores<NB>(i_begin, half, c.key_end, s_a);
+        if ((i_begin + 1) * 32 > c.key_end) mask_scores(i_begin, quad, c.key_end, s_a);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            float tmax = max16(s_a[nb]);
-            tmax = fmaxf(tmax, other_half(tmax));
+        for (int qb = 0; qb < kQB; ++qb) {
+            float tmax = s_a[0][qb][0];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                w.neg_m[nb][r] = -tmax;
-                s_a[nb][r] -= tmax;
+            for (int e = 1; e < 8; ++e) tmax = fmaxf(tmax, s_a[e / 4][qb][e % 4]);
+            tmax = quad_max(tmax);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                w.neg_m[qb][e] = -tmax;
+                s_a[0][qb][e] -= tmax;
+                s_a[1][qb][e] -= tmax;
             }
-            s_b[nb] = s_a[nb];
+            s_b[0][qb] = s_a[0][qb];
+            s_b[1][qb] = s_a[1][qb];
             Pack16 z;
             z.u = make_uint4(0, 0, 0, 0);
-            p_b[nb][0] = z.v;               // probabilities of the round before the first: none
-            p_b[nb][1] = z.v;
+            p_b[qb] = z.v;                  // probabilities of the round before the first: none
+            asm volatile("" : "+v"(p_b[qb]));            // in registers from here on, not formed in front of their product
         }
 
         // ---- the pipeline, two steps at a time; step i_end only flushes the PV product of
         // the last round (and a step past it, if the count is odd, adds nothing)
         int i = i_begin;
-        for (; (i + 3) * 32 <= c.key_end; i += 2) {      // rounds i+1 and i+2 are whole
-            pipeline_step<D, NB, 0, false, CHECK>(lds0, c, i, i == i_begin, w, s_a, s_b, p_b, p_a);
-            pipeline_step<D, NB, 1, false, CHECK>(lds0, c, i + 1, false, w, s_b, s_a, p_a, p_b);
+        auto whole_tiles = [&](int end) {                // tiles while rounds i+1 and i+2 are whole
+            for (; (i + 3) * 32 <= c.key_end && i < end; i += 2) {
+                pipeline_step<D, 0, false, CHECK>(lds0, c, i, i == i_begin, w, s_a, s_b, p_b, p_a);
+                pipeline_step<D, 1, false, CHECK>(lds0, c, i + 1, false, w, s_b, s_a, p_a, p_b);
+            }
+        };
+        if (!CHECK && (i + 11) * 32 <= c.key_end) {
+            // four tiles at a time, each with its stage known at compile time: 343 instructions a tile
+            // instead of 390 at head_dim 128, 242 instead of 284 at 64.  The first tile comes before
+            // them (its V fetches stay in stage 0), so they start in stage 1.
+            whole_tiles(i_begin + 2);
+#pragma unroll
+            for (int kk = 0; kk < D / 32; ++kk) w.k_addr[kk] -= T::kStageBytes;
+            for (; (i + 9) * 32 <= c.key_end; i += 8) {
+                static_for<1, kStages + 1>([&](auto tc) {
+                    constexpr int STAGE = decltype(tc)::value % kStages, step = 2 * (decltype(tc)::value - 1);
+                    pipeline_step<D, 0, false, CHECK, STAGE>(lds0, c, i + step, false, w, s_a, s_b, p_b, p_a);
+                    pipeline_step<D, 1, false, CHECK, STAGE>(lds0, c, i + step + 1, false, w, s_b, s_a, p_a, p_b);
+                });
+            }
+#pragma unroll
+            for (int kk = 0; kk < D / 32; ++kk) w.k_addr[kk] += T::kStageBytes;
+            w.issue_off = 3 * T::kStageBytes;            // as the first tile left it
         }
+        whole_tiles(i_end);
         for (; i <= i_end; i += 2) {
-            pipeline_step<D, NB, 0, true, CHECK>(lds0, c, i, i == i_begin, w, s_a, s_b, p_b, p_a);
-            pipeline_step<D, NB, 1, true, CHECK>(lds0, c, i + 1, false, w, s_b, s_a, p_a, p_b);
+            pipeline_step<D, 0, true, CHECK>(lds0, c, i, i == i_begin, w, s_a, s_b, p_b, p_a);
+            pipeline_step<D, 1, true, CHECK>(lds0, c, i + 1, false, w, s_b, s_a, p_a, p_b);
         }
         };   // run_segment
 
@@ -892,23 +932,26 @@ __global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const Attn
         {
             // anything in this lane's row sums or accumulators that is not finite, or within 2^7 of
             // not being so (partial rows are stored as bf16)?  y - y is 0 for every finite y
-            settle_acc<D, NB>(w.acc, false);
+            settle_acc<D>(w.acc, false);
             float probe = 0.0f;
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const float yl = w.l_run[nb] * 128.0f;
-                probe += yl - yl;
+            for (int qb = 0; qb < kQB; ++qb) {
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
+                for (int e = 0; e < row_sums(D); ++e) {
+                    const float yl = w.l_run[qb][e] * 128.0f;
+                    probe += yl - yl;
+                }
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const float y = w.acc[mb][nb][r] * 128.0f;
+                for (int mb = 0; mb < G; ++mb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float y = w.acc[mb][qb][r] * 128.0f;
                         probe += y - y;
                     }
             }
             // the barrier also makes sure that every wave has left the segment's tiles
             if (__syncthreads_or(!(probe == 0.0f))) {
-                start_tiles<D, NB>(lds0, a, seg, c, w, n, stride_tok);
+                start_tiles<D>(lds0, a, seg, c, w, n, stride_tok);
                 run_segment(std::true_type{});
             }
         }
@@ -918,29 +961,29 @@ __global__ __launch_bounds__(waves_of(NB) * 64) void attention_kernel(const Attn
         const Segment nxt = next_segment(walk, a, tpu, lp, gridDim.x);
         if (nxt.valid) {
             __syncthreads();        // every wave has left this segment's tiles before their stages are refilled
-            start_tiles<D, NB>(lds0, a, nxt, c, w, n, stride_tok);
-            load_q<D, NB>(a, nxt, w, n, stride_tok, wave, opaque(lane_id) % 32, opaque(lane_id) / 32);
+            start_tiles<D>(lds0, a, nxt, c, w, n, stride_tok);
+            load_q<D>(a, nxt, w, n, stride_tok, wave, opaque(lane_id) % 16, opaque(lane_id) / 16);
         }
 
         // ---- results of this segment: final rows, or (a unit shared with other workgroups)
         // running maximum, row sum and unnormalised rows into this workgroup's slot
-        settle_acc<D, NB>(w.acc, false);
-        const int lane = opaque(lane_id), col = lane % 32, half = lane / 32;
+        settle_acc<D>(w.acc, false);
+        const int lane = opaque(lane_id), col = lane % 16, quad = lane / 16;
         const bool whole = (t_begin == 0) && (uint32_t(t_stop) == tpu);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const float l_tot = w.l_run[nb] + other_half(w.l_run[nb]);
-            const int row0 = wave * (32 * NB) + nb * 32;
+        for (int qb = 0; qb < kQB; ++qb) {
+            const float l_tot = quad_sum(row_sums(D) == 2 ? w.l_run[qb][0] + w.l_run[qb][row_sums(D) - 1] : w.l_run[qb][0]);
+            const int row0 = wave * (16 * kQB) + qb * 16;
             if (whole) {
                 const int q0 = qtile * kBM + row0;
-                store_rows<D, NB>(out_lds, w.acc, nb, 1.0f / l_tot, a.o + head_off + int64_t(q0) * stride_tok, stride_tok, n - q0, lane);
+                store_rows<D>(out_lds, w.acc, qb, 1.0f / l_tot, a.o + head_off + int64_t(q0) * stride_tok, stride_tok, n - q0, lane);
             } else {
                 float *slot = a.ws + (size_t(2) * lp + (first_segment ? 0 : 1)) * slot_floats<D>();
-                if (half == 0) {
-                    slot[row0 + col] = -w.neg_m[nb][0];
+                if (quad == 0) {
+                    slot[row0 + col] = -w.neg_m[qb][0];
                     slot[kBM + row0 + col] = l_tot;
                 }
-                store_rows<D, NB>(out_lds, w.acc, nb, 1.0f, reinterpret_cast<__bf16 *>(slot + 2 * kBM) + row0 * D, D, 32, lane);
+                store_rows<D>(out_lds, w.acc, qb, 1.0f, reinterpret_cast<__bf16 *>(slot + 2 * kBM) + row0 * D, D, 16, lane);
             }
         }
         first_segment = false;
@@ -1006,7 +1049,7 @@ __global__ __launch_bounds__(32 * (D / 16)) void combine_kernel(const AttnParams
 template <int D>
 int64_t workspace_bytes_for(int cus) { return int64_t(2) * cus * slot_floats<D>() * int64_t(sizeof(float)); }
 
-template <int D, int NB>
+template <int D>
 int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hipStream_t stream) {
     int dev = 0;
     const int cus = lp::device_compute_units(&dev);
@@ -1065,17 +1108,17 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     // The dynamic-LDS limit is an attribute of the function on a device: set once per device
     // (a repeated set by a racing host thread is harmless).
     static std::atomic<uint64_t> attr_set{0};
-    const void *kern = reinterpret_cast<const void *>(&attention_kernel<D, NB>);
+    const void *kern = reinterpret_cast<const void *>(&attention_kernel<D>);
     const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
     if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Tile<D, NB>::kBytes);
+        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Tile<D>::kBytes);
         if (e != hipSuccess) {
             lp::set_last_hip_error(int(e));
             return LP_ERR_HIP;
         }
         attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
     }
-    int rc = lp::launch_kernel(kern, dim3(n_wg), dim3(waves_of(NB) * 64), Tile<D, NB>::kBytes, stream, a);
+    int rc = lp::launch_kernel(kern, dim3(n_wg), dim3(kWaves * 64), Tile<D>::kBytes, stream, a);
     if (rc != LP_OK || a.ws == nullptr) return rc;
     return lp::launch_kernel(reinterpret_cast<const void *>(&combine_kernel<D>), dim3(uint32_t(a.shared_units), kBM / 32),
                              dim3(32 * (D / 16)), 0, stream, a, a.shared_wgs);
@@ -1150,8 +1193,8 @@ int attention_call(const void *q, const void *k, const void *v, void *o, int32_t
     a.scale_log2e = scale * 1.4426950408889634f;
     a.n = int(n_tokens);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (head_dim == 128) return launch<128, blocks_per_wave(128)>(a, int(all_heads), workspace, workspace_bytes, st);
-    return launch<64, blocks_per_wave(64)>(a, int(all_heads), workspace, workspace_bytes, st);
+    if (head_dim == 128) return launch<128>(a, int(all_heads), workspace, workspace_bytes, st);
+    return launch<64>(a, int(all_heads), workspace, workspace_bytes, st);
 }
 
 }  // namespace

@@ -443,8 +443,7 @@ __device__ __forceinline__ void run_tile(uint32_t lds0, const GemmArgs &a, int f
                 for (int b = 0; b < FB / kHeads; ++b)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) s += acc[hh * (FB / kHeads) + b][t][i] * acc[hh * (FB / kHeads) + b][t][i];
-                s += __shfl_xor(s, 16, 64);
-                ss[t][hh] = s + __shfl_xor(s, 32, 64);
+                ss[t][hh] = lp::over_quads(s, [](float x, float y) { return x + y; });
             }
         if (tid < kMaxPairs) *LP_LDS_PTR(f32x4, uintptr_t(rope_lds + 16 * tid)) = turns_pre;
         *LP_LDS_PTR(f32x2, uintptr_t(gain_lds + 4 * f_pre)) = gain_pre;
