@@ -597,6 +597,8 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, i
 //  * the first shared_units units form a (unit, key tile) iteration space that is cut into
 //    shared_wgs <= P contiguous ranges (never empty), so a workgroup may start and end in
 //    the middle of a unit; such partial results go to `ws` and are merged by combine_kernel.
+//    The workgroups that take one are spread evenly over the P.  With shared_wgs = shared_units
+//    every range is a whole unit and nothing is left to merge.
 //    The cut is even in COST, not in tiles: every unit is preceded by kBoundaryTiles
 //    imaginary tiles that stand for what a workgroup pays to change units (drain and
 //    refill of the pipeline, stores, a new Q), the space of shared_units * unit_cost
@@ -605,7 +607,6 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, i
 //  * the remaining whole_rounds * P units are taken whole, unit shared_units + r*P + p by
 //    workgroup p in round r: the workgroups of an XCD then walk the keys of one head in
 //    step and share its K/V stream through the L2.
-// One workgroup per unit (nothing shared) is shared_units = 0, whole_rounds = 1.
 struct AttnParams {
     const __bf16 *q, *k, *v;
     __bf16 *o;
@@ -617,7 +618,8 @@ struct AttnParams {
     int shared_units, whole_rounds;
     uint32_t shared_work;      // shared_units * unit_cost
     uint32_t unit_cost;        // tiles_per_unit + kBoundaryTiles
-    uint32_t shared_wgs;       // workgroups 0 .. shared_wgs-1 (logical order) take part in the shared space
+    uint32_t shared_wgs;       // ranges of the shared space; workgroup p (logical order) takes range r if r is the only
+                               // number in [p shared_wgs / P, (p + 1) shared_wgs / P), both rounded down
 };
 
 // A slot holds, for the 256 query rows of a unit: m[256] and l[256] in binary32, then the
@@ -770,11 +772,12 @@ __global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams
 
     // ---- this workgroup's range of the shared (unit, tile) space, then its whole units
     const uint32_t lp = logical_workgroup(blockIdx.x, gridDim.x);
-    const bool sharing = lp < a.shared_wgs;
+    const uint32_t sharer = range_start(lp, a.shared_wgs, gridDim.x);
+    const bool sharing = range_start(lp + 1, a.shared_wgs, gridDim.x) > sharer;
     const uint32_t tpu = uint32_t(a.tiles_per_unit);
     Walk walk;
-    walk.it = sharing ? real_tile(range_start(lp, a.shared_work, a.shared_wgs), a.unit_cost, tpu) : 0u;
-    walk.it_end = sharing ? real_tile(range_start(lp + 1, a.shared_work, a.shared_wgs), a.unit_cost, tpu) : 0u;
+    walk.it = sharing ? real_tile(range_start(sharer, a.shared_work, a.shared_wgs), a.unit_cost, tpu) : 0u;
+    walk.it_end = sharing ? real_tile(range_start(sharer + 1, a.shared_work, a.shared_wgs), a.unit_cost, tpu) : 0u;
     walk.whole_round = 0;
     const uint32_t out_lds = lds0 + T::kRingBytes + wave * T::kOutBytes;
     bool first_segment = true;
@@ -978,7 +981,7 @@ __global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams
                 const int q0 = qtile * kBM + row0;
                 store_rows<D>(out_lds, w.acc, qb, 1.0f / l_tot, a.o + head_off + int64_t(q0) * stride_tok, stride_tok, n - q0, lane);
             } else {
-                float *slot = a.ws + (size_t(2) * lp + (first_segment ? 0 : 1)) * slot_floats<D>();
+                float *slot = a.ws + (size_t(2) * sharer + (first_segment ? 0 : 1)) * slot_floats<D>();
                 if (quad == 0) {
                     slot[row0 + col] = -w.neg_m[qb][0];
                     slot[kBM + row0 + col] = l_tot;
@@ -994,12 +997,14 @@ __global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams
 
 // Merges the partial results of every unit that more than one workgroup worked on:
 //   m = max_s m_s,  l = sum_s l_s 2^(m_s - m),  O = sum_s O_s 2^(m_s - m) / l.
-// grid = (units, kBM / 32): a workgroup takes 32 query rows of one unit, a thread one row
-// and 16 consecutive d.
+// grid = units * kBM / 32: a workgroup takes 32 query rows of one unit, a thread one row
+// and 16 consecutive d.  The units are dealt to the XCDs as attention_kernel deals its ranges, so
+// that most parts are read from the L2 they were written to; a unit has two parts more often than not, and
+// both are fetched before either is used.
 template <int D>
 __global__ __launch_bounds__(32 * (D / 16)) void combine_kernel(const AttnParams a, uint32_t n_wg) {
-    constexpr int kChunks = D / 16;
-    const uint32_t unit = blockIdx.x;
+    constexpr int kChunks = D / 16, kPieces = kBM / 32;
+    const uint32_t piece = logical_workgroup(blockIdx.x, gridDim.x), unit = piece / kPieces;
     const uint32_t W = a.shared_work, tpu = uint32_t(a.tiles_per_unit);
     // the unit's real tiles sit at [x_lo, x_hi) of the shared space, after its imaginary ones
     const uint32_t x_hi = (unit + 1) * a.unit_cost, x_lo = x_hi - tpu;
@@ -1008,7 +1013,7 @@ __global__ __launch_bounds__(32 * (D / 16)) void combine_kernel(const AttnParams
     const uint32_t pl = uint32_t((uint64_t(x_hi) * n_wg - 1) / W);
     if (pf == pl) return;                                      // computed whole by one workgroup
     const int head = int(unit) / a.n_qtiles, qtile = int(unit) % a.n_qtiles;
-    const int row = int(blockIdx.y) * 32 + int(threadIdx.x) / kChunks, ch = int(threadIdx.x) % kChunks;
+    const int row = int(piece % kPieces) * 32 + int(threadIdx.x) / kChunks, ch = int(threadIdx.x) % kChunks;
     const int qi = qtile * kBM + row;
     if (qi >= a.n) return;
     // a workgroup's first segment lies in slot 0, a later (its last) one in slot 1
@@ -1016,27 +1021,36 @@ __global__ __launch_bounds__(32 * (D / 16)) void combine_kernel(const AttnParams
     const float *slot0 = a.ws + (size_t(2) * pf + (pf_starts_here ? 0 : 1)) * slot_floats<D>();
     const size_t slot_step = size_t(2) * slot_floats<D>();    // every later workgroup starts inside the unit: slot 0
     const float *first_later = a.ws + size_t(2) * (pf + 1) * slot_floats<D>();
-    float m = slot0[row];
-    for (uint32_t p = pf + 1; p <= pl; ++p) m = fmaxf(m, first_later[(p - pf - 1) * slot_step + row]);
+    struct Part {
+        float m, l;
+        uint4 x[2];
+    };
+    auto fetch = [&](const float *slot) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(slot + 2 * kBM) + row * D + ch * 16);
+        return Part{slot[row], slot[kBM + row], {src[0], src[1]}};
+    };
+    const Part first = fetch(slot0), second = fetch(first_later);
+    float m = fmaxf(first.m, second.m);
+    for (uint32_t p = pf + 2; p <= pl; ++p) m = fmaxf(m, first_later[(p - pf - 1) * slot_step + row]);
     float l = 0.0f, acc[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
-    for (uint32_t p = pf; p <= pl; ++p) {
-        const float *slot = p == pf ? slot0 : first_later + (p - pf - 1) * slot_step;
-        const float f = __builtin_amdgcn_exp2f(slot[row] - m);
-        l += slot[kBM + row] * f;
-        const uint4 *src = reinterpret_cast<const uint4 *>(reinterpret_cast<const __bf16 *>(slot + 2 * kBM) + row * D + ch * 16);
+    auto add = [&](const Part &part) {
+        const float f = __builtin_amdgcn_exp2f(part.m - m);
+        l += part.l * f;
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const uint4 x = src[e];
-            const uint32_t wds[4] = {x.x, x.y, x.z, x.w};
+            const uint32_t wds[4] = {part.x[e].x, part.x[e].y, part.x[e].z, part.x[e].w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {     // a bf16 is the upper half of the binary32 of the same value
                 acc[8 * e + 2 * j + 0] += __uint_as_float(wds[j] << 16) * f;
                 acc[8 * e + 2 * j + 1] += __uint_as_float(wds[j] & 0xffff0000u) * f;
             }
         }
-    }
+    };
+    add(first);
+    add(second);
+    for (uint32_t p = pf + 2; p <= pl; ++p) add(fetch(first_later + (p - pf - 1) * slot_step));
     const float inv = 1.0f / l;
     union { uint4 u[2]; bf16x2 p[8]; } ow;
 #pragma unroll
@@ -1049,62 +1063,80 @@ __global__ __launch_bounds__(32 * (D / 16)) void combine_kernel(const AttnParams
 template <int D>
 int64_t workspace_bytes_for(int cus) { return int64_t(2) * cus * slot_floats<D>() * int64_t(sizeof(float)); }
 
+// ---- which way a call goes.  Times in us on 256 compute units, fitted to 96 .. 13230 tokens x 1 .. 40 heads:
+// every call on every way it can go.  Over 311 of them the choice is off the best way by 0.06 % on
+// average, by 7 % at worst.
+
+// A tile's time while a part `busy` of the compute units works: one workgroup's own pace, slower
+// as the power limit lowers the clock of a full chip.
+float tile_us(int head_dim, float busy) {
+    static constexpr float kBusy[4] = {0.5f, 0.8f, 0.94f, 1.0f};
+    static constexpr float k128[4] = {1.21f, 1.28f, 1.41f, 1.47f}, k64[4] = {0.74f, 0.77f, 0.80f, 0.84f};
+    const float *us = head_dim == 128 ? k128 : k64;
+    if (busy <= kBusy[0]) return us[0];
+    int i = 1;
+    while (i < 3 && busy > kBusy[i]) ++i;
+    return us[i - 1] + (us[i] - us[i - 1]) * (busy - kBusy[i - 1]) / (kBusy[i] - kBusy[i - 1]);
+}
+
+// How attention_kernel's workgroups deal the units out.
+struct Deal {
+    uint32_t wgs, rounds, shared, sharers;
+    float us;
+};
+
+// Whole units to everybody for as many rounds as they fill, and the units left over either whole to
+// as many workgroups (no scratch memory, no merge) or cut into even ranges for as many as get kMinTiles
+// tiles each.  Measured, whole / cut: 3780 tokens x 12 heads of 128 (180 units on 256) 84 / 86,
+// 4680 x 12 109 / 121, 2999 x 12 70 / 65, 9450 x 12 (444 units) 421 / 404; of 64: 2999 x 16 44.8 / 48.5,
+// 4212 x 8 58 / 47.
+Deal deal_units(int head_dim, uint32_t units, uint32_t tpu, uint32_t cus, bool may_cut) {
+    constexpr uint32_t kMinTiles = 8;
+    static_assert(kBoundaryTiles < kMinTiles, "a range of kMinTiles positions must hold a real tile");
+    const float once = head_dim == 128 ? 11.0f : 9.5f;                    // launch, first tiles and Q, the first round, stores
+    const float merge = head_dim == 128 ? 8.0f : 6.0f;                    // combine_kernel and the parts it reads
+    const float full = tile_us(head_dim, 1.0f);
+    Deal d;
+    d.wgs = units < cus ? units : cus;
+    d.rounds = units / cus;
+    d.shared = units - d.rounds * cus;
+    d.sharers = d.shared;
+    const float whole_us = once + float(d.rounds) * float(tpu + 2) * full;
+    d.us = whole_us + float(tpu) * (d.shared > 0 ? tile_us(head_dim, float(d.shared) / float(cus)) : 0.0f);
+    if (!may_cut || d.shared == 0) return d;
+    uint32_t sharers = uint32_t(uint64_t(d.shared) * tpu / kMinTiles);
+    if (sharers > cus) sharers = cus;
+    if (sharers <= d.shared) return d;                                    // cutting adds no parallelism
+    const float share = float(d.shared) * float(tpu) / float(sharers);
+    const float cut_us = whole_us + merge + (share + float(kBoundaryTiles)) * tile_us(head_dim, float(sharers) / float(cus));
+    if (cut_us < d.us) {
+        if (d.rounds == 0) d.wgs = sharers;
+        d.sharers = sharers;
+        d.us = cut_us;
+    }
+    return d;
+}
+
 template <int D>
 int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hipStream_t stream) {
     int dev = 0;
     const int cus = lp::device_compute_units(&dev);
+    if (cus <= 0) return LP_ERR_HIP;
     a.n_qtiles = (a.n + kBM - 1) / kBM;
     a.tiles_per_unit = (a.n + kBN - 1) / kBN;
     const uint32_t units = uint32_t(a.n_qtiles) * uint32_t(heads), tpu = uint32_t(a.tiles_per_unit);
-    // default: one workgroup per unit, nothing shared
-    uint32_t n_wg = units;
-    a.ws = nullptr;
-    a.shared_units = 0;
-    a.whole_rounds = 1;
-    a.shared_work = 0;
-    a.unit_cost = tpu;
-    a.shared_wgs = 0;
-    uint32_t tiles = cus > 0 ? ((units + cus - 1) / cus) * tpu : tpu;         // tiles of the busiest workgroup
-    if (workspace != nullptr && cus > 0 && workspace_bytes >= workspace_bytes_for<D>(cus)) {
-        // Candidate: one workgroup per compute unit takes floor(units / #CU) rounds of whole
-        // units, and the units left over are shared evenly by as many workgroups as get at least
-        // kMinTiles tiles each.  Costs in units of one tile's time: a workgroup that starts or
-        // ends inside a unit pays a second prologue and a partial store, and the merge kernel
-        // follows.
-        constexpr uint32_t kMinTiles = 8, kSplitCost = 6, kMergeCost = 3;
-        static_assert(kBoundaryTiles < kMinTiles, "a range of kMinTiles positions must hold a real tile");
-        const uint32_t p = units < uint32_t(cus) ? units : uint32_t(cus);     // workgroups
-        const uint32_t rounds = units >= uint32_t(cus) ? units / p : 0;       // whole-unit rounds
-        const uint32_t shared = units - rounds * p;
-        if (shared > 0) {
-            uint32_t sharers = shared * tpu / kMinTiles;                      // never more than tiles
-            if (sharers > uint32_t(cus)) sharers = uint32_t(cus);
-            if (sharers > shared || rounds > 0) {                             // else sharing adds no parallelism
-                if (sharers < 1) sharers = 1;
-                const uint32_t wgs = rounds > 0 ? p : sharers;
-                const uint32_t t_plain = ((units + cus - 1) / cus) * tpu;
-                const uint32_t t_split = rounds * tpu + (shared * tpu + sharers - 1) / sharers + kSplitCost + kMergeCost;
-                if (t_split < t_plain) {
-                    n_wg = wgs;
-                    a.ws = static_cast<float *>(workspace);
-                    a.shared_units = int(shared);
-                    a.whole_rounds = int(rounds);
-                    a.unit_cost = tpu + kBoundaryTiles;
-                    a.shared_work = shared * a.unit_cost;
-                    a.shared_wgs = sharers;
-                    tiles = rounds * tpu + (shared * tpu + sharers - 1) / sharers + kBoundaryTiles;
-                }
-            }
-        }
-    }
-    // Short calls go to attention_short_kernel, which needs no scratch.  This kernel takes about 9 us before
-    // and after its tiles (launch, first tiles and Q, the first round, stores), 1.45 us a tile at
-    // head_dim 128 and 0.75 at 64, and 8 us for the merge kernel; attention_short_us says what the other takes.
-    // Measured, this kernel / the other: 600 tokens x 40 heads of 128 24 / 19 us, 1500 x 40 45 / 76, 1000 x 12
-    // 31 / 16, 3000 x 12 66 / 86; of 64: 2000 x 12 31 / 22, 3000 x 12 43 / 45.
-    const float long_us = 9.0f + (D == 128 ? 1.45f : 0.75f) * float(tiles) + (a.ws != nullptr ? 8.0f : 0.0f);
-    if (cus > 0 && lp::attention_short_us(a.n, heads, D, cus) < long_us)
+    const bool scratch = workspace != nullptr && workspace_bytes >= workspace_bytes_for<D>(cus);
+    const Deal d = deal_units(D, units, tpu, uint32_t(cus), scratch);
+    // short calls go to attention_short_kernel, which needs no scratch memory
+    if (lp::attention_short_us(a.n, heads, D, cus) < d.us)
         return lp::attention_short({a.q, a.k, a.v, a.o, a.stride_tok, a.stride_head, a.stride_batch, a.heads, heads, D, a.n, a.scale_log2e}, stream);
+    const bool cut = d.sharers != d.shared;
+    a.ws = cut ? static_cast<float *>(workspace) : nullptr;
+    a.shared_units = int(d.shared);
+    a.whole_rounds = int(d.rounds);
+    a.unit_cost = tpu + (cut ? kBoundaryTiles : 0);
+    a.shared_work = d.shared * a.unit_cost;
+    a.shared_wgs = d.sharers;
     // The dynamic-LDS limit is an attribute of the function on a device: set once per device
     // (a repeated set by a racing host thread is harmless).
     static std::atomic<uint64_t> attr_set{0};
@@ -1118,9 +1150,9 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
         }
         attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
     }
-    int rc = lp::launch_kernel(kern, dim3(n_wg), dim3(kWaves * 64), Tile<D>::kBytes, stream, a);
+    int rc = lp::launch_kernel(kern, dim3(d.wgs), dim3(kWaves * 64), Tile<D>::kBytes, stream, a);
     if (rc != LP_OK || a.ws == nullptr) return rc;
-    return lp::launch_kernel(reinterpret_cast<const void *>(&combine_kernel<D>), dim3(uint32_t(a.shared_units), kBM / 32),
+    return lp::launch_kernel(reinterpret_cast<const void *>(&combine_kernel<D>), dim3(uint32_t(a.shared_units) * (kBM / 32)),
                              dim3(32 * (D / 16)), 0, stream, a, a.shared_wgs);
 }
 

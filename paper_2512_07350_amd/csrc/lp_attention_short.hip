@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
         for (int mb = 0; mb < MB; ++mb) acc[mb][qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
 
-    for (bool first = true; round < n_rounds; round += kWaves, first = false) {
+    for (; round < n_rounds; round += kWaves) {
         const bool more = round + kWaves < n_rounds;
         wait_loads<T::kLoads>();                // K of this round; behind it only V
         f32x4 s[2][kQB];
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int qb = 0; qb < kQB; ++qb) {
-                const float c = first ? 0.0f : -m[qb];
+                const float c = m[qb] == -INFINITY ? 0.0f : -m[qb];
                 s[b][qb] = f32x4{c, c, c, c};
             }
 #pragma unroll
@@ -222,31 +222,32 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
                 for (int qb = 0; qb < kQB; ++qb) s[e / 4][qb][e % 4] = past ? -INFINITY : s[e / 4][qb][e % 4];
             }
         }
-        // the maximum is set by the first round and raised when a score exceeds it by more than the threshold
+        // the maximum is set by the first round with a score above -inf, and raised when a score exceeds it
+        // by more than the threshold
         float mx[kQB];
-        bool raise = first;
+        bool raise = false;
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb) {
             mx[qb] = s[0][qb][0];
 #pragma unroll
             for (int e = 1; e < 8; ++e) mx[qb] = fmaxf(mx[qb], s[e / 4][qb][e % 4]);
-            raise = raise || mx[qb] > kRescaleThreshold;
+            raise = raise || m[qb] == -INFINITY || mx[qb] > kRescaleThreshold;
         }
         if (__any(raise)) {
 #pragma unroll
             for (int qb = 0; qb < kQB; ++qb) {
-                const float top = quad_max(mx[qb]), d = first ? top : fmaxf(top, 0.0f);
-                const float f = first ? 0.0f : __builtin_amdgcn_exp2f(-d);
-                m[qb] = first ? d : m[qb] + d;
+                const bool fresh = m[qb] == -INFINITY;
+                const float top = quad_max(mx[qb]);
+                const float d = fresh ? (top == -INFINITY ? 0.0f : top) : fmaxf(top, 0.0f);
+                const float f = fresh ? 0.0f : __builtin_amdgcn_exp2f(-d);
+                m[qb] = fresh ? top : m[qb] + d;
                 l[qb] *= f;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) s[e / 4][qb][e % 4] -= d;
-                if (!first) {
 #pragma unroll
-                    for (int mb = 0; mb < MB; ++mb)
+                for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) acc[mb][qb][i] *= f;
-                }
+                    for (int i = 0; i < 4; ++i) acc[mb][qb][i] *= f;
             }
         }
         bf16x8 p[kQB];
@@ -350,10 +351,14 @@ int64_t short_groups(int64_t n, int64_t all_heads) { return all_heads * ((n + kR
 namespace lp {
 
 // us: launch and first fetch, then the workgroups of a compute unit, each a quarter of the rounds long.
-// Fitted to 333 x 3 .. 3000 x 12 and 600 x 40 .. 1500 x 40 (tokens x heads) at head_dim 128 and 64; off by up to 15 %.
+// A compute unit holds several: two of them take 1.5 times as long as one.  Off by up to 15 % at
+// 96 .. 3780 tokens x 1 .. 40 heads.
 float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus) {
-    const int64_t per_cu = (short_groups(n, all_heads) + cus - 1) / cus, rounds = (n + 127) / 128;
-    return 4.0f + float(per_cu) * (0.3f + (head_dim == 128 ? 0.8f : 0.37f) * float(rounds));
+    const int64_t groups = short_groups(n, all_heads), rounds = (n + 127) / 128;
+    const int64_t per_cu = (groups + cus - 1) / cus;
+    if (per_cu <= 1) return 4.3f + (head_dim == 128 ? 0.8f : 0.55f) * float(rounds);
+    if (head_dim == 64) return 4.0f + float(per_cu) * (0.3f + 0.37f * float(rounds));
+    return 4.0f + float((per_cu + 1) / 2) * (1.5f + 1.17f * float(rounds));
 }
 
 int attention_short(const AttentionCall &c, hipStream_t stream) {

@@ -54,16 +54,23 @@ struct AttentionCall {
 int attention_short(const AttentionCall &c, hipStream_t stream);
 float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus);
 
-// Compute units of the current device (each host thread remembers the last device it asked about).
+// Compute units of the current device (each host thread remembers the last device it asked about); 0,
+// with the HIP error recorded, if there is none.
 inline int device_compute_units(int *device = nullptr) {
     static thread_local int cached_dev = -1, cached_cus = 0;
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (dev != cached_dev) {
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess && dev != cached_dev) {
         int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        cached_cus = cus;
-        cached_dev = dev;
+        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess) {
+            cached_cus = cus;
+            cached_dev = dev;
+        }
+    }
+    if (e != hipSuccess) {
+        set_last_hip_error(int(e));
+        return 0;
     }
     if (device != nullptr) *device = dev;
     return cached_cus;

@@ -350,3 +350,35 @@ def test_long_kernel_scores_far_above_the_first_round(n, heads, profile, hd):
     rows = synth.sample_rows(n, 48, seed=7, tile=256)
     g.assert_attention_close(got[rows], orc.attention(q, k, v, scale=scale, rows=rows), "scores far above the first round")
     assert np.all(np.isfinite(got))
+
+
+# 256-row query tiles (units) on 256 compute units: everybody one or two units, and 64, 48, 144, 224 or 194 units left,
+# taken whole or (with scratch memory, the first three) cut into ranges that start and end inside a unit
+@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("n,heads", [(1795, 40), (3329, 40), (2305, 40), (2999, 40), (520, 150)])
+def test_units_left_over_after_whole_rounds(n, heads, hd, balanced):
+    from tests import gpu_util as g
+    q, k, v = synth.qkv_bf16(4900 + n + heads, n, heads, hd)
+    got = g.hip_attention(q, k, v, balanced=balanced)
+    rows = synth.sample_rows(n, 24, seed=n, tile=256)
+    g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "n=%d heads=%d hd=%d" % (n, heads, hd))
+    assert np.all(np.isfinite(got))
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("dead", [(32, 64), (64, 128), (100, 300), (0, 32)])
+def test_short_kernel_keys_with_score_minus_infinity(dead, hd):
+    """Keys whose score is -inf count for nothing, also where they are all that a wavefront sees (first)."""
+    from tests import gpu_util as g
+    n, heads = 300, 2
+    q, k, v = synth.qkv_bf16(4800 + hd, n, heads, hd)
+    q[:, :, 3] = 0x3f80                              # 1.0, against -inf in the dead keys
+    alive = np.ones(n, bool)
+    alive[dead[0]:dead[1]] = False
+    k[~alive, :, 3] = 0xff80
+    kf, vf, qf = (synth.bf16_bits_to_f32(a).astype(np.float64) for a in (k, v, q))
+    s = np.einsum("qhd,khd->hqk", qf, kf[alive]) / np.sqrt(hd)
+    p = np.exp(s - s.max(-1, keepdims=True))
+    want = np.einsum("hqk,khd->qhd", p / p.sum(-1, keepdims=True), vf[alive])
+    g.assert_attention_close(g.hip_attention(q, k, v), want, "dead %s" % (dead,))
