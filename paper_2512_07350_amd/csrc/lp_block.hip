@@ -146,10 +146,12 @@ __device__ __forceinline__ void static_for(F &&f) {
 }
 
 // The tile of one workgroup: WF x WT wavefronts, each with FB x TB blocks of 16 features x 16
-// tokens, and S LDS stages of one k-tile (W rows, then x rows).
-template <int WF_, int WT_, int FB_, int TB_, int S_>
+// tokens, and S LDS stages of one k-tile (W rows, then x rows).  With SPLIT the wavefronts share k while they
+// form the products (product_split_k) and the blocks from then on.
+template <int WF_, int WT_, int FB_, int TB_, int S_, bool SPLIT_ = false>
 struct Tiling {
     static constexpr int WF = WF_, WT = WT_, FB = FB_, TB = TB_, S = S_;
+    static constexpr bool SPLIT = SPLIT_;
     static constexpr int kWaves = WF * WT, kThreads = 64 * kWaves;
     static constexpr int kF = WF * FB * 16, kT = WT * TB * 16;            // features and tokens of the tile
     static constexpr int kWBytes = kF * kRowBytes, kStage = kWBytes + kT * kRowBytes;
@@ -157,7 +159,10 @@ struct Tiling {
     static constexpr int kOut = kWaves * 16 * FB * 32;                    // result staging, see store_tile
     // + rotary table + sums of squares + per wave the bias and gain of its features
     static constexpr int kEpilogue = kOut + kMaxPairs * 16 + kWaves * TB * 16 * 4 + kWaves * FB * 16 * 8;
-    static constexpr int kLds = kRing > kEpilogue ? kRing : kEpilogue;
+    static constexpr int kParts = SPLIT ? WF * WT * WF * WT * FB * TB * 1024 : 0;   // every wave's products of the whole tile
+    static constexpr int kMost = kRing > kParts ? kRing : kParts, kLds = kMost > kEpilogue ? kMost : kEpilogue;
+    static_assert(kLds <= 160 * 1024, "the LDS of a compute unit");
+    static_assert(!SPLIT || (WF * WT == 4 && S % 2 == 0 && S >= 6), "one k-step of 32 of a pair of k-tiles per wave");
     static constexpr int FH = FB / 2;                                     // blocks in a lo (or hi) half of a wave's features
     // wave-wide loads (8 rows each) per wave and stage: X = x rows and the lo halves of W, Y = the hi halves
     static constexpr int kLoadsW = kF / 16 / kWaves, kLoadsX = kT / 8 / kWaves;
@@ -319,6 +324,105 @@ __device__ __forceinline__ void product(uint32_t lds0, const GemmArgs &a, int f0
         for (int t = 0; t < TB; ++t) asm volatile("" : "+v"(acc[f][t]));
 }
 
+// The same for calls of few tiles and a long k: the four waves of a workgroup share k.
+//
+// What bounds it.  In every small tiling a compute unit takes in 82 to 90 GB/s through the global -> LDS path
+// (64 x 64: 16 KB and 0.2 us a k-tile, whether 2 or 100 workgroups run, the data in L2 or not), so with
+// compute units to spare a smaller tile is the faster one.  A 64 x 32 tile has too few products per k-tile to
+// keep four waves that share its rows apart from LDS and the barrier (0.19 us with two such waves); here a wave takes
+// all of the tile's rows for one k-step of 32 out of a pair of k-tiles, every byte is read from LDS once,
+// and the four partial tiles are added up through LDS at the end: 0.12 us a k-tile.  A wave holds the
+// operands of two pairs: behind the one barrier of a pair it fetches those of the next pair and sends for the pair
+// S / 2 later, under the products of this one.  520 x 5120 -> 640: 17.3 to 13.7 us; 100 x 3072 -> 3072: 12.0 to 9.9.
+// A 64 x 64 tile gains nothing from it (17.4), and operands fetched straight into registers are slower (30).
+//
+// Leaves the wave's own FB x TB blocks in acc, like product().
+template <typename C>
+__device__ __forceinline__ void product_split_k(uint32_t lds0, const GemmArgs &a, int f0, int t0, int wave, int lane,
+                                                f32x4 (&acc)[C::FB][C::TB]) {
+    constexpr int FB = C::WF * C::FB, TB = C::WT * C::TB, S = C::S, W = C::kWaves, kLoads = C::X + C::Y;
+    const int col = lane % 16, quad = lane / 16;
+    const int64_t w_rows = min(int64_t(C::kF), int64_t(a.d_out) - f0), x_rows = min(int64_t(C::kT), int64_t(a.n) - t0);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16 *>(a.w + int64_t(f0) * a.d_in), 0, int(w_rows * a.d_in * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16 *>(a.x + int64_t(t0) * a.d_in), 0, int(x_rows * a.d_in * 2), 0x00020000);
+    const int n_kt = a.d_in / kBK;
+    // As in product(): a load moves 8 rows, and all of a wave's groups of rows have the parity of the wave.  A k-tile
+    // past the last is sent for outside the buffers (nothing is fetched, zeros arrive), which leaves one body
+    // for every pair: behind the loads waited for there are always as many others.
+    const uint32_t row_bytes = uint32_t(a.d_in) * 2;
+    const uint32_t voff = uint32_t(lane / 8) * row_bytes + 16 * ((lane % 8) ^ swz((wave & 1) * 8 + lane / 8));
+    auto load = [&](int i, int kt, uint32_t stage) {
+        const bool is_x = i < C::kLoadsX;
+        const int rows8 = wave + (is_x ? i : i - C::kLoadsX) * W;
+        load_to_lds_16(is_x ? x_rsrc : w_rsrc, __builtin_amdgcn_readfirstlane(lds0 + stage + (is_x ? C::kWBytes : 0) + rows8 * 1024),
+                       kt < n_kt ? voff : 0x80000000u,
+                       __builtin_amdgcn_readfirstlane(uint32_t(kt) * kRowBytes + uint32_t(rows8) * 8 * row_bytes));
+    };
+    auto load_pair = [&](int i, int kt, uint32_t stage) { load(i % kLoads, kt + i / kLoads, stage + (i / kLoads) * C::kStage); };
+    // operand addresses of this wave's k-step in the first pair of stages
+    const uint32_t w_addr = lds0 + (wave / 2) * C::kStage + col * kRowBytes + 16 * ((4 * (wave % 2) + quad) ^ swz(col));
+    const uint32_t x_addr = w_addr + C::kWBytes;
+    struct Operands {
+        bf16x8 w[FB], x[TB];
+    };
+    auto read = [&](Operands &o, uint32_t stage) {
+#pragma unroll
+        for (int t = 0; t < TB; ++t) o.x[t] = lds_load<bf16x8>(x_addr + stage + t * 16 * kRowBytes);
+#pragma unroll
+        for (int f = 0; f < FB; ++f) o.w[f] = lds_load<bf16x8>(w_addr + stage + f * 16 * kRowBytes);
+    };
+    f32x4 part[FB][TB];
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int t = 0; t < TB; ++t) part[f][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int p = 0; p < S; p += 2)
+#pragma unroll
+        for (int i = 0; i < 2 * kLoads; ++i) load_pair(i, p, p * C::kStage);
+    stage_barrier<(S - 2) * kLoads>();                   // the first pair has landed
+    Operands even, odd;                                  // of the pairs of even and odd number
+    read(even, 0);
+    uint32_t cur = 0;                                    // first stage of the pair at kt
+    auto pair = [&](int kt, const Operands &now, Operands &next) {
+        const uint32_t nxt = cur + 2 * C::kStage == C::kRing ? 0u : cur + 2 * C::kStage;
+        stage_barrier<(S - 4) * kLoads>();               // the next pair has landed; every wave has its operands of this one, whose stages are free
+        read(next, nxt);
+        static_for<0, FB>([&](auto fc) {
+            constexpr int f = decltype(fc)::value;
+#pragma unroll
+            for (int t = 0; t < TB; ++t) part[f][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.w[f], now.x[t], part[f][t], 0, 0, 0);
+            static_for<f * 2 * kLoads / FB, (f + 1) * 2 * kLoads / FB>([&](auto ic) { load_pair(decltype(ic)::value, kt + S, cur); });
+        });
+        cur = nxt;
+    };
+    for (int kt = 0;; kt += 4) {
+        pair(kt, even, odd);
+        if (kt + 2 >= n_kt) break;
+        pair(kt + 2, odd, even);
+        if (kt + 4 >= n_kt) break;
+    }
+    // every wave's partial tile through LDS; a wave adds up its own blocks, in the order of the waves
+    stage_barrier<0>();
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int t = 0; t < TB; ++t) *LP_LDS_PTR(f32x4, uintptr_t(lds0 + ((wave * FB + f) * TB + t) * 1024 + 16 * lane)) = part[f][t];
+    __syncthreads();
+    const int f_own = (wave / C::WT) * C::FB, t_own = (wave % C::WT) * C::TB;
+#pragma unroll
+    for (int f = 0; f < C::FB; ++f)
+#pragma unroll
+        for (int t = 0; t < C::TB; ++t) {
+            f32x4 sum = lds_load<f32x4>(lds0 + ((f_own + f) * TB + t_own + t) * 1024 + 16 * lane);
+#pragma unroll
+            for (int w = 1; w < W; ++w) sum += lds_load<f32x4>(lds0 + ((w * FB + f_own + f) * TB + t_own + t) * 1024 + 16 * lane);
+            acc[f][t] = sum;
+        }
+}
+
 // Per-head RMS normalisation and rotary encoding, in place, of the features a wave holds in acc
 // (those of one section of q or k): block f, token block t, element i of lane (col, quad) is
 // feature 16 f + 4 quad + i of token 16 t + col.  sum_sq(t, h) is the sum of squares over the
@@ -415,7 +519,8 @@ __device__ __forceinline__ void run_tile(uint32_t lds0, const GemmArgs &a, int f
         turns_pre = f32x4{tp[0], tp[1], tp[2], 0.0f};
     }
     f32x4 acc[FB][TB];
-    product<C>(lds0, a, f0, t0, wave, lane, acc);
+    if constexpr (C::SPLIT) product_split_k<C>(lds0, a, f0, t0, wave, lane, acc);
+    else product<C>(lds0, a, f0, t0, wave, lane, acc);
 
     stage_barrier<0>();                                  // the ring is free: every wave has read its last operand
     const uint32_t out_lds = lds0 + wave * (16 * FB * 32), rope_lds = lds0 + C::kOut, ss_lds = rope_lds + kMaxPairs * 16;
@@ -478,7 +583,7 @@ __device__ __forceinline__ void run_tile(uint32_t lds0, const GemmArgs &a, int f
 // P's tiles are ordered in panels of kPanel token tiles, feature tile by feature tile inside a
 // panel: the workgroups an XCD runs at a time share their W and x rows through its L2.
 template <bool QKV, int HD, typename P, typename R>
-__global__ __launch_bounds__(P::kThreads, 2) void gemm_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(P::kThreads, P::SPLIT ? 1 : 2) void gemm_kernel(const GemmArgs a) {
     static_assert(P::kThreads == R::kThreads && P::kF % R::kF == 0 && P::kT % R::kT == 0, "R cuts P");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const uint32_t lds0 = uint32_t(uintptr_t(LP_LDS_PTR(unsigned char, smem)));
@@ -595,6 +700,7 @@ using Tile256x128 = Tiling<2, 4, 8, 2, 3>;
 using Tile128x128 = Tiling<2, 4, 4, 2, 4>;
 using Tile128x64 = Tiling<4, 2, 2, 2, 5>;
 using Tile64x64 = Tiling<2, 2, 2, 2, 5>;
+using Split64x32 = Tiling<2, 2, 2, 1, 8, true>;
 
 // How a call is cut.  A round is one tile on every compute unit (two of the smallest).  Measured per
 // round and k-tile of 64, in us (4096 .. 1024 tokens and features so that one round is full or half
@@ -606,7 +712,7 @@ struct TileCost {
 };
 constexpr TileCost kTileCost[] = {
     {256, 256, 1, 1.01f, 1.41f, 5.0f}, {256, 128, 1, 0.58f, 0.80f, 3.5f}, {128, 128, 1, 0.35f, 0.445f, 2.5f},
-    {128, 64, 1, 0.27f, 0.307f, 0.4f}, {64, 64, 2, 0.19f, 0.36f, 0.4f},
+    {128, 64, 1, 0.27f, 0.307f, 0.4f}, {64, 64, 2, 0.19f, 0.36f, 0.4f}, {64, 32, 1, 0.118f, 0.125f, 1.6f},
 };
 constexpr int kCutNone = -1;
 
@@ -631,7 +737,7 @@ struct Plan {
 // tiles that fill the chip once: 13230 x 5120 -> 5120 is 4 rounds of 256 x 256 tiles and 16 tiles
 // more, 546 us with them whole and 494 us with those 16 cut into 128 x 64; 3780 x 1536 -> 4608 (one
 // round and 14 tiles) 67 and 48 us; 2737 x 1024 -> 1024 (44 tiles) 22 us whole, 10.3 us as 176 tiles of
-// 128 x 128; 520 x 5120 -> 640 (9 tiles) 85 and 18 us as 90 tiles of 64 x 64.
+// 128 x 128; 520 x 5120 -> 640 (9 tiles) 85 us, 17 us as 90 tiles of 64 x 64 and 14 us as 170 of 64 x 32.
 Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
     static constexpr int kCuts[][2] = {{0, 1}, {0, 2}, {0, 3}, {2, 3}};   // the pairs compiled below
     const int n_kt = d_in / kBK;
@@ -643,7 +749,7 @@ Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
         best = Plan{tile, cut, whole};
         best_us = us;
     };
-    for (int k = 0; k < (small_ok ? 5 : 4); ++k) offer(k, kCutNone, count(k), tiles_cost(kTileCost[k], count(k), n_kt, cus));
+    for (int k = 0; k < (small_ok ? 6 : 4); ++k) offer(k, kCutNone, count(k), tiles_cost(kTileCost[k], count(k), n_kt, cus));
     for (const auto &p : kCuts) {
         const TileCost &big = kTileCost[p[0]], &small = kTileCost[p[1]];
         const int64_t tiles = count(p[0]), whole = tiles / cus * cus;
@@ -701,6 +807,9 @@ int launch_gemm(GemmArgs a, hipStream_t stream) {
         case 3 * 8: return launch_tiles<QKV, HD, Tile128x64, Tile128x64>(a, p.whole, stream);
         case 4 * 8:
             if constexpr (kSmall) return launch_tiles<QKV, HD, Tile64x64, Tile64x64>(a, p.whole, stream);
+            [[fallthrough]];
+        case 5 * 8:
+            if constexpr (kSmall) return launch_tiles<QKV, HD, Split64x32, Split64x32>(a, p.whole, stream);
             [[fallthrough]];
         default: return launch_tiles<QKV, HD, Tile256x256, Tile256x256>(a, p.whole, stream);
     }

@@ -65,6 +65,8 @@ def test_linear_matches_oracle(n, d_in, d_out, with_bias):
 
 @pytest.mark.parametrize("n,d_in,d_out", [
     (1, 64, 128), (63, 64, 128), (65, 128, 384), (129, 320, 256),     # 64 x 64 tiles; 1, 2 and 5 k-tiles (5 stages), ragged tokens
+    # 64 x 32, four wavefronts share k: 17 .. 20 k-tiles (pairs in turns of two), one token, ragged tokens, more than one tile
+    (1, 1088, 128), (33, 1152, 384), (95, 1216, 256), (161, 1280, 1152),
     (2563, 64, 640),                    # 128 x 64
     (2737, 1024, 1024),                 # 128 x 128
     (12001, 1024, 384),                 # 128 x 128, the last tiles cut into 128 x 64
@@ -123,6 +125,8 @@ def test_qkv_projection_matches_oracle(heads, hd, grid, offset, split, base, wit
 
 @pytest.mark.parametrize("heads,hd,grid", [
     (8, 64, (3, 5, 9)),                  # 64 x 64 tiles: a head per tile row
+    (18, 64, (3, 5, 7)),                 # 64 x 32, wavefronts share k: two of them share a head
+    (20, 64, (1, 3, 11)),                # the same, ragged tokens
     (8, 128, (3, 5, 9)),                 # 128 x 64: four wavefronts share a head
     (16, 64, (3, 13, 17)),               # 128 x 128: one head per wavefront
     (8, 128, (3, 20, 20)),               # 128 x 128: two wavefronts share a head
