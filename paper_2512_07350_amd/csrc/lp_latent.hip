@@ -231,6 +231,8 @@ __global__ __launch_bounds__(kThreads) void reconstruct_kernel(const float *__re
     for (int c = 0; c < VEC; ++c) { A[c] = 0.0f; Z[c] = 0.0f; }
     const V *pv = reinterpret_cast<const V *>(preds);
     const V *uv = reinterpret_cast<const V *>(g.uncond);
+    V zv;
+    if (GUIDED) zv = reinterpret_cast<const V *>(g.z)[i];      // under way while the predictions are blended
     if (LANE_K) {
         const int k_lo = x0 >= a.ovl ? int(fastdiv(uint32_t(x0 - a.ovl), a.core_div)) : 0;
         const int k_hi = min(a.K - 1, int(fastdiv(uint32_t(x0 + a.ovl), a.core_div)));
@@ -263,7 +265,6 @@ __global__ __launch_bounds__(kThreads) void reconstruct_kernel(const float *__re
 #pragma unroll
     for (int c = 0; c < VEC; ++c) rf[c] = (Z[c] == 1.0f) ? A[c] : __fdiv_rn(A[c], Z[c]);   // Eq. 17 (A/1 = A)
     if (GUIDED) {
-        const V zv = reinterpret_cast<const V *>(g.z)[i];
         const float *zf = reinterpret_cast<const float *>(&zv);
 #pragma unroll
         for (int c = 0; c < VEC; ++c) rf[c] = __fadd_rn(__fmul_rn(g.a, zf[c]), __fmul_rn(g.b, rf[c]));   // Eq. 6
