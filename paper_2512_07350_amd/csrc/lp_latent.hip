@@ -51,12 +51,16 @@ struct VecT<2> { using type = float2; };
 template <>
 struct VecT<1> { using type = float; };
 
+// Arguments.  A kernel meets its arguments in memory that no cache holds yet, one line after the other, and
+// a small call is little else: scalars come first and what belongs to one part stands together.
 struct PartitionArgs {
-    uint32_t n_vec[LP_MAX_PARTS];     // vectors in sub-latent k
-    uint32_t dst_off[LP_MAX_PARTS];   // first vector of sub-latent k in the packed buffer
-    uint32_t src_off[LP_MAX_PARTS];   // s_k * inner, in vectors
-    FastDiv run[LP_MAX_PARTS];        // len_k * inner, in vectors (contiguous run per outer index)
-    uint32_t src_stride;              // extent * inner, in vectors
+    uint32_t src_stride;      // extent * inner, in vectors
+    struct Part {
+        uint32_t n_vec;       // vectors in sub-latent k
+        uint32_t dst_off;     // first vector of sub-latent k in the packed buffer
+        uint32_t src_off;     // s_k * inner, in vectors
+        FastDiv run;          // len_k * inner, in vectors (contiguous run per outer index)
+    } part[LP_MAX_PARTS];
 };
 
 // Eq. 10.  grid = (blocks over the largest sub-latent, K).
@@ -66,12 +70,12 @@ __global__ __launch_bounds__(kThreads) void partition_kernel(const float *__rest
                                                              const PartitionArgs a) {
     using V = typename VecT<VEC>::type;
     const int k = blockIdx.y;
-    const uint32_t n_vec = a.n_vec[k];
+    const uint32_t n_vec = a.part[k].n_vec;
     const uint32_t base = blockIdx.x * (kThreads * UNROLL) + threadIdx.x;
     if (blockIdx.x * (kThreads * UNROLL) >= n_vec) return;
-    const FastDiv run = a.run[k];
-    const V *src = reinterpret_cast<const V *>(z) + a.src_off[k];
-    V *dst = reinterpret_cast<V *>(subs) + a.dst_off[k];
+    const FastDiv run = a.part[k].run;
+    const V *src = reinterpret_cast<const V *>(z) + a.part[k].src_off;
+    V *dst = reinterpret_cast<V *>(subs) + a.part[k].dst_off;
     if (blockIdx.x * (kThreads * UNROLL) + kThreads * UNROLL <= n_vec) {
         // whole block in range: all loads in flight before the first store
         V val[UNROLL];
@@ -97,12 +101,6 @@ __global__ __launch_bounds__(kThreads) void partition_kernel(const float *__rest
 }
 
 struct ReconstructArgs {
-    int32_t s[LP_MAX_PARTS];            // Eq. 9
-    int32_t e[LP_MAX_PARTS];
-    int32_t len[LP_MAX_PARTS];          // l_k
-    int32_t delta_start[LP_MAX_PARTS];  // Eq. 11
-    int32_t delta_end[LP_MAX_PARTS];
-    uint32_t off[LP_MAX_PARTS];         // first vector of prediction k
     int32_t K;
     uint32_t n_vec;                     // vectors in the latent
     uint32_t inner_vec;                 // inner / VEC (X_PER_ELEM = false), else unused
@@ -110,6 +108,12 @@ struct ReconstructArgs {
     FastDiv inner_div;                  // inner, in vectors (X_PER_ELEM = false)
     FastDiv core_div;                   // L * p: core length in latent units (LANE_K)
     int32_t ovl;                        // O * p: overlap in latent units (LANE_K)
+    struct Part {
+        int32_t s, e;                   // Eq. 9
+        int32_t len;                    // l_k
+        int32_t delta_start, delta_end; // Eq. 11
+        uint32_t off;                   // first vector of prediction k
+    } part[LP_MAX_PARTS];
 };
 
 // What the guided step adds to the reconstruction (Eq. 4 before it, Eq. 6 after it).
@@ -124,15 +128,15 @@ struct GuidedArgs {
 // (Eq. 10 along the next rotating dimension), written in the same pass.
 struct ScatterArgs {
     float *subs;                        // packed sub-latents of the next step; nullptr = none
-    int32_t s[LP_MAX_PARTS];            // Eq. 9 of the next step's plan
-    int32_t e[LP_MAX_PARTS];
-    int32_t len[LP_MAX_PARTS];
-    uint32_t off[LP_MAX_PARTS];         // first vector of sub-latent k
     int32_t K;
     uint32_t inner_vec;                 // inner / VEC, or 1 when the next partition dim is the vectorised one
     int32_t x_per_elem;                 // the next partition dim is the vectorised one
     FastDiv lat_run;                    // extent * inner of the next dim, in vectors
     FastDiv inner_div;                  // inner of the next dim, in vectors
+    struct Part {
+        int32_t s, e, len;              // Eq. 9 of the next step's plan
+        uint32_t off;                   // first vector of sub-latent k
+    } part[LP_MAX_PARTS];
 };
 
 // Eq. 12 at local position j; the cases in the order the paper gives them.
@@ -203,12 +207,12 @@ __global__ __launch_bounds__(kThreads) void reconstruct_kernel(const float *__re
     if (LANE_K) {
         const int t = threadIdx.x;
         if (t < a.K) {
-            plan_s[t] = a.s[t];
-            plan_e[t] = a.e[t];
-            plan_len[t] = a.len[t];
-            plan_ds[t] = a.delta_start[t];
-            plan_de[t] = a.delta_end[t];
-            plan_off[t] = a.off[t];
+            plan_s[t] = a.part[t].s;
+            plan_e[t] = a.part[t].e;
+            plan_len[t] = a.part[t].len;
+            plan_ds[t] = a.part[t].delta_start;
+            plan_de[t] = a.part[t].delta_end;
+            plan_off[t] = a.part[t].off;
         }
         __syncthreads();
     }
@@ -251,13 +255,14 @@ __global__ __launch_bounds__(kThreads) void reconstruct_kernel(const float *__re
         }
     } else {
         for (int k = 0; k < a.K; ++k) {
-            const int32_t s = a.s[k];
-            if (x0 < s || x0 >= a.e[k]) continue;
+            const ReconstructArgs::Part &q = a.part[k];
+            const int32_t s = q.s;
+            if (x0 < s || x0 >= q.e) continue;
             const int32_t j0 = x0 - s;
-            const int32_t len = a.len[k];
-            const uint64_t idx = uint64_t(a.off[k]) + (uint64_t(o) * uint32_t(len) + uint32_t(j0)) * a.inner_vec + r_in;
-            blend_term<VEC, false>(GUIDED ? guide<VEC>(pv[idx], uv[idx], g.w) : pv[idx], j0, len, a.delta_start[k],
-                                   a.delta_end[k], A, Z);
+            const int32_t len = q.len;
+            const uint64_t idx = uint64_t(q.off) + (uint64_t(o) * uint32_t(len) + uint32_t(j0)) * a.inner_vec + r_in;
+            blend_term<VEC, false>(GUIDED ? guide<VEC>(pv[idx], uv[idx], g.w) : pv[idx], j0, len, q.delta_start,
+                                   q.delta_end, A, Z);
         }
     }
     V res;
@@ -286,10 +291,10 @@ __global__ __launch_bounds__(kThreads) void reconstruct_kernel(const float *__re
         }
         V *dst = reinterpret_cast<V *>(sc.subs);
         for (int k = 0; k < sc.K; ++k) {
-            const int32_t s = sc.s[k];
-            if (x2 < s || x2 >= sc.e[k]) continue;      // (a vector never straddles s_k or e_k)
-            const uint64_t row = uint64_t(o2) * uint32_t(sc.len[k]) + uint32_t(x2 - s);
-            dst[sc.x_per_elem ? uint64_t(sc.off[k]) + row / VEC : uint64_t(sc.off[k]) + row * sc.inner_vec + r2] = res;
+            const ScatterArgs::Part &q = sc.part[k];
+            if (x2 < q.s || x2 >= q.e) continue;        // (a vector never straddles s_k or e_k)
+            const uint64_t row = uint64_t(o2) * uint32_t(q.len) + uint32_t(x2 - q.s);
+            dst[sc.x_per_elem ? uint64_t(q.off) + row / VEC : uint64_t(q.off) + row * sc.inner_vec + r2] = res;
         }
     }
 }
@@ -384,12 +389,12 @@ int launch_partition(const lp_plan *pl, const float *z, float *subs, hipStream_t
     uint32_t max_vec = 0;
     for (int k = 0; k < pl->K; ++k) {
         const lp_part_info &q = pl->part[k];
-        a.n_vec[k] = uint32_t(q.n_elems / VEC);
-        a.dst_off[k] = uint32_t(q.elem_offset / VEC);
-        a.src_off[k] = uint32_t(int64_t(q.s) * pl->inner / VEC);
+        a.part[k].n_vec = uint32_t(q.n_elems / VEC);
+        a.part[k].dst_off = uint32_t(q.elem_offset / VEC);
+        a.part[k].src_off = uint32_t(int64_t(q.s) * pl->inner / VEC);
         const uint32_t run = uint32_t(int64_t(q.len) * pl->inner / VEC);
-        a.run[k] = make_fastdiv(run ? run : 1);
-        if (a.n_vec[k] > max_vec) max_vec = a.n_vec[k];
+        a.part[k].run = make_fastdiv(run ? run : 1);
+        if (a.part[k].n_vec > max_vec) max_vec = a.part[k].n_vec;
     }
     a.src_stride = uint32_t(int64_t(pl->extent) * pl->inner / VEC);
     if (max_vec == 0) return LP_OK;
@@ -406,12 +411,7 @@ int launch_reconstruct(const lp_plan *pl, const float *preds, float *out, const 
     a.K = pl->K;
     for (int k = 0; k < pl->K; ++k) {
         const lp_part_info &q = pl->part[k];
-        a.s[k] = q.s;
-        a.e[k] = q.e;
-        a.len[k] = q.len;
-        a.delta_start[k] = q.delta_start;
-        a.delta_end[k] = q.delta_end;
-        a.off[k] = uint32_t(q.elem_offset / VEC);
+        a.part[k] = {q.s, q.e, q.len, q.delta_start, q.delta_end, uint32_t(q.elem_offset / VEC)};
     }
     a.n_vec = uint32_t(pl->latent_elems / VEC);
     a.lat_run = make_fastdiv(uint32_t(int64_t(pl->extent) * pl->inner / VEC));
@@ -430,10 +430,7 @@ int launch_reconstruct(const lp_plan *pl, const float *preds, float *out, const 
         sc.K = next->K;
         for (int k = 0; k < next->K; ++k) {
             const lp_part_info &q = next->part[k];
-            sc.s[k] = q.s;
-            sc.e[k] = q.e;
-            sc.len[k] = q.len;
-            sc.off[k] = uint32_t(q.elem_offset / VEC);
+            sc.part[k] = {q.s, q.e, q.len, uint32_t(q.elem_offset / VEC)};
         }
         sc.x_per_elem = (next->inner % VEC) != 0;
         sc.inner_vec = sc.x_per_elem ? 1 : uint32_t(next->inner / VEC);
