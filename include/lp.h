@@ -184,10 +184,10 @@ int lp_reconstruct_guided_step_partition(const lp_plan *plan, const float *cond_
  * irrelevant on entry and undefined on return.  With it the work is dealt evenly
  * over the compute units whatever n_tokens and heads are (partial results of a
  * query tile that two workgroups share pass through the workspace and a second
- * small kernel merges them); with NULL (or too small a workspace) one workgroup
- * is launched per 256-row query tile and head, which leaves compute units idle
- * when their number does not divide the tile count.  Two calls that overlap in
- * time must not share a workspace.
+ * small kernel merges them) wherever that is faster; with NULL (or too small a
+ * workspace) a 256-row query tile of a head is always one workgroup's, which
+ * leaves compute units idle when their number does not divide the tile count.
+ * Two calls that overlap in time must not share a workspace.
  * Short calls (a few hundred tokens, or a few heads) run a kernel of their own
  * that needs no workspace.
  * Products run on bf16 MFMA with binary32 accumulation; q is multiplied by
