@@ -702,7 +702,7 @@ using Tile128x64 = Tiling<4, 2, 2, 2, 5>;
 using Tile64x64 = Tiling<2, 2, 2, 2, 5>;
 using Split64x32 = Tiling<2, 2, 2, 1, 8, true>;
 
-// How a call is cut.  A round is one tile on every compute unit (two of the smallest).  Measured per
+// How a call is cut.  A round is one tile on every compute unit (two of 64 x 64).  Measured per
 // round and k-tile of 64, in us (4096 .. 1024 tokens and features so that one round is full or half
 // full, d_in 1536 and 5120): `part` with at most half of the compute units busy, `full` with all of
 // them, where the power limit lowers the clock; `once` is what a tile costs besides (first loads, stores).
