@@ -1117,6 +1117,22 @@ Deal deal_units(int head_dim, uint32_t units, uint32_t tpu, uint32_t cus, bool m
     return d;
 }
 
+// Which way a call goes: the cheaper of the short kernel, where its grid is one that can be launched, and
+// attention_kernel.
+struct Route {
+    lp::AttentionWay way;
+    Deal deal;
+};
+
+Route pick_route(int head_dim, int64_t n, int all_heads, int cus, bool scratch) {
+    const uint32_t units = uint32_t((n + kBM - 1) / kBM) * uint32_t(all_heads), tpu = uint32_t((n + kBN - 1) / kBN);
+    Route r;
+    r.deal = deal_units(head_dim, units, tpu, uint32_t(cus), scratch);
+    r.way = r.deal.sharers != r.deal.shared ? lp::kAttentionCut : lp::kAttentionWhole;
+    if (lp::attention_short_launchable(n, all_heads) && lp::attention_short_us(n, all_heads, head_dim, cus) < r.deal.us) r.way = lp::kAttentionShort;
+    return r;
+}
+
 template <int D>
 int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hipStream_t stream) {
     int dev = 0;
@@ -1124,13 +1140,14 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     if (cus <= 0) return LP_ERR_HIP;
     a.n_qtiles = (a.n + kBM - 1) / kBM;
     a.tiles_per_unit = (a.n + kBN - 1) / kBN;
-    const uint32_t units = uint32_t(a.n_qtiles) * uint32_t(heads), tpu = uint32_t(a.tiles_per_unit);
+    const uint32_t tpu = uint32_t(a.tiles_per_unit);
     const bool scratch = workspace != nullptr && workspace_bytes >= workspace_bytes_for<D>(cus);
-    const Deal d = deal_units(D, units, tpu, uint32_t(cus), scratch);
+    const Route r = pick_route(D, a.n, heads, cus, scratch);
+    const Deal &d = r.deal;
     // short calls go to attention_short_kernel, which needs no scratch memory
-    if (lp::attention_short_us(a.n, heads, D, cus) < d.us)
+    if (r.way == lp::kAttentionShort)
         return lp::attention_short({a.q, a.k, a.v, a.o, a.stride_tok, a.stride_head, a.stride_batch, a.heads, heads, D, a.n, a.scale_log2e}, stream);
-    const bool cut = d.sharers != d.shared;
+    const bool cut = r.way == lp::kAttentionCut;
     a.ws = cut ? static_cast<float *>(workspace) : nullptr;
     a.shared_units = int(d.shared);
     a.whole_rounds = int(d.rounds);
@@ -1159,6 +1176,10 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
+
+extern "C" int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch) {
+    return pick_route(head_dim, n, all_heads, cus, scratch != 0).way;
+}
 
 extern "C" int64_t lp_attention_workspace_size(int32_t head_dim) {
     if (head_dim != 64 && head_dim != 128) return LP_ERR_UNSUPPORTED;

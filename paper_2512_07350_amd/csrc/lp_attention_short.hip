@@ -350,6 +350,8 @@ int64_t short_groups(int64_t n, int64_t all_heads) { return all_heads * ((n + kR
 
 namespace lp {
 
+bool attention_short_launchable(int64_t n, int64_t all_heads) { return short_groups(n, all_heads) * (64 * kWaves) <= kMaxLaunchThreads; }
+
 // us: launch and first fetch, then the workgroups of a compute unit, each a quarter of the rounds long.
 // A compute unit holds several: two of them take 1.5 times as long as one.  Off by up to 15 % at
 // 96 .. 3780 tokens x 1 .. 40 heads.

@@ -707,14 +707,18 @@ using Split64x32 = Tiling<2, 2, 2, 1, 8, true>;
 // full, d_in 1536 and 5120): `part` with at most half of the compute units busy, `full` with all of
 // them, where the power limit lowers the clock; `once` is what a tile costs besides (first loads, stores).
 struct TileCost {
-    int f, t, per_cu;
+    int f, t, threads, per_cu;
     float part, full, once;
 };
 constexpr TileCost kTileCost[] = {
-    {256, 256, 1, 1.01f, 1.41f, 5.0f}, {256, 128, 1, 0.58f, 0.80f, 3.5f}, {128, 128, 1, 0.35f, 0.445f, 2.5f},
-    {128, 64, 1, 0.27f, 0.307f, 0.4f}, {64, 64, 2, 0.19f, 0.36f, 0.4f}, {64, 32, 1, 0.118f, 0.125f, 1.6f},
+    {256, 256, 512, 1, 1.01f, 1.41f, 5.0f}, {256, 128, 512, 1, 0.58f, 0.80f, 3.5f}, {128, 128, 512, 1, 0.35f, 0.445f, 2.5f},
+    {128, 64, 512, 1, 0.27f, 0.307f, 0.4f}, {64, 64, 256, 2, 0.19f, 0.36f, 0.4f}, {64, 32, 256, 1, 0.118f, 0.125f, 1.6f},
 };
 constexpr int kCutNone = -1;
+template <typename C, int TILE>
+constexpr bool describes() { return C::kF == kTileCost[TILE].f && C::kT == kTileCost[TILE].t && C::kThreads == kTileCost[TILE].threads; }
+static_assert(describes<Tile256x256, 0>() && describes<Tile256x128, 1>() && describes<Tile128x128, 2>() && describes<Tile128x64, 3>() &&
+              describes<Tile64x64, 4>() && describes<Split64x32, 5>(), "the table is in the order of the tilings");
 
 // us for `tiles` tiles of one kind over n_kt k-tiles
 float tiles_cost(const TileCost &c, int64_t tiles, int n_kt, int cus) {
@@ -744,18 +748,19 @@ Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
     auto count = [&](int k) { return ((n + kTileCost[k].t - 1) / kTileCost[k].t) * ((d_out + kTileCost[k].f - 1) / kTileCost[k].f); };
     Plan best{0, kCutNone, 0};
     float best_us = 0.0f;
-    auto offer = [&](int tile, int cut, int64_t whole, float us) {
-        if (best.whole != 0 && us >= best_us) return;
+    auto offer = [&](int tile, int cut, int64_t whole, int64_t workgroups, float us) {
+        // the largest tiling, offered first, stands where a smaller one has more threads than a launch may
+        if (best.whole != 0 && (us >= best_us || workgroups * kTileCost[tile].threads > lp::kMaxLaunchThreads)) return;
         best = Plan{tile, cut, whole};
         best_us = us;
     };
-    for (int k = 0; k < (small_ok ? 6 : 4); ++k) offer(k, kCutNone, count(k), tiles_cost(kTileCost[k], count(k), n_kt, cus));
+    for (int k = 0; k < (small_ok ? 6 : 4); ++k) offer(k, kCutNone, count(k), count(k), tiles_cost(kTileCost[k], count(k), n_kt, cus));
     for (const auto &p : kCuts) {
         const TileCost &big = kTileCost[p[0]], &small = kTileCost[p[1]];
         const int64_t tiles = count(p[0]), whole = tiles / cus * cus;
         if (whole == 0 || whole == tiles) continue;
         const int64_t parts = (tiles - whole) * (big.f / small.f) * (big.t / small.t);
-        offer(p[0], p[1], whole, tiles_cost(big, whole, n_kt, cus) + tiles_cost(small, parts, n_kt, cus));
+        offer(p[0], p[1], whole, whole + parts, tiles_cost(big, whole, n_kt, cus) + tiles_cost(small, parts, n_kt, cus));
     }
     return best;
 }
@@ -791,9 +796,12 @@ int launch_tiles(GemmArgs a, int64_t whole, hipStream_t stream) {
     return lp::launch_kernel(kern, dim3(uint32_t(grid)), dim3(P::kThreads), kLds, stream, a);
 }
 
+// head_dim 0: lp_linear; a head of 128 does not fit the smallest tiles' features
+constexpr bool small_tilings(int head_dim) { return head_dim <= 64; }
+
 template <bool QKV, int HD>
 int launch_gemm(GemmArgs a, hipStream_t stream) {
-    constexpr bool kSmall = !QKV || HD <= 64;             // a head does not fit the smallest tile's features
+    constexpr bool kSmall = small_tilings(QKV ? HD : 0);
     const int cus = lp::device_compute_units();
     if (cus <= 0) return LP_ERR_HIP;
     const Plan p = pick_plan(a.n, a.d_in, a.d_out, kSmall, cus);
@@ -824,6 +832,19 @@ int check_gemm_shape(int64_t n, int32_t d_in, int32_t d_out) {
 }
 
 }  // namespace
+
+extern "C" int lp_internal_gemm_way(int64_t n, int32_t d_in, int32_t d_out, int32_t head_dim, int32_t cus, int64_t way[6]) {
+    const Plan p = pick_plan(n, d_in, d_out, small_tilings(head_dim), cus);
+    const TileCost &c = kTileCost[p.tile], &r = kTileCost[p.cut < 0 ? p.tile : p.cut];
+    const int64_t tiles = ((n + c.t - 1) / c.t) * ((d_out + c.f - 1) / c.f);
+    way[0] = c.f;
+    way[1] = c.t;
+    way[2] = p.cut < 0 ? 0 : r.f;
+    way[3] = p.cut < 0 ? 0 : r.t;
+    way[4] = p.whole + (tiles - p.whole) * (c.f / r.f) * (c.t / r.t);
+    way[5] = c.threads;
+    return LP_OK;
+}
 
 extern "C" int lp_linear(const void *x, const void *w, const float *bias, void *y, int64_t n, int32_t d_in, int32_t d_out,
                          void *stream) {

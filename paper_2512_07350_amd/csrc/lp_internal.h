@@ -23,6 +23,22 @@ struct lp_plan {
 
 namespace lp {
 void set_last_hip_error(int err);
+
+// A launch has at most this many threads (a dispatch states its grid as 32-bit thread counts).
+constexpr int64_t kMaxLaunchThreads = (int64_t(1) << 32) - 1;
+
+// The ways an attention call can go: the kernel whose wavefronts share the keys, or attention_kernel with every
+// query tile whole, or with the tiles of the last round cut into ranges and merged.
+enum AttentionWay { kAttentionShort, kAttentionWhole, kAttentionCut };
+}
+
+// Which way a call of these sizes goes on a device of `cus` compute units.  Host arithmetic for the tests (a
+// test of one kernel states that its sizes run that kernel); not part of the library's interface.
+extern "C" {
+int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch);   // an AttentionWay
+// head_dim 0: lp_linear.  way: features and tokens of a tile, those of the tiles that cut the last round (0: none),
+// the workgroups, and the threads of each.
+int lp_internal_gemm_way(int64_t n, int32_t d_in, int32_t d_out, int32_t head_dim, int32_t cus, int64_t way[6]);
 }
 
 #ifdef __HIPCC__
@@ -50,8 +66,9 @@ struct AttentionCall {
     int32_t n;
     float scale_log2e;
 };
-// The kernel for short sequences (lp_attention_short.hip) and what it is expected to take.
+// The kernel for short sequences (lp_attention_short.hip), whether its grid fits a launch, and what it is expected to take.
 int attention_short(const AttentionCall &c, hipStream_t stream);
+bool attention_short_launchable(int64_t n, int64_t all_heads);
 float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus);
 
 // Compute units of the current device (each host thread remembers the last device it asked about); 0,

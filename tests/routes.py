@@ -1,0 +1,32 @@
+"""The library's internal say on which way a call goes, for tests that are about one kernel."""
+import ctypes as C
+from collections import namedtuple
+
+from paper_2512_07350_amd import binding as lp
+
+WAYS = ("short", "whole", "cut")
+GemmWay = namedtuple("GemmWay", "tile cut workgroups threads")
+
+
+def _cus(cus):
+    if cus is None:
+        import torch
+        cus = torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
+    return cus
+
+
+def attention(n, all_heads, head_dim, scratch=True, cus=None):
+    """"short": the wavefronts of a workgroup share the keys; "whole": 256-row query tiles, each one workgroup's;
+    "cut": those of the last round shared between workgroups and merged."""
+    fn = lp._lib().lp_internal_attention_way
+    fn.argtypes, fn.restype = [C.c_int64] + [C.c_int32] * 4, C.c_int
+    return WAYS[fn(n, all_heads, head_dim, _cus(cus), int(scratch))]
+
+
+def gemm(n, d_in, d_out, head_dim=0, cus=None):
+    """head_dim 0: lp_linear, else lp_qkv_projection (d_out = 3 d_in)."""
+    fn = lp._lib().lp_internal_gemm_way
+    fn.argtypes, fn.restype = [C.c_int64] + [C.c_int32] * 4 + [C.POINTER(C.c_int64)], C.c_int
+    way = (C.c_int64 * 6)()
+    assert fn(n, d_in, d_out, head_dim, _cus(cus), way) == 0
+    return GemmWay((way[0], way[1]), (way[2], way[3]) if way[2] else None, way[4], way[5])

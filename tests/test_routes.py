@@ -1,0 +1,31 @@
+"""Which kernel a call runs is host arithmetic (prices fitted to measured times): its choices without a GPU.
+
+The library's internal functions say which way a call of given sizes would go on a device of `cus` compute units.
+"""
+import pytest
+
+from tests import routes
+
+CUS = 256
+MAX_THREADS = 2 ** 32 - 1        # of a launch: a dispatch states its grid as 32-bit thread counts
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("scratch", [True, False])
+@pytest.mark.parametrize("n,heads", [(64, 1 << 23), (33, 1 << 23), (96, (1 << 24) // 3), (256, 1 << 21), (32, (1 << 24) - 1)])
+def test_attention_never_takes_a_grid_that_cannot_be_launched(n, heads, scratch, hd):
+    """Millions of very short heads: the short kernel takes 256 threads for every 32 rows of a head."""
+    threads = 256 * heads * -(-n // 32)
+    way = routes.attention(n, heads, hd, scratch, CUS)
+    assert way == ("short" if threads <= MAX_THREADS else "whole")
+
+
+@pytest.mark.parametrize("head_dim", [0, 64, 128])
+@pytest.mark.parametrize("d_in", [64, 128, 512, 5120])
+def test_gemm_never_takes_a_grid_that_cannot_be_launched(d_in, head_dim):
+    """Tilings smaller than 256 x 256 are left out where they would need 2^32 threads; 256 x 256 takes the call."""
+    for d_out in (128, 384, 1536, 15360, 1 << 20):
+        for shift in range(10, 31):
+            for n in (1 << shift, (1 << shift) - 77, 3 << (shift - 1)):
+                way = routes.gemm(n, d_in, d_out, head_dim, CUS)
+                assert way.workgroups * way.threads <= MAX_THREADS or (way.tile, way.cut) == ((256, 256), None), (n, d_out, way)
