@@ -1063,9 +1063,10 @@ __global__ __launch_bounds__(32 * (D / 16)) void combine_kernel(const AttnParams
 template <int D>
 int64_t workspace_bytes_for(int cus) { return int64_t(2) * cus * slot_floats<D>() * int64_t(sizeof(float)); }
 
-// ---- which way a call goes.  Times in us on 256 compute units, fitted to 96 .. 13230 tokens x 1 .. 40 heads:
-// every call on every way it can go.  Over 311 of them the choice is off the best way by 0.06 % on
-// average, by 7 % at worst.
+// ---- which way a call goes.  Times in us on 256 compute units, fitted to two grids on which every call was
+// timed on every way it can go: 96 .. 13230 tokens x 1 .. 40 heads (311 calls) and 1 .. 5000 tokens x 1 .. 5000
+// heads (1054).  The choice is off the best way by 0.03 % on average and 4 % at worst on the first, by 0.13 % and
+// 11 % on the second (200 tokens x 256 heads of 64: 13.1 us for 11.8).
 
 // A tile's time while a part `busy` of the compute units works: one workgroup's own pace, slower
 // as the power limit lowers the clock of a full chip.
@@ -1090,18 +1091,21 @@ struct Deal {
 // tiles each.  Measured, whole / cut: 3780 tokens x 12 heads of 128 (180 units on 256) 84 / 86,
 // 4680 x 12 109 / 121, 2999 x 12 70 / 65, 9450 x 12 (444 units) 421 / 404; of 64: 2999 x 16 44.8 / 48.5,
 // 4212 x 8 58 / 47.
-Deal deal_units(int head_dim, uint32_t units, uint32_t tpu, uint32_t cus, bool may_cut) {
+Deal deal_units(int head_dim, uint32_t units, uint32_t tpu, uint32_t cus, float bytes_us, bool may_cut) {
     constexpr uint32_t kMinTiles = 8;
     static_assert(kBoundaryTiles < kMinTiles, "a range of kMinTiles positions must hold a real tile");
-    const float once = head_dim == 128 ? 11.0f : 9.5f;                    // launch, first tiles and Q, the first round, stores
-    const float merge = head_dim == 128 ? 8.0f : 6.0f;                    // combine_kernel and the parts it reads
+    const float once = head_dim == 128 ? 10.5f : 8.8f;                    // launch, first tiles and Q, the first round, stores
+    const float change = head_dim == 128 ? 4.1f : 5.5f;                   // from one unit to the next, in tile times
+    const float merge = head_dim == 128 ? 8.0f : 5.0f;                    // combine_kernel and the parts it reads
     const float full = tile_us(head_dim, 1.0f);
     Deal d;
     d.wgs = units < cus ? units : cus;
     d.rounds = units / cus;
     d.shared = units - d.rounds * cus;
     d.sharers = d.shared;
-    const float whole_us = once + float(d.rounds) * float(tpu + 2) * full;
+    const float changes = float(d.rounds) - (d.rounds > 0 && d.shared == 0 ? 1.0f : 0.0f);
+    // 0.3: what of the transfers the products do not cover
+    const float whole_us = once + 0.3f * bytes_us + (float(d.rounds) * float(tpu) + changes * change) * full;
     d.us = whole_us + float(tpu) * (d.shared > 0 ? tile_us(head_dim, float(d.shared) / float(cus)) : 0.0f);
     if (!may_cut || d.shared == 0) return d;
     uint32_t sharers = uint32_t(uint64_t(d.shared) * tpu / kMinTiles);
@@ -1127,7 +1131,7 @@ struct Route {
 Route pick_route(int head_dim, int64_t n, int all_heads, int cus, bool scratch) {
     const uint32_t units = uint32_t((n + kBM - 1) / kBM) * uint32_t(all_heads), tpu = uint32_t((n + kBN - 1) / kBN);
     Route r;
-    r.deal = deal_units(head_dim, units, tpu, uint32_t(cus), scratch);
+    r.deal = deal_units(head_dim, units, tpu, uint32_t(cus), lp::attention_bytes_us(n, all_heads, head_dim), scratch);
     r.way = r.deal.sharers != r.deal.shared ? lp::kAttentionCut : lp::kAttentionWhole;
     if (lp::attention_short_launchable(n, all_heads) && lp::attention_short_us(n, all_heads, head_dim, cus) < r.deal.us) r.way = lp::kAttentionShort;
     return r;

@@ -70,6 +70,10 @@ struct AttentionCall {
 int attention_short(const AttentionCall &c, hipStream_t stream);
 bool attention_short_launchable(int64_t n, int64_t all_heads);
 float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus);
+// us that q, k, v and o take at the rate of a large copy, 4.7 TB/s
+inline float attention_bytes_us(int64_t n, int64_t all_heads, int head_dim) {
+    return 8.0f * float(n) * float(all_heads) * float(head_dim) / 4.7e6f;
+}
 
 // Compute units of the current device (each host thread remembers the last device it asked about); 0,
 // with the HIP error recorded, if there is none.

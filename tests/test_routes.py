@@ -29,3 +29,22 @@ def test_gemm_never_takes_a_grid_that_cannot_be_launched(d_in, head_dim):
             for n in (1 << shift, (1 << shift) - 77, 3 << (shift - 1)):
                 way = routes.gemm(n, d_in, d_out, head_dim, CUS)
                 assert way.workgroups * way.threads <= MAX_THREADS or (way.tile, way.cut) == ((256, 256), None), (n, d_out, way)
+
+
+# us on 256 compute units, short kernel / 256-row query tiles (whole or cut), with scratch memory: calls of many heads and
+# a few hundred tokens, where the dearer way costs 14 % and more
+@pytest.mark.parametrize("n,heads,hd,way", [
+    (225, 256, 128, "long"),     # 28.9 / 21.7
+    (200, 256, 128, "long"),     # 25.5 / 19.8
+    (200, 200, 128, "long"),     # 21.9 / 17.8
+    (160, 256, 128, "long"),     # 19.1 / 16.0
+    (384, 256, 128, "long"),     # 48.9 / 41.7
+    (257, 1000, 64, "short"),    # 55.9 / 80.9
+    (300, 640, 64, "short"),     # 42.6 / 55.9
+    (129, 2000, 64, "short"),    # 51.0 / 66.9
+    (600, 400, 64, "short"),     # 67.7 / 78.4
+    (850, 150, 64, "short"),     # 48.4 / 55.6
+    (200, 4, 64, "short"), (1000, 12, 128, "short"), (2999, 16, 64, "long"), (3780, 12, 128, "long"),
+])
+def test_attention_takes_the_faster_way(n, heads, hd, way):
+    assert (routes.attention(n, heads, hd, True, CUS) == "short") == (way == "short")
