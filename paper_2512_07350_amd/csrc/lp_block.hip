@@ -702,17 +702,18 @@ using Tile128x64 = Tiling<4, 2, 2, 2, 5>;
 using Tile64x64 = Tiling<2, 2, 2, 2, 5>;
 using Split64x32 = Tiling<2, 2, 2, 1, 8, true>;
 
-// How a call is cut.  A round is one tile on every compute unit (two of 64 x 64).  Measured per
-// round and k-tile of 64, in us (4096 .. 1024 tokens and features so that one round is full or half
-// full, d_in 1536 and 5120): `part` with at most half of the compute units busy, `full` with all of
-// them, where the power limit lowers the clock; `once` is what a tile costs besides (first loads, stores).
+// How a call is cut.  A round is one tile on every compute unit (two of 64 x 64).  Per round, in us, fitted to 1332 calls timed
+// on every tiling (1 .. 200000 tokens, d_in 64 .. 13824, d_out 128 .. 13824; 7 .. 11 % rms a tiling): a k-tile of 64, and `once`, what a
+// tile costs besides (first loads, stores); `part` with at most half of the compute units busy, `full` with all of
+// them, where the power limit lowers the clock and the stores of all tiles share the memory's rate.
 struct TileCost {
     int f, t, threads, per_cu;
-    float part, full, once;
+    float part, full, once_part, once_full;
 };
 constexpr TileCost kTileCost[] = {
-    {256, 256, 512, 1, 1.01f, 1.41f, 5.0f}, {256, 128, 512, 1, 0.58f, 0.80f, 3.5f}, {128, 128, 512, 1, 0.35f, 0.445f, 2.5f},
-    {128, 64, 512, 1, 0.27f, 0.307f, 0.4f}, {64, 64, 256, 2, 0.19f, 0.36f, 0.4f}, {64, 32, 256, 1, 0.118f, 0.125f, 1.6f},
+    {256, 256, 512, 1, 1.05f, 1.39f, 1.7f, 5.5f},  {256, 128, 512, 1, 0.58f, 0.80f, 0.8f, 3.3f},
+    {128, 128, 512, 1, 0.335f, 0.458f, 0.0f, 2.2f}, {128, 64, 512, 1, 0.235f, 0.295f, 0.0f, 1.6f},
+    {64, 64, 256, 2, 0.17f, 0.32f, 0.0f, 1.3f},     {64, 32, 256, 1, 0.09f, 0.13f, 0.4f, 1.3f},
 };
 constexpr int kCutNone = -1;
 template <typename C, int TILE>
@@ -723,11 +724,12 @@ static_assert(describes<Tile256x256, 0>() && describes<Tile256x128, 1>() && desc
 // us for `tiles` tiles of one kind over n_kt k-tiles
 float tiles_cost(const TileCost &c, int64_t tiles, int n_kt, int cus) {
     const int64_t slots = int64_t(cus) * c.per_cu, rounds = tiles / slots, rest = tiles - rounds * slots;
-    float us = float(rounds) * (c.full * float(n_kt) + c.once);
+    float us = float(rounds) * (c.full * float(n_kt) + c.once_full);
     if (rest > 0) {
         const float u = float(rest) / float(slots);
-        const float per = u <= 0.5f ? c.part : c.part + (u - 0.5f) * 2.0f * (c.full - c.part);
-        us += per * float(n_kt) + c.once;
+        // from half to all of the compute units; with two tiles to a unit every tile beyond one each shares its unit
+        const float f = u <= 0.5f ? 0.0f : c.per_cu > 1 ? 1.0f : (u - 0.5f) * 2.0f;
+        us += (c.part + f * (c.full - c.part)) * float(n_kt) + c.once_part + f * (c.once_full - c.once_part);
     }
     return us;
 }
@@ -742,6 +744,10 @@ struct Plan {
 // more, 546 us with them whole and 494 us with those 16 cut into 128 x 64; 3780 x 1536 -> 4608 (one
 // round and 14 tiles) 67 and 48 us; 2737 x 1024 -> 1024 (44 tiles) 22 us whole, 10.3 us as 176 tiles of
 // 128 x 128; 520 x 5120 -> 640 (9 tiles) 85 us, 17 us as 90 tiles of 64 x 64 and 14 us as 170 of 64 x 32.
+// With a k of a few tiles a round is its first loads and its stores, and large tiles are the cheaper ones: 60000 x 64 -> 3840
+// takes 96 us in 256 x 256 tiles and 219 in 128 x 64; in the kernel of two tilings such rounds take up to 20 %
+// longer (24000 x 256 -> 5120: 87 us whole, 106 cut), so that a cut has to promise 5 % there.
+// Over the calls above of 6.5 us and more the choice is off the best tiling by 1.4 % on average.
 Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
     static constexpr int kCuts[][2] = {{0, 1}, {0, 2}, {0, 3}, {2, 3}};   // the pairs compiled below
     const int n_kt = d_in / kBK;
@@ -760,7 +766,8 @@ Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
         const int64_t tiles = count(p[0]), whole = tiles / cus * cus;
         if (whole == 0 || whole == tiles) continue;
         const int64_t parts = (tiles - whole) * (big.f / small.f) * (big.t / small.t);
-        offer(p[0], p[1], whole, whole + parts, tiles_cost(big, whole, n_kt, cus) + tiles_cost(small, parts, n_kt, cus));
+        const float cut_us = tiles_cost(big, whole, n_kt, cus) + tiles_cost(small, parts, n_kt, cus);
+        offer(p[0], p[1], whole, whole + parts, n_kt < 12 ? 1.05f * cut_us : cut_us);
     }
     return best;
 }

@@ -48,3 +48,30 @@ def test_gemm_never_takes_a_grid_that_cannot_be_launched(d_in, head_dim):
 ])
 def test_attention_takes_the_faster_way(n, heads, hd, way):
     assert (routes.attention(n, heads, hd, True, CUS) == "short") == (way == "short")
+
+
+# us on 256 compute units of the tiles taken / of 128 x 64 tiles: products of a short k, where a tile is little more than
+# its first loads and its stores
+@pytest.mark.parametrize("n,d_in,d_out,tiles", [
+    (200000, 64, 1536, [(256, 256)]),              # 130 / 292
+    (60000, 64, 3840, [(256, 256)]),               # 96 / 219
+    (10000, 64, 13824, [(256, 256)]),              # 59 / 131
+    (4096, 64, 5120, [(256, 256)]),                # 13 / 23
+    (200000, 128, 640, [(256, 256)]),              # 78 / 162
+    (6500, 128, 5120, [(256, 256)]),               # 22 / 39
+    (60000, 256, 640, [(256, 256), (256, 128)]),   # 35 / 59
+    (1500, 256, 5120, [(256, 256), (256, 128)]),   # 10 / 14
+])
+def test_gemm_of_a_short_k_takes_large_tiles(n, d_in, d_out, tiles):
+    assert routes.gemm(n, d_in, d_out, 0, CUS).tile in tiles
+
+
+@pytest.mark.parametrize("n,d_in,d_out,tile,cut", [
+    (520, 5120, 640, (64, 32), None), (13230, 5120, 5120, (256, 256), (128, 64)), (13230, 5120, 15360, (256, 256), (128, 128)),
+    (3780, 1536, 4608, (256, 256), (128, 64)), (3780, 1536, 1536, (256, 128), None), (2737, 1024, 1024, (128, 128), None),
+    (24000, 256, 5120, (256, 256), None),          # 87 us; 106 with the last round cut: short rounds take longer in the kernel of two tilings
+    (300, 13824, 3840, (128, 64), None),           # 59 us; 77 in 64 x 64: two of them on one compute unit take twice as long
+])
+def test_gemm_tiles_of_the_block(n, d_in, d_out, tile, cut):
+    way = routes.gemm(n, d_in, d_out, 0, CUS)
+    assert (way.tile, way.cut) == (tile, cut)
