@@ -1,6 +1,6 @@
 """lp_attention_static (the entry point for callers that cannot allocate) against lp_attention.
 
-Two calls in a row on the one device-resident scratch array, the second with a smaller input,
+Calls in a row on the one device-resident scratch array, each smaller than the one before it,
 each compared with the workspace entry point on the same inputs (same kernels, same split of
 the work: bit-identical) and with the oracle at the attention tolerance.
 """
@@ -9,6 +9,7 @@ import pytest
 
 from oracle import lp_oracle as orc
 from paper_2512_07350_amd import synth
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -29,11 +30,28 @@ def test_static_scratch_two_calls_second_smaller():
     from tests import gpu_util as g
     from paper_2512_07350_amd import binding as lp
     assert lp.lp_attention_static_scratch_bytes() >= lp.lp_attention_workspace_size(128)
-    # shapes whose query tiles are shared between workgroups, so the scratch really carries
-    # partial results: first the larger, then a smaller one that leaves most slots untouched
+    # few heads: all three run the short kernel, which leaves the scratch array alone
     for n, heads, hd, seed in ((3000, 3, 128, 811), (700, 2, 128, 812), (333, 5, 64, 813)):
         q, k, v = synth.qkv_bf16(seed, n, heads, hd)
         got = _static(q, k, v)
         ref = g.hip_attention(q, k, v, balanced=True)
         assert np.array_equal(got, ref), "n=%d: differs from lp_attention with a workspace" % n
         g.assert_attention_close(got, orc.attention(q, k, v), "static n=%d" % n)
+
+
+@pytest.mark.parametrize("calls", [
+    [(3000, 12, 128), (1500, 12, 128), (5000, 1, 128)],      # 144 and 72 query tiles for 256 compute units; 20, each in about ten parts
+    [(2305, 40, 64), (3000, 12, 64), (5000, 2, 64)],         # 144 tiles left after a round of whole ones; 144; 40
+    [(5000, 7, 64), (1500, 12, 128)],                        # the slots of another head_dim lie elsewhere in the array
+], ids=["128", "64", "64 then 128"])
+def test_static_scratch_carries_the_parts_of_shared_query_tiles(calls):
+    """Calls whose query tiles are cut: every one finds the slots as the larger call before it left them."""
+    from tests import gpu_util as g
+    for i, (n, heads, hd) in enumerate(calls):
+        assert routes.attention(n, heads, hd, scratch=True) == "cut"
+        q, k, v = synth.qkv_bf16(820 + i + n + hd, n, heads, hd)
+        got = _static(q, k, v)
+        ref = g.hip_attention(q, k, v, balanced=True)
+        assert np.array_equal(got, ref), "n=%d: differs from lp_attention with a workspace" % n
+        rows = synth.sample_rows(n, 96, seed=n, tile=256)
+        g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "static n=%d" % n)
