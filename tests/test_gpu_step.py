@@ -5,6 +5,7 @@ import pytest
 
 from oracle import lp_oracle as orc
 from paper_2512_07350_amd import synth
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -79,7 +80,8 @@ def test_step_replays_from_a_captured_graph():
     o = torch.empty_like(q)
     ws, ws_bytes = g.workspace(hd)
     # a second, larger call whose query tiles are shared between workgroups (workspace + merge kernel)
-    n2, heads2, hd2 = 1000, 3, 128
+    n2, heads2, hd2 = 1500, 12, 128
+    assert routes.attention(n, heads, hd) == "short" and routes.attention(n2, heads2, hd2) == "cut"
     q2, k2, v2 = (g.to_dev_bf16(a) for a in synth.qkv_bf16(4, n2, heads2, hd2))
     o2 = torch.empty_like(q2)
     ws2, ws2_bytes = g.workspace(hd2)
