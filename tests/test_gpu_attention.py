@@ -8,6 +8,7 @@ import pytest
 
 from oracle import lp_oracle as orc
 from paper_2512_07350_amd import synth
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -309,12 +310,26 @@ def test_scores_far_above_the_first_round(balanced, hd, profile):
 
 
 
-# With 40 heads these lengths run the kernel of 256-row query tiles; the same lengths with few heads, and
-# everything of a few hundred tokens, run the kernel whose wavefronts share the keys.
-@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+# Lengths that run the kernel of 256-row query tiles at either head dim, with 104 tiles left after a round: cut with scratch
+# memory, whole without.  33 .. 36 key tiles (four are unrolled), the last of 1, 2, 31 .. 33, 63 or 64 keys.
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("n", [2049, 2080, 2081, 2112, 2113, 2145, 2176, 2178, 2239, 2240, 2271, 2304])
+def test_long_kernel_at_tile_and_round_edges(n, hd, balanced):
+    from tests import gpu_util as g
+    assert routes.attention(n, 40, hd, balanced) == ("cut" if balanced else "whole")
+    q, k, v = synth.qkv_bf16(4500 + 2 * n + hd, n, 40, hd)
+    got = g.hip_attention(q, k, v, balanced=balanced)
+    rows = synth.sample_rows(n, 48, seed=n, tile=256)
+    g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "n=%d hd=%d" % (n, hd))
+    assert np.all(np.isfinite(got))
+
+
+# 40 heads: the lengths around which a call changes from one kernel to the other
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("n", [1536, 1537, 1567, 1599, 1600, 1601, 1632, 1791, 1793, 2047])
-def test_long_kernel_at_tile_and_round_edges(n, hd, balanced):
+def test_lengths_around_the_change_of_kernels(n, hd, balanced):
     from tests import gpu_util as g
     q, k, v = synth.qkv_bf16(4500 + 2 * n + hd, n, 40, hd)
     got = g.hip_attention(q, k, v, balanced=balanced)
@@ -323,11 +338,27 @@ def test_long_kernel_at_tile_and_round_edges(n, hd, balanced):
     assert np.all(np.isfinite(got))
 
 
-# the rounds of 32 keys are dealt to four wavefronts: no round, one, a ragged last one, one more than the others
+# The shortest calls that run the kernel of 256-row query tiles (hundreds of heads): 3 tiles and more, below, at and above the 352 and 608 keys from
+# which four tiles, and four more, are unrolled.
+@pytest.mark.parametrize("n,hd", [(n, 128) for n in (129, 160, 161, 192, 193, 255, 256, 321, 351, 352, 353, 384, 416, 449, 511, 575, 607, 608, 609, 640)]
+                         + [(n, 64) for n in (225, 255, 256, 385, 415, 416, 447, 448, 449, 480, 511, 512, 609, 640, 641, 673, 704, 705)])
+def test_long_kernel_on_few_tiles(n, hd):
+    from tests import gpu_util as g
+    heads = 256
+    assert routes.attention(n, heads, hd) == routes.attention(n, heads, hd, scratch=False) == "whole"
+    q, k, v = synth.qkv_bf16(4600 + 2 * n + hd, n, heads, hd)
+    got = g.hip_attention(q, k, v)
+    rows = synth.sample_rows(n, 24, seed=n, tile=256)
+    g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "n=%d hd=%d" % (n, hd))
+    assert np.all(np.isfinite(got))
+
+
+# The kernel for short calls: the rounds of 32 keys are dealt to four wavefronts: no round, one, a ragged last one, one more than the others
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("n", [3, 30, 62, 98, 126, 130, 161, 225, 383, 385, 1151])
 def test_short_kernel_at_round_edges(n, hd):
     from tests import gpu_util as g
+    assert routes.attention(n, 2, hd) == "short"
     q, k, v = synth.qkv_bf16(4700 + 2 * n + hd, n, 2, hd)
     g.assert_attention_close(g.hip_attention(q, k, v), orc.attention(q, k, v), "n=%d hd=%d" % (n, hd))
 
@@ -338,6 +369,7 @@ def test_short_kernel_at_round_edges(n, hd):
 def test_long_kernel_scores_far_above_the_first_round(n, heads, profile, hd):
     """test_scores_far_above_the_first_round at lengths that run the kernel of 256-row query tiles."""
     from tests import gpu_util as g
+    assert routes.attention(n, heads, hd) == ("whole" if heads == 40 else "cut")
     rng = np.random.default_rng(4321)
     base = np.where(rng.random((heads, hd)) < 0.5, -1.0, 1.0).astype(np.float32)
     level = np.where(np.arange(n) < 40, 0.0, 32.0) if profile == "cliff" else np.minimum(np.floor(np.arange(n) / 32.0), 32.0)
@@ -352,13 +384,14 @@ def test_long_kernel_scores_far_above_the_first_round(n, heads, profile, hd):
     assert np.all(np.isfinite(got))
 
 
-# 256-row query tiles (units) on 256 compute units: everybody one or two units, and 64, 48, 144, 224 or 194 units left,
-# taken whole or (with scratch memory, the first three) cut into ranges that start and end inside a unit
-@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
-@pytest.mark.parametrize("hd", [64, 128])
-@pytest.mark.parametrize("n,heads", [(1795, 40), (3329, 40), (2305, 40), (2999, 40), (520, 150)])
+# 256-row query tiles (units) on 256 compute units: everybody one or two units, and 48, 64, 104, 144, 194 or 224 units
+# left, taken whole or (with scratch memory, up to 144 of them) cut into ranges that start and end inside a unit
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
+@pytest.mark.parametrize("n,heads,hd", [(1795, 40, 128), (2305, 40, 128), (3329, 40, 128), (2999, 40, 128), (700, 150, 128),
+                                        (2049, 40, 64), (2305, 40, 64), (3329, 40, 64), (2999, 40, 64), (700, 150, 64)])
 def test_units_left_over_after_whole_rounds(n, heads, hd, balanced):
     from tests import gpu_util as g
+    assert routes.attention(n, heads, hd, balanced) == ("cut" if balanced and n not in (2999, 700) else "whole")
     q, k, v = synth.qkv_bf16(4900 + n + heads, n, heads, hd)
     got = g.hip_attention(q, k, v, balanced=balanced)
     rows = synth.sample_rows(n, 24, seed=n, tile=256)
