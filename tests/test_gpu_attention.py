@@ -415,3 +415,98 @@ def test_short_kernel_keys_with_score_minus_infinity(dead, hd):
     p = np.exp(s - s.max(-1, keepdims=True))
     want = np.einsum("hqk,khd->qhd", p / p.sum(-1, keepdims=True), vf[alive])
     g.assert_attention_close(g.hip_attention(q, k, v), want, "dead %s" % (dead,))
+
+
+# Calls of twelve heads in all that are cut with scratch memory and whole without: padded and head-major layouts, items one
+# after the other and side by side.  Every gap of q, k, v and o holds NaN: nothing is read from it or written to it.
+@pytest.mark.parametrize("balanced", [True, False], ids=["cut", "whole"])
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("layout", ["token-padded", "head-major", "head-major-padded", "items-padded", "items-side-by-side"])
+def test_long_kernel_layouts(layout, hd, balanced):
+    from tests import gpu_util as g
+    import torch
+    from paper_2512_07350_amd import binding as lp
+    n = 2999
+    batch = 2 if layout.startswith("items") else 1
+    heads = 12 // batch
+    assert routes.attention(n, 12, hd, balanced) == ("cut" if balanced else "whole")
+    if layout == "token-padded":
+        stride_head, stride_batch = hd + 8, 0
+        stride_tok = heads * stride_head + 24
+    elif layout == "head-major":
+        stride_tok, stride_head, stride_batch = hd, n * hd, 0
+    elif layout == "head-major-padded":
+        stride_tok, stride_batch = hd + 16, 0
+        stride_head = n * stride_tok + 40
+    elif layout == "items-padded":
+        stride_head = hd + 8
+        stride_tok = heads * stride_head + 8
+        stride_batch = n * stride_tok + 72
+    else:
+        stride_head = hd + 8
+        stride_batch = heads * stride_head + 16
+        stride_tok = batch * stride_batch + 8
+    total = (batch - 1) * stride_batch + (n - 1) * stride_tok + (heads - 1) * stride_head + hd + 64
+    where = (np.arange(batch)[:, None, None, None] * stride_batch + np.arange(n)[:, None, None] * stride_tok
+             + np.arange(heads)[:, None] * stride_head + np.arange(hd))
+    items = [synth.qkv_bf16(5100 + hd + b, n, heads, hd) for b in range(batch)]
+
+    def pack(j):
+        buf = np.full(total, 0x7fc0, dtype=np.uint16)
+        buf[where] = np.stack([it[j] for it in items])
+        return g.to_dev_bf16(buf)
+
+    qd, kd, vd = pack(0), pack(1), pack(2)
+    od = torch.full((total,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ws, ws_bytes = g.workspace(hd) if balanced else (None, 0)
+    lp.lp_attention_batch(qd, kd, vd, od, batch, n, heads, hd, stride_batch, stride_tok, stride_head, 0.0, ws, ws_bytes, g.stream())
+    torch.cuda.synchronize()
+    out = g.from_dev_bf16(od)
+    got = out[where]
+    assert np.all(np.isfinite(got))
+    rows = synth.sample_rows(n, 64, seed=hd, tile=256)
+    for b, (q, k, v) in enumerate(items):
+        g.assert_attention_close(got[b][rows], orc.attention(q, k, v, rows=rows), "%s item %d hd=%d" % (layout, b, hd))
+    out[where] = np.nan
+    assert np.all(np.isnan(out)), "wrote outside its rows"
+
+
+# The parts of a query tile: one tile of few heads in about ten parts each, up to tiles in two
+@pytest.mark.parametrize("n,heads,hd", [(5000, 1, 128), (5000, 2, 64), (7410, 2, 128), (3329, 5, 128), (5000, 7, 128), (5000, 7, 64), (2721, 12, 64)])
+def test_query_tiles_cut_into_parts(n, heads, hd):
+    """Cut and merged against the oracle and against a call without scratch memory."""
+    from tests import gpu_util as g
+    assert routes.attention(n, heads, hd) == "cut" and routes.attention(n, heads, hd, scratch=False) != "cut"
+    q, k, v = synth.qkv_bf16(9100 + n + heads, n, heads, hd)
+    rows = synth.sample_rows(n, 160, seed=n, tile=256)
+    want = orc.attention(q, k, v, rows=rows)
+    cut = g.hip_attention(q, k, v)
+    plain = g.hip_attention(q, k, v, balanced=False)
+    g.assert_attention_close(cut[rows], want, "cut n=%d" % n)
+    assert np.all(np.isfinite(cut))
+    assert np.max(np.abs(cut - plain)) <= 2e-2
+
+
+@pytest.mark.parametrize("balanced", [True, False], ids=["cut", "whole"])
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("order", ["rising", "falling"])
+def test_long_kernel_scores_that_keep_rising(order, hd, balanced):
+    """test_scores_that_keep_rising_along_the_keys in the kernel of 256-row query tiles: about half a log2 unit a
+    round, so that a tile's parts have maxima far apart and the first round's lies 47 units below the last one's."""
+    from tests import gpu_util as g
+    n, heads = 3000, 12
+    assert routes.attention(n, heads, hd, balanced) == ("cut" if balanced else "whole")
+    rng = np.random.default_rng(97)
+    base = rng.standard_normal((heads, hd)).astype(np.float32)
+    base /= np.linalg.norm(base, axis=1, keepdims=True)
+    qf = np.broadcast_to(base[None] * np.float32(np.sqrt(hd)) * 4.0, (n, heads, hd)) + 0.05 * rng.standard_normal((n, heads, hd)).astype(np.float32)
+    ramp = (np.arange(n, dtype=np.float32) / 32.0 * 0.0875)[:, None, None]
+    kf = base[None] * ramp + 0.05 * rng.standard_normal((n, heads, hd)).astype(np.float32)
+    vf = rng.standard_normal((n, heads, hd)).astype(np.float32)
+    q, k, v = (synth.f32_to_bf16_bits(a) for a in (qf, kf, vf))
+    if order == "falling":
+        k, v = k[::-1].copy(), v[::-1].copy()
+    got = g.hip_attention(q, k, v, balanced=balanced)
+    rows = synth.sample_rows(n, 64, seed=hd, tile=256)
+    g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "%s scores" % order)
+    assert np.all(np.isfinite(got))
