@@ -83,8 +83,8 @@ def workspace(head_dim: int):
 
 def hip_attention(q: np.ndarray, k: np.ndarray, v: np.ndarray, scale: float = 0.0, balanced: bool = True) -> np.ndarray:
     """q, k, v: uint16 [n, heads, d] token-major.  Returns float32 [n, heads, d].
-    balanced=True passes a workspace (the launch configuration the benchmark times);
-    False launches one workgroup per query tile and head."""
+    balanced=True passes a workspace (the launch configuration the benchmark times); without one no query
+    tile is shared between workgroups.  Which kernel runs follows from the sizes: tests/routes.py."""
     n, heads, d = q.shape
     qd, kd, vd = to_dev_bf16(q), to_dev_bf16(k), to_dev_bf16(v)
     od = torch.full((n, heads, d), float("nan"), dtype=torch.bfloat16, device="cuda")

@@ -13,7 +13,7 @@ from tests import routes
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 200, 255, 256, 257, 320, 513, 1000])
 def test_small_full_oracle(n, hd, balanced):
@@ -27,9 +27,8 @@ def test_small_full_oracle(n, hd, balanced):
 
 @pytest.mark.parametrize("n,heads,hd", [(3000, 1, 128), (2048, 2, 128), (700, 5, 64), (5000, 7, 64), (64, 40, 128)])
 def test_work_split_across_workgroups(n, heads, hd):
-    """Few (query tile, head) units: with a workspace every unit is shared by several
-    workgroups and the merge kernel produces the output; must agree with the oracle and
-    with the unsplit launch."""
+    """Few (query tile, head) units, with and without scratch memory, whichever kernel that runs (5000 x 7 is cut
+    and merged, see also test_query_tiles_cut_into_parts): must agree with the oracle and with each other."""
     from tests import gpu_util as g
     q, k, v = synth.qkv_bf16(9000 + n + heads, n, heads, hd)
     rows = synth.sample_rows(n, 160, seed=n, tile=256)
@@ -43,7 +42,7 @@ def test_work_split_across_workgroups(n, heads, hd):
 
 
 @pytest.mark.parametrize("layout", ["outer", "inner"])
-@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 @pytest.mark.parametrize("n,heads,hd,batch", [(1000, 3, 128, 2), (333, 2, 64, 3), (64, 1, 128, 2), (1, 2, 64, 2)])
 def test_batch_items_are_independent_calls(n, heads, hd, batch, balanced, layout):
     """lp_attention_batch (the conditional / unconditional pair of Eq. 4 is batch = 2): every item
@@ -78,7 +77,7 @@ def test_tiny_config_partitions_full_oracle():
         g.assert_attention_close(g.hip_attention(q, k, v), orc.attention(q, k, v), "tiny k=%d" % k_part)
 
 
-@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 def test_medium_full_oracle_spans_many_tiles(balanced):
     # 3276 tokens (the smallest 33-frame partition along H), all rows, 2 heads
     from tests import gpu_util as g
@@ -209,8 +208,8 @@ def test_14b_shape_sampled_rows():
 
 
 def test_random_shapes_and_layouts():
-    """Seeded random token counts, head counts, head dims, batch sizes and padded strides, in both
-    launch modes; every item against the oracle on all rows."""
+    """Seeded random token counts, head counts, head dims, batch sizes and padded strides, with and without scratch
+    memory (calls of few heads: all of them run the kernel for short calls); every item against the oracle on all rows."""
     from tests import gpu_util as g
     import torch
     from paper_2512_07350_amd import binding as lp
@@ -257,11 +256,11 @@ def test_random_shapes_and_layouts():
         assert np.all(np.isnan(out[~written])), "case %d wrote outside its rows" % case
 
 
-@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 def test_scores_that_keep_rising_along_the_keys(balanced):
     """Keys ordered so that the scores grow by about two octaves from one 32-key round to the
     next: the running maximum has to be raised (and the accumulated output rescaled) over and
-    over, across tiles and across the parts of a query tile that different workgroups compute."""
+    over, and the parts that different wavefronts of the kernel for short calls compute have maxima far apart."""
     from tests import gpu_util as g
     n, heads, hd = 1500, 2, 128
     rng = np.random.default_rng(99)
@@ -280,14 +279,14 @@ def test_scores_that_keep_rising_along_the_keys(balanced):
     g.assert_attention_close(got_r, want, "falling scores")
 
 
-@pytest.mark.parametrize("balanced", [True, False], ids=["balanced", "tile-per-workgroup"])
+@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("profile", ["ramp", "cliff"])
 def test_scores_far_above_the_first_round(balanced, hd, profile):
     """Scores that climb 8 log2 units per 32-key round up to 2^256 times the first round's level
     and stay there ("ramp"), or get there in one step ("cliff"): exp2 of a score relative to the first round's maximum overflows
-    binary32, which the kernel has to notice and recover from (it repeats the segment with the
-    running-maximum check).  Every operand is exactly representable, the scale is chosen so that
+    binary32, so the kernel for short calls, which these sizes run, has to raise its maximum in time (the kernel of 256-row
+    query tiles repeats a stretch of keys: test_long_kernel_scores_far_above_the_first_round).  Every operand is exactly representable, the scale is chosen so that
     the pre-scaled queries are too, so the stated tolerance applies unchanged."""
     from tests import gpu_util as g
     n, heads = 1500, 2
