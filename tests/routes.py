@@ -5,7 +5,12 @@ from collections import namedtuple
 from paper_2512_07350_amd import binding as lp
 
 WAYS = ("short", "whole", "cut")
-GemmWay = namedtuple("GemmWay", "tile cut workgroups threads")
+
+
+class GemmWay(namedtuple("GemmWay", "tile cut workgroups threads")):
+    def __str__(self):
+        """Features x tokens of a tile, + those of the tiles that cut the last round."""
+        return "%dx%d" % self.tile + ("+%dx%d" % self.cut if self.cut else "")
 
 
 def _cus(cus):

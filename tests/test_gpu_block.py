@@ -12,6 +12,7 @@ import pytest
 
 from oracle import lp_oracle as orc
 from paper_2512_07350_amd import synth
+from tests import routes
 
 pytestmark = pytest.mark.gpu
 
@@ -63,22 +64,23 @@ def test_linear_matches_oracle(n, d_in, d_out, with_bias):
     _close(_linear(x, w, b), orc.linear(x, w, b), "linear %dx%d->%d" % (n, d_in, d_out))
 
 
-@pytest.mark.parametrize("n,d_in,d_out", [
-    (1, 64, 128), (63, 64, 128), (65, 128, 384), (129, 320, 256),     # 64 x 64 tiles; 1, 2 and 5 k-tiles (5 stages), ragged tokens
-    # 64 x 32, four wavefronts share k: 17 .. 20 k-tiles (pairs in turns of two), one token, ragged tokens, more than one tile
-    (1, 1088, 128), (33, 1152, 384), (95, 1216, 256), (161, 1280, 1152),
-    (2563, 64, 640),                    # 128 x 64
-    (2737, 1024, 1024),                 # 128 x 128
-    (12001, 1024, 384),                 # 128 x 128, the last tiles cut into 128 x 64
-    (4097, 512, 1536),                  # 256 x 128; one token in the last tile
-    (3783, 128, 3840),                  # 256 x 256; as many k-tiles as stages; d_out not a multiple of 256
-    (3600, 128, 4608),                  # 256 x 256, the last tiles cut into 128 x 64
-    (4097, 1024, 4608),                 # ... into 128 x 128, some of them wholly past the last token
-    (3601, 512, 6144),                  # ... into 256 x 128
+@pytest.mark.parametrize("n,d_in,d_out,way", [
+    (1, 64, 128, "64x64"), (63, 64, 128, "64x64"), (65, 128, 384, "64x64"), (129, 320, 256, "64x64"),     # 1, 2 and 5 k-tiles (5 stages), ragged tokens
+    # four wavefronts share k: 17 .. 20 k-tiles (pairs in turns of two), one token, ragged tokens, more than one tile
+    (1, 1088, 128, "64x32"), (33, 1152, 384, "64x32"), (95, 1216, 256, "64x32"), (161, 1280, 1152, "64x32"),
+    (66, 64, 8448, "128x64"), (900, 1088, 1152, "128x64"),
+    (2563, 64, 640, "128x128"), (2737, 1024, 1024, "128x128"),
+    (13211, 128, 384, "128x128+128x64"),
+    (12001, 1024, 384, "256x128"), (4097, 512, 1536, "256x128"),      # the second: one token in the last tile
+    (3783, 128, 3840, "256x256"),                                     # as many k-tiles as stages; d_out not a multiple of 256
+    (3600, 128, 4608, "256x256+128x64"),
+    (4097, 1024, 4608, "256x256+128x128"),                            # some of the small tiles wholly past the last token
+    (3601, 512, 6144, "256x256+256x128"),
 ])
-def test_linear_of_every_tiling_on_sampled_tokens(n, d_in, d_out):
-    """The tilings are chosen from the sizes (named for 256 compute units).  The oracle evaluates both
+def test_linear_of_every_tiling_on_sampled_tokens(n, d_in, d_out, way):
+    """The tilings are chosen from the sizes; the test says which one it is about.  The oracle evaluates both
     sides of every 64-token tile edge among the first and last tiles, and random tokens; all features."""
+    assert str(routes.gemm(n, d_in, d_out)) == way
     x = _bits(1200 + n, (n, d_in))
     w = _bits(1300 + n, (d_out, d_in), scale=d_in ** -0.5)
     b = synth.normal_f32(1400 + n, (d_out,))
@@ -123,18 +125,23 @@ def test_qkv_projection_matches_oracle(heads, hd, grid, offset, split, base, wit
         _close(a, e, "%s heads=%d hd=%d grid=%s" % (name, heads, hd, grid))
 
 
-@pytest.mark.parametrize("heads,hd,grid", [
-    (8, 64, (3, 5, 9)),                  # 64 x 64 tiles: a head per tile row
-    (18, 64, (3, 5, 7)),                 # 64 x 32, wavefronts share k: two of them share a head
-    (20, 64, (1, 3, 11)),                # the same, ragged tokens
-    (8, 128, (3, 5, 9)),                 # 128 x 64: four wavefronts share a head
-    (16, 64, (3, 13, 17)),               # 128 x 128: one head per wavefront
-    (8, 128, (3, 20, 20)),               # 128 x 128: two wavefronts share a head
-    (4, 128, (7, 23, 31)),               # 256 x 128
-    (12, 128, (9, 20, 20)),              # 256 x 256, the last tiles cut
-    (10, 128, (7, 23, 23)),              # 256 x 256 tiles that reach from one section into the next
+@pytest.mark.parametrize("heads,hd,grid,way", [
+    (8, 64, (3, 5, 9), "64x32"), (20, 64, (1, 3, 11), "64x32"),       # wavefronts share k; two of them share a head
+    (18, 64, (3, 5, 7), "64x64"), (2, 64, (3, 11, 11), "64x64"),      # a head per tile row
+    (2, 64, (3, 23, 39), "128x64"),
+    (8, 128, (3, 5, 9), "128x64"), (1, 128, (3, 11, 11), "128x64"),   # four wavefronts share a head
+    (16, 64, (3, 13, 17), "128x128"),                                 # one head per wavefront
+    (8, 128, (3, 20, 20), "128x128"), (1, 128, (4, 26, 29), "128x128"),     # two wavefronts share a head
+    (2, 64, (13, 29, 35), "128x128+128x64"), (1, 128, (13, 29, 35), "128x128+128x64"),
+    (2, 64, (15, 19, 31), "256x128"), (4, 128, (7, 23, 31), "256x128"),
+    (2, 64, (17, 27, 36), "256x256"),
+    (10, 128, (7, 23, 23), "256x256"),                                # tiles that reach from one section into the next
+    (4, 64, (18, 31, 39), "256x256+128x64"), (12, 128, (9, 20, 20), "256x256+128x64"),
+    (4, 64, (18, 35, 37), "256x256+128x128"), (2, 128, (18, 35, 37), "256x256+128x128"),
+    (4, 64, (23, 31, 37), "256x256+256x128"), (2, 128, (23, 31, 37), "256x256+256x128"),
 ])
-def test_qkv_projection_of_every_tiling_on_sampled_tokens(heads, hd, grid):
+def test_qkv_projection_of_every_tiling_on_sampled_tokens(heads, hd, grid, way):
+    assert str(routes.gemm(grid[0] * grid[1] * grid[2], heads * hd, 3 * heads * hd, hd)) == way
     dm, n = heads * hd, grid[0] * grid[1] * grid[2]
     x = _bits(1500 + n, (n, dm))
     w = _bits(1600 + n, (3 * dm, dm), scale=dm ** -0.5)
