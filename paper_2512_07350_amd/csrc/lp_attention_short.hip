@@ -133,8 +133,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
 #pragma unroll
     for (int i = 0; i < T::kLoads; ++i) {
         const int row = i * T::kRowsPerLoad + lane / T::kGran, g = lane % T::kGran;
-        k_voff[i] = uint32_t(row) * tok_bytes + 16 * (g ^ T::swz_k(row));
-        v_voff[i] = uint32_t(row) * tok_bytes + 16 * (g ^ T::swz_v(row));
+        // of fewer than 32 tokens the rows past the last all lie where the first of them does: behind the buffer and,
+        // however far apart tokens are, below 2^31 bytes
+        const uint32_t row_off = uint32_t(min(row, n)) * tok_bytes;
+        k_voff[i] = row_off + 16 * (g ^ T::swz_k(row));
+        v_voff[i] = row_off + 16 * (g ^ T::swz_v(row));
     }
     auto issue_k = [&](int round) {
 #pragma unroll

@@ -509,3 +509,24 @@ def test_long_kernel_scores_that_keep_rising(order, hd, balanced):
     rows = synth.sample_rows(n, 64, seed=hd, tile=256)
     g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "%s scores" % order)
     assert np.all(np.isfinite(got))
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_rows_past_the_end_are_not_read_at_any_stride(hd):
+    """Two tokens 2^27 + 8 elements apart: rows 16 and 17 of a round of 32 keys, which do not exist, lie 2^32 bytes and a
+    little more behind the first, and 32-bit offsets would place them inside the buffer.  It holds NaN there."""
+    import torch
+    from tests import gpu_util as g
+    from paper_2512_07350_amd import binding as lp
+    n, stride = 2, (1 << 27) + 8
+    assert routes.attention(n, 1, hd) == "short"
+    bits = synth.qkv_bf16(5300 + hd, n, 1, hd)
+    bufs = [torch.full((stride + hd,), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+    for buf, b in zip(bufs, bits):
+        for tok in range(n):
+            buf[tok * stride:tok * stride + hd] = g.to_dev_bf16(b[tok, 0])
+    q, k, v, o = bufs
+    lp.lp_attention(q, k, v, o, n, 1, hd, stride, hd, 0.0, None, 0, g.stream())
+    torch.cuda.synchronize()
+    got = np.stack([g.from_dev_bf16(o[tok * stride:tok * stride + hd]) for tok in range(n)])[:, None]
+    g.assert_attention_close(got, orc.attention(*bits), "tokens far apart")
