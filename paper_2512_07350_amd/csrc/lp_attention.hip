@@ -1066,7 +1066,8 @@ int64_t workspace_bytes_for(int cus) { return int64_t(2) * cus * slot_floats<D>(
 // ---- which way a call goes.  Times in us on 256 compute units, fitted to two grids on which every call was
 // timed on every way it can go: 96 .. 13230 tokens x 1 .. 40 heads (311 calls) and 1 .. 5000 tokens x 1 .. 5000
 // heads (1054).  The choice is off the best way by 0.03 % on average and 4 % at worst on the first, by 0.13 % and
-// 11 % on the second (200 tokens x 256 heads of 64: 13.1 us for 11.8).
+// 11 % on the second (200 tokens x 256 heads of 64: 13.1 us for 11.8); by 0.2 % and 8 % over 603 calls whose rows are whole
+// lines between those of other heads, by 0.2 % and 17 % over 880 whose rows are split (2895 x 4 of 128: 42.2 us for 36.0).
 
 // A tile's time while a part `busy` of the compute units works: one workgroup's own pace, slower
 // as the power limit lowers the clock of a full chip.
@@ -1128,13 +1129,20 @@ struct Route {
     Deal deal;
 };
 
-Route pick_route(int head_dim, int64_t n, int all_heads, int cus, bool scratch) {
+Route pick_route(int head_dim, int64_t n, int all_heads, int cus, bool scratch, bool split) {
     const uint32_t units = uint32_t((n + kBM - 1) / kBM) * uint32_t(all_heads), tpu = uint32_t((n + kBN - 1) / kBN);
     Route r;
     r.deal = deal_units(head_dim, units, tpu, uint32_t(cus), lp::attention_bytes_us(n, all_heads, head_dim), scratch);
     r.way = r.deal.sharers != r.deal.shared ? lp::kAttentionCut : lp::kAttentionWhole;
-    if (lp::attention_short_launchable(n, all_heads) && lp::attention_short_us(n, all_heads, head_dim, cus) < r.deal.us) r.way = lp::kAttentionShort;
+    if (lp::attention_short_launchable(n, all_heads) && lp::attention_short_us(n, all_heads, head_dim, cus, split) < r.deal.us) r.way = lp::kAttentionShort;
     return r;
+}
+
+// Whether the rows of a head's K or V are split over 128-byte lines that they do not fill: neither whole lines of
+// their own nor one directly behind the other.
+bool rows_split(uint64_t k, uint64_t v, int64_t stride_tok, int64_t stride_head, int64_t stride_batch, int heads, int batch, int head_dim) {
+    const uint64_t offsets = k | v | uint64_t(stride_tok) * 2 | (heads > 1 ? uint64_t(stride_head) * 2 : 0) | (batch > 1 ? uint64_t(stride_batch) * 2 : 0);
+    return offsets % 128 != 0 && (stride_tok - head_dim) * 2 >= 128;
 }
 
 template <int D>
@@ -1146,7 +1154,9 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     a.tiles_per_unit = (a.n + kBN - 1) / kBN;
     const uint32_t tpu = uint32_t(a.tiles_per_unit);
     const bool scratch = workspace != nullptr && workspace_bytes >= workspace_bytes_for<D>(cus);
-    const Route r = pick_route(D, a.n, heads, cus, scratch);
+    const bool split = rows_split(uint64_t(uintptr_t(a.k)), uint64_t(uintptr_t(a.v)), a.stride_tok, a.stride_head, a.stride_batch, a.heads,
+                                  heads / a.heads, D);
+    const Route r = pick_route(D, a.n, heads, cus, scratch, split);
     const Deal &d = r.deal;
     // short calls go to attention_short_kernel, which needs no scratch memory
     if (r.way == lp::kAttentionShort)
@@ -1181,8 +1191,13 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 }  // namespace
 
-extern "C" int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch) {
-    return pick_route(head_dim, n, all_heads, cus, scratch != 0).way;
+extern "C" int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch, int32_t split) {
+    return pick_route(head_dim, n, all_heads, cus, scratch != 0, split != 0).way;
+}
+
+extern "C" int lp_internal_attention_rows_split(uint64_t k, uint64_t v, int64_t stride_tok, int64_t stride_head, int64_t stride_batch, int32_t heads,
+                                                int32_t batch, int32_t head_dim) {
+    return rows_split(k, v, stride_tok, stride_head, stride_batch, heads, batch, head_dim);
 }
 
 extern "C" int64_t lp_attention_workspace_size(int32_t head_dim) {

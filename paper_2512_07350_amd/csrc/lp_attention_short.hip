@@ -359,13 +359,16 @@ bool attention_short_launchable(int64_t n, int64_t all_heads) { return short_gro
 // A compute unit holds several: two of them take 1.5 times as long as one.  Many heads bring q, k, v and o
 // from and to memory faster than their few tokens need products: part of those transfers comes on top (192
 // tokens x 2000 heads of 128: 176 us, 83 without it).  Off by 7 % (rms) at 1 .. 5000 tokens x 1 .. 5000 heads.
-float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus) {
+// Rows that lie split over one line more than they fill, with other heads' rows in between (padded or side by side at odd
+// offsets), take a round of a full chip a third longer, as every K / V row is fetched once per 32 query rows: 1628 tokens x
+// 25 heads of 64 49.0 us, 30.0 in whole lines; the 256-row tiles lose nothing (30.1 / 29.8).
+float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus, bool split) {
     const int64_t groups = short_groups(n, all_heads), rounds = (n + 127) / 128;
     const int64_t per_cu = (groups + cus - 1) / cus;
     if (per_cu <= 1) return 4.3f + (head_dim == 128 ? 0.8f : 0.55f) * float(rounds);
     const float bytes_us = attention_bytes_us(n, all_heads, head_dim);
-    if (head_dim == 64) return 4.2f + float(per_cu) * (0.27f + 0.33f * float(rounds)) + 0.4f * bytes_us;
-    return 3.7f + float((per_cu + 1) / 2) * (1.0f + 1.15f * float(rounds)) + 0.8f * bytes_us;
+    if (head_dim == 64) return 4.2f + float(per_cu) * (0.27f + (split ? 0.47f : 0.33f) * float(rounds)) + 0.4f * bytes_us;
+    return 3.7f + float((per_cu + 1) / 2) * (1.0f + (split ? 1.35f : 1.15f) * float(rounds)) + 0.8f * bytes_us;
 }
 
 int attention_short(const AttentionCall &c, hipStream_t stream) {

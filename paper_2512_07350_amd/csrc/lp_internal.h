@@ -35,7 +35,10 @@ enum AttentionWay { kAttentionShort, kAttentionWhole, kAttentionCut };
 // Which way a call of these sizes goes on a device of `cus` compute units.  Host arithmetic for the tests (a
 // test of one kernel states that its sizes run that kernel); not part of the library's interface.
 extern "C" {
-int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch);   // an AttentionWay
+int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch, int32_t split);   // an AttentionWay
+// 1 if the rows of K or V lie split over cache lines (`split` above; addresses in bytes, strides in elements)
+int lp_internal_attention_rows_split(uint64_t k, uint64_t v, int64_t stride_tok, int64_t stride_head, int64_t stride_batch, int32_t heads,
+                                     int32_t batch, int32_t head_dim);
 // head_dim 0: lp_linear.  way: features and tokens of a tile, those of the tiles that cut the last round (0: none),
 // the workgroups, and the threads of each.
 int lp_internal_gemm_way(int64_t n, int32_t d_in, int32_t d_out, int32_t head_dim, int32_t cus, int64_t way[6]);
@@ -69,7 +72,7 @@ struct AttentionCall {
 // The kernel for short sequences (lp_attention_short.hip), whether its grid fits a launch, and what it is expected to take.
 int attention_short(const AttentionCall &c, hipStream_t stream);
 bool attention_short_launchable(int64_t n, int64_t all_heads);
-float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus);
+float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus, bool split);
 // us that q, k, v and o take at the rate of a large copy, 4.7 TB/s
 inline float attention_bytes_us(int64_t n, int64_t all_heads, int head_dim) {
     return 8.0f * float(n) * float(all_heads) * float(head_dim) / 4.7e6f;

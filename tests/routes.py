@@ -20,12 +20,19 @@ def _cus(cus):
     return cus
 
 
-def attention(n, all_heads, head_dim, scratch=True, cus=None):
+def attention(n, all_heads, head_dim, scratch=True, cus=None, split=False):
     """"short": the wavefronts of a workgroup share the keys; "whole": 256-row query tiles, each one workgroup's;
-    "cut": those of the last round shared between workgroups and merged."""
+    "cut": those of the last round shared between workgroups and merged.  split: see rows_split."""
     fn = lp._lib().lp_internal_attention_way
-    fn.argtypes, fn.restype = [C.c_int64] + [C.c_int32] * 4, C.c_int
-    return WAYS[fn(n, all_heads, head_dim, _cus(cus), int(scratch))]
+    fn.argtypes, fn.restype = [C.c_int64] + [C.c_int32] * 5, C.c_int
+    return WAYS[fn(n, all_heads, head_dim, _cus(cus), int(scratch), int(split))]
+
+
+def rows_split(k, v, stride_tok, stride_head, stride_batch, heads, batch, head_dim):
+    """Whether the rows of K or V (byte addresses k, v) lie split over cache lines, with other rows in between."""
+    fn = lp._lib().lp_internal_attention_rows_split
+    fn.argtypes, fn.restype = [C.c_uint64] * 2 + [C.c_int64] * 3 + [C.c_int32] * 3, C.c_int
+    return bool(fn(k, v, stride_tok, stride_head, stride_batch, heads, batch, head_dim))
 
 
 def gemm(n, d_in, d_out, head_dim=0, cus=None):

@@ -428,7 +428,8 @@ def test_long_kernel_layouts(layout, hd, balanced):
     n = 2999
     batch = 2 if layout.startswith("items") else 1
     heads = 12 // batch
-    assert routes.attention(n, 12, hd, balanced) == ("cut" if balanced else "whole")
+    for split in (False, True):
+        assert routes.attention(n, 12, hd, balanced, split=split) == ("cut" if balanced else "whole")
     if layout == "token-padded":
         stride_head, stride_batch = hd + 8, 0
         stride_tok = heads * stride_head + 24

@@ -50,6 +50,39 @@ def test_attention_takes_the_faster_way(n, heads, hd, way):
     assert (routes.attention(n, heads, hd, True, CUS) == "short") == (way == "short")
 
 
+# us, short kernel / 256-row query tiles, of calls whose rows are split over cache lines (short kernel with whole lines)
+@pytest.mark.parametrize("n,heads,hd,whole_lines", [
+    (1628, 25, 64, "short"),     # 49.0 / 30.1 (30.0)
+    (1542, 22, 64, "short"),     # 36.5 / 28.2 (28.5)
+    (861, 201, 64, "short"),     # 94.0 / 73.1
+    (1063, 73, 64, "short"),     # 51.7 / 43.8
+    (1625, 38, 128, "short"),    # 97.9 / 76.0 (87.9)
+    (1777, 17, 128, "short"),    # 54.3 / 46.5 (49.3)
+    (3427, 21, 64, "cut"), (2963, 11, 128, "cut"),
+])
+def test_split_rows_keep_a_call_from_the_short_kernel(n, heads, hd, whole_lines):
+    assert routes.attention(n, heads, hd, True, CUS) == whole_lines
+    assert routes.attention(n, heads, hd, True, CUS, split=True) in ("whole", "cut")
+
+
+def test_split_rows_leave_small_calls_with_the_short_kernel():
+    for n, heads, hd in ((200, 4, 64), (600, 24, 64), (1000, 12, 128)):      # 10.0 / 16.7 and 17.8 / 27.8 us for the latter two
+        assert routes.attention(n, heads, hd, True, CUS, split=True) == "short"
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_which_rows_are_split(hd):
+    base = 1 << 20
+    one = lambda k=base, v=base, tok=3 * hd, head=hd, batch=0, heads=3, items=1: routes.rows_split(k, v, tok, head, batch, heads, items, hd)
+    assert not one()
+    assert one(k=base + 16) and one(v=base + 64) and not one(k=base + 128)
+    assert one(tok=3 * hd + 8) and one(tok=3 * (hd + 8), head=hd + 8)
+    assert not one(head=hd + 8, heads=1, tok=4 * hd)                         # no second head, no second item
+    assert not one(batch=9 * hd + 8) and one(batch=9 * hd + 8, items=2)
+    assert not one(k=base + 16, tok=hd, head=100 * hd)                       # head-major: one row directly behind the other
+    assert not one(tok=hd + 8, head=100 * (hd + 8)) and one(tok=hd + 72, head=100 * (hd + 72))
+
+
 # us on 256 compute units of the tiles taken / of 128 x 64 tiles: products of a short k, where a tile is little more than
 # its first loads and its stores
 @pytest.mark.parametrize("n,d_in,d_out,tiles", [
