@@ -183,7 +183,7 @@ __device__ __forceinline__ void blend_term(const typename VecT<VEC>::type p, int
 // Eq. 13-17.  X_PER_ELEM: the partition dim is the vectorised (fastest) one, so
 // each element of a vector has its own coordinate x and its own weight.
 // LANE_K: the lanes of a wave sit at many different x (short inner runs), so a
-// wave as a whole touches every partition.  Each lane then walks only the k
+// wave as a whole touches every partition, or there are many partitions.  Each lane then walks only the k
 // range that can cover its x -- from s_k >= k L p - O p and e_k <= (k+1) L p + O p,
 // floor((x - O p) / (L p)) <= k <= floor((x + O p) / (L p)) -- with the plan
 // held in LDS; the test against s_k and e_k still decides.  Otherwise a wave
@@ -421,8 +421,10 @@ int launch_reconstruct(const lp_plan *pl, const float *preds, float *out, const 
     const int32_t p = pl->dim == 0 ? pl->cfg.pT : pl->dim == 1 ? pl->cfg.pH : pl->cfg.pW;
     a.core_div = make_fastdiv(uint32_t(pl->L) * uint32_t(p));
     a.ovl = pl->O * p;
-    // a wave of 64 vectors sits on at least 64 / inner_vec different x
-    const bool lane_k = x_per_elem || a.inner_vec < 16;
+    // a wave of 64 vectors sits on at least 64 / inner_vec different x.  The loop over all k has a part's scalars to fetch in
+    // every turn, a lane's own range has the plan to stage first: 8 parts of the 19.4 MB latent (along H) 9.8 / 10.0 us,
+    // as a guided step 15.6 / 15.9; 12 parts of 13.2 MB (along T) 8.0 / 6.5, 32 of 22.6 MB 17.0 / 8.8.
+    const bool lane_k = x_per_elem || a.inner_vec < 16 || pl->K > 8;
     dim3 grid((a.n_vec + kThreads - 1) / kThreads);
     ScatterArgs sc{};
     if (SCATTER) {

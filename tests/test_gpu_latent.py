@@ -26,6 +26,12 @@ CASES = [
     ((3, 5, 7, 40), (1, 1, 4), 4, 1, (2,)),              # split along W by rows through LDS: 105 rows, the last workgroup takes 9
     ((2, 2, 3, 8208), (1, 1, 4), 3, 2, (2,)),            # a row of 32832 bytes: too long for the row kernel's LDS share
     ((1, 1, 70, 24), (1, 1, 4), 2, 1, (2,)),             # rows of 24 floats, sub-latent rows of 16
+    ((3, 24, 48, 80), P122, 8, 1, (0, 1)),               # long inner runs: the most parts that every lane loops over, ...
+    ((3, 24, 48, 80), P122, 9, 1, (0, 1)),               # ... one more, where each lane has its own range of them
+    ((3, 24, 48, 80), P122, 12, 5, (0, 1)),              # up to seven partitions meet, the last cores empty or past the end
+    ((2, 40, 36, 80), P122, 18, 0, (0, 1)),              # no overlap; empty partitions along T
+    ((1, 130, 4, 80), P122, 64, 2, (0,)),                # as many as a plan holds
+    ((2, 20, 10, 31), (1, 1, 1), 10, 2, (0, 1)),         # scalar path
 ]
 
 
