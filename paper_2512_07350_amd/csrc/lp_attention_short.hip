@@ -105,7 +105,9 @@ __device__ __forceinline__ void wait_loads() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PENDING) : "memory");
 }
 
-template <int D>
+// FAR: tokens so far apart that the 32 rows of a round reach past 2^32 bytes, so that a 32-bit offset would place some of the
+// rows past the last inside the buffer (which has less than 2^31 bytes).  They all go where the first of them lies, behind it.  A kernel of its own: the clamp in every call cost one of 1248 tokens x 4 heads of 128 4 %.
+template <int D, bool FAR>
 __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const ShortParams a) {
     using T = Round<D>;
     constexpr int KS = D / 32, MB = D / 16;
@@ -133,9 +135,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
 #pragma unroll
     for (int i = 0; i < T::kLoads; ++i) {
         const int row = i * T::kRowsPerLoad + lane / T::kGran, g = lane % T::kGran;
-        // of fewer than 32 tokens the rows past the last all lie where the first of them does: behind the buffer and,
-        // however far apart tokens are, below 2^31 bytes
-        const uint32_t row_off = uint32_t(min(row, n)) * tok_bytes;
+        const uint32_t row_off = uint32_t(FAR ? min(row, n) : row) * tok_bytes;
         k_voff[i] = row_off + 16 * (g ^ T::swz_k(row));
         v_voff[i] = row_off + 16 * (g ^ T::swz_v(row));
     }
@@ -328,11 +328,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
     }
 }
 
-template <int D>
+template <int D, bool FAR>
 int launch_short(ShortParams a, int64_t groups, hipStream_t stream) {
     // the dynamic-LDS limit is an attribute of the function on a device: set once per device
     static std::atomic<uint64_t> attr_set{0};
-    const void *kern = reinterpret_cast<const void *>(&attention_short_kernel<D>);
+    const void *kern = reinterpret_cast<const void *>(&attention_short_kernel<D, FAR>);
     int dev = 0;
     lp::device_compute_units(&dev);
     const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
@@ -385,7 +385,9 @@ int attention_short(const AttentionCall &c, hipStream_t stream) {
     a.n_blocks = (c.n + kRows - 1) / kRows;
     a.scale_log2e = c.scale_log2e;
     const int64_t groups = short_groups(c.n, c.all_heads);
-    return c.head_dim == 128 ? launch_short<128>(a, groups, stream) : launch_short<64>(a, groups, stream);
+    const bool far = c.stride_tok * 2 * 32 >= int64_t(1) << 32;
+    if (c.head_dim == 128) return far ? launch_short<128, true>(a, groups, stream) : launch_short<128, false>(a, groups, stream);
+    return far ? launch_short<64, true>(a, groups, stream) : launch_short<64, false>(a, groups, stream);
 }
 
 }  // namespace lp
