@@ -57,29 +57,11 @@
 #include <atomic>
 #include <type_traits>
 
-#include "lp_internal.h"
+#include "lp_device.h"
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-
-#define LP_LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
-
-// f(integral_constant<int, I>) for I = FROM .. TO-1: a loop whose index is a constant
-// expression inside the body.
-template <int FROM, int TO, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (FROM < TO) {
-        f(std::integral_constant<int, FROM>{});
-        static_for<FROM + 1, TO>(f);
-    }
-}
+using namespace lp;
 
 constexpr int kBM = 256;                      // query rows per workgroup
 constexpr int kWaves = 4;                     // wavefronts per workgroup, one per SIMD
@@ -93,7 +75,7 @@ constexpr float kRescaleThreshold = 8.0f;     // log2 units the running max may 
 constexpr uint32_t kBoundaryTiles = 4;        // what changing units costs a workgroup, in tile times
 
 template <int D>
-struct Tile {
+struct Tile : TileSwizzle<D> {
     static constexpr int kRowBytes = D * 2;
     static constexpr int kGran = kRowBytes / 16;            // 16-byte granules per row
     static constexpr int kTileBytes = kBN * kRowBytes;      // one K or one V tile
@@ -105,28 +87,7 @@ struct Tile {
     static constexpr int kReach = kStages * kStageBytes <= 65536 ? kStages : 2;
     static constexpr int kRowsPerInstr = 1024 / kRowBytes;  // rows one wave-wide 16-byte load covers
     static constexpr int kInstrPerTile = kBN / kRowsPerInstr;
-    // Granule XOR masks; reader and writer use the same functions.  A K read takes, per 16 lanes, one
-    // granule of the rows 8 (r / 4) + r % 4 (+ 4): their 16 places must differ modulo the 256 bytes of
-    // the banks.  A V read takes, per 32 lanes, two granules of the rows 0-3 and 8-11 (+ 4, + 16).
-    __device__ static int swz_k(int row) { return D == 128 ? (row & 3) | ((row >> 1) & 12) : ((row >> 1) & 1) | ((row >> 2) & 6); }
-    __device__ static int swz_v(int row) { return D == 128 ? 2 * ((row & 3) | ((row >> 1) & 4)) : (row & 2) | ((row >> 1) & 4); }
 };
-
-union Pack16 {
-    uint4 u;
-    bf16x8 v;
-    bf16x4 h[2];
-    bf16x2 p[4];
-};
-
-// A query's scores lie with the four lanes of equal lane % 16.
-__device__ __forceinline__ float quad_max(float x) { return lp::over_quads(x, [](float a, float b) { return fmaxf(a, b); }); }
-__device__ __forceinline__ float quad_sum(float x) { return lp::over_quads(x, [](float a, float b) { return a + b; }); }
-
-__device__ __forceinline__ bf16x2 to_bf16x2(float lo, float hi) {
-    f32x2 f = {lo, hi};
-    return __builtin_convertvector(f, bf16x2);
-}
 
 // Wait until at most `pending` of this wave's global->LDS loads are still in flight.
 template <int PENDING>
@@ -143,7 +104,6 @@ __device__ __forceinline__ void lds_wait() {
     __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
 }
 
-// LDS accesses below use 32-bit LDS byte addresses held in registers.
 // The same value, but not a loop invariant as far as the compiler can tell.
 __device__ __forceinline__ int opaque(int x) {
     asm volatile("" : "+v"(x));
@@ -155,11 +115,6 @@ __device__ __forceinline__ int opaque(int x) {
 __device__ __forceinline__ void move_address(uint32_t &addr, uint32_t delta) {
     addr += delta;
     asm volatile("" : "+v"(addr));
-}
-
-template <typename V>
-__device__ __forceinline__ V lds_load(uint32_t addr) {
-    return *LP_LDS_PTR(const V, uintptr_t(addr));
 }
 
 // What a lane needs to know to move tiles from global memory into LDS.
@@ -178,14 +133,8 @@ struct Lane {
     int t_end;                               // one past the segment's last tile
 };
 
-// One wave-wide global -> LDS load: lane L fetches the 16 bytes at byte offset voff + soff of
-// the buffer and they land at LDS address lds_addr + 16 L (lds_addr is wave-uniform and goes
-// through M0; bytes outside the buffer arrive as zeros).  Written as an assembly statement so
-// that the compiler keeps no record of it: told about such a load, it waits for ALL of them
-// (vmcnt(0)) before the next LDS read of any address, which would put the whole memory latency
-// of the tile just sent for in front of the operand reads of the tiles in use.  The waits that
-// order these loads against the reads of their own stage are wait_tile_loads + barrier.
-// Nothing else in this file uses M0.
+// The global -> LDS loads of a K and a V block (see load_to_lds_16): the waits that order them against the reads of their own
+// stage are wait_tile_loads + barrier.  Nothing else in this file uses M0.
 template <int V_LDS_OFFSET>
 __device__ __forceinline__ void load_kv_to_lds_16(__amdgpu_buffer_rsrc_t k_rsrc, __amdgpu_buffer_rsrc_t v_rsrc, uint32_t k_lds,
                                                   uint32_t k_voff, uint32_t v_voff, uint32_t soff) {
@@ -643,14 +592,6 @@ __device__ __forceinline__ uint32_t range_start(uint32_t p, uint32_t W, uint32_t
 __device__ __forceinline__ uint32_t real_tile(uint32_t x, uint32_t unit_cost, uint32_t tpu) {
     const uint32_t unit = x / unit_cost, r = x - unit * unit_cost, imaginary = unit_cost - tpu;
     return unit * tpu + (r > imaginary ? r - imaginary : 0u);
-}
-
-// Workgroup ids are dealt round robin to the 8 XCDs; remap so that each XCD owns a
-// contiguous stretch of the iteration space and the K/V of a head stay in one XCD's L2.
-__device__ __forceinline__ uint32_t logical_workgroup(uint32_t b, uint32_t n_wg) {
-    const uint32_t xcd = b % 8, slot = b / 8;
-    const uint32_t base = n_wg / 8, rem = n_wg % 8;
-    return xcd * base + (xcd < rem ? xcd : rem) + slot;
 }
 
 // A segment: the tiles [t_begin, t_stop) of one unit.
@@ -1168,26 +1109,15 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     a.unit_cost = tpu + (cut ? kBoundaryTiles : 0);
     a.shared_work = d.shared * a.unit_cost;
     a.shared_wgs = d.sharers;
-    // The dynamic-LDS limit is an attribute of the function on a device: set once per device
-    // (a repeated set by a racing host thread is harmless).
     static std::atomic<uint64_t> attr_set{0};
     const void *kern = reinterpret_cast<const void *>(&attention_kernel<D>);
-    const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
-    if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Tile<D>::kBytes);
-        if (e != hipSuccess) {
-            lp::set_last_hip_error(int(e));
-            return LP_ERR_HIP;
-        }
-        attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
-    }
-    int rc = lp::launch_kernel(kern, dim3(d.wgs), dim3(kWaves * 64), Tile<D>::kBytes, stream, a);
+    int rc = allow_lds(kern, Tile<D>::kBytes, dev, attr_set);
+    if (rc != LP_OK) return rc;
+    rc = lp::launch_kernel(kern, dim3(d.wgs), dim3(kWaves * 64), Tile<D>::kBytes, stream, a);
     if (rc != LP_OK || a.ws == nullptr) return rc;
     return lp::launch_kernel(reinterpret_cast<const void *>(&combine_kernel<D>), dim3(uint32_t(a.shared_units) * (kBM / 32)),
                              dim3(32 * (D / 16)), 0, stream, a, a.shared_wgs);
 }
-
-bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
 

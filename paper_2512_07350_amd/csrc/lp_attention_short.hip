@@ -26,17 +26,11 @@
 
 #include <atomic>
 
-#include "lp_internal.h"
+#include "lp_device.h"
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-
-#define LP_LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
+using namespace lp;
 
 constexpr int kWaves = 4;                     // wavefronts of a workgroup; they share the keys
 constexpr int kQB = 2;                        // 16-row query blocks of a workgroup
@@ -53,7 +47,7 @@ struct ShortParams {
 };
 
 template <int D>
-struct Round {
+struct Round : TileSwizzle<D> {
     static constexpr int kRowBytes = D * 2, kGran = kRowBytes / 16;    // a K or V row and its 16-byte granules
     static constexpr int kTileBytes = 32 * kRowBytes;                  // K or V of a round
     static constexpr int kRingBytes = kWaves * 2 * kTileBytes;         // K then V, for every wavefront
@@ -61,43 +55,7 @@ struct Round {
     static constexpr int kMergeBytes = kWaves * (kPartBytes + kRows * 8);
     static constexpr int kLds = kRingBytes > kMergeBytes ? kRingBytes : kMergeBytes;
     static constexpr int kRowsPerLoad = 1024 / kRowBytes, kLoads = 32 / kRowsPerLoad;   // wave-wide loads of a tile
-    // granule XOR masks as in attention_kernel: the rows that one LDS access touches lie in different banks
-    __device__ static int swz_k(int row) { return D == 128 ? (row & 3) | ((row >> 1) & 12) : ((row >> 1) & 1) | ((row >> 2) & 6); }
-    __device__ static int swz_v(int row) { return D == 128 ? 2 * ((row & 3) | ((row >> 1) & 4)) : (row & 2) | ((row >> 1) & 4); }
 };
-
-union Pack16 {
-    uint4 u;
-    bf16x8 v;
-    bf16x4 h[2];
-    bf16x2 p[4];
-};
-
-template <typename V>
-__device__ __forceinline__ V lds_load(uint32_t addr) {
-    return *LP_LDS_PTR(const V, uintptr_t(addr));
-}
-template <typename V>
-__device__ __forceinline__ void lds_store(uint32_t addr, const V &x) {
-    *LP_LDS_PTR(V, uintptr_t(addr)) = x;
-}
-
-__device__ __forceinline__ bf16x2 to_bf16x2(float lo, float hi) {
-    f32x2 f = {lo, hi};
-    return __builtin_convertvector(f, bf16x2);
-}
-
-__device__ __forceinline__ float quad_max(float x) { return lp::over_quads(x, [](float a, float b) { return fmaxf(a, b); }); }
-__device__ __forceinline__ float quad_sum(float x) { return lp::over_quads(x, [](float a, float b) { return a + b; }); }
-
-// One wave-wide global -> LDS load of 1024 bytes (an assembly statement for the reason given in
-// lp_attention.hip); bytes outside the buffer arrive as zeros.
-__device__ __forceinline__ void load_to_lds_16(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory", "m0");
-}
 
 // At most PENDING of this wavefront's loads are still in flight.
 template <int PENDING>
@@ -118,9 +76,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
     const int lane = tid % 64, col = lane % 16, quad = lane / 16;
     const int n = a.n;
 
-    // workgroup ids are dealt round robin to the 8 XCDs: the blocks of a head go to one of them
-    const uint32_t xcd = blockIdx.x % 8, slot = blockIdx.x / 8, base = gridDim.x / 8, rem = gridDim.x % 8;
-    const uint32_t unit = xcd * base + (xcd < rem ? xcd : rem) + slot;
+    const uint32_t unit = logical_workgroup(blockIdx.x, gridDim.x);        // the blocks of a head go to one XCD
     const int bh = int(unit) / a.n_blocks, q0 = (int(unit) - bh * a.n_blocks) * kRows;
     const int item = bh / a.heads;
     const int64_t head_off = int64_t(item) * a.stride_batch + int64_t(bh - item * a.heads) * a.stride_head;
@@ -330,20 +286,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
 
 template <int D, bool FAR>
 int launch_short(ShortParams a, int64_t groups, hipStream_t stream) {
-    // the dynamic-LDS limit is an attribute of the function on a device: set once per device
     static std::atomic<uint64_t> attr_set{0};
     const void *kern = reinterpret_cast<const void *>(&attention_short_kernel<D, FAR>);
     int dev = 0;
-    lp::device_compute_units(&dev);
-    const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
-    if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
-        const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, Round<D>::kLds);
-        if (e != hipSuccess) {
-            lp::set_last_hip_error(int(e));
-            return LP_ERR_HIP;
-        }
-        attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
-    }
+    device_compute_units(&dev);
+    const int rc = allow_lds(kern, Round<D>::kLds, dev, attr_set);
+    if (rc != LP_OK) return rc;
     return lp::launch_kernel(kern, dim3(uint32_t(groups)), dim3(kWaves * 64), Round<D>::kLds, stream, a);
 }
 

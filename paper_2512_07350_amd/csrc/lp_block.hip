@@ -28,42 +28,16 @@
 #include <cmath>
 #include <type_traits>
 
-#include "lp_internal.h"
+#include "lp_device.h"
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-
-#define LP_LDS_PTR(T, p) ((__attribute__((address_space(3))) T *)(p))
+using namespace lp;
 
 constexpr int kBK = 64;                  // k per LDS stage
 constexpr int kRowBytes = kBK * 2;       // one tile row: 64 bf16
 constexpr int kPanel = 8;                // token tiles per panel of the tile order
 constexpr int kMaxPairs = 64;            // rotary pairs per head (head_dim <= 128)
-
-// floor(n / d) for 0 <= n < 2^31 as (n * magic) >> shift (64-bit product); see make_fastdiv.
-struct FastDiv {
-    uint32_t magic, shift, d;
-};
-
-FastDiv make_fastdiv(uint32_t d) {
-    FastDiv f;
-    f.d = d;
-    uint32_t l = 0;
-    while ((uint64_t(1) << l) < d) ++l;
-    f.shift = 31 + l;
-    f.magic = uint32_t(((unsigned __int128)1 << f.shift) / d + 1);
-    return f;
-}
-
-__device__ __forceinline__ uint32_t fastdiv(uint32_t n, const FastDiv &f) {
-    return uint32_t((uint64_t(n) * f.magic) >> f.shift);
-}
 
 // What the normalisation + rotation needs besides the data.
 struct RopeArgs {
@@ -86,39 +60,10 @@ struct GemmArgs {
     RopeArgs rope;
 };
 
-__device__ __forceinline__ bf16x2 to_bf16x2(float lo, float hi) {
-    f32x2 f = {lo, hi};
-    return __builtin_convertvector(f, bf16x2);
-}
-
-template <typename V>
-__device__ __forceinline__ V lds_load(uint32_t addr) {
-    return *LP_LDS_PTR(const V, uintptr_t(addr));
-}
-
 // granule XOR mask of a tile row (reader and writer use the same function): with 128-byte rows
 // the 16-byte granule g of row r lives at position g ^ swz(r), which makes the ds_read_b128 of
 // 16 rows x 4 granules free of bank conflicts (SQ_LDS_BANK_CONFLICT: 1.6 % of the LDS cycles)
 __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
-
-// One wave-wide global -> LDS load of 1024 bytes (see lp_attention.hip for why this is an
-// assembly statement): lane L's 16 bytes at byte offset voff + soff of the buffer land at
-// lds_addr + 16 L; bytes outside the buffer arrive as zeros.
-__device__ __forceinline__ void load_to_lds_16(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds_addr, uint32_t voff, uint32_t soff) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
-                 : "memory", "m0");
-}
-
-// Workgroup ids are dealt round robin to the 8 XCDs; remap so that each XCD owns a contiguous
-// stretch of the tile order (see the panels in gemm_kernel) and what neighbouring tiles share
-// stays in one XCD's L2.
-__device__ __forceinline__ uint32_t logical_workgroup(uint32_t b, uint32_t n_wg) {
-    const uint32_t xcd = b % 8, slot = b / 8;
-    const uint32_t base = n_wg / 8, rem = n_wg % 8;
-    return xcd * base + (xcd < rem ? xcd : rem) + slot;
-}
 
 // One matrix instruction, acc += a . b, as an assembly statement: such statements keep their
 // program order, and the LDS reads written between them stay between them.  The compiler does
@@ -134,15 +79,6 @@ template <int PENDING>
 __device__ __forceinline__ void stage_barrier() {
     static_assert(PENDING >= 0 && PENDING < 64, "vmcnt range");
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(PENDING) : "memory");
-}
-
-// f(integral_constant<int, I>) for I = FROM .. TO-1
-template <int FROM, int TO, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (FROM < TO) {
-        f(std::integral_constant<int, FROM>{});
-        static_for<FROM + 1, TO>(f);
-    }
 }
 
 // The tile of one workgroup: WF x WT wavefronts, each with FB x TB blocks of 16 features x 16
@@ -662,8 +598,6 @@ __global__ __launch_bounds__(256) void norm_rope_kernel(__bf16 *x, const float *
     if (live) *reinterpret_cast<uint4 *>(p) = out.u;
 }
 
-bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
 // Fills the device-side rotary description; LP_OK or the error.
 int make_rope_args(const lp_rope *rope, int64_t n, int32_t head_dim, float eps, RopeArgs *out) {
     if (rope == nullptr) return LP_ERR_INVALID_ARG;
@@ -775,24 +709,16 @@ Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
 template <bool QKV, int HD, typename P, typename R>
 int launch_tiles(GemmArgs a, int64_t whole, hipStream_t stream) {
     constexpr int kLds = P::kLds > R::kLds ? P::kLds : R::kLds;
-    // the dynamic-LDS limit is an attribute of the function on a device: set once per device
     static std::atomic<uint64_t> attr_set{0};
     const void *kern = reinterpret_cast<const void *>(&gemm_kernel<QKV, HD, P, R>);
     int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    const hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) {
         lp::set_last_hip_error(int(e));
         return LP_ERR_HIP;
     }
-    const uint64_t dev_bit = dev < 64 ? (uint64_t(1) << dev) : 0;
-    if ((attr_set.load(std::memory_order_relaxed) & dev_bit) == 0) {
-        e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-        if (e != hipSuccess) {
-            lp::set_last_hip_error(int(e));
-            return LP_ERR_HIP;
-        }
-        attr_set.fetch_or(dev_bit, std::memory_order_relaxed);
-    }
+    const int rc = allow_lds(kern, kLds, dev, attr_set);
+    if (rc != LP_OK) return rc;
     a.n_ftiles = (a.d_out + P::kF - 1) / P::kF;
     a.n_ttiles = (a.n + P::kT - 1) / P::kT;
     const int64_t tiles = int64_t(a.n_ftiles) * a.n_ttiles;

@@ -99,16 +99,5 @@ inline int device_compute_units(int *device = nullptr) {
     if (device != nullptr) *device = dev;
     return cached_cus;
 }
-
-// op over the four lanes of equal lane % 16 (the four quads of a matrix instruction's column), in every
-// one of them.  The swaps exchange rows of 16 (32) lanes between two copies of x, after which one copy
-// holds the first and the other the second of each pair of rows.
-template <typename Op>
-__device__ __forceinline__ float over_quads(float x, Op &&op) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    x = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
 }  // namespace lp
 #endif

@@ -13,34 +13,13 @@
 // element has exactly one writer.
 #include <hip/hip_runtime.h>
 
-#include "lp_internal.h"
+#include "lp_device.h"
 
 namespace {
 
+using namespace lp;
+
 constexpr int kThreads = 256;
-
-// floor(n / d) for 0 <= n < 2^31 as (n * magic) >> shift with a 64-bit product.
-// With l = ceil(log2 d), magic = floor(2^(31+l) / d) + 1 < 2^32 and shift = 31 + l,
-// magic*d = 2^shift + e with 0 < e <= 2^l, so the error term n*e/(d*2^shift) < 1/d.
-struct FastDiv {
-    uint32_t magic;
-    uint32_t shift;
-    uint32_t d;
-};
-
-FastDiv make_fastdiv(uint32_t d) {
-    FastDiv f;
-    f.d = d;
-    uint32_t l = 0;
-    while ((uint64_t(1) << l) < d) ++l;
-    f.shift = 31 + l;
-    f.magic = uint32_t(((unsigned __int128)1 << f.shift) / d + 1);
-    return f;
-}
-
-__device__ __forceinline__ uint32_t fastdiv(uint32_t n, const FastDiv &f) {
-    return uint32_t((uint64_t(n) * f.magic) >> f.shift);
-}
 
 template <int VEC>
 struct VecT;
