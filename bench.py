@@ -299,9 +299,9 @@ class Run:
         achieved = att_flops / (att_ms * 1e-3) / 1e12
         res = {
             "value": att_flops / wall / 1e12, "ms_per_step": wall * 1e3 / steps, "spinup_steps": spin_steps,
-            "roofline": {"kernel": "attention_kernel<%d,%d>, timed per lp_attention call (the interval also holds the "
+            "roofline": {"kernel": "attention_kernel<%d>, timed per lp_attention call (the interval also holds the "
                                    "combine_kernel<%d> that merges shared query tiles, when there is one, and the launch gap)"
-                                   % (w.head_dim, attention_rows_per_wave() // 32, w.head_dim),
+                                   % (w.head_dim, w.head_dim),
                          "bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                          "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
                          "launches": att_launches, "avg_launch_ms": round(att_ms / max(att_launches, 1), 5),
@@ -339,13 +339,6 @@ def rate(nbytes, ms, steps):
         return None
     gbps = nbytes / (ms * 1e-3) / 1e9
     return {"GBps": round(gbps, 1), "avg_us": round(ms * 1e3 / steps, 2), "frac": round(gbps / PEAK_HBM_GBPS, 4)}
-
-
-def attention_rows_per_wave():
-    """Query rows one wavefront of attention_kernel owns (read from the kernel source, for the label only)."""
-    import re
-    m = re.search(r"constexpr int blocks_per_wave\([^)]*\) \{ return (\d+); \}", open(ATTENTION_SOURCE).read())
-    return 32 * int(m.group(1)) if m else 32
 
 
 def traffic_record(path, workload, guided):

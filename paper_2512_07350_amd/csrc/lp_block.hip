@@ -262,14 +262,14 @@ __device__ __forceinline__ void product(uint32_t lds0, const GemmArgs &a, int f0
 
 // The same for calls of few tiles and a long k: the four waves of a workgroup share k.
 //
-// What bounds it.  In every small tiling a compute unit takes in 82 to 90 GB/s through the global -> LDS path
-// (64 x 64: 16 KB and 0.2 us a k-tile, whether 2 or 100 workgroups run, the data in L2 or not), so with
-// compute units to spare a smaller tile is the faster one.  A 64 x 32 tile has too few products per k-tile to
-// keep four waves that share its rows apart from LDS and the barrier (0.19 us with two such waves); here a wave takes
-// all of the tile's rows for one k-step of 32 out of a pair of k-tiles, every byte is read from LDS once,
-// and the four partial tiles are added up through LDS at the end: 0.12 us a k-tile.  A wave holds the
-// operands of two pairs: behind the one barrier of a pair it fetches those of the next pair and sends for the pair
-// S / 2 later, under the products of this one.  520 x 5120 -> 640: 17.3 to 13.7 us; 100 x 3072 -> 3072: 12.0 to 9.9.
+// What bounds it: what a compute unit takes in through the global -> LDS path, per k-tile of d_in 5120 to 10240.  In 64 x 32
+// tiles of 12 KB 132 GB/s with 2 to 32 workgroups, 74 to 93 with 80 to 256 of them (0.093 and 0.13 to 0.17 us); in 64 x 64 and
+// 128 x 64 tiles 72 to 74 with 160 to 256.  So with compute units to spare the tile with fewer bytes is the faster one.
+// A 64 x 32 tile has too few products per k-tile to keep four waves that share its rows apart from LDS and the barrier
+// (0.19 us with two such waves); here a wave takes all of the tile's rows for one k-step of 32 out of a pair of k-tiles, every
+// byte is read from LDS once, and the four partial tiles are added up through LDS at the end.  A wave holds the operands of
+// two pairs: behind the one barrier of a pair it fetches those of the next pair and sends for the pair S / 2 later, under
+// the products of this one.  520 x 5120 -> 640: 17.3 to 13.7 us; 100 x 3072 -> 3072: 12.0 to 9.9.
 // A 64 x 64 tile gains nothing from it (17.4), and operands fetched straight into registers are slower (30).
 //
 // Leaves the wave's own FB x TB blocks in acc, like product().
@@ -406,7 +406,7 @@ __device__ __forceinline__ void norm_rope(f32x4 (&acc)[C::FB][C::TB], F &&sum_sq
 
 // Writes a wave's results, rounded to bf16, to dst + token * row_stride + feature: 16 tokens at
 // a time pass through the wave's own LDS (16-byte granules XORed with the row) and leave as
-// whole 128-byte lines.
+// rows of FB * 32 bytes: two whole lines, one, or (the tilings of 64 and fewer tokens) half of one.
 template <typename C>
 __device__ __forceinline__ void store_tile(uint32_t out_lds, const f32x4 (&acc)[C::FB][C::TB], __bf16 *dst, int64_t row_stride,
                                            int tokens_valid, int lane) {
@@ -759,7 +759,7 @@ int launch_gemm(GemmArgs a, hipStream_t stream) {
 // shape limits of the product: k in whole tiles, 32-bit byte offsets inside a tile's rows
 int check_gemm_shape(int64_t n, int32_t d_in, int32_t d_out) {
     if (n < 0 || d_in < 1 || d_out < 1) return LP_ERR_INVALID_ARG;
-    if (d_in % kBK != 0 || d_out % 128 != 0) return LP_ERR_UNSUPPORTED;   // whole k tiles; a wave stores 128 features per token
+    if (d_in % kBK != 0 || d_out % 128 != 0) return LP_ERR_UNSUPPORTED;   // whole k-tiles; whole wave tiles of features (32, 64 or 128)
     if (int64_t(256) * d_in * 2 >= (int64_t(1) << 31) || n >= (int64_t(1) << 31)) return LP_ERR_UNSUPPORTED;
     return LP_OK;
 }
@@ -805,7 +805,7 @@ extern "C" int lp_qkv_projection(const void *x, const void *w_qkv, const float *
     const int64_t dm64 = int64_t(heads) * head_dim;
     if (3 * dm64 >= (int64_t(1) << 31)) return LP_ERR_UNSUPPORTED;
     const int32_t dm = int32_t(dm64);
-    if (dm % 128 != 0) return LP_ERR_UNSUPPORTED;          // a wave's 128 features must not straddle q | k | v
+    if (dm % 128 != 0) return LP_ERR_UNSUPPORTED;          // a wave's features (up to 128) must not straddle q | k | v
     const int chk = check_gemm_shape(n_tokens, dm, 3 * dm);
     if (chk != LP_OK) return chk;
     if (n_tokens == 0) return LP_OK;
