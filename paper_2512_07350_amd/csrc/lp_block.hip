@@ -117,8 +117,9 @@ struct Tiling {
 // Each half of a stage is refilled as soon as the barrier after its read has passed, so a load has one
 // and a half tiles' products to arrive in and no wait ever drains the queue.  A barrier stands
 // PRE products into its phase: the waves meet with products still in the pipeline.
-// 1131 -> 1380 TFLOP/s (32x32x16 products: 1312; 256 x 256 tile, same box); matrix pipeline busy
-// 76 % of the cycles, at a clock that the power limit holds to 1.65 GHz.
+// 1131 -> 1380 TFLOP/s (32x32x16 products: 1312; 256 x 256 tile, back to back on one box); matrix pipeline busy
+// 76 % of the cycles, at a clock that the power limit holds to 1.65 GHz.  Among other kernels, with its epilogue, the
+// projection runs at 1050 to 1370 by the clock the card has at the time (1.98 to 1.52 ms, 1.76 on average).
 template <typename C>
 __device__ __forceinline__ void product(uint32_t lds0, const GemmArgs &a, int f0, int t0, int wave, int lane,
                                         f32x4 (&acc)[C::FB][C::TB]) {
