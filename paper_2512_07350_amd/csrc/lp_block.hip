@@ -637,18 +637,19 @@ using Tile128x64 = Tiling<4, 2, 2, 2, 5>;
 using Tile64x64 = Tiling<2, 2, 2, 2, 5>;
 using Split64x32 = Tiling<2, 2, 2, 1, 8, true>;
 
-// How a call is cut.  A round is one tile on every compute unit (two of 64 x 64).  Per round, in us, fitted to 1332 calls timed
-// on every tiling (1 .. 200000 tokens, d_in 64 .. 13824, d_out 128 .. 13824; 7 .. 11 % rms a tiling): a k-tile of 64, and `once`, what a
-// tile costs besides (first loads, stores); `part` with at most half of the compute units busy, `full` with all of
-// them, where the power limit lowers the clock and the stores of all tiles share the memory's rate.
+// How a call is cut.  A round is one tile on every compute unit (two of 64 x 64).  Per round, in us, fitted to 4004 calls (3133
+// products of 1 .. 200000 tokens, d_in 64 .. 13824, d_out 128 .. 13824, and 871 QKV projections), each timed on every tiling,
+// so that the tiling chosen is the fastest: a k-tile of 64, and `once`, what a tile costs besides (first loads, stores); `part`
+// with at most half of the compute units busy, `full` with all of them, where the power limit lowers the clock and
+// the stores of all tiles share the memory's rate.
 struct TileCost {
     int f, t, threads, per_cu;
     float part, full, once_part, once_full;
 };
 constexpr TileCost kTileCost[] = {
-    {256, 256, 512, 1, 1.05f, 1.39f, 1.7f, 5.5f},  {256, 128, 512, 1, 0.58f, 0.80f, 0.8f, 3.3f},
-    {128, 128, 512, 1, 0.335f, 0.458f, 0.0f, 2.2f}, {128, 64, 512, 1, 0.235f, 0.295f, 0.0f, 1.6f},
-    {64, 64, 256, 2, 0.17f, 0.32f, 0.0f, 1.3f},     {64, 32, 256, 1, 0.09f, 0.13f, 0.4f, 1.3f},
+    {256, 256, 512, 1, 1.198f, 1.252f, 3.22f, 5.24f}, {256, 128, 512, 1, 0.647f, 0.737f, 1.92f, 3.16f},
+    {128, 128, 512, 1, 0.313f, 0.493f, 1.78f, 1.95f}, {128, 64, 512, 1, 0.207f, 0.304f, 1.10f, 1.16f},
+    {64, 64, 256, 2, 0.164f, 0.340f, 0.80f, 1.54f},   {64, 32, 256, 1, 0.096f, 0.107f, 1.27f, 1.30f},
 };
 constexpr int kCutNone = -1;
 template <typename C, int TILE>
@@ -682,7 +683,8 @@ struct Plan {
 // With a k of a few tiles a round is its first loads and its stores, and large tiles are the cheaper ones: 60000 x 64 -> 3840
 // takes 96 us in 256 x 256 tiles and 219 in 128 x 64; in the kernel of two tilings such rounds take up to 20 %
 // longer (24000 x 256 -> 5120: 87 us whole, 106 cut), so that a cut has to promise 5 % there.
-// Over the calls above of 6.5 us and more the choice is off the best tiling by 1.4 % on average.
+// One round of 120 to 250 tiles of 128 x 64 is faster than one of half as many of 128 x 128: 1271 x 704 -> 1536 6.7 and 8.1 us.
+// Over the calls above the choice is off the best tiling by 0.4 % on average, by more than 10 % in 20 of them.
 Plan pick_plan(int64_t n, int32_t d_in, int32_t d_out, bool small_ok, int cus) {
     static constexpr int kCuts[][2] = {{0, 1}, {0, 2}, {0, 3}, {2, 3}};   // the pairs compiled below
     const int n_kt = d_in / kBK;

@@ -99,6 +99,22 @@ def test_gemm_of_a_short_k_takes_large_tiles(n, d_in, d_out, tiles):
     assert routes.gemm(n, d_in, d_out, 0, CUS).tile in tiles
 
 
+# us of the tiles taken / of those with twice the features or tokens, or half: one round that fills half of the chip
+@pytest.mark.parametrize("n,d_in,d_out,head_dim,tile", [
+    (1271, 704, 1536, 0, (128, 64)),      # 6.7 / 8.1
+    (5095, 1792, 384, 0, (128, 64)),      # 11.6 / 14.2
+    (14871, 896, 128, 0, (128, 64)),      # 7.6 / 8.9
+    (1327, 1344, 1408, 0, (128, 64)),     # 9.2 / 11.6
+    (135, 1792, 3200, 0, (64, 32)),       # 6.5 / 8.2
+    (572, 1216, 768, 0, (64, 32)),        # 5.3 / 6.4
+    (532, 1024, 3072, 128, (128, 64)),    # 9.6 / 11.7
+    (910, 512, 1536, 128, (128, 64)),     # 7.3 / 9.0
+    (2420, 256, 768, 64, (128, 64)),      # 6.6 / 7.8
+])
+def test_gemm_fills_the_chip_with_the_smaller_tile(n, d_in, d_out, head_dim, tile):
+    assert routes.gemm(n, d_in, d_out, head_dim, CUS).tile == tile
+
+
 @pytest.mark.parametrize("n,d_in,d_out,tile,cut", [
     (520, 5120, 640, (64, 32), None), (13230, 5120, 5120, (256, 256), (128, 64)), (13230, 5120, 15360, (256, 256), (128, 128)),
     (3780, 1536, 4608, (256, 256), (128, 64)), (3780, 1536, 1536, (256, 128), None), (2737, 1024, 1024, (128, 128), None),
