@@ -21,8 +21,14 @@
 // The products are 16x16x32 and not 32x32x16: the part is limited by power, and a loop of nothing
 // but products on N(0,1) operands sustains 2077 TFLOP/s with the former and 1837 with the latter.
 // The kernel's own step on the same schedule: 1258 TFLOP/s with 32x32x16, 1373 with 16x16x32, 1408
-// with four tiles unrolled (13230 tokens, 40 heads of 128; at head_dim 64 1068, 1065 and 1170: there the
-// vector issue slots bind, and the unrolled addresses free some).
+// with four tiles unrolled (13230 tokens, 40 heads of 128).
+//
+// What a step costs follows from what a SIMD issues for its one wavefront (measured in loops of nothing else): a product
+// 8 cycles of issue and 16 of the matrix pipeline, a vector instruction 4, an exponential 8; v_dot2c_f32_bf16 goes through
+// the matrix pipeline and holds it 16 cycles.  With the row sums as 16 dots a step, and windows of unequal length, a step took 1450
+// cycles at head_dim 128 (1024 of products); with the row sums as four products and the windows evened out 1120: 13230
+// tokens, 40 heads of 128 2590 -> 2350 us, 2999 x 16 of 64 45.4 -> 40.4 us.  Without any row sums it would be 2.5 % less,
+// with the probabilities added one by one in binary32 it is 4 % more (12 % at head_dim 64, where issue binds).
 //
 // Details that matter for speed:
 //  * Q is multiplied by scale*log2(e) once and re-rounded to bf16, and the score
@@ -37,9 +43,9 @@
 //    more than kRescaleThreshold, in a rarely taken, wave-uniform branch that rescales the
 //    output accumulators.
 //  * The score product of round r+1, the softmax of round r and the PV product of round
-//    r-1 share one step, and the step's vector and LDS work is cut into one small window
-//    per matrix instruction (pipeline_step), so that the one wavefront of a SIMD has its
-//    next product ready when the matrix pipeline takes it.
+//    r-1 (with the row sums, the same probabilities times an operand of ones) share one step, and the step's vector and
+//    LDS work is cut into one small window per matrix instruction (pipeline_step), so that the one wavefront of a
+//    SIMD has its next product ready when the matrix pipeline takes it.
 //  * The key order inside a 32-key round is permuted (MFMA row r of the round's block b is
 //    key 8 (r / 4) + 4 b + r % 4) so that the 8 probabilities a lane feeds to one MFMA
 //    belong to 8 consecutive keys; V^T operands then come from two ds_read_b64_tr_b16
@@ -66,9 +72,6 @@ using namespace lp;
 constexpr int kBM = 256;                      // query rows per workgroup
 constexpr int kWaves = 4;                     // wavefronts per workgroup, one per SIMD
 constexpr int kQB = kBM / (16 * kWaves);      // 16-query blocks of a wavefront: 64 rows
-// Row sums kept per query: two at head_dim 64, where two pairs of scores are added between LDS
-// fetches and the compiler would put a wait state between additions to the same one.
-constexpr int row_sums(int head_dim) { return head_dim == 64 ? 2 : 1; }
 constexpr int kBN = 64;                       // keys per LDS tile (two rounds of 32)
 constexpr int kStages = 4;                    // LDS stages: three tiles in use plus one arriving
 constexpr float kRescaleThreshold = 8.0f;     // log2 units the running max may lag behind
@@ -221,10 +224,6 @@ __device__ __forceinline__ void exp2_to(float &p, float s) { asm volatile("v_exp
 __device__ __forceinline__ void pack_bf16(uint32_t &w, float lo, float hi) {
     asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(w) : "v"(lo), "v"(hi));
 }
-// The row sum adds the rounded probabilities: l += 1 * lo + 1 * hi.
-__device__ __forceinline__ void add_to_row_sum(uint32_t pair, float &l) {
-    asm volatile("v_dot2c_f32_bf16 %0, %1, %2" : "+v"(l) : "s"(0x3f803f80), "v"(pair));
-}
 
 // Scores written by matrix instructions become readable by vector instructions: 16 wait
 // states cover the passes of the last product plus its write-back.
@@ -239,39 +238,40 @@ __device__ __forceinline__ void settle_scores(f32x4 (&s)[2][kQB], bool wait) {
 // The same for the accumulators in the AGPRs (before they are rescaled or stored), and, with
 // after = true, between vector writes to them and the next matrix instruction.
 template <int D>
-__device__ __forceinline__ void settle_acc(f32x4 (&acc)[D / 16][kQB], bool after) {
+__device__ __forceinline__ void settle_acc(f32x4 (&acc)[D / 16][kQB], f32x4 (&l_acc)[kQB], bool after) {
     if (after) asm volatile("s_nop 3");
     else asm volatile("s_nop 15\n\ts_nop 7");
 #pragma unroll
-    for (int mb = 0; mb < D / 16; ++mb)
+    for (int qb = 0; qb < kQB; ++qb) {
+        asm volatile("" : "+a"(l_acc[qb]));
 #pragma unroll
-        for (int qb = 0; qb < kQB; ++qb) asm volatile("" : "+a"(acc[mb][qb]));
+        for (int mb = 0; mb < D / 16; ++mb) asm volatile("" : "+a"(acc[mb][qb]));
+    }
 }
 
 // Lazy running maximum.  Score accumulators start at neg_m = -m (m = running maximum, log2
 // units), so s holds scores relative to m that will be exponentiated NEXT.  If any of them
 // exceeds kRescaleThreshold, raise the maximum by delta and rescale what was accumulated
 // under the old one: these scores, the output accumulators, the row sums, and the
-// probabilities p_pending that have been computed but not yet multiplied into acc.
+// probabilities p_pending that have been computed but not yet multiplied into either.
 template <int D>
 __device__ __forceinline__ void raise_maximum(const float (&lane_max)[kQB], f32x4 (&s)[2][kQB], f32x4 (&neg_m)[kQB],
-                                              bf16x8 (&p_pending)[kQB], f32x4 (&acc)[D / 16][kQB], float (&l_run)[kQB][row_sums(D)]) {
+                                              bf16x8 (&p_pending)[kQB], f32x4 (&acc)[D / 16][kQB], f32x4 (&l_acc)[kQB]) {
     bool raise = false;
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) raise = raise || (lane_max[qb] > kRescaleThreshold);
     if (__builtin_expect(__any(raise) != 0, 0)) {     // the branch body is laid out away from the loop
-        settle_acc<D>(acc, false);
+        settle_acc<D>(acc, l_acc, false);
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb) {
             const float delta = fmaxf(quad_max(lane_max[qb]), 0.0f);           // the maximum never goes down
             const float alpha = __builtin_amdgcn_exp2f(-delta);
 #pragma unroll
-            for (int e = 0; e < row_sums(D); ++e) l_run[qb][e] *= alpha;
-#pragma unroll
             for (int i = 0; i < 4; ++i) {
                 s[0][qb][i] -= delta;
                 s[1][qb][i] -= delta;
                 neg_m[qb][i] -= delta;
+                l_acc[qb][i] *= alpha;
             }
 #pragma unroll
             for (int mb = 0; mb < D / 16; ++mb)
@@ -285,7 +285,7 @@ __device__ __forceinline__ void raise_maximum(const float (&lane_max)[kQB], f32x
                 t.p[e] = to_bf16x2(__uint_as_float(w[e] << 16) * alpha, __uint_as_float(w[e] & 0xffff0000u) * alpha);
             p_pending[qb] = t.v;
         }
-        settle_acc<D>(acc, true);
+        settle_acc<D>(acc, l_acc, true);
     }
 }
 
@@ -311,10 +311,11 @@ template <int D>
 struct Pipe {
     bf16x8 qreg[kQB][D / 32];      // Q^T operands (pre-scaled)
     bf16x8 opreg[D / 16];          // LDS operands: K rows before a score product, V^T blocks before a PV product
+    bf16x8 ones;                   // 1.0 in every element: the A operand of the row sums
     f32x4 acc[D / 16][kQB];        // O^T accumulators
+    f32x4 l_acc[kQB];              // row sums, each of the four elements (and every lane of a query) the same
     f32x4 neg_m[kQB];              // -m in every element (m = running maximum, log2 units, common to
                                    // the four lanes of a query): the initial value of every score accumulator
-    float l_run[kQB][row_sums(D)]; // this lane's share of the running sum
     uint32_t k_addr[D / 32];       // LDS addresses of the K operands in the stage at k_off
     uint32_t v_addr[D / 16];       // LDS addresses of the V operands in the stage at v_off
     uint32_t k_off, v_off;         // stage offsets k_addr / v_addr currently point into
@@ -348,9 +349,8 @@ __device__ __forceinline__ void store_rows(uint32_t out_lds, const f32x4 (&acc)[
     }
 }
 
-// The part of the softmax that trails the exponentials.  Pair k holds scores 2 k, 2 k + 1 counted block
-// by block: word k % 4 of the operand of query block k / 4.  convert_pairs rounds the pairs [FROM, TO)
-// to packed bf16 words (and completes an operand with its fourth word), sum_pairs adds them to the row sums.
+// Rounds the pairs of probabilities [FROM, TO) to packed bf16 words and completes an operand with its fourth word.  Pair k
+// holds scores 2 k, 2 k + 1 counted block by block: word k % 4 of the operand of query block k / 4.
 template <int FROM, int TO>
 __device__ __forceinline__ void convert_pairs(const float (&ex)[kQB * 8], uint32_t (&pw)[kQB][4], bf16x8 (&p_cur)[kQB]) {
     static_for<FROM, TO>([&](auto kc) {
@@ -363,13 +363,31 @@ __device__ __forceinline__ void convert_pairs(const float (&ex)[kQB * 8], uint32
         }
     });
 }
-template <int FROM, int TO, int SUMS>
-__device__ __forceinline__ void sum_pairs(const uint32_t (&pw)[kQB][4], float (&l_run)[kQB][SUMS]) {
-    static_for<FROM, TO>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        add_to_row_sum(pw[k / 4][k % 4], l_run[k / 4][k % SUMS]);
-    });
-}
+
+// Where in a step what stands.  A step is (2 G + 1) kQB windows, one per product: G = D / 16 score groups, the group of
+// the row sums, G PV groups (a group is the kQB products that share an operand).  After an odd window there is room for
+// two instructions, after an even one for the exponential that leads the next (see pipeline_step).
+template <int D>
+struct Windows {
+    static constexpr int G = D / 16, M = (2 * G + 1) * kQB;
+    static constexpr int kPv = (G + 1) * kQB;                             // first window of the PV phase
+    static constexpr int E = kQB * 8, kEvery = 2 * G * kQB / E;           // exponentials, and windows per exponential
+    static_assert(kEvery == 2 || kEvery == 1, "the exponentials fill the products' windows");
+    static constexpr int odd(int m) { return m | 1; }
+    // the V^T operand of PV group g is fetched into the registers that score group g has read, a half at a time
+    static constexpr int fetch_v(int g, int half) { return odd(g * kQB + kQB - 1) + 2 * half; }
+    // the K operand g of the next score phase into those that PV group g has read
+    static constexpr int fetch_k(int g) { return kPv + g * kQB + kQB - 1; }
+    // load g of the next tile (K block g / 2, then its V block), behind the write of M0 in the window of load g - 1
+    static constexpr int load(int g) { return kPv + g * kQB + kQB - 3; }
+    static constexpr int v_before(int m) {                                // V fetches (halves) issued before window m
+        int c = 0;
+        for (int g = 0; g < G; ++g)
+            for (int h = 0; h < 2; ++h) c += fetch_v(g, h) < m;
+        return c;
+    }
+    static_assert(kQB % 2 == 0 && fetch_v(G - 1, 1) < kPv && fetch_k(G - 1) < M, "a fetch stands in its own phase");
+};
 
 template <int BYTES>
 __device__ __forceinline__ uint32_t next_stage(uint32_t off) {
@@ -445,90 +463,75 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, i
         }
     }
 
-    // The step's products come in G score groups and then G PV groups (a group is the kQB products
-    // that share one LDS operand).  The wavefront is alone on its SIMD, so the matrix pipeline is
-    // busy only if the next product is issued before the one before it has passed: the vector
-    // and LDS work of the step is therefore cut into one small window per product -- the
-    // exponentials of round i, a conversion and a row-sum update for every second of them, the
-    // refill of the operand registers the group has just read (half a V^T operand or a K operand
-    // per window), in even steps the next tile's loads.  In a window the softmax work comes before the
-    // product and the LDS fetch directly after it: with the exponential between product and fetch the
-    // same instructions took 7 % longer.
-    constexpr int G = D / 16;                   // groups per phase
-    constexpr int M = 2 * G * kQB;              // products per step
-    constexpr int E = kQB * 8;                  // exponentials per step
-    constexpr int PP = row_sums(D);             // pairs of scores per group
-    static_assert(E == 4 * G * PP, "the exponentials fill the groups");
+    // The step's products come in G score groups, the group of the row sums and G PV groups.  The wavefront is alone on
+    // its SIMD, which takes an instruction of it every 4 cycles (an exponential 8) and gives a product 8 of the 16 it takes: the
+    // matrix pipeline stays busy if no more than 8 cycles of other instructions stand between two products.  The
+    // vector and LDS work of the step is therefore cut into one small window per product (struct Windows): at head_dim
+    // 128 the exponentials of round i alternate with what is shorter, a conversion, the refill of the operand
+    // registers that a group has read (half a V^T operand or a K operand), in even steps the next tile's loads.  At 64
+    // there are twice as many exponentials to a product and the windows are longer than it.
+    // Row sums are products too, with an operand of ones: four per step.  As v_dot2c_f32_bf16 of the packed pairs they
+    // held the matrix pipeline as long as a product each, 16 of them a step.
+    using W = Windows<D>;
+    constexpr int G = W::G, M = W::M, E = W::E, kEvery = W::kEvery;
     uint32_t pw[kQB][4];
     float ex[E];
     Pack16 vop;
-    // The softmax work of a window: of the pairs of group g the exponentials, of those of the group before
-    // the conversions, of those of the one before that the row sums.
-    auto softmax_window = [&](auto mc) {
-        constexpr int m = decltype(mc)::value, g = m / kQB, qb = m % kQB;
-        if constexpr (PP == 2 || qb % 2 == 1) {
-            constexpr int x = PP == 1 ? 2 * g + qb / 2 : 4 * g + qb;
-            exp2_to(ex[x], s_cur[(x / 4) % 2][x / 8][x % 4]);
-        }
-        constexpr int cvt = PP * (g - 1) + qb, dot = PP * (g - 2) + qb - PP;
-        if constexpr (g > 0 && qb < PP) convert_pairs<cvt, cvt + 1>(ex, pw, p_cur);
-        if constexpr (g > 1 && qb >= PP && qb < 2 * PP) sum_pairs<dot, dot + 1, PP>(pw, w.l_run);
-    };
     static_for<0, M>([&](auto mc) {
         constexpr int m = decltype(mc)::value, g = m / kQB, qb = m % kQB;
-        softmax_window(mc);
-        // Operand arrivals are checked for half a phase at a time.  In issue order the LDS queue
-        // holds, at the start of the score phase, the G K fetches of the previous PV phase: all
-        // but the newest G/2 cover groups 0 .. G/2-1; by group G/2 the newest are G/2 groups
-        // of V fetches (2 each), so lgkmcnt(G) covers the rest.  The PV phase mirrors this with
+        // pair k is rounded in the second window after its second exponential
+        if constexpr (m % (2 * kEvery) == 0 && m > 0 && m / kEvery <= E) convert_pairs<m / (2 * kEvery) - 1, m / (2 * kEvery)>(ex, pw, p_cur);
+        if constexpr (m % kEvery == kEvery - 1 && m / kEvery < E) {
+            constexpr int x = m / kEvery;
+            exp2_to(ex[x], s_cur[(x / 4) % 2][x / 8][x % 4]);
+        }
+        // Operand arrivals are checked for half a phase at a time.  In issue order the LDS queue holds, at the start of the
+        // score phase, the G K fetches of the previous PV phase: all but the newest G / 2 cover groups 0 .. G / 2 - 1;
+        // by group G / 2 the newest are the V fetches so far.  The PV phase mirrors this with
         // 2 G V fetches followed by one K fetch per group.
         if constexpr (qb == 0 && g == 0) lds_wait<G / 2>();
-        if constexpr (qb == 0 && g == G / 2) lds_wait<G>();
-        if constexpr (qb == 0 && g == G) lds_wait<G>();
-        if constexpr (qb == 0 && g == G + G / 2) lds_wait<G / 2>();
-        if constexpr (g < G) {
-            if constexpr (g < 2) mfma_score_init(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][0], w.neg_m[qb]);
-            else mfma_score(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][g / 2]);
-            if constexpr (qb == 0 && (kFixed ? kVHop : SUB == 1)) move_address(w.v_addr[g], v_delta);
-            if constexpr (qb == kQB - 2) vop.h[0] = load_v_half<D, 1 - SUB, 0, kVOff>(w.v_addr, g);
-            if constexpr (qb == kQB - 1) {
-                vop.h[1] = load_v_half<D, 1 - SUB, 1, kVOff>(w.v_addr, g);
-                w.opreg[g] = vop.v;
+        if constexpr (qb == 0 && g == G / 2) lds_wait<W::v_before(m)>();
+        if constexpr (qb == 0 && g == G + 1) lds_wait<G>();
+        if constexpr (qb == 0 && g == G + 1 + G / 2) lds_wait<G / 2>();
+        if constexpr (g < 2) mfma_score_init(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][0], w.neg_m[qb]);
+        else if constexpr (g < G) mfma_score(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][g / 2]);
+        else if constexpr (g == G) mfma_pv(w.l_acc[qb], w.ones, p_prev[qb]);
+        else mfma_pv(w.acc[g - G - 1][qb], w.opreg[g - G - 1], p_prev[qb]);
+        static_for<0, G>([&](auto oc) {
+            constexpr int o = decltype(oc)::value;
+            if constexpr (m == W::fetch_v(o, 0)) {
+                if constexpr (kFixed ? kVHop : SUB == 1) move_address(w.v_addr[o], v_delta);
+                vop.h[0] = load_v_half<D, 1 - SUB, 0, kVOff>(w.v_addr, o);
             }
-        } else {
-            constexpr int j = g - G;
-            mfma_pv(w.acc[j][qb], w.opreg[j], p_prev[qb]);
-            // the tile's load statements, evenly over the PV groups
-            constexpr int kLd = Lane<D>::kLd, every = G / kLd, ld = j / every;
-            if constexpr (qb == kQB - 1) {
-                if constexpr (j % 2 == 0 && (kFixed ? kKHop : SUB == 0)) move_address(w.k_addr[j / 2], k_delta);
-                w.opreg[j] = load_k_operand<D, SUB, kKOff>(w.k_addr, j);
-            } else if constexpr (SUB == 0 && j % every == 0) {
-                if constexpr (!kFixed) {
-                    if constexpr (qb == 0) issue_tile_part<D, ld>(lds0, c, issue_soff, issue_stage);
-                } else {
-                    constexpr int kDst = ((STAGE + kStages - 2) % kStages) * T::kStageBytes;
-                    if constexpr (qb == 0) set_m0<kDst>(c.ld_base[ld]);
-                    if constexpr (qb == 1) {
-                        load_to_lds_16(c.k_rsrc, c.k_voff[ld], issue_soff);
-                        set_m0<kDst + T::kTileBytes>(c.ld_base[ld]);
-                    }
-                    if constexpr (qb == 2) load_to_lds_16(c.v_rsrc, c.v_voff[ld], issue_soff);
+            if constexpr (m == W::fetch_v(o, 1)) {
+                vop.h[1] = load_v_half<D, 1 - SUB, 1, kVOff>(w.v_addr, o);
+                w.opreg[o] = vop.v;
+            }
+            if constexpr (m == W::fetch_k(o)) {
+                if constexpr (o % 2 == 0 && (kFixed ? kKHop : SUB == 0)) move_address(w.k_addr[o / 2], k_delta);
+                w.opreg[o] = load_k_operand<D, SUB, kKOff>(w.k_addr, o);
+            }
+            // the tile's load statements, one block to a PV group (both blocks to every second one outside the unrolled part)
+            if constexpr (SUB == 0 && kFixed) {
+                constexpr int kDst = ((STAGE + kStages - 2) % kStages) * T::kStageBytes;
+                if constexpr (m == W::load(0) - 2 && o == 0) set_m0<kDst>(c.ld_base[0]);
+                if constexpr (m == W::load(o)) {
+                    if constexpr (o % 2 == 0) load_to_lds_16(c.k_rsrc, c.k_voff[o / 2], issue_soff);
+                    else load_to_lds_16(c.v_rsrc, c.v_voff[o / 2], issue_soff);
+                    if constexpr (o + 1 < G) set_m0<kDst + (o % 2 == 0 ? T::kTileBytes : 0)>(c.ld_base[(o + 1) / 2]);
                 }
             }
-        }
+            if constexpr (SUB == 0 && !kFixed && m == W::load(o) && o % 2 == 0) issue_tile_part<D, o / 2>(lds0, c, issue_soff, issue_stage);
+        });
         if constexpr (SUB == 0 && m == G * kQB - 1) {
             // tile t+1, issued one tile ago; what is still on its way from LDS is V of tile t-1
             asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         }
-        if constexpr (m == G * kQB + 2 * kQB) {        // the last score product has left the pipeline
+        if constexpr (m == W::kPv + kQB) {             // the last score product has left the pipeline
             settle_scores(s_nxt, false);
             if (MASK) mask_scores(i + 1, c.quad, c.key_end, s_nxt);
         }
     });
-    // what the last groups left to convert and to add
-    convert_pairs<E / 2 - PP, E / 2>(ex, pw, p_cur);
-    sum_pairs<E / 2 - 2 * PP, E / 2, PP>(pw, w.l_run);
     if constexpr (CHECK) {                     // the repeated run only, see run_segment
         float lane_max[kQB];
 #pragma unroll
@@ -537,7 +540,7 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, i
 #pragma unroll
             for (int e = 1; e < 8; ++e) lane_max[qb] = fmaxf(lane_max[qb], s_nxt[e / 4][qb][e % 4]);
         }
-        raise_maximum<D>(lane_max, s_nxt, w.neg_m, p_cur, w.acc, w.l_run);
+        raise_maximum<D>(lane_max, s_nxt, w.neg_m, p_cur, w.acc, w.l_acc);
     }
 }
 
@@ -726,6 +729,12 @@ __global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams
     Segment seg = next_segment(walk, a, tpu, lp, gridDim.x);
     if (!seg.valid) return;
     Pipe<D> w;
+    {
+        Pack16 t;
+        t.u = make_uint4(0x3f803f80, 0x3f803f80, 0x3f803f80, 0x3f803f80);
+        w.ones = t.v;
+        asm volatile("" : "+v"(w.ones));
+    }
     start_tiles<D>(lds0, a, seg, c, w, n, stride_tok);
     load_q<D>(a, seg, w, n, stride_tok, wave, col, quad);
 
@@ -772,10 +781,8 @@ __global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams
 #pragma unroll
             for (int qb = 0; qb < kQB; ++qb) w.acc[mb][qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int qb = 0; qb < kQB; ++qb)
-#pragma unroll
-            for (int e = 0; e < row_sums(D); ++e) w.l_run[qb][e] = 0.0f;
-        settle_acc<D>(w.acc, true);
+        for (int qb = 0; qb < kQB; ++qb) w.l_acc[qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        settle_acc<D>(w.acc, w.l_acc, true);
 
         // ---- LDS operand addresses in stage 0 (recomputed from an opaque copy of the lane
         // index: kept as loop invariants they would be held in registers through the pipeline)
@@ -876,15 +883,12 @@ __global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams
         {
             // anything in this lane's row sums or accumulators that is not finite, or within 2^7 of
             // not being so (partial rows are stored as bf16)?  y - y is 0 for every finite y
-            settle_acc<D>(w.acc, false);
+            settle_acc<D>(w.acc, w.l_acc, false);
             float probe = 0.0f;
 #pragma unroll
             for (int qb = 0; qb < kQB; ++qb) {
-#pragma unroll
-                for (int e = 0; e < row_sums(D); ++e) {
-                    const float yl = w.l_run[qb][e] * 128.0f;
-                    probe += yl - yl;
-                }
+                const float yl = w.l_acc[qb][0] * 128.0f;
+                probe += yl - yl;
 #pragma unroll
                 for (int mb = 0; mb < G; ++mb)
 #pragma unroll
@@ -911,12 +915,12 @@ __global__ __launch_bounds__(kWaves * 64) void attention_kernel(const AttnParams
 
         // ---- results of this segment: final rows, or (a unit shared with other workgroups)
         // running maximum, row sum and unnormalised rows into this workgroup's slot
-        settle_acc<D>(w.acc, false);
+        settle_acc<D>(w.acc, w.l_acc, false);
         const int lane = opaque(lane_id), col = lane % 16, quad = lane / 16;
         const bool whole = (t_begin == 0) && (uint32_t(t_stop) == tpu);
 #pragma unroll
         for (int qb = 0; qb < kQB; ++qb) {
-            const float l_tot = quad_sum(row_sums(D) == 2 ? w.l_run[qb][0] + w.l_run[qb][row_sums(D) - 1] : w.l_run[qb][0]);
+            const float l_tot = w.l_acc[qb][0];
             const int row0 = wave * (16 * kQB) + qb * 16;
             if (whole) {
                 const int q0 = qtile * kBM + row0;
