@@ -15,13 +15,21 @@
 // Products, operand layouts and the order of keys in a round are those of attention_kernel (16x16x32
 // MFMA, S^T = K Q^T and O^T += V^T P^T, K rows permuted so that a lane's eight probabilities are eight
 // consecutive keys, V read transposed); the products are builtins here: with 32 rows a wavefront
-// needs 166 registers and two workgroups share a compute unit.
+// needs 190 registers at head_dim 128 (126 at 64) and two (four) workgroups share a compute unit.
 //
 // Measured (us, attention_kernel / this): 200 tokens, 4 heads of 64: 9.9 / 4.5; 333, 3 of 128: 17.8 /
 // 6.6; 1000, 12 of 128: 32 / 16.4; 2000, 12 of 128: 43 / 42; 3000, 12 of 128: 67 / 86.  One stage per
 // wavefront, whose K half is refilled once the scores are formed and whose V half after the PV
 // product, and two workgroups per compute unit are faster than two whole stages and one workgroup
 // (1000 tokens, 12 heads of 128: 16.4 / 23.1); eight wavefronts per workgroup 20.9; 64 rows 22.8.
+//
+// A compute unit takes in about 100 GB/s through the global -> LDS path here (32 KB per 128 keys and workgroup in 0.33 us at
+// head_dim 64), and its SIMDs issue for several wavefronts: what a round costs besides its products and exponentials counts.  The row
+// sums as products, the score products started at -m without a look at it, and one write of M0 for four loads: 1000 tokens, 12
+// heads of 64 10.0 -> 9.65 us, 600 x 24 of 64 8.05 -> 7.85, 333 x 3 of 128 7.15 -> 7.0, 200 x 4 of 64 4.7 as before.
+// Not kept: a merge of one barrier in which each wavefront finishes a quarter of the columns (200 x 4 of 64 4.95), 64 rows at
+// head_dim 64 and 48 at 128 with two workgroups to a compute unit (1628 x 25 of 64 28.7 / 30.9; 3000 x 12 of 128 84.8 / 68,
+// 59 in 256-row tiles).
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -63,6 +71,16 @@ __device__ __forceinline__ void wait_loads() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PENDING) : "memory");
 }
 
+// Four wave-wide global -> LDS loads to consecutive KB of LDS behind one write of M0: an instruction's offset counts on both
+// sides, so lane offset i has to lie 1024 i below the bytes it fetches.
+__device__ __forceinline__ void load_to_lds_4x16(__amdgpu_buffer_rsrc_t rsrc, uint32_t lds_addr, uint32_t v0, uint32_t v1, uint32_t v2, uint32_t v3, uint32_t soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %5, %6 offen lds\n\tbuffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\tbuffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
+                 :
+                 : "s"(lds_addr), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "s"(rsrc), "s"(soff)
+                 : "memory", "m0");
+}
+
 // FAR: tokens so far apart that the 32 rows of a round reach past 2^32 bytes, so that a 32-bit offset would place some of the
 // rows past the last inside the buffer (which has less than 2^31 bytes).  They all go where the first of them lies, behind it.  A kernel of its own: the clamp in every call cost one of 1248 tokens x 4 heads of 128 4 %.
 template <int D, bool FAR>
@@ -91,25 +109,21 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
 #pragma unroll
     for (int i = 0; i < T::kLoads; ++i) {
         const int row = i * T::kRowsPerLoad + lane / T::kGran, g = lane % T::kGran;
-        const uint32_t row_off = uint32_t(FAR ? min(row, n) : row) * tok_bytes;
+        const uint32_t row_off = uint32_t(FAR ? min(row, n) : row) * tok_bytes - 1024 * (i % 4);     // not below 0: rows do not overlap
         k_voff[i] = row_off + 16 * (g ^ T::swz_k(row));
         v_voff[i] = row_off + 16 * (g ^ T::swz_v(row));
     }
-    auto issue_k = [&](int round) {
+    auto issue = [&](const __amdgpu_buffer_rsrc_t &rsrc, uint32_t lds, const uint32_t (&voff)[T::kLoads], int round) {
 #pragma unroll
-        for (int i = 0; i < T::kLoads; ++i)
-            load_to_lds_16(k_rsrc, __builtin_amdgcn_readfirstlane(k_lds + i * 1024), k_voff[i], uint32_t(round) * 32 * tok_bytes);
-    };
-    auto issue_v = [&](int round) {
-#pragma unroll
-        for (int i = 0; i < T::kLoads; ++i)
-            load_to_lds_16(v_rsrc, __builtin_amdgcn_readfirstlane(v_lds + i * 1024), v_voff[i], uint32_t(round) * 32 * tok_bytes);
+        for (int i = 0; i < T::kLoads; i += 4)
+            load_to_lds_4x16(rsrc, __builtin_amdgcn_readfirstlane(lds + i * 1024), voff[i], voff[i + 1], voff[i + 2], voff[i + 3],
+                             uint32_t(round) * 32 * tok_bytes);
     };
     const int n_rounds = (n + 31) / 32;
     int round = wave;
     if (round < n_rounds) {
-        issue_k(round);
-        issue_v(round);
+        issue(k_rsrc, k_lds, k_voff, round);
+        issue(v_rsrc, v_lds, v_voff, round);
     }
 
     // Q^T operands, multiplied by scale * log2(e) and rounded to bf16 again; rows past the end repeat
@@ -139,12 +153,16 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
     for (int mb = 0; mb < MB; ++mb)
         v_addr[mb] = v_lds + vrow * T::kRowBytes + 8 * (col % 2) + 16 * ((2 * mb + (col % 4) / 2) ^ T::swz_v(vrow));
 
-    f32x4 acc[MB][kQB];
-    float m[kQB], l[kQB];                       // m: log2 units, common to the four lanes of a query
+    // neg_m = -m in every element (m: running maximum, log2 units, common to the four lanes of a query), what the score products
+    // start at; 0 as long as no score was above -inf, which limit = -inf says.  l: row sums, the same in every element.
+    f32x4 acc[MB][kQB], l[kQB], neg_m[kQB];
+    float limit[kQB];                           // a score relative to m above this raises m
+    Pack16 ones;
+    ones.u = make_uint4(0x3f803f80, 0x3f803f80, 0x3f803f80, 0x3f803f80);
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
-        m[qb] = -INFINITY;
-        l[qb] = 0.0f;
+        limit[qb] = -INFINITY;
+        l[qb] = neg_m[qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) acc[mb][qb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
@@ -154,25 +172,19 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
         wait_loads<T::kLoads>();                // K of this round; behind it only V
         f32x4 s[2][kQB];
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int qb = 0; qb < kQB; ++qb) {
-                const float c = m[qb] == -INFINITY ? 0.0f : -m[qb];
-                s[b][qb] = f32x4{c, c, c, c};
-            }
-#pragma unroll
         for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const bf16x8 ka = lds_load<bf16x8>(k_addr[kk] + 4 * b * T::kRowBytes);
 #pragma unroll
-                for (int qb = 0; qb < kQB; ++qb) s[b][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, q[qb][kk], s[b][qb], 0, 0, 0);
+                for (int qb = 0; qb < kQB; ++qb)
+                    s[b][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, q[qb][kk], kk == 0 ? neg_m[qb] : s[b][qb], 0, 0, 0);
             }
         if (more) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // every K operand has left LDS
-            issue_k(round + kWaves);
+            issue(k_rsrc, k_lds, k_voff, round + kWaves);
         }
-        if ((round + 1) * 32 > n) {             // keys past the end: score -inf
+        if (__builtin_expect((round + 1) * 32 > n, 0)) {           // keys past the end: score -inf
             const int kbase = round * 32 + 8 * quad;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -190,23 +202,22 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
             mx[qb] = s[0][qb][0];
 #pragma unroll
             for (int e = 1; e < 8; ++e) mx[qb] = fmaxf(mx[qb], s[e / 4][qb][e % 4]);
-            raise = raise || m[qb] == -INFINITY || mx[qb] > kRescaleThreshold;
+            raise = raise | (mx[qb] > limit[qb]);
         }
-        if (__any(raise)) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
 #pragma unroll
             for (int qb = 0; qb < kQB; ++qb) {
-                const bool fresh = m[qb] == -INFINITY;
+                const bool fresh = limit[qb] == -INFINITY;
                 const float top = quad_max(mx[qb]);
                 const float d = fresh ? (top == -INFINITY ? 0.0f : top) : fmaxf(top, 0.0f);
                 const float f = fresh ? 0.0f : __builtin_amdgcn_exp2f(-d);
-                m[qb] = fresh ? top : m[qb] + d;
+                limit[qb] = fresh && top == -INFINITY ? -INFINITY : kRescaleThreshold;
+                neg_m[qb] -= d;
                 l[qb] *= f;
+                s[0][qb] -= d;
+                s[1][qb] -= d;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) s[e / 4][qb][e % 4] -= d;
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[mb][qb][i] *= f;
+                for (int mb = 0; mb < MB; ++mb) acc[mb][qb] *= f;
             }
         }
         bf16x8 p[kQB];
@@ -214,12 +225,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
         for (int qb = 0; qb < kQB; ++qb) {
             Pack16 t;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+            for (int e = 0; e < 4; ++e)
                 t.p[e] = to_bf16x2(__builtin_amdgcn_exp2f(s[e / 2][qb][(2 * e) % 4]), __builtin_amdgcn_exp2f(s[e / 2][qb][(2 * e) % 4 + 1]));
-                l[qb] = __builtin_amdgcn_fdot2_f32_bf16(t.p[e], ones, l[qb], false);     // the row sum adds the rounded probabilities
-            }
             p[qb] = t.v;
+            // the row sum adds the rounded probabilities, as one product (a v_dot2 per pair holds the matrix pipeline as long each)
+            l[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, p[qb], l[qb], 0, 0, 0);
         }
         if (more) wait_loads<T::kLoads>();      // V of this round; behind it only the next round's K
         else wait_loads<0>();
@@ -234,17 +244,18 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attention_short_kernel(const S
         }
         if (more) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // every V operand has left LDS
-            issue_v(round + kWaves);
+            issue(v_rsrc, v_lds, v_voff, round + kWaves);
         }
     }
 
     // ---- merge: maxima and row sums through LDS, then the rows, scaled to the common maximum
     __syncthreads();                            // every wavefront has left its ring (its loads have all landed)
     const uint32_t ml_lds = lds0 + kWaves * T::kPartBytes;
+    float m[kQB];
 #pragma unroll
     for (int qb = 0; qb < kQB; ++qb) {
-        l[qb] = quad_sum(l[qb]);
-        if (quad == 0) lds_store(ml_lds + 8 * (wave * kRows + qb * 16 + col), f32x2{m[qb], l[qb]});
+        m[qb] = limit[qb] == -INFINITY ? -INFINITY : -neg_m[qb][0];
+        if (quad == 0) lds_store(ml_lds + 8 * (wave * kRows + qb * 16 + col), f32x2{m[qb], l[qb][0]});
     }
     __syncthreads();
 #pragma unroll
