@@ -478,7 +478,9 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, i
     float ex[E];
     Pack16 vop;
     static_for<0, M>([&](auto mc) {
-        constexpr int m = decltype(mc)::value, g = m / kQB, qb = m % kQB;
+        // every second group runs backwards: neighbours then share an operand throughout, and what does not change costs less
+        // power (13230 tokens, 40 heads of 128: 2280 -> 2251 us)
+        constexpr int m = decltype(mc)::value, g = m / kQB, at = m % kQB, qb = g % 2 ? kQB - 1 - at : at;
         // pair k is rounded in the second window after its second exponential
         if constexpr (m % (2 * kEvery) == 0 && m > 0 && m / kEvery <= E) convert_pairs<m / (2 * kEvery) - 1, m / (2 * kEvery)>(ex, pw, p_cur);
         if constexpr (m % kEvery == kEvery - 1 && m / kEvery < E) {
@@ -489,10 +491,10 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, i
         // score phase, the G K fetches of the previous PV phase: all but the newest G / 2 cover groups 0 .. G / 2 - 1;
         // by group G / 2 the newest are the V fetches so far.  The PV phase mirrors this with
         // 2 G V fetches followed by one K fetch per group.
-        if constexpr (qb == 0 && g == 0) lds_wait<G / 2>();
-        if constexpr (qb == 0 && g == G / 2) lds_wait<W::v_before(m)>();
-        if constexpr (qb == 0 && g == G + 1) lds_wait<G>();
-        if constexpr (qb == 0 && g == G + 1 + G / 2) lds_wait<G / 2>();
+        if constexpr (at == 0 && g == 0) lds_wait<G / 2>();
+        if constexpr (at == 0 && g == G / 2) lds_wait<W::v_before(m)>();
+        if constexpr (at == 0 && g == G + 1) lds_wait<G>();
+        if constexpr (at == 0 && g == G + 1 + G / 2) lds_wait<G / 2>();
         if constexpr (g < 2) mfma_score_init(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][0], w.neg_m[qb]);
         else if constexpr (g < G) mfma_score(s_nxt[g % 2][qb], w.opreg[g], w.qreg[qb][g / 2]);
         else if constexpr (g == G) mfma_pv(w.l_acc[qb], w.ones, p_prev[qb]);
