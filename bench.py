@@ -35,7 +35,7 @@ METRIC = "lp_attention TFLOP/s (% bf16 MFMA peak); partition+stitch GB/s (% HBM)
 HEADLINE = 3                  # dit14b-81f-720p
 LOOP = 4                      # the 50-step loop on the 81-frame 480p latent
 LOOP_STEPS = 50
-ATTENTION_SOURCE = os.path.join(ROOT, "paper_2512_07350_amd", "csrc", "lp_attention.hip")
+ATTENTION_SOURCE = os.path.join(ROOT, "paper_2512_07350_amd", "csrc", "lp_attention_kernel.h")
 
 
 def main() -> int:

@@ -5,6 +5,7 @@ next to this file so that it travels with the source tree; nothing is installed.
 """
 from __future__ import annotations
 
+import concurrent.futures
 import os
 import subprocess
 import sys
@@ -14,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "liblp_mi355x.so")
 
-SOURCES = ["lp_plan.cpp", "lp_latent.hip", "lp_attention.hip", "lp_attention_short.hip", "lp_block.hip"]
+SOURCES = ["lp_plan.cpp", "lp_latent.hip", "lp_attention.hip", "lp_attention_64.hip", "lp_attention_128.hip", "lp_attention_short.hip",
+           "lp_block.hip"]
 
 # Packed-FP32 instructions are kept off for every device translation unit.
 HOST = ["-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC, "-Wall", "-Wno-unused-function"]
@@ -33,15 +35,17 @@ def _hipcc() -> str:
 def build_library(verbose: bool = False) -> str:
     """Compile every source for gfx950 and link the shared library.  Always rebuilds."""
     hipcc = _hipcc()
-    objs = []
     obj_dir = os.path.join(HERE, "_build")
     os.makedirs(obj_dir, exist_ok=True)
-    for src in SOURCES:
+
+    def compile_one(src):
         obj = os.path.join(obj_dir, src + ".o")
         flags = DEVICE if src.endswith(".hip") else HOST
-        cmd = [hipcc, *flags, *PER_FILE.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
-        _run(cmd, verbose)
-        objs.append(obj)
+        _run([hipcc, *flags, *PER_FILE.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj], verbose)
+        return obj
+
+    with concurrent.futures.ThreadPoolExecutor(4) as pool:        # the attention kernels take minutes
+        objs = list(pool.map(compile_one, SOURCES))
     tmp = LIB + ".tmp.%d" % os.getpid()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs], verbose)
     os.replace(tmp, LIB)

@@ -1,7 +1,7 @@
 // lp_attention for short sequences and few heads.
 //
 // What bounds such a call is not the matrix pipeline but a chain: launch, first bytes of Q and K from
-// memory, one round of products after the other, results.  attention_kernel (lp_attention.hip) gives
+// memory, one round of products after the other, results.  attention_kernel (lp_attention_kernel.h) gives
 // a workgroup 256 query rows, so 200 tokens of 4 heads are four workgroups that walk all keys one
 // round after the other.  Here a workgroup takes 32 query rows of a head and its four wavefronts
 // share the KEYS: wavefront w takes the rounds w, w + 4, ... of 32 keys, each with its own
@@ -324,10 +324,10 @@ bool attention_short_launchable(int64_t n, int64_t all_heads) { return short_gro
 float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus, bool split) {
     const int64_t groups = short_groups(n, all_heads), rounds = (n + 127) / 128;
     const int64_t per_cu = (groups + cus - 1) / cus;
-    if (per_cu <= 1) return 4.3f + (head_dim == 128 ? 0.8f : 0.55f) * float(rounds);
+    if (per_cu <= 1) return head_dim == 128 ? 4.73f + 0.75f * float(rounds) : 4.274f + 0.437f * float(rounds);
     const float bytes_us = attention_bytes_us(n, all_heads, head_dim);
-    if (head_dim == 64) return 4.2f + float(per_cu) * (0.27f + (split ? 0.47f : 0.33f) * float(rounds)) + 0.4f * bytes_us;
-    return 3.7f + float((per_cu + 1) / 2) * (1.0f + (split ? 1.35f : 1.15f) * float(rounds)) + 0.8f * bytes_us;
+    if (head_dim == 64) return 4.026f + float(per_cu) * (0.26f + (split ? 0.446f : 0.328f) * float(rounds)) + 0.404f * bytes_us;
+    return 3.76f + 0.516f * float(per_cu) + float((per_cu + 1) / 2) * (split ? 1.35f : 1.066f) * float(rounds) + 0.782f * bytes_us;
 }
 
 int attention_short(const AttentionCall &c, hipStream_t stream) {

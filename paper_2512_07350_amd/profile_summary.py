@@ -135,7 +135,7 @@ def source_sha256() -> str:
     """SHA-256 of the attention kernel's source file as it is in this tree."""
     import hashlib
     here = os.path.dirname(os.path.abspath(__file__))
-    return hashlib.sha256(open(os.path.join(here, "csrc", "lp_attention.hip"), "rb").read()).hexdigest()
+    return hashlib.sha256(open(os.path.join(here, "csrc", "lp_attention_kernel.h"), "rb").read()).hexdigest()
 
 
 def counters(paths, kernel: str) -> None:
