@@ -795,8 +795,7 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
             asm volatile("" : "+v"(p_b[qb]));            // in registers from here on, not formed in front of their product
         }
 
-        // ---- the pipeline, two steps at a time; step i_end only flushes the PV product of
-        // the last round (and a step past it, if the count is odd, adds nothing)
+        // ---- the pipeline, two steps at a time; step i_end only flushes the PV product of the last round
         int i = i_begin;
         auto whole_tiles = [&](int end) {                // tiles while rounds i+1 and i+2 are whole
             for (; (i + 3) * 32 <= c.key_end && i < end; i += 2) {
@@ -825,30 +824,34 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
         whole_tiles(i_end);
         for (; i <= i_end; i += 2) {
             pipeline_step<D, QB, 0, true, CHECK>(lds0, c, i, i == i_begin, w, s_a, s_b, p_b, p_a);
-            pipeline_step<D, QB, 1, true, CHECK>(lds0, c, i + 1, false, w, s_b, s_a, p_a, p_b);
+            if (i < i_end) pipeline_step<D, QB, 1, true, CHECK>(lds0, c, i + 1, false, w, s_b, s_a, p_a, p_b);
         }
         };   // run_segment
 
         run_segment(std::false_type{});
         {
             // anything in this lane's row sums or accumulators that is not finite, or within 2^7 of
-            // not being so (partial rows are stored as bf16)?  y - y is 0 for every finite y
+            // not being so (partial rows are stored as bf16)?  As integers, the largest positive and the largest negative
+            // magnitude (an infinity and any NaN lie above every number): half an instruction each per register
             settle_acc<D, QB>(w.acc, w.l_acc, false);
-            float probe = 0.0f;
+            constexpr uint32_t kTooLarge = (127 + 121) << 23;          // 2^121
+            int32_t pos = 0;
+            uint32_t neg = 0;
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                const float yl = w.l_acc[qb][0] * 128.0f;
-                probe += yl - yl;
+            for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-                for (int mb = 0; mb < G; ++mb)
+                for (int mb = 0; mb <= G; ++mb) {
+                    const f32x4 &x = mb < G ? w.acc[mb][qb] : w.l_acc[qb];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float y = w.acc[mb][qb][r] * 128.0f;
-                        probe += y - y;
+                    for (int r = 0; r < 4; r += 2) {
+                        const uint32_t y0 = __float_as_uint(x[r]), y1 = __float_as_uint(x[r + 1]);
+                        pos = max(max(int32_t(y0), int32_t(y1)), pos);
+                        neg = max(max(y0, y1), neg);
                     }
-            }
+                }
+            const bool too_large = pos >= int32_t(kTooLarge) || neg >= (0x80000000u | kTooLarge);
             // the barrier also makes sure that every wave has left the segment's tiles
-            if (__syncthreads_or(!(probe == 0.0f))) {
+            if (__syncthreads_or(too_large)) {
                 start_tiles<D>(lds0, a, seg, c, n, stride_tok);
                 run_segment(std::true_type{});
             }
