@@ -83,11 +83,14 @@ __device__ __forceinline__ void stage_barrier() {
 
 // The tile of one workgroup: WF x WT wavefronts, each with FB x TB blocks of 16 features x 16
 // tokens, and S LDS stages of one k-tile (W rows, then x rows).  With SPLIT the wavefronts share k while they
-// form the products (product_split_k) and the blocks from then on.
-template <int WF_, int WT_, int FB_, int TB_, int S_, bool SPLIT_ = false>
+// form the products (product_split_k) and the blocks from then on; kWide: one wavefront to a SIMD (product_wide).
+enum How { kShared, kSplitK, kWide };    // product, product_split_k, product_wide
+template <int WF_, int WT_, int FB_, int TB_, int S_, How HOW_ = kShared>
 struct Tiling {
     static constexpr int WF = WF_, WT = WT_, FB = FB_, TB = TB_, S = S_;
-    static constexpr bool SPLIT = SPLIT_;
+    static constexpr How HOW = HOW_;
+    static constexpr bool SPLIT = HOW == kSplitK;
+    using Column = Tiling<WF_, WT_, FB_, 1, S_, HOW_>;                   // 16 of a wave's tokens
     static constexpr int kWaves = WF * WT, kThreads = 64 * kWaves;
     static constexpr int kF = WF * FB * 16, kT = WT * TB * 16;            // features and tokens of the tile
     static constexpr int kWBytes = kF * kRowBytes, kStage = kWBytes + kT * kRowBytes;
@@ -103,7 +106,7 @@ struct Tiling {
     // wave-wide loads (8 rows each) per wave and stage: X = x rows and the lo halves of W, Y = the hi halves
     static constexpr int kLoadsW = kF / 16 / kWaves, kLoadsX = kT / 8 / kWaves;
     static constexpr int X = kLoadsX + kLoadsW, Y = kLoadsW;
-    static_assert(kWaves % 2 == 0 && kF % (16 * kWaves) == 0 && kT % (8 * kWaves) == 0 && FB % 2 == 0, "whole loads");
+    static_assert(kWaves % 2 == 0 && kF % (16 * kWaves) == 0 && (kT % (8 * kWaves) == 0 || TB == 1) && FB % 2 == 0, "whole loads");
 };
 
 // acc[f][t] += W[f0 + ..] . x[t0 + ..]^T over all of k.
@@ -259,6 +262,142 @@ __device__ __forceinline__ void product(uint32_t lds0, const GemmArgs &a, int f0
     for (int f = 0; f < FB; ++f)
 #pragma unroll
         for (int t = 0; t < TB; ++t) asm volatile("" : "+v"(acc[f][t]));
+}
+
+// acc += the same into an accumulation register.
+__device__ __forceinline__ void mfma_acc(f32x4 &acc, const bf16x8 &a, const bf16x8 &b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// M0 for the next load (base + off), then, an instruction or more later, the load.
+__device__ __forceinline__ void set_m0(uint32_t base, uint32_t off) {
+    asm volatile("s_add_u32 m0, %0, %1" ::"s"(base), "s"(off) : "memory", "m0", "scc");
+}
+__device__ __forceinline__ void load_at_m0(const __amdgpu_buffer_rsrc_t &rsrc, uint32_t voff, uint32_t soff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
+// The same with one wavefront to a SIMD (128 features x 128 or 64 tokens each), accumulators in the accumulation registers.
+//
+// With eight wavefronts of 128 x 64 a k-tile of 256 x 256 is 192 KB read from LDS and 64 KB written to it, as many cycles of its 128
+// bytes as the products take; four of 128 x 128 read 128 KB, which is less power too.  Alone on its SIMD a wavefront keeps the
+// matrix pipeline busy if no more than 8 cycles of other instructions (two) stand between two products, so that a load is a write of
+// M0 before a product and the load behind it, and lane offsets hold what a scalar addition per load did.  Half as many
+// wavefronts fill the stages and store the tile more slowly: from 32 k-tiles on this is the faster (256 x 256 that nothing cuts: 64).
+// us, eight / four: 13230 x 5120 -> 5120 495.6 / 484.4, 15278 x 5120 -> 5120 582 / 569, 4051 x 4096 -> 1536 (256 x 128) 49.1 / 46.8;
+// 4265 x 512 -> 2048 15.4 / 17.4.  Not with the QKV epilogue, which one wavefront to a SIMD takes longer for (8192 x 2048 -> 6144
+// 158 / 168), nor for 128 x 128 (no change).
+template <typename C>
+__device__ __forceinline__ void product_wide(uint32_t lds0, const GemmArgs &a, int f0, int t0, int wave, int lane,
+                                             f32x4 (&acc)[C::FB][C::TB]) {
+    constexpr int FB = C::FB, TB = C::TB, FH = C::FH, S = C::S, W = C::kWaves;
+    const int col = lane % 16, quad = lane / 16;
+    const int fw = wave / C::WT, tw = wave % C::WT;
+    const int64_t w_rows = min(int64_t(C::kF), int64_t(a.d_out) - f0), x_rows = min(int64_t(C::kT), int64_t(a.n) - t0);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16 *>(a.w + int64_t(f0) * a.d_in), 0, int(w_rows * a.d_in * 2), 0x00020000);
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<__bf16 *>(a.x + int64_t(t0) * a.d_in), 0, int(x_rows * a.d_in * 2), 0x00020000);
+    const uint32_t row_bytes = uint32_t(a.d_in) * 2;
+    constexpr int kHalfGroups = FH * 2;
+    auto lo_group = [&](int i) { const int g = wave + i * W; return (g / kHalfGroups) * 2 * kHalfGroups + g % kHalfGroups; };
+    // load i of a stage: x rows, the lo halves of W, the hi halves; lane offsets with the group in them, the k-tile is the scalar offset
+    constexpr int N = C::X + C::Y;
+    uint32_t voff[N], dst[N];
+    {
+        const uint32_t v0 = uint32_t(lane / 8) * row_bytes + 16 * ((lane % 8) ^ swz((wave & 1) * 8 + lane / 8));
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int g = i < C::kLoadsX ? wave + i * W : i < C::X ? lo_group(i - C::kLoadsX) : lo_group(i - C::X) + kHalfGroups;
+            voff[i] = v0 + uint32_t(g) * 8 * row_bytes;
+            dst[i] = __builtin_amdgcn_readfirstlane(lds0 + (i < C::kLoadsX ? C::kWBytes : 0) + uint32_t(g) * 1024);
+        }
+    }
+    uint32_t w_addr[2], x_addr[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        w_addr[s] = lds0 + (fw * FB * 16 + col) * kRowBytes + 16 * ((4 * s + quad) ^ swz(col));
+        x_addr[s] = lds0 + C::kWBytes + (tw * TB * 16 + col) * kRowBytes + 16 * ((4 * s + quad) ^ swz(col));
+    }
+    bf16x8 lo[FH][2], hi[FH][2], xop[TB][2];
+    auto read_lo = [&](int m, int s) { lo[m][s] = lds_load<bf16x8>(w_addr[s] + m * 16 * kRowBytes); };
+    auto read_hi = [&](int m, int s) { hi[m][s] = lds_load<bf16x8>(w_addr[s] + (FH + m) * 16 * kRowBytes); };
+    auto read_x = [&](int t, int s) { xop[t][s] = lds_load<bf16x8>(x_addr[s] + t * 16 * kRowBytes); };
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            acc[f][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            asm volatile("" : "+a"(acc[f][t]));
+        }
+    const int n_kt = a.d_in / kBK;
+#pragma unroll
+    for (int p = 0; p < S; ++p)
+        if (p < n_kt)
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                set_m0(dst[i], p * C::kStage);
+                asm volatile("s_nop 0");
+                load_at_m0(i < C::kLoadsX ? x_rsrc : w_rsrc, voff[i], uint32_t(p) * kRowBytes);
+            }
+    if (n_kt >= S) stage_barrier<C::Y + (S - 1) * N>();  // the first tile's X group has landed
+    else stage_barrier<0>();
+#pragma unroll
+    for (int m = 0; m < FH; ++m) read_lo(m, 0);
+#pragma unroll
+    for (int t = 0; t < TB; ++t) read_x(t, 0);
+
+    // Products per k-step of a phase; before a phase's barrier; and the windows over which a phase's loads are spread
+    constexpr int PK = FH * TB, PRE = FH + TB + 3;
+    constexpr int kRest = 2 * PK - PRE, kEveryX = kRest / C::X > 0 ? kRest / C::X : 1, kEveryY = kRest / C::Y > 0 ? kRest / C::Y : 1;
+    static_assert(PRE < PK && kRest >= 2 * FH && C::X <= kRest && C::Y <= kRest && PK + TB <= 2 * PK, "everything has its window");
+    uint32_t cur = 0;
+    auto tile = [&](int kt, auto left_c) {
+        constexpr int LEFT = decltype(left_c)::value;
+        constexpr bool REFILL = LEFT >= S;
+        constexpr int AHEAD = REFILL ? S - 1 : LEFT;
+        const uint32_t soff = uint32_t(kt + S) * kRowBytes;
+        auto tcol = [](int m, int i) constexpr { return (m & 1) ? TB - 1 - i % TB : i % TB; };
+        // ---- phase 1: lo x x; meanwhile the rest of this tile's x and lo operands, then hi
+        static_for<0, 2 * PK>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, s = i / PK, m = (i % PK) / TB, t = tcol(m, i), j = i - PRE;
+            constexpr bool kLoad = REFILL && j >= 0 && j % kEveryX == 0 && j / kEveryX < C::X;
+            if constexpr (i == PRE) stage_barrier<AHEAD * N>();
+            if constexpr (kLoad) set_m0(dst[j / kEveryX], cur);
+            mfma_acc(acc[m][t], lo[m][s], xop[t][s]);
+            if constexpr (kLoad) load_at_m0(j / kEveryX < C::kLoadsX ? x_rsrc : w_rsrc, voff[j / kEveryX], soff);
+            if constexpr (i < FH) read_lo(i, 1);
+            else if constexpr (i < FH + TB) read_x(i - FH, 1);
+            if constexpr (j >= 0 && j < 2 * FH) read_hi(j % FH, j / FH);
+        });
+        // ---- phase 2: hi x x; meanwhile the first k-step of the next tile's lo and x operands
+        const uint32_t nxt = cur + C::kStage == C::kRing ? 0u : cur + C::kStage;
+        const uint32_t delta = nxt - cur;
+        static_for<0, 2 * PK>([&](auto ic) {
+            constexpr int i = decltype(ic)::value, s = i / PK, m = (i % PK) / TB, t = tcol(m, i), j = i - PRE;
+            constexpr bool kLoad = REFILL && j >= 0 && j % kEveryY == 0 && j / kEveryY < C::Y;
+            if constexpr (i == PRE && LEFT > 0) stage_barrier<(AHEAD - 1) * N + C::Y + (REFILL ? C::X : 0)>();
+            if constexpr (kLoad) set_m0(dst[C::X + j / kEveryY], cur);
+            mfma_acc(acc[FH + m][t], hi[m][s], xop[t][s]);
+            if constexpr (kLoad) load_at_m0(w_rsrc, voff[C::X + j / kEveryY], soff);
+            if constexpr (LEFT > 0) {
+                if constexpr (i < 2) { w_addr[i] += delta; x_addr[i] += delta; }
+                if constexpr (j >= 0 && j < FH) read_lo(j, 0);
+                if constexpr (i >= PK && i < PK + TB) read_x(i - PK, 0);      // the first k-step's have had their last product
+            }
+        });
+        cur = nxt;
+    };
+    int kt = 0;
+    for (; kt + S < n_kt; ++kt) tile(kt, std::integral_constant<int, S>{});
+    static_for<0, S>([&](auto lc) {
+        constexpr int LEFT = S - 1 - decltype(lc)::value;
+        if (kt + LEFT == n_kt - 1) tile(kt++, std::integral_constant<int, LEFT>{});
+    });
+    asm volatile("s_nop 15\n\ts_nop 7");
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int t = 0; t < TB; ++t) asm volatile("" : "+a"(acc[f][t]));
 }
 
 // The same for calls of few tiles and a long k: the four waves of a workgroup share k.
@@ -457,12 +596,29 @@ __device__ __forceinline__ void run_tile(uint32_t lds0, const GemmArgs &a, int f
     }
     f32x4 acc[FB][TB];
     if constexpr (C::SPLIT) product_split_k<C>(lds0, a, f0, t0, wave, lane, acc);
+    else if constexpr (C::HOW == kWide) product_wide<C>(lds0, a, f0, t0, wave, lane, acc);
     else product<C>(lds0, a, f0, t0, wave, lane, acc);
 
     stage_barrier<0>();                                  // the ring is free: every wave has read its last operand
     const uint32_t out_lds = lds0 + wave * (16 * FB * 32), rope_lds = lds0 + C::kOut, ss_lds = rope_lds + kMaxPairs * 16;
     const uint32_t bias_lds = ss_lds + C::kWaves * TB * 16 * 4 + wave * FB * 16 * 8, gain_lds = bias_lds + FB * 16 * 4;
     *LP_LDS_PTR(f32x2, uintptr_t(bias_lds + 4 * f_pre)) = bias_pre;
+    if constexpr (C::HOW == kWide) {                     // 16 tokens at a time, out of the accumulation registers
+        static_assert(!QKV, "lp_linear's");
+        using One = typename C::Column;
+        if (!live) return;
+        const int tok_first = t0 + (wave % C::WT) * TB * 16;
+        __bf16 *dst = a.out[0] + int64_t(tok_first) * dm + fbase;
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            if (tok_first + 16 * t >= a.n) break;
+            f32x4 y[FB][1];
+#pragma unroll
+            for (int f = 0; f < FB; ++f) y[f][0] = acc[f][t] + lds_load<f32x4>(bias_lds + 4 * (16 * f + 4 * quad));
+            store_tile<One>(out_lds, y, dst + int64_t(16 * t) * dm, dm, a.n - tok_first - 16 * t, lane);
+        }
+        return;
+    }
 #pragma unroll
     for (int f = 0; f < FB; ++f) {
         const f32x4 b4 = lds_load<f32x4>(bias_lds + 4 * (16 * f + 4 * quad));
@@ -520,7 +676,7 @@ __device__ __forceinline__ void run_tile(uint32_t lds0, const GemmArgs &a, int f
 // P's tiles are ordered in panels of kPanel token tiles, feature tile by feature tile inside a
 // panel: the workgroups an XCD runs at a time share their W and x rows through its L2.
 template <bool QKV, int HD, typename P, typename R>
-__global__ __launch_bounds__(P::kThreads, P::SPLIT ? 1 : 2) void gemm_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(P::kThreads, P::HOW == kShared ? 2 : 1) void gemm_kernel(const GemmArgs a) {
     static_assert(P::kThreads == R::kThreads && P::kF % R::kF == 0 && P::kT % R::kT == 0, "R cuts P");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const uint32_t lds0 = uint32_t(uintptr_t(LP_LDS_PTR(unsigned char, smem)));
@@ -635,7 +791,12 @@ using Tile256x128 = Tiling<2, 4, 8, 2, 3>;
 using Tile128x128 = Tiling<2, 4, 4, 2, 4>;
 using Tile128x64 = Tiling<4, 2, 2, 2, 5>;
 using Tile64x64 = Tiling<2, 2, 2, 2, 5>;
-using Split64x32 = Tiling<2, 2, 2, 1, 8, true>;
+// The same sizes with four wavefronts, for lp_linear with a long k
+using Wide256x256 = Tiling<2, 2, 8, 8, 2, kWide>;
+using Wide256x128 = Tiling<2, 2, 8, 4, 3, kWide>;
+using Four128x128 = Tiling<2, 2, 4, 4, 4>;
+using Four128x64 = Tiling<2, 2, 4, 2, 5>;
+using Split64x32 = Tiling<2, 2, 2, 1, 8, kSplitK>;
 
 // How a call is cut.  A round is one tile on every compute unit (two of 64 x 64).  Per round, in us, fitted to 4004 calls (3133
 // products of 1 .. 200000 tokens, d_in 64 .. 13824, d_out 128 .. 13824, and 871 QKV projections), each timed on every tiling,
@@ -735,12 +896,26 @@ int launch_tiles(GemmArgs a, int64_t whole, hipStream_t stream) {
 // head_dim 0: lp_linear; a head of 128 does not fit the smallest tiles' features
 constexpr bool small_tilings(int head_dim) { return head_dim <= 64; }
 
+// Whether lp_linear runs a plan's tiles of 256 features with four wavefronts: see product_wide.
+bool four_waves(const Plan &p, int32_t d_in) { return p.tile <= 1 && d_in / kBK >= (p.tile == 0 && p.cut == kCutNone ? 64 : 32); }
+
 template <bool QKV, int HD>
 int launch_gemm(GemmArgs a, hipStream_t stream) {
     constexpr bool kSmall = small_tilings(QKV ? HD : 0);
     const int cus = lp::device_compute_units();
     if (cus <= 0) return LP_ERR_HIP;
     const Plan p = pick_plan(a.n, a.d_in, a.d_out, kSmall, cus);
+    if constexpr (!QKV) {
+        if (four_waves(p, a.d_in)) {
+            switch (p.tile * 8 + p.cut + 1) {
+                case 0 * 8: return launch_tiles<QKV, HD, Wide256x256, Wide256x256>(a, p.whole, stream);
+                case 0 * 8 + 2: return launch_tiles<QKV, HD, Wide256x256, Wide256x128>(a, p.whole, stream);
+                case 0 * 8 + 3: return launch_tiles<QKV, HD, Wide256x256, Four128x128>(a, p.whole, stream);
+                case 0 * 8 + 4: return launch_tiles<QKV, HD, Wide256x256, Four128x64>(a, p.whole, stream);
+                default: return launch_tiles<QKV, HD, Wide256x128, Wide256x128>(a, p.whole, stream);
+            }
+        }
+    }
     switch (p.tile * 8 + p.cut + 1) {
         case 0 * 8 + 2: return launch_tiles<QKV, HD, Tile256x256, Tile256x128>(a, p.whole, stream);
         case 0 * 8 + 3: return launch_tiles<QKV, HD, Tile256x256, Tile128x128>(a, p.whole, stream);
@@ -778,7 +953,7 @@ extern "C" int lp_internal_gemm_way(int64_t n, int32_t d_in, int32_t d_out, int3
     way[2] = p.cut < 0 ? 0 : r.f;
     way[3] = p.cut < 0 ? 0 : r.t;
     way[4] = p.whole + (tiles - p.whole) * (c.f / r.f) * (c.t / r.t);
-    way[5] = c.threads;
+    way[5] = head_dim == 0 && four_waves(p, d_in) ? Wide256x256::kThreads : c.threads;
     return LP_OK;
 }
 
