@@ -185,8 +185,8 @@ int lp_reconstruct_guided_step_partition(const lp_plan *plan, const float *cond_
  * over the compute units whatever n_tokens and heads are (partial results of a
  * query tile that two workgroups share pass through the workspace and a second
  * small kernel merges them) wherever that is faster; with NULL (or too small a
- * workspace) a 256-row query tile of a head is always one workgroup's, which
- * leaves compute units idle when their number does not divide the tile count.
+ * workspace) a query tile (256, 192 or 128 rows of a head) is always one
+ * workgroup's, which leaves compute units idle in the last round.
  * Two calls that overlap in time must not share a workspace.
  * Short calls (a few hundred tokens, or a few heads) run a kernel of their own
  * that needs no workspace.
@@ -220,7 +220,7 @@ int lp_attention(const void *q, const void *k, const void *v, void *o, int64_t n
  * batch > 1: the items one after the other (stride_batch at least the extent of one item), or,
  * token-major, the items of a token side by side (stride_tok >= batch * stride_batch,
  * stride_batch >= heads * stride_head); stride_batch a multiple of 8.  One launch deals all
- * batch * heads * ceil(n_tokens / 256) query tiles over the compute units together, which for
+ * query tiles of all batch * heads heads over the compute units together, which for
  * sequences of a few thousand tokens is measurably faster than one call per item.
  */
 int lp_attention_batch(const void *q, const void *k, const void *v, void *o, int32_t batch, int64_t n_tokens,

@@ -17,8 +17,8 @@
 // consecutive keys, V read transposed); the products are builtins here: with 32 rows a wavefront
 // needs 190 registers at head_dim 128 (126 at 64) and two (four) workgroups share a compute unit.
 //
-// Measured (us, attention_kernel / this): 200 tokens, 4 heads of 64: 9.9 / 4.5; 333, 3 of 128: 17.8 /
-// 6.6; 1000, 12 of 128: 32 / 16.4; 2000, 12 of 128: 43 / 42; 3000, 12 of 128: 67 / 86.  One stage per
+// Measured (us, attention_kernel in its best tiles / this): 200 tokens, 4 heads of 64: 7.8 / 4.8; 333, 3 of 128: 11.5 /
+// 7.1; 1000, 12 of 128: 18.2 / 15.4; 2000, 12 of 128: 29 / 41; 3000, 12 of 128: 53 / 85.  One stage per
 // wavefront, whose K half is refilled once the scores are formed and whose V half after the PV
 // product, and two workgroups per compute unit are faster than two whole stages and one workgroup
 // (1000 tokens, 12 heads of 128: 16.4 / 23.1); eight wavefronts per workgroup 20.9; 64 rows 22.8.
