@@ -12,6 +12,9 @@ from tests import routes
 
 pytestmark = pytest.mark.gpu
 
+# what routes.attention_tiles says of a call: 256-row query tiles, those of the last round cut into ranges and merged; or none cut
+CUT, WHOLE = (256, 0, True), (256, 0, False)
+
 
 @pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 @pytest.mark.parametrize("hd", [64, 128])
@@ -27,8 +30,8 @@ def test_small_full_oracle(n, hd, balanced):
 
 @pytest.mark.parametrize("n,heads,hd", [(3000, 1, 128), (2048, 2, 128), (700, 5, 64), (5000, 7, 64), (64, 40, 128)])
 def test_work_split_across_workgroups(n, heads, hd):
-    """Few (query tile, head) units, with and without scratch memory, whichever kernel that runs (5000 x 7 is cut
-    and merged, see also test_query_tiles_cut_into_parts): must agree with the oracle and with each other."""
+    """Few (query tile, head) units, with and without scratch memory, whichever kernel that runs (for calls that are cut
+    and merged see test_query_tiles_cut_into_parts): must agree with the oracle and with each other."""
     from tests import gpu_util as g
     q, k, v = synth.qkv_bf16(9000 + n + heads, n, heads, hd)
     rows = synth.sample_rows(n, 160, seed=n, tile=256)
@@ -309,27 +312,31 @@ def test_scores_far_above_the_first_round(balanced, hd, profile):
 
 
 
-# Lengths that run the kernel of 256-row query tiles at either head dim, with 104 tiles left after a round: cut with scratch
-# memory, whole without.  33 .. 36 key tiles (four are unrolled), the last of 1, 2, 31 .. 33, 63 or 64 keys.
-@pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
+# Lengths whose last key tile holds 1, 2, 31 .. 33, 63 or 64 keys (four tiles are unrolled): 33 .. 36 key tiles of 40 heads, in
+# 192-row query tiles; 66 .. 69 of 2 heads, cut with scratch memory into about seven ranges a query tile.
+EDGES = (2049, 2080, 2081, 2112, 2113, 2145, 2176, 2178, 2239, 2240, 2271, 2304)
+
+
 @pytest.mark.parametrize("hd", [64, 128])
-@pytest.mark.parametrize("n", [2049, 2080, 2081, 2112, 2113, 2145, 2176, 2178, 2239, 2240, 2271, 2304])
-def test_long_kernel_at_tile_and_round_edges(n, hd, balanced):
+@pytest.mark.parametrize("n,heads,tiles", [(n + 2112, 2, CUT) for n in EDGES] + [(n, 40, (192, 0, False)) for n in EDGES])
+def test_long_kernel_at_tile_and_round_edges(n, heads, tiles, hd):
     from tests import gpu_util as g
-    assert routes.attention(n, 40, hd, balanced) == ("cut" if balanced else "whole")
-    q, k, v = synth.qkv_bf16(4500 + 2 * n + hd, n, 40, hd)
+    balanced = tiles == CUT
+    assert routes.attention_tiles(n, heads, hd, balanced) == tiles
+    q, k, v = synth.qkv_bf16(4500 + 2 * n + hd, n, heads, hd)
     got = g.hip_attention(q, k, v, balanced=balanced)
-    rows = synth.sample_rows(n, 48, seed=n, tile=256)
+    rows = synth.sample_rows(n, 48, seed=n, tile=tiles[0])
     g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "n=%d hd=%d" % (n, hd))
     assert np.all(np.isfinite(got))
 
 
-# 40 heads: the lengths around which a call changes from one kernel to the other
+# 40 heads: a round of 256-row query tiles (1536 tokens) and what follows it, and around the lengths where smaller tiles are one more to a head
 @pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("n", [1536, 1537, 1567, 1599, 1600, 1601, 1632, 1791, 1793, 2047])
-def test_lengths_around_the_change_of_kernels(n, hd, balanced):
+def test_lengths_around_the_change_of_tiles(n, hd, balanced):
     from tests import gpu_util as g
+    assert routes.attention_tiles(n, 40, hd, balanced) == (WHOLE if n == 1536 else (192, 0, False))
     q, k, v = synth.qkv_bf16(4500 + 2 * n + hd, n, 40, hd)
     got = g.hip_attention(q, k, v, balanced=balanced)
     rows = synth.sample_rows(n, 48, seed=n, tile=256)
@@ -337,18 +344,21 @@ def test_lengths_around_the_change_of_kernels(n, hd, balanced):
     assert np.all(np.isfinite(got))
 
 
-# The shortest calls that run the kernel of 256-row query tiles (hundreds of heads): 3 tiles and more, below, at and above the 352 and 608 keys from
-# which four tiles, and four more, are unrolled.
-@pytest.mark.parametrize("n,hd", [(n, 128) for n in (129, 160, 161, 192, 193, 255, 256, 321, 351, 352, 353, 384, 416, 449, 511, 575, 607, 608, 609, 640)]
-                         + [(n, 64) for n in (225, 255, 256, 385, 415, 416, 447, 448, 449, 480, 511, 512, 609, 640, 641, 673, 704, 705)])
-def test_long_kernel_on_few_tiles(n, hd):
+# The shortest calls that attention_kernel runs (hundreds of heads): 3 tiles and more, below, at and above the 352 and 608 keys from
+# which four tiles, and four more, are unrolled; rows of the query tiles that each runs in.
+FEW_TILES = {128: {192: (129, 160, 161, 192, 321, 351, 352, 353, 384, 575), 256: (193, 255, 256, 416, 449, 511), 128: (607, 608, 609, 640)},
+             64: {256: (225, 255, 256, 385, 415, 416, 447, 448, 449, 480, 511, 512, 641, 673, 704, 705), 128: (609, 640)}}
+
+
+@pytest.mark.parametrize("n,hd,rows", [(n, hd, rows) for hd in FEW_TILES for rows in FEW_TILES[hd] for n in FEW_TILES[hd][rows]])
+def test_long_kernel_on_few_tiles(n, hd, rows):
     from tests import gpu_util as g
     heads = 256
-    assert routes.attention(n, heads, hd) == routes.attention(n, heads, hd, scratch=False) == "whole"
+    assert routes.attention_tiles(n, heads, hd) == routes.attention_tiles(n, heads, hd, scratch=False) == (rows, 0, False)
     q, k, v = synth.qkv_bf16(4600 + 2 * n + hd, n, heads, hd)
     got = g.hip_attention(q, k, v)
-    rows = synth.sample_rows(n, 24, seed=n, tile=256)
-    g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "n=%d hd=%d" % (n, hd))
+    picked = synth.sample_rows(n, 24, seed=n, tile=rows)
+    g.assert_attention_close(got[picked], orc.attention(q, k, v, rows=picked), "n=%d hd=%d" % (n, hd))
     assert np.all(np.isfinite(got))
 
 
@@ -364,11 +374,13 @@ def test_short_kernel_at_round_edges(n, hd):
 
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("profile", ["ramp", "cliff"])
-@pytest.mark.parametrize("n,heads", [(1500, 40), (3000, 12)], ids=["whole tiles", "shared tiles"])
-def test_long_kernel_scores_far_above_the_first_round(n, heads, profile, hd):
-    """test_scores_far_above_the_first_round at lengths that run the kernel of 256-row query tiles."""
+@pytest.mark.parametrize("n,heads,tiles", [(1500, 40, WHOLE), (5000, 2, CUT), (2000, 70, CUT), (3000, 12, (192, 0, False))],
+                         ids=["whole tiles", "seven parts a tile", "parts behind two rounds of whole tiles", "192 rows"])
+def test_long_kernel_scores_far_above_the_first_round(n, heads, tiles, profile, hd):
+    """test_scores_far_above_the_first_round in attention_kernel: a part of a query tile that holds the first keys is walked again
+    with a running maximum, and merged with parts whose maximum lies 2^256 above its first one."""
     from tests import gpu_util as g
-    assert routes.attention(n, heads, hd) == ("whole" if heads == 40 else "cut")
+    assert routes.attention_tiles(n, heads, hd) == tiles
     rng = np.random.default_rng(4321)
     base = np.where(rng.random((heads, hd)) < 0.5, -1.0, 1.0).astype(np.float32)
     level = np.where(np.arange(n) < 40, 0.0, 32.0) if profile == "cliff" else np.minimum(np.floor(np.arange(n) / 32.0), 32.0)
@@ -383,17 +395,25 @@ def test_long_kernel_scores_far_above_the_first_round(n, heads, profile, hd):
     assert np.all(np.isfinite(got))
 
 
-# 256-row query tiles (units) on 256 compute units: everybody one or two units, and 48, 64, 104, 144, 194 or 224 units
-# left, taken whole or (with scratch memory, up to 144 of them) cut into ranges that start and end inside a unit
+# Query tiles (units) on 256 compute units, more than one to each.  256 rows: everybody one, two or three, and 16, 64, 88, 48, 112 or 72 units
+# left, with scratch memory cut into ranges that start and end inside a unit.  Then what takes the calls of other numbers
+# left, which scratch memory makes no difference to.
+FINE, LAST = (192, 0, False), (256, 192, False)
+
+
 @pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
-@pytest.mark.parametrize("n,heads,hd", [(1795, 40, 128), (2305, 40, 128), (3329, 40, 128), (2999, 40, 128), (700, 150, 128),
-                                        (2049, 40, 64), (2305, 40, 64), (3329, 40, 64), (2999, 40, 64), (700, 150, 64)])
-def test_units_left_over_after_whole_rounds(n, heads, hd, balanced):
+@pytest.mark.parametrize("n,heads,hd,cut,plain", [(n, heads, hd, CUT, plain) for n, heads, plain in [
+    (4104, 16, FINE), (5008, 16, FINE), (3700, 40, LAST), (2000, 70, LAST), (5400, 40, LAST), (3000, 70, LAST)] for hd in (64, 128)]
+    + [(n, heads, hd, t, t) for n, heads, hd, t in [
+        (1795, 40, 128, FINE), (2305, 40, 128, (128, 0, False)), (3329, 40, 128, FINE), (2999, 40, 128, WHOLE), (700, 150, 128, WHOLE),
+        (2049, 40, 64, FINE), (2305, 40, 64, LAST), (3329, 40, 64, FINE), (2999, 40, 64, WHOLE), (700, 150, 64, WHOLE)]])
+def test_units_left_over_after_whole_rounds(n, heads, hd, cut, plain, balanced):
     from tests import gpu_util as g
-    assert routes.attention(n, heads, hd, balanced) == ("cut" if balanced and n not in (2999, 700) else "whole")
+    tiles = cut if balanced else plain
+    assert routes.attention_tiles(n, heads, hd, balanced) == tiles
     q, k, v = synth.qkv_bf16(4900 + n + heads, n, heads, hd)
     got = g.hip_attention(q, k, v, balanced=balanced)
-    rows = synth.sample_rows(n, 24, seed=n, tile=256)
+    rows = synth.sample_rows(n, 24, seed=n, tile=tiles[0])
     g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "n=%d heads=%d hd=%d" % (n, heads, hd))
     assert np.all(np.isfinite(got))
 
@@ -416,8 +436,9 @@ def test_short_kernel_keys_with_score_minus_infinity(dead, hd):
     g.assert_attention_close(g.hip_attention(q, k, v), want, "dead %s" % (dead,))
 
 
-# Calls of twelve heads in all that are cut with scratch memory and whole without: padded and head-major layouts, items one
-# after the other and side by side.  Every gap of q, k, v and o holds NaN: nothing is read from it or written to it.
+# Sixteen heads in all: 288 query tiles of 256 rows, 32 of them left after a round and cut into nine parts each with scratch memory, or 192-row
+# tiles without: padded and head-major layouts, items one after the other and side by side.  Every gap of q, k, v and o holds
+# NaN: nothing is read from it or written to it.
 @pytest.mark.parametrize("balanced", [True, False], ids=["cut", "whole"])
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("layout", ["token-padded", "head-major", "head-major-padded", "items-padded", "items-side-by-side"])
@@ -425,11 +446,11 @@ def test_long_kernel_layouts(layout, hd, balanced):
     from tests import gpu_util as g
     import torch
     from paper_2512_07350_amd import binding as lp
-    n = 2999
+    n = 4500
     batch = 2 if layout.startswith("items") else 1
-    heads = 12 // batch
+    heads = 16 // batch
     for split in (False, True):
-        assert routes.attention(n, 12, hd, balanced, split=split) == ("cut" if balanced else "whole")
+        assert routes.attention_tiles(n, 16, hd, balanced, split=split) == (CUT if balanced else (192, 0, False))
     if layout == "token-padded":
         stride_head, stride_batch = hd + 8, 0
         stride_tok = heads * stride_head + 24
@@ -471,12 +492,13 @@ def test_long_kernel_layouts(layout, hd, balanced):
     assert np.all(np.isnan(out)), "wrote outside its rows"
 
 
-# The parts of a query tile: one tile of few heads in about ten parts each, up to tiles in two
-@pytest.mark.parametrize("n,heads,hd", [(5000, 1, 128), (5000, 2, 64), (7410, 2, 128), (3329, 5, 128), (5000, 7, 128), (5000, 7, 64), (2721, 12, 64)])
+# The parts of a query tile: few heads, tiles in about ten parts each, down to two or three (112 tiles left on 256 compute units)
+@pytest.mark.parametrize("n,heads,hd", [(5000, 1, 128), (5000, 2, 64), (7410, 2, 128), (4800, 4, 128), (4800, 4, 64), (5400, 12, 64), (3500, 20, 128),
+                                        (3700, 40, 64), (5400, 40, 128)])
 def test_query_tiles_cut_into_parts(n, heads, hd):
     """Cut and merged against the oracle and against a call without scratch memory."""
     from tests import gpu_util as g
-    assert routes.attention(n, heads, hd) == "cut" and routes.attention(n, heads, hd, scratch=False) != "cut"
+    assert routes.attention_tiles(n, heads, hd) == CUT and not routes.attention_tiles(n, heads, hd, scratch=False).cut
     q, k, v = synth.qkv_bf16(9100 + n + heads, n, heads, hd)
     rows = synth.sample_rows(n, 160, seed=n, tile=256)
     want = orc.attention(q, k, v, rows=rows)
@@ -487,26 +509,26 @@ def test_query_tiles_cut_into_parts(n, heads, hd):
     assert np.max(np.abs(cut - plain)) <= 2e-2
 
 
-@pytest.mark.parametrize("balanced", [True, False], ids=["cut", "whole"])
+@pytest.mark.parametrize("n,heads,tiles", [(5000, 2, CUT), (2000, 70, CUT), (1500, 40, WHOLE), (3000, 12, (192, 0, False))],
+                         ids=["seven parts a tile", "parts behind two rounds of whole tiles", "whole tiles", "192 rows"])
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("order", ["rising", "falling"])
-def test_long_kernel_scores_that_keep_rising(order, hd, balanced):
-    """test_scores_that_keep_rising_along_the_keys in the kernel of 256-row query tiles: about half a log2 unit a
-    round, so that a tile's parts have maxima far apart and the first round's lies 47 units below the last one's."""
+def test_long_kernel_scores_that_keep_rising(order, hd, n, heads, tiles):
+    """test_scores_that_keep_rising_along_the_keys in attention_kernel: the first round's maximum lies 47 log2 units below the
+    last one's, so that the parts of a tile have maxima 7 (seven parts) and more units apart."""
     from tests import gpu_util as g
-    n, heads = 3000, 12
-    assert routes.attention(n, heads, hd, balanced) == ("cut" if balanced else "whole")
+    assert routes.attention_tiles(n, heads, hd) == tiles
     rng = np.random.default_rng(97)
     base = rng.standard_normal((heads, hd)).astype(np.float32)
     base /= np.linalg.norm(base, axis=1, keepdims=True)
     qf = np.broadcast_to(base[None] * np.float32(np.sqrt(hd)) * 4.0, (n, heads, hd)) + 0.05 * rng.standard_normal((n, heads, hd)).astype(np.float32)
-    ramp = (np.arange(n, dtype=np.float32) / 32.0 * 0.0875)[:, None, None]
+    ramp = (np.arange(n, dtype=np.float32) / n * 8.2)[:, None, None]            # 4 x 8.2 / ln 2 = 47 log2 units
     kf = base[None] * ramp + 0.05 * rng.standard_normal((n, heads, hd)).astype(np.float32)
     vf = rng.standard_normal((n, heads, hd)).astype(np.float32)
     q, k, v = (synth.f32_to_bf16_bits(a) for a in (qf, kf, vf))
     if order == "falling":
         k, v = k[::-1].copy(), v[::-1].copy()
-    got = g.hip_attention(q, k, v, balanced=balanced)
+    got = g.hip_attention(q, k, v)
     rows = synth.sample_rows(n, 64, seed=hd, tile=256)
     g.assert_attention_close(got[rows], orc.attention(q, k, v, rows=rows), "%s scores" % order)
     assert np.all(np.isfinite(got))
