@@ -40,15 +40,17 @@ def test_static_scratch_two_calls_second_smaller():
 
 
 @pytest.mark.parametrize("calls", [
-    [(3000, 12, 128), (1500, 12, 128), (5000, 1, 128)],      # 144 and 72 query tiles for 256 compute units; 20, each in about ten parts
-    [(2305, 40, 64), (3000, 12, 64), (5000, 2, 64)],         # 144 tiles left after a round of whole ones; 144; 40
-    [(5000, 7, 64), (1500, 12, 128)],                        # the slots of another head_dim lie elsewhere in the array
-], ids=["128", "64", "64 then 128"])
+    [(4500, 16, 128), (7410, 2, 128), (5000, 1, 128)],       # query tiles cut over 256 compute units: 32 left after a round; 58; 20, each in about ten parts
+    [(3700, 40, 64), (4800, 4, 64), (5000, 2, 64)],          # 88 left after two rounds; 76; 40
+    [(4800, 4, 64), (5000, 1, 128)],                         # the slots of the other head_dim lie elsewhere in the array
+    [(7410, 2, 128), (5000, 2, 64)],
+], ids=["128", "64", "64 then 128", "128 then 64"])
 def test_static_scratch_carries_the_parts_of_shared_query_tiles(calls):
     """Calls whose query tiles are cut: every one finds the slots as the larger call before it left them."""
     from tests import gpu_util as g
+    for n, heads, hd in calls:
+        assert routes.attention_tiles(n, heads, hd).cut
     for i, (n, heads, hd) in enumerate(calls):
-        assert routes.attention(n, heads, hd, scratch=True) == "cut"
         q, k, v = synth.qkv_bf16(820 + i + n + hd, n, heads, hd)
         got = _static(q, k, v)
         ref = g.hip_attention(q, k, v, balanced=True)
