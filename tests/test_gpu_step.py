@@ -79,17 +79,21 @@ def test_step_replays_from_a_captured_graph():
     q, k, v = (g.to_dev_bf16(a) for a in synth.qkv_bf16(3, n, heads, hd))
     o = torch.empty_like(q)
     ws, ws_bytes = g.workspace(hd)
-    # a second, larger call whose query tiles are shared between workgroups (workspace + merge kernel)
-    n2, heads2, hd2 = 1500, 12, 128
-    assert routes.attention(n, heads, hd) == "short" and routes.attention(n2, heads2, hd2) == "cut"
+    # a second call whose query tiles are shared between workgroups (workspace + merge kernel), and a third in whole tiles of 128 rows
+    n2, heads2, hd2 = 5000, 1, 128
+    n3, heads3, hd3 = 1500, 12, 128
+    assert routes.attention_tiles(n, heads, hd).rows == 0 and routes.attention_tiles(n2, heads2, hd2).cut
+    assert routes.attention_tiles(n3, heads3, hd3) == (128, 0, False)
     q2, k2, v2 = (g.to_dev_bf16(a) for a in synth.qkv_bf16(4, n2, heads2, hd2))
-    o2 = torch.empty_like(q2)
+    q3, k3, v3 = (g.to_dev_bf16(a) for a in synth.qkv_bf16(5, n3, heads3, hd3))
+    o2, o3 = torch.empty_like(q2), torch.empty_like(q3)
     ws2, ws2_bytes = g.workspace(hd2)
 
     def step(stream):
         lp.lp_partition(plan, zd, subs, stream)
         lp.lp_attention(q, k, v, o, n, heads, hd, heads * hd, hd, 0.0, ws, ws_bytes, stream)
         lp.lp_attention(q2, k2, v2, o2, n2, heads2, hd2, heads2 * hd2, hd2, 0.0, ws2, ws2_bytes, stream)
+        lp.lp_attention(q3, k3, v3, o3, n3, heads3, hd3, heads3 * hd3, hd3, 0.0, ws2, ws2_bytes, stream)
         lp.lp_reconstruct_guided_step(plan, subs, uncond, 2.0, zd, 1.0, -0.25, out, stream)
 
     step(g.stream())                      # eager warm-up: one-time function attributes are set here
@@ -101,13 +105,14 @@ def test_step_replays_from_a_captured_graph():
         zd.copy_(torch.from_numpy(synth.latent(10 + rep, w.latent)))
         q.copy_(g.to_dev_bf16(synth.qkv_bf16(20 + rep, n, heads, hd)[0]))
         k2.copy_(g.to_dev_bf16(synth.qkv_bf16(30 + rep, n2, heads2, hd2)[1]))
-        for t in (out, o, o2, subs):
+        k3.copy_(g.to_dev_bf16(synth.qkv_bf16(40 + rep, n3, heads3, hd3)[1]))
+        for t in (out, o, o2, o3, subs):
             t.fill_(float("nan"))
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
-        got_out, got_o, got_o2, got_subs = out.clone(), o.clone(), o2.clone(), subs.clone()
-        for t in (out, o, o2, subs):
+        got_out, got_o, got_o2, got_o3, got_subs = out.clone(), o.clone(), o2.clone(), o3.clone(), subs.clone()
+        for t in (out, o, o2, o3, subs):
             t.fill_(float("nan"))
         step(g.stream())
         torch.cuda.synchronize()
@@ -115,8 +120,13 @@ def test_step_replays_from_a_captured_graph():
         assert torch.equal(got_out, out), rep
         assert torch.equal(got_o.view(torch.int16), o.view(torch.int16)), rep
         assert torch.equal(got_o2.view(torch.int16), o2.view(torch.int16)), rep
-        assert not torch.isnan(o2.float()).any()
-    # and the last eager result is the oracle's
+        assert torch.equal(got_o3.view(torch.int16), o3.view(torch.int16)), rep
+        assert not torch.isnan(o2.float()).any() and not torch.isnan(o3.float()).any()
+    # and the last eager results are the oracle's
+    for got, args in ((o2, (q2, k2, v2)), (o3, (q3, k3, v3))):
+        rows = synth.sample_rows(got.shape[0], 48, seed=5, tile=256)
+        bits = [t.view(torch.int16).cpu().numpy().view(np.uint16) for t in args]
+        g.assert_attention_close(g.from_dev_bf16(got)[rows], orc.attention(*bits, rows=rows), "replayed call")
     ref_plan = orc.plan(w.latent, w.patch, w.K, dim, **w.overlap_args())
     z_h = zd.cpu().numpy()
     want = orc.guided_step(ref_plan, orc.partition(ref_plan, z_h), uncond.cpu().numpy(), 2.0, z_h, 1.0, -0.25)
