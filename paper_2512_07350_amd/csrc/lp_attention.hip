@@ -120,29 +120,19 @@ Deal deal_finer(int head_dim, int64_t n, int all_heads, uint32_t cus, const Deal
     return best;
 }
 
-// Which way a call goes: `way` is the cheaper of the short kernel, where its grid is one that can be launched, and 256-row
-// units; smaller units take the call from either where they are cheaper still (`finer`).
+// What runs: the short kernel, or units as `deal` says.
 struct Route {
-    lp::AttentionWay way;
-    bool finer;
+    bool short_kernel;
+    bool cut;            // units of the last round are shared and merged
     Deal deal;
 };
 
+// The cheapest of the short kernel, where its grid is one that can be launched, and units of 256 rows, whole or cut, and of fewer.
 Route pick_route(int head_dim, int64_t n, int all_heads, int cus, bool scratch, bool split) {
     Route r;
-    r.deal = deal_large(head_dim, n, all_heads, uint32_t(cus), scratch);
-    r.way = r.deal.sharers != r.deal.shared ? lp::kAttentionCut : lp::kAttentionWhole;
-    float us = r.deal.us;
-    if (lp::attention_short_launchable(n, all_heads)) {
-        const float short_us = lp::attention_short_us(n, all_heads, head_dim, cus, split);
-        if (short_us < us) {
-            r.way = lp::kAttentionShort;
-            us = short_us;
-        }
-    }
-    const Deal finer = deal_finer(head_dim, n, all_heads, uint32_t(cus), r.deal);
-    r.finer = (finer.qb != kMostQB || finer.tail != 0) && finer.us < us;
-    if (r.finer) r.deal = finer;
+    r.deal = deal_finer(head_dim, n, all_heads, uint32_t(cus), deal_large(head_dim, n, all_heads, uint32_t(cus), scratch));
+    r.short_kernel = lp::attention_short_launchable(n, all_heads) && lp::attention_short_us(n, all_heads, head_dim, cus, split) < r.deal.us;
+    r.cut = !r.short_kernel && r.deal.sharers != r.deal.shared;
     return r;
 }
 
@@ -166,10 +156,9 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     const Route r = pick_route(D, a.n, heads, cus, scratch, split);
     const Deal &d = r.deal;
     // short calls go to attention_short_kernel, which needs no scratch memory
-    if (r.way == lp::kAttentionShort && !r.finer)
+    if (r.short_kernel)
         return lp::attention_short({a.q, a.k, a.v, a.o, a.stride_tok, a.stride_head, a.stride_batch, a.heads, heads, D, a.n, a.scale_log2e}, stream);
-    const bool cut = r.way == lp::kAttentionCut && !r.finer;
-    a.ws = cut ? static_cast<float *>(workspace) : nullptr;
+    a.ws = r.cut ? static_cast<float *>(workspace) : nullptr;
     a.n_qtiles = (a.n + unit_rows(d.qb) - 1) / unit_rows(d.qb);
     if (d.tail != 0) {                      // d.shared of these, behind the rounds
         const int large = int(d.rounds * d.wgs);
@@ -181,7 +170,7 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
     }
     a.shared_units = d.tail != 0 ? 0 : int(d.shared);
     a.whole_rounds = int(d.rounds);
-    a.unit_cost = tpu + (cut ? kBoundaryTiles : 0);
+    a.unit_cost = tpu + (r.cut ? kBoundaryTiles : 0);
     a.shared_work = uint32_t(a.shared_units) * a.unit_cost;
     a.shared_wgs = d.tail != 0 ? 0 : d.sharers;
     return (D == 128 ? lp::attention_tiles_128 : lp::attention_tiles_64)(a, d.qb, d.tail, d.wgs, dev, stream);
@@ -189,16 +178,11 @@ int launch(AttnParams a, int heads, void *workspace, int64_t workspace_bytes, hi
 
 }  // namespace
 
-extern "C" int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch, int32_t split) {
-    return pick_route(head_dim, n, all_heads, cus, scratch != 0, split != 0).way;
-}
-
 extern "C" int lp_internal_attention_tiles(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch, int32_t split, int32_t tiles[3]) {
     const Route r = pick_route(head_dim, n, all_heads, cus, scratch != 0, split != 0);
-    const bool is_short = r.way == lp::kAttentionShort && !r.finer;
-    tiles[0] = is_short ? 0 : unit_rows(r.deal.qb);
-    tiles[1] = is_short ? 0 : unit_rows(r.deal.tail);
-    tiles[2] = r.way == lp::kAttentionCut && !r.finer;
+    tiles[0] = r.short_kernel ? 0 : unit_rows(r.deal.qb);
+    tiles[1] = r.short_kernel ? 0 : unit_rows(r.deal.tail);
+    tiles[2] = r.cut;
     return LP_OK;
 }
 

@@ -26,19 +26,13 @@ void set_last_hip_error(int err);
 
 // A launch has at most this many threads (a dispatch states its grid as 32-bit thread counts).
 constexpr int64_t kMaxLaunchThreads = (int64_t(1) << 32) - 1;
-
-// The ways an attention call can go: the kernel whose wavefronts share the keys, or attention_kernel with 256-row query tiles, every
-// one whole, or with the tiles of the last round cut into ranges and merged.  Smaller tiles of attention_kernel, whole, take a call
-// from any of these where they are faster.
-enum AttentionWay { kAttentionShort, kAttentionWhole, kAttentionCut };
 }
 
 // Which way a call of these sizes goes on a device of `cus` compute units.  Host arithmetic for the tests (a
 // test of one kernel states that its sizes run that kernel); not part of the library's interface.
 extern "C" {
-// an AttentionWay: the cheapest of the three, before smaller tiles are looked at
-int lp_internal_attention_way(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch, int32_t split);
-// what runs.  tiles: query rows of attention_kernel's tiles (0: the short kernel), those of its last round (0: the same), 1 if it is cut
+// tiles: query rows of attention_kernel's tiles (0: the short kernel, whose wavefronts share the keys), those of its last round (0: the
+// same), 1 if the tiles of the last round are cut into ranges and merged
 int lp_internal_attention_tiles(int64_t n, int32_t all_heads, int32_t head_dim, int32_t cus, int32_t scratch, int32_t split, int32_t tiles[3]);
 // 1 if the rows of K or V lie split over cache lines (`split` above; addresses in bytes, strides in elements)
 int lp_internal_attention_rows_split(uint64_t k, uint64_t v, int64_t stride_tok, int64_t stride_head, int64_t stride_batch, int32_t heads,

@@ -4,8 +4,6 @@ from collections import namedtuple
 
 from paper_2512_07350_amd import binding as lp
 
-WAYS = ("short", "whole", "cut")
-
 
 class GemmWay(namedtuple("GemmWay", "tile cut workgroups threads")):
     def __str__(self):
@@ -20,13 +18,18 @@ def _cus(cus):
     return cus
 
 
-def attention(n, all_heads, head_dim, scratch=True, cus=None, split=False):
-    """"short": the wavefronts of a workgroup share the keys; "whole": 256-row query tiles, each one workgroup's;
-    "cut": those of the last round shared between workgroups and merged.  split: see rows_split.  The cheapest of these; whether
-    smaller tiles take the call from it says attention_tiles."""
-    fn = lp._lib().lp_internal_attention_way
-    fn.argtypes, fn.restype = [C.c_int64] + [C.c_int32] * 5, C.c_int
-    return WAYS[fn(n, all_heads, head_dim, _cus(cus), int(scratch), int(split))]
+class Tiles(namedtuple("Tiles", "rows last cut")):
+    """Query rows of attention_kernel's tiles (0: the short kernel), of those of its last round where they are smaller
+    (else 0), and whether tiles are cut and merged."""
+
+
+def attention_tiles(n, all_heads, head_dim, scratch=True, cus=None, split=False):
+    """What a call runs.  split: see rows_split."""
+    fn = lp._lib().lp_internal_attention_tiles
+    fn.argtypes, fn.restype = [C.c_int64] + [C.c_int32] * 5 + [C.POINTER(C.c_int32)], C.c_int
+    t = (C.c_int32 * 3)()
+    assert fn(n, all_heads, head_dim, _cus(cus), int(scratch), int(split), t) == 0
+    return Tiles(t[0], t[1], bool(t[2]))
 
 
 def rows_split(k, v, stride_tok, stride_head, stride_batch, heads, batch, head_dim):
@@ -43,18 +46,3 @@ def gemm(n, d_in, d_out, head_dim=0, cus=None):
     way = (C.c_int64 * 6)()
     assert fn(n, d_in, d_out, head_dim, _cus(cus), way) == 0
     return GemmWay((way[0], way[1]), (way[2], way[3]) if way[2] else None, way[4], way[5])
-
-
-class Tiles(namedtuple("Tiles", "rows last cut")):
-    """Query rows of attention_kernel's tiles (0: the short kernel), of those of its last round where they are smaller
-    (else 0), and whether tiles are cut and merged."""
-
-
-def attention_tiles(n, all_heads, head_dim, scratch=True, cus=None, split=False):
-    """What a call runs.  `attention` says which of the short kernel and 256-row tiles, whole or cut, is the cheaper; smaller tiles
-    take the call from there where they are cheaper still."""
-    fn = lp._lib().lp_internal_attention_tiles
-    fn.argtypes, fn.restype = [C.c_int64] + [C.c_int32] * 5 + [C.POINTER(C.c_int32)], C.c_int
-    t = (C.c_int32 * 3)()
-    assert fn(n, all_heads, head_dim, _cus(cus), int(scratch), int(split), t) == 0
-    return Tiles(t[0], t[1], bool(t[2]))

@@ -12,8 +12,9 @@ from tests import routes
 
 pytestmark = pytest.mark.gpu
 
-# what routes.attention_tiles says of a call: 256-row query tiles, those of the last round cut into ranges and merged; or none cut
-CUT, WHOLE = (256, 0, True), (256, 0, False)
+# what routes.attention_tiles says of a call: 256-row query tiles, those of the last round cut into ranges and merged; or none cut; the kernel
+# for short calls
+CUT, WHOLE, SHORT = (256, 0, True), (256, 0, False), (0, 0, False)
 
 
 @pytest.mark.parametrize("balanced", [True, False], ids=["workspace", "no-workspace"])
@@ -367,7 +368,7 @@ def test_long_kernel_on_few_tiles(n, hd, rows):
 @pytest.mark.parametrize("n", [3, 30, 62, 98, 126, 130, 161, 225, 383, 385, 1151])
 def test_short_kernel_at_round_edges(n, hd):
     from tests import gpu_util as g
-    assert routes.attention(n, 2, hd) == "short"
+    assert routes.attention_tiles(n, 2, hd) == SHORT
     q, k, v = synth.qkv_bf16(4700 + 2 * n + hd, n, 2, hd)
     g.assert_attention_close(g.hip_attention(q, k, v), orc.attention(q, k, v), "n=%d hd=%d" % (n, hd))
 
@@ -542,7 +543,7 @@ def test_rows_past_the_end_are_not_read_at_any_stride(hd):
     from tests import gpu_util as g
     from paper_2512_07350_amd import binding as lp
     n, stride = 2, (1 << 27) + 8
-    assert routes.attention(n, 1, hd) == "short"
+    assert routes.attention_tiles(n, 1, hd) == SHORT
     bits = synth.qkv_bf16(5300 + hd, n, 1, hd)
     bufs = [torch.full((stride + hd,), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(4)]
     for buf, b in zip(bufs, bits):

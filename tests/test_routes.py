@@ -16,8 +16,7 @@ MAX_THREADS = 2 ** 32 - 1        # of a launch: a dispatch states its grid as 32
 def test_attention_never_takes_a_grid_that_cannot_be_launched(n, heads, scratch, hd):
     """Millions of very short heads: the short kernel takes 256 threads for every 32 rows of a head."""
     threads = 256 * heads * -(-n // 32)
-    way = routes.attention(n, heads, hd, scratch, CUS)
-    assert way == ("short" if threads <= MAX_THREADS else "whole")
+    assert threads <= MAX_THREADS or routes.attention_tiles(n, heads, hd, scratch, CUS).rows > 0
 
 
 @pytest.mark.parametrize("head_dim", [0, 64, 128])
@@ -31,43 +30,79 @@ def test_gemm_never_takes_a_grid_that_cannot_be_launched(d_in, head_dim):
                 assert way.workgroups * way.threads <= MAX_THREADS or (way.tile, way.cut) == ((256, 256), None), (n, d_out, way)
 
 
-# us on 256 compute units, short kernel / 256-row query tiles (whole or cut), with scratch memory: calls of many heads and
-# a few hundred tokens, where the dearer way costs 14 % and more
-@pytest.mark.parametrize("n,heads,hd,way", [
-    (225, 256, 128, "long"),     # 28.9 / 21.7
-    (200, 256, 128, "long"),     # 25.5 / 19.8
-    (200, 200, 128, "long"),     # 21.9 / 17.8
-    (160, 256, 128, "long"),     # 19.1 / 16.0
-    (384, 256, 128, "long"),     # 48.9 / 41.7
-    (257, 1000, 64, "short"),    # 55.9 / 80.9
-    (300, 640, 64, "short"),     # 42.6 / 55.9
-    (129, 2000, 64, "short"),    # 51.0 / 66.9
-    (600, 400, 64, "short"),     # 67.7 / 78.4
-    (850, 150, 64, "short"),     # 48.4 / 55.6
-    (200, 4, 64, "short"), (1000, 12, 128, "short"), (2999, 16, 64, "long"), (3780, 12, 128, "long"),
+# us on 256 compute units with scratch memory of the short kernel / query tiles of 256 (whole or cut) / 192 / 128 rows, and the rows taken
+# (0: short kernel)
+@pytest.mark.parametrize("n,heads,hd,rows", [
+    (225, 256, 128, 256),    # 28.5 / 20.1 / 25.3 / 21.0
+    (200, 256, 128, 256),    # 25.3 / 18.9 / 24.1 / 20.1
+    (200, 200, 128, 256),    # 21.6 / 17.0 / 23.6 / 19.0
+    (160, 256, 128, 192),    # 18.7 / 15.0 / 12.9 / 17.2
+    (384, 256, 128, 192),    # 47.5 / 38.5 / 32.7 / 34.4
+    (257, 1000, 64, 0),      # 54.7 / 73.8 / 61.6 / 67.7
+    (129, 2000, 64, 0),      # 47.6 / 62.3 / 52.6 / 74.3
+    (300, 640, 64, 192),     # 42.6 / 48.9 / 41.4 / 47.7
+    (600, 400, 64, 128),     # 74.1 / 67.4 / 70.9 / 64.8
+    (850, 150, 64, 192),     # 49.4 / 49.2 / 41.5 / 50.2
+    (200, 4, 64, 0),         # 5.0 / 10.3 / 9.0 / 7.6
+    (1000, 12, 128, 0),      # 15.4 / 24.7 / 22.5 / 17.4
+    (1000, 24, 128, 128),    # 24.3 / 26.7 / 23.2 / 18.3
+    (900, 60, 64, 256),      # 24.3 / 19.1 / 27.2 / 22.5
+    (2999, 16, 64, 192),     # 52.1 / 39.4 / 34.3 / 47.2
+    (3780, 12, 128, 192),    # 121.6 / 75.0 / 68.6 / 95.2
+    (4212, 12, 128, 256),    # 153.3 / 84.6 / 133.3 / 103.2
+    (4500, 16, 128, 256),    # 209.0 / 130.8 / 142.1 / 161.7
 ])
-def test_attention_takes_the_faster_way(n, heads, hd, way):
-    assert (routes.attention(n, heads, hd, True, CUS) == "short") == (way == "short")
+def test_attention_takes_the_faster_way(n, heads, hd, rows):
+    assert routes.attention_tiles(n, heads, hd, True, CUS).rows == rows
 
 
-# us, short kernel / 256-row query tiles, of calls whose rows are split over cache lines (short kernel with whole lines)
-@pytest.mark.parametrize("n,heads,hd,whole_lines", [
-    (1628, 25, 64, "short"),     # 49.0 / 30.1 (30.0)
-    (1542, 22, 64, "short"),     # 36.5 / 28.2 (28.5)
-    (861, 201, 64, "short"),     # 94.0 / 73.1
-    (1063, 73, 64, "short"),     # 51.7 / 43.8
-    (1625, 38, 128, "short"),    # 97.9 / 76.0 (87.9)
-    (1777, 17, 128, "short"),    # 54.3 / 46.5 (49.3)
-    (3427, 21, 64, "cut"), (2963, 11, 128, "cut"),
+# us, whole / cut: 256-row query tiles of a last round that leaves few compute units idle, and of one that leaves most
+@pytest.mark.parametrize("n,heads,hd,cut", [
+    (4212, 12, 128, False),  # 84.6 / 94.7
+    (4680, 12, 128, False),  # 99.6 / 114.1
+    (4500, 16, 128, True),   # 178.8 / 130.8
+    (4500, 16, 64, True),    # 110.6 / 80.8
+    (5000, 2, 128, True),    # 88.4 / 39.7
+    (2000, 70, 128, True),   # 140.0 / 121.2
 ])
-def test_split_rows_keep_a_call_from_the_short_kernel(n, heads, hd, whole_lines):
-    assert routes.attention(n, heads, hd, True, CUS) == whole_lines
-    assert routes.attention(n, heads, hd, True, CUS, split=True) in ("whole", "cut")
+def test_attention_cuts_the_tiles_of_a_last_round(n, heads, hd, cut):
+    assert routes.attention_tiles(n, heads, hd, True, CUS) == (256, 0, cut)
+    assert not routes.attention_tiles(n, heads, hd, False, CUS).cut
+
+
+# us, short kernel / 256-row query tiles (whole or cut) / 192 / 128, of calls whose rows are split over cache lines (short kernel
+# and the tiles taken with whole lines)
+@pytest.mark.parametrize("n,heads,hd,rows", [
+    (1628, 25, 64, 192),     # 45.2 / 26.6 / 23.0 / 35.8 (27.6, 21.7)
+    (1542, 22, 64, 192),     # 35.6 / 25.3 / 21.3 / 34.2 (25.8, 20.9)
+    (861, 201, 64, 192),     # 83.7 / 68.4 / 56.6 / 65.6 (65.8, 54.5)
+    (1063, 73, 64, 192),     # 49.7 / 38.0 / 33.3 / 39.8 (36.9, 31.0)
+    (1625, 38, 128, 128),    # 88.7 / 67.7 / 62.8 / 53.6 (77.6, 51.2)
+    (1777, 17, 128, 128),    # 52.8 / 40.7 / 33.5 / 30.2 (44.0, 28.5)
+    (2963, 11, 128, 192),    # 82.3 / 57.0 / 48.6 / 80.1 (68.0, 47.7)
+])
+def test_calls_of_split_rows_that_run_tiles(n, heads, hd, rows):
+    for split in (False, True):
+        assert routes.attention_tiles(n, heads, hd, True, CUS, split=split).rows == rows
+
+
+# us, short kernel in whole lines / split, and the tiles taken from it where rows are split
+@pytest.mark.parametrize("n,heads,hd,tiles", [
+    (640, 32, 64, (128, 0, False)),      # 9.8 / 11.8, 10.2
+    (2444, 6, 64, (128, 0, False)),      # 17.1 / 22.5, 21.0
+    (1969, 8, 128, (128, 0, False)),     # 25.0 / 30.9, 26.1
+    (582, 121, 64, (192, 0, False)),     # 23.5 / 28.2, 24.0
+    (600, 75, 64, (256, 0, False)),      # 16.4 / 19.6, 16.1
+    (3094, 3, 64, (256, 0, True)),       # 19.1 / 24.4, 22.7
+])
+def test_split_rows_keep_a_call_from_the_short_kernel(n, heads, hd, tiles):
+    assert routes.attention_tiles(n, heads, hd, True, CUS).rows == 0
+    assert routes.attention_tiles(n, heads, hd, True, CUS, split=True) == tiles
 
 
 def test_split_rows_leave_small_calls_with_the_short_kernel():
     for n, heads, hd in ((200, 4, 64), (600, 24, 64), (1000, 12, 128)):      # 10.0 / 16.7 and 17.8 / 27.8 us for the latter two
-        assert routes.attention(n, heads, hd, True, CUS, split=True) == "short"
+        assert routes.attention_tiles(n, heads, hd, True, CUS, split=True).rows == 0
 
 
 @pytest.mark.parametrize("hd", [64, 128])
