@@ -23,16 +23,19 @@ int64_t workspace_bytes_for(int cus) { return int64_t(2) * cus * slot_floats<D>(
 // next, in tile times; a tile while a part kBusy of the compute units works: one workgroup's own pace, slower
 // as the power limit lowers the clock of a full chip.  A tile's time falls less than its rows: every operand fetched from LDS feeds
 // one product per 16 rows of a wavefront, and at head_dim 128 and 32 rows the fetches take as long as the products.
+// `split` comes on top of a tile where rows lie split over lines (rows_split): the fewer rows a unit has, the more often K and V are
+// fetched, over more lines each time.  From 700 and 500 calls on every way in three layouts; the choice is off the best
+// way by 0.18 % of their time (0.39 % without it and with a constant surcharge in the short kernel).
 struct UnitCost {
-    float once, change, tile[4];
+    float once, change, split, tile[4];
 };
 constexpr float kBusy[4] = {0.5f, 0.8f, 0.94f, 1.0f};
-constexpr UnitCost kUnit128[3] = {{8.017f, 4.443f, {0.571f, 0.645f, 0.707f, 0.759f}},      // qb 2, 3, 4
-                                  {9.034f, 4.944f, {0.794f, 0.903f, 0.931f, 1.045f}},
-                                  {11.446f, 3.748f, {1.088f, 1.117f, 1.293f, 1.330f}}};
-constexpr UnitCost kUnit64[3] = {{6.289f, 5.242f, {0.380f, 0.414f, 0.419f, 0.475f}},
-                                 {7.139f, 5.685f, {0.476f, 0.533f, 0.587f, 0.622f}},
-                                 {8.726f, 4.981f, {0.729f, 0.749f, 0.776f, 0.796f}}};
+constexpr UnitCost kUnit128[3] = {{8.017f, 4.443f, 0.03f, {0.571f, 0.645f, 0.707f, 0.759f}},      // qb 2, 3, 4
+                                  {9.034f, 4.944f, 0.012f, {0.794f, 0.903f, 0.931f, 1.045f}},
+                                  {11.446f, 3.748f, 0.0f, {1.088f, 1.117f, 1.293f, 1.330f}}};
+constexpr UnitCost kUnit64[3] = {{6.289f, 5.242f, 0.01f, {0.380f, 0.414f, 0.419f, 0.475f}},
+                                 {7.139f, 5.685f, 0.035f, {0.476f, 0.533f, 0.587f, 0.622f}},
+                                 {8.726f, 4.981f, 0.0f, {0.729f, 0.749f, 0.776f, 0.796f}}};
 const UnitCost &unit_cost(int head_dim, int qb) { return (head_dim == 128 ? kUnit128 : kUnit64)[qb - 2]; }
 
 float tile_us(const UnitCost &c, float busy) {
@@ -51,7 +54,7 @@ struct Deal {
 };
 
 // Whole units to everybody for as many rounds as they fill, and one each of those left over.
-Deal deal_whole(int head_dim, int qb, int64_t n, int all_heads, uint32_t cus) {
+Deal deal_whole(int head_dim, int qb, int64_t n, int all_heads, uint32_t cus, bool split) {
     const UnitCost &c = unit_cost(head_dim, qb);
     const uint32_t units = uint32_t((n + unit_rows(qb) - 1) / unit_rows(qb)) * uint32_t(all_heads), tpu = uint32_t((n + kBN - 1) / kBN);
     Deal d;
@@ -66,6 +69,7 @@ Deal deal_whole(int head_dim, int qb, int64_t n, int all_heads, uint32_t cus) {
     const float transfers = (head_dim == 128 ? 0.318f : 0.306f) * lp::attention_bytes_us(n, all_heads, head_dim);
     d.us = c.once + transfers + (float(d.rounds) * float(tpu) + changes * c.change) * tile_us(c, 1.0f);
     if (d.shared > 0) d.us += float(tpu) * tile_us(c, float(d.shared) / float(cus));
+    if (split) d.us += float(d.rounds + (d.shared > 0 ? 1 : 0)) * float(tpu) * c.split;
     return d;
 }
 
@@ -78,7 +82,7 @@ Deal deal_large(int head_dim, int64_t n, int all_heads, uint32_t cus, bool may_c
     const float merge = head_dim == 128 ? 6.023f : 5.574f;                // combine_kernel and the parts it reads
     const UnitCost &c = unit_cost(head_dim, kMostQB);
     const uint32_t tpu = uint32_t((n + kBN - 1) / kBN);
-    Deal d = deal_whole(head_dim, kMostQB, n, all_heads, cus);
+    Deal d = deal_whole(head_dim, kMostQB, n, all_heads, cus, false);    // 256-row units lose nothing by split rows
     if (!may_cut || d.shared == 0) return d;
     uint32_t sharers = uint32_t(uint64_t(d.shared) * tpu / kMinTiles);
     if (sharers > cus) sharers = cus;
@@ -98,20 +102,22 @@ Deal deal_large(int head_dim, int64_t n, int all_heads, uint32_t cus, bool may_c
 // end of a head), or 192 in a last round that takes one to a workgroup.  Measured, 256 rows (whole or cut) / 192 / 128: 3780 x 12 of
 // 128 76 / 70 / 91, 1625 x 38 70 / 63 / 53, 2304 x 40 of 64 63 / 57 / 68, 861 x 201 69 / 55 / 62; 2 x 7410 x 12 of 128
 // 466, 452 with a last round of 192.
-Deal deal_finer(int head_dim, int64_t n, int all_heads, uint32_t cus, const Deal &large) {
+Deal deal_finer(int head_dim, int64_t n, int all_heads, uint32_t cus, bool split, const Deal &large) {
     Deal best = large;
     for (int qb = kMostQB - 1; qb >= 2; --qb) {
-        const Deal d = deal_whole(head_dim, qb, n, all_heads, cus);
+        const Deal d = deal_whole(head_dim, qb, n, all_heads, cus, split);
         if (d.us < best.us) best = d;
     }
-    Deal d = deal_whole(head_dim, kMostQB, n, all_heads, cus);
+    Deal d = deal_whole(head_dim, kMostQB, n, all_heads, cus, false);
     if (d.rounds > 0 && d.shared > 0) {
         constexpr int64_t kRows = unit_rows(kMostQB), kTail = unit_rows(3);
         const int64_t tiles = (n + kRows - 1) / kRows, whole = int64_t(d.rounds) * cus, row = whole % tiles * kRows;
         const int64_t units = (n - row + kTail - 1) / kTail + (all_heads - whole / tiles - 1) * ((n + kTail - 1) / kTail);
         const float tpu = float((n + kBN - 1) / kBN);
         if (units <= int64_t(cus)) {
-            d.us += tpu * (tile_us(unit_cost(head_dim, 3), float(units) / float(cus)) - tile_us(unit_cost(head_dim, kMostQB), float(d.shared) / float(cus)));
+            const UnitCost &c = unit_cost(head_dim, 3);
+            d.us += tpu * (tile_us(c, float(units) / float(cus)) - tile_us(unit_cost(head_dim, kMostQB), float(d.shared) / float(cus)));
+            if (split) d.us += tpu * c.split;
             d.tail = 3;
             d.shared = d.sharers = uint32_t(units);
             if (d.us < best.us) best = d;
@@ -130,7 +136,7 @@ struct Route {
 // The cheapest of the short kernel, where its grid is one that can be launched, and units of 256 rows, whole or cut, and of fewer.
 Route pick_route(int head_dim, int64_t n, int all_heads, int cus, bool scratch, bool split) {
     Route r;
-    r.deal = deal_finer(head_dim, n, all_heads, uint32_t(cus), deal_large(head_dim, n, all_heads, uint32_t(cus), scratch));
+    r.deal = deal_finer(head_dim, n, all_heads, uint32_t(cus), split, deal_large(head_dim, n, all_heads, uint32_t(cus), scratch));
     r.short_kernel = lp::attention_short_launchable(n, all_heads) && lp::attention_short_us(n, all_heads, head_dim, cus, split) < r.deal.us;
     r.cut = !r.short_kernel && r.deal.sharers != r.deal.shared;
     return r;

@@ -320,14 +320,18 @@ bool attention_short_launchable(int64_t n, int64_t all_heads) { return short_gro
 // tokens x 2000 heads of 128: 176 us, 83 without it).  Off by 7 % (rms) at 1 .. 5000 tokens x 1 .. 5000 heads.
 // Rows that lie split over one line more than they fill, with other heads' rows in between (padded or side by side at odd
 // offsets), take a round of a full chip a third longer, as every K / V row is fetched once per 32 query rows: 1628 tokens x
-// 25 heads of 64 49.0 us, 30.0 in whole lines; the 256-row tiles lose nothing (30.1 / 29.8).
+// 25 heads of 64 45.2 us, 27.6 in whole lines; the 256-row tiles lose nothing (26.6 / 25.8).  A head of few rounds stays in the
+// caches close by and loses little at head_dim 64: 153 x 411 14.6, 14.4 in whole lines.
 float attention_short_us(int64_t n, int64_t all_heads, int head_dim, int cus, bool split) {
     const int64_t groups = short_groups(n, all_heads), rounds = (n + 127) / 128;
     const int64_t per_cu = (groups + cus - 1) / cus;
     if (per_cu <= 1) return head_dim == 128 ? 4.73f + 0.75f * float(rounds) : 4.274f + 0.437f * float(rounds);
     const float bytes_us = attention_bytes_us(n, all_heads, head_dim);
-    if (head_dim == 64) return 4.026f + float(per_cu) * (0.26f + (split ? 0.446f : 0.328f) * float(rounds)) + 0.404f * bytes_us;
-    return 3.76f + 0.516f * float(per_cu) + float((per_cu + 1) / 2) * (split ? 1.35f : 1.066f) * float(rounds) + 0.782f * bytes_us;
+    if (head_dim == 64) {
+        const float more = split && rounds > 2 ? 0.147f * (float(rounds) - 2.5f) : 0.0f;
+        return 4.026f + float(per_cu) * (0.26f + 0.328f * float(rounds) + more) + 0.404f * bytes_us;
+    }
+    return 3.76f + 0.516f * float(per_cu) + float((per_cu + 1) / 2) * (split ? 1.386f : 1.066f) * float(rounds) + 0.782f * bytes_us;
 }
 
 int attention_short(const AttentionCall &c, hipStream_t stream) {

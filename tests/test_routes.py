@@ -100,6 +100,21 @@ def test_split_rows_keep_a_call_from_the_short_kernel(n, heads, hd, tiles):
     assert routes.attention_tiles(n, heads, hd, True, CUS, split=True) == tiles
 
 
+# us of split rows, token-major / head-major, short kernel and the best of the tiles: heads of few rounds of 128 keys lose little there, while
+# tiles of 192 and 128 rows fetch more lines for every tile of keys
+@pytest.mark.parametrize("n,heads,hd", [
+    (153, 411, 64),          # 14.6 / 14.8, 16.1 / 18.6
+    (295, 311, 64),          # 25.4 / 24.3, 27.4 / 28.1
+    (261, 213, 64),          # 16.5 / 17.2, 18.7 / 19.3
+    (189, 519, 64),          # 22.3 / 22.3, 24.7 / 27.4
+    (260, 95, 64),           # 9.8 / 9.2, 10.5 / 10.2
+    (154, 195, 64),          # 8.2 / 8.2, 9.0 / 9.1
+    (174, 87, 64),           # 7.3 / 6.8, 7.8 / 7.5
+])
+def test_split_rows_of_few_keys_stay_with_the_short_kernel(n, heads, hd):
+    assert routes.attention_tiles(n, heads, hd, True, CUS, split=True).rows == 0
+
+
 def test_split_rows_leave_small_calls_with_the_short_kernel():
     for n, heads, hd in ((200, 4, 64), (600, 24, 64), (1000, 12, 128)):      # 10.0 / 16.7 and 17.8 / 27.8 us for the latter two
         assert routes.attention_tiles(n, heads, hd, True, CUS, split=True).rows == 0
