@@ -165,11 +165,6 @@ __device__ __forceinline__ void product(uint32_t lds0, const GemmArgs &a, int f0
     auto read_hi = [&](int m, int s) { hi[m][s] = lds_load<bf16x8>(w_addr[s] + (FH + m) * 16 * kRowBytes); };
     auto read_x = [&](int t, int s) { xop[t][s] = lds_load<bf16x8>(x_addr[s] + t * 16 * kRowBytes); };
 
-#pragma unroll
-    for (int f = 0; f < FB; ++f)
-#pragma unroll
-        for (int t = 0; t < TB; ++t) acc[f][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
     const int n_kt = a.d_in / kBK;
 #pragma unroll
     for (int p = 0; p < S; ++p) {
@@ -180,6 +175,14 @@ __device__ __forceinline__ void product(uint32_t lds0, const GemmArgs &a, int f0
             for (int i = 0; i < C::Y; ++i) load_y(i, p, p * C::kStage);
         }
     }
+    // in registers from here on: zeroed right in front of the first products they would be read a wait state too early
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int t = 0; t < TB; ++t) {
+            acc[f][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            asm volatile("" : "+v"(acc[f][t]));
+        }
     if (n_kt >= S) stage_barrier<C::Y + (S - 1) * (C::X + C::Y)>();     // the first tile's X group has landed
     else stage_barrier<0>();
 #pragma unroll
