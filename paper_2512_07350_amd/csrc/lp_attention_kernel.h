@@ -135,7 +135,9 @@ struct Lane {
 };
 
 // The global -> LDS loads of a K and a V block (see load_to_lds_16): the waits that order them against the reads of their own
-// stage are wait_tile_loads + barrier.  Nothing else in this file uses M0.
+// stage are wait_tile_loads + barrier.  M0 belongs to these and to set_m0 / load_to_lds_16 below, whose value lives on from one window to
+// the next: nothing may write it between a set_m0 and its load.  The compiler has no use for M0 in these kernels;
+// tests/test_wait_states.py looks for one in the built library.
 template <int V_LDS_OFFSET>
 __device__ __forceinline__ void load_kv_to_lds_16(__amdgpu_buffer_rsrc_t k_rsrc, __amdgpu_buffer_rsrc_t v_rsrc, uint32_t k_lds,
                                                   uint32_t k_voff, uint32_t v_voff, uint32_t soff) {
@@ -486,7 +488,7 @@ __device__ __forceinline__ void pipeline_step(uint32_t lds0, const Lane<D> &c, i
         // every second group runs backwards: neighbours then share an operand throughout, and what does not change costs less
         // power (13230 tokens, 40 heads of 128: 2280 -> 2251 us)
         constexpr int m = decltype(mc)::value, g = m / QB, at = m % QB, qb = g % 2 ? QB - 1 - at : at;
-        // pair k is rounded in the second window after its second exponential
+        // pair k is rounded in the window behind its second exponential's
         if constexpr (m % (2 * kEvery) == 0 && m > 0 && m / kEvery <= E) convert_pairs<m / (2 * kEvery) - 1, m / (2 * kEvery)>(ex, pw, p_cur);
         if constexpr (m % kEvery == kEvery - 1 && m / kEvery < E) {
             constexpr int x = m / kEvery;
@@ -804,9 +806,9 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
             }
         };
         if (!CHECK && (i + 11) * 32 <= c.key_end) {
-            // four tiles at a time, each with its stage known at compile time: 343 instructions a tile
-            // instead of 390 at head_dim 128, 242 instead of 284 at 64.  The first tile comes before
-            // them (its V fetches stay in stage 0), so they start in stage 1.
+            // four tiles at a time, each with its stage known at compile time: 318, 260, 202 instructions a tile (QB = 4, 3, 2)
+            // instead of 366, 309, 250 at head_dim 128, 221, 176, 134 instead of 258, 216, 174 at 64.  The first tile comes
+            // before them (its V fetches stay in stage 0), so they start in stage 1.
             whole_tiles(i_begin + 2);
 #pragma unroll
             for (int kk = 0; kk < D / 32; ++kk) w.k_addr[kk] -= T::kStageBytes;
@@ -840,7 +842,7 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-                for (int mb = 0; mb <= G; ++mb) {
+                for (int mb = 0; mb <= G; ++mb) {          // (of the row sums all four elements, which are the same)
                     const f32x4 &x = mb < G ? w.acc[mb][qb] : w.l_acc[qb];
 #pragma unroll
                     for (int r = 0; r < 4; r += 2) {

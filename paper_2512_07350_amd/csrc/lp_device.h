@@ -116,7 +116,6 @@ __device__ __forceinline__ float over_quads(float x, Op &&op) {
     return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 __device__ __forceinline__ float quad_max(float x) { return over_quads(x, [](float a, float b) { return fmaxf(a, b); }); }
-__device__ __forceinline__ float quad_sum(float x) { return over_quads(x, [](float a, float b) { return a + b; }); }
 
 // Lets kernel `fn` have `bytes` of dynamic LDS on device `dev`.  The limit is an attribute of the function on a device: set
 // once per device, `done` holding a bit for each (a repeated set by a racing host thread is harmless).

@@ -4,6 +4,10 @@ built library, along every path of every kernel that has such statements.
 v_mfma_f32_16x16x32_bf16 may read a register that a vector instruction wrote once two other wait states have passed, and what it writes
 may be read by anything but a product that accumulates on it after seven (four passes and three).  A wait state is an instruction of the
 same wavefront, or one of the s_nop's.  The kernels whose products are builtins are the compiler's.
+
+Likewise M0, which the global -> LDS loads take their LDS address from: statements write it, and a load (some windows later, in the
+attention kernel and the wide products) uses it.  One other wait state stands between them, and nothing else writes it there: every write
+is used before the next one.
 """
 import os
 import re
@@ -51,6 +55,7 @@ class Instruction:
         if both:
             self.writes |= registers(ops[1])
         self.sum_on = registers(ops[3]) if self.product else set()
+        self.writes_m0, self.uses_m0 = ops[0] == "m0", self.op.startswith("buffer_load") and rest.endswith(" lds")
 
 
 def kernels(path, tmp):
@@ -101,6 +106,23 @@ def too_close(code, before):
     return bad
 
 
+def m0_lost(code, before):
+    """Loads whose M0 was written right in front of them, and writes of M0 that meet another write before a load."""
+    bad = [i for i, x in enumerate(code) if x.uses_m0 and any(code[j].writes_m0 for j in before[i])]
+    for i in (i for i, x in enumerate(code) if x.writes_m0):
+        paths, seen = list(before[i]), set()
+        while paths:
+            j = paths.pop()
+            if j in seen or code[j].uses_m0:
+                continue
+            seen.add(j)
+            if code[j].writes_m0:
+                bad.append(i)
+            else:
+                paths += before[j]
+    return bad
+
+
 def test_wait_states_around_products(tmp_path):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump beside hipcc")
@@ -109,6 +131,7 @@ def test_wait_states_around_products(tmp_path):
         count += sum(x.product for x in code) > 0
         bad = too_close(code, before)
         assert not bad, (name, [(code[j].op, code[i].op, passed) for i, j, passed in bad[:4]])
+        assert not m0_lost(code, before), name
     assert count >= 8 + 30             # attention_kernel in four forms at either head_dim; the tilings of the products
 
 
@@ -125,3 +148,8 @@ def test_the_check_sees_what_stands_too_close():
     assert not found(product, "s_nop 6", "v_exp_f32_e32 v0, v5")
     assert found(product, "v_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[20:23], a[0:3]") == [(1, 0, 0)]
     assert found(product, "ds_write_b128 v0, v[4:7]") == [(1, 0, 0)]
+    load = "buffer_load_dwordx4 v0, s[4:7], s8 offen lds"
+    lost = lambda *lines: m0_lost([Instruction(l) for l in lines], [[j] if j >= 0 else [] for j in range(-1, len(lines) - 1)])
+    assert not lost("s_add_u32 m0, s0, 16", product, load, "s_mov_b32 m0, s1", "s_nop 0", load)
+    assert lost("s_mov_b32 m0, s1", load) == [1]
+    assert lost("s_mov_b32 m0, s1", product, "s_mov_b32 m0, -1", product, load) == [2]
