@@ -285,10 +285,12 @@ __device__ __forceinline__ void load_at_m0(const __amdgpu_buffer_rsrc_t &rsrc, u
 // bytes as the products take; four of 128 x 128 read 128 KB, which is less power too.  Alone on its SIMD a wavefront keeps the
 // matrix pipeline busy if no more than 8 cycles of other instructions (two) stand between two products, so that a load is a write of
 // M0 before a product and the load behind it, and lane offsets hold what a scalar addition per load did.  Half as many
-// wavefronts fill the stages and store the tile more slowly: from 32 k-tiles on this is the faster (256 x 256 that nothing cuts: 64).
-// us, eight / four: 13230 x 5120 -> 5120 495.6 / 484.4, 15278 x 5120 -> 5120 582 / 569, 4051 x 4096 -> 1536 (256 x 128) 49.1 / 46.8;
-// 4265 x 512 -> 2048 15.4 / 17.4.  Not with the QKV epilogue, which one wavefront to a SIMD takes longer for (8192 x 2048 -> 6144
-// 158 / 168), nor for 128 x 128 (no change).
+// wavefronts fill the stages and store the tile more slowly.  Four / eight, time: 1.06 to 1.10 at 8 k-tiles, 1.00 to 1.01 at 32, 0.99
+// to 1.01 at 40, 0.97 to 0.99 at 64, 0.94 to 0.98 at 96; from 33 to 39 k-tiles seven calls of other sizes 0.98 to 1.00, so that
+// the line (four_waves) lies where neither side gains.  13230 x 5120 -> 5120 466.6 / 460.5 us, 4096 x 6144 -> 1536 67.9 / 64.4.
+// Not with the QKV epilogue, which one wavefront to a SIMD takes longer for, by what the products gain: 8192 x 2048 -> 6144 158.9 /
+// 170.8, 8192 x 3072 -> 9216 355 / 369, and with 80 k-tiles 8192 x 5120 -> 15360 911.5 / 910.3, 13230 x 5120 1467 / 1438,
+// 11340 x 5120 1273 / 1277, 4096 x 5120 468.4 / 468.4.  Nor for 128 x 128 (no change).
 template <typename C>
 __device__ __forceinline__ void product_wide(uint32_t lds0, const GemmArgs &a, int f0, int t0, int wave, int lane,
                                              f32x4 (&acc)[C::FB][C::TB]) {
@@ -405,9 +407,11 @@ __device__ __forceinline__ void product_wide(uint32_t lds0, const GemmArgs &a, i
 
 // The same for calls of few tiles and a long k: the four waves of a workgroup share k.
 //
-// What bounds it: what a compute unit takes in through the global -> LDS path, per k-tile of d_in 5120 to 10240.  In 64 x 32
-// tiles of 12 KB 132 GB/s with 2 to 32 workgroups, 74 to 93 with 80 to 256 of them (0.093 and 0.13 to 0.17 us); in 64 x 64 and
-// 128 x 64 tiles 72 to 74 with 160 to 256.  So with compute units to spare the tile with fewer bytes is the faster one.
+// What bounds it: what a compute unit takes in, and that depends on where the bytes are.  A k-tile of 12 KB takes 0.07 to 0.085 us
+// (150 GB/s a compute unit) while the rows of W and x that an XCD's workgroups read fit its L2, and 0.13 to 0.17 us (72 to 92
+// GB/s) where they come from behind it, with 30 workgroups as with 250.  Six, eight and twelve stages (72, 96, 144 KB sent for): 14.5,
+// 13.5, 13.8 us at 520 x 5120 -> 640, so it is not what the stages have under way.  64 x 64 and 128 x 64 tiles take in 72 to 74
+// GB/s with 160 to 256 workgroups, so with compute units to spare the tile with fewer bytes is the faster one.
 // A 64 x 32 tile has too few products per k-tile to keep four waves that share its rows apart from LDS and the barrier
 // (0.19 us with two such waves); here a wave takes all of the tile's rows for one k-step of 32 out of a pair of k-tiles, every
 // byte is read from LDS once, and the four partial tiles are added up through LDS at the end.  A wave holds the operands of
@@ -801,7 +805,11 @@ using Four128x128 = Tiling<2, 2, 4, 4, 4>;
 using Four128x64 = Tiling<2, 2, 4, 2, 5>;
 using Split64x32 = Tiling<2, 2, 2, 1, 8, kSplitK>;
 
-// How a call is cut.  A round is one tile on every compute unit (two of 64 x 64).  Per round, in us, fitted to 4004 calls (3133
+// How a call is cut.  The prices are those of the kernels of eight wavefronts; from 32 k-tiles on lp_linear runs the plan's tiles of
+// 256 features with four (four_waves), which are up to 6 % faster and change no plan: of 160 products of 32 to 120 k-tiles, timed in
+// every tiling with the wavefronts it would run with, none was more than 5 % off the fastest, 1.0 % on average with the spread of the times in it.
+//
+// A round is one tile on every compute unit (two of 64 x 64).  Per round, in us, fitted to 4004 calls (3133
 // products of 1 .. 200000 tokens, d_in 64 .. 13824, d_out 128 .. 13824, and 871 QKV projections), each timed on every tiling,
 // so that the tiling chosen is the fastest: a k-tile of 64, and `once`, what a tile costs besides (first loads, stores); `part`
 // with at most half of the compute units busy, `full` with all of them, where the power limit lowers the clock and
