@@ -19,7 +19,6 @@ from __future__ import annotations
 
 import argparse
 import concurrent.futures
-import hashlib
 import json
 import os
 import sys
@@ -35,7 +34,6 @@ METRIC = "lp_attention TFLOP/s (% bf16 MFMA peak); partition+stitch GB/s (% HBM)
 HEADLINE = 3                  # dit14b-81f-720p
 LOOP = 4                      # the 50-step loop on the 81-frame 480p latent
 LOOP_STEPS = 50
-ATTENTION_SOURCE = os.path.join(ROOT, "paper_2512_07350_amd", "csrc", "lp_attention_kernel.h")
 
 
 def main() -> int:
@@ -343,10 +341,11 @@ def rate(nbytes, ms, steps):
 
 def traffic_record(path, workload, guided):
     """HBM bytes per lp_attention launch from the tracked rocprofv3 --pmc record of this workload -- only if the
-    record was taken with the attention source as it is now (it names the file's SHA-256); else null."""
+    record was taken with the attention sources as they are now (it names their SHA-256); else null."""
     if guided or not path or not os.path.exists(path):
         return None
-    sha = hashlib.sha256(open(ATTENTION_SOURCE, "rb").read()).hexdigest()
+    from paper_2512_07350_amd.profile_summary import source_sha256
+    sha = source_sha256()
     doc = json.load(open(path))
     for rec in doc.get("records", [doc]):
         if rec.get("workload") == workload and rec.get("attention_source_sha256") == sha:

@@ -10,7 +10,7 @@ per kernel of this library.  `traffic` reads the `*_counter_collection.csv` file
 `bench.py --copy-calibration`, scales them by what the same counter reads for the plain device
 copy of known size, and prints bytes per launch; with --json it also writes (or replaces) this
 workload's record in the file `bench.py` reads for `roofline.traffic`; the record carries the
-SHA-256 of the attention source in this tree, so summarise before changing that file.  `counters` prints the mean per dispatch of every
+SHA-256 of the attention sources in this tree, so summarise before changing them.  `counters` prints the mean per dispatch of every
 counter found for one kernel in any number of `--pmc` runs.  Host-side text processing only: no GPU, no oracle.
 """
 from __future__ import annotations
@@ -131,11 +131,14 @@ def traffic(fetch_dir: str, write_dir: str, workload: str, out_json: str | None,
             fh.write("\n")
 
 
-def source_sha256() -> str:
-    """SHA-256 of the attention kernel's source file as it is in this tree."""
+def source_sha256(csrc: str = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc")) -> str:
+    """SHA-256 of everything that decides what an attention call moves: its kernels, its dispatch (which tiles a call runs, and
+    whether they are cut and merged) and the headers they share."""
     import hashlib
-    here = os.path.dirname(os.path.abspath(__file__))
-    return hashlib.sha256(open(os.path.join(here, "csrc", "lp_attention_kernel.h"), "rb").read()).hexdigest()
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(csrc, "lp_attention*"))) + [os.path.join(csrc, n) for n in ("lp_device.h", "lp_internal.h")]:
+        h.update(os.path.basename(path).encode() + b"\0" + open(path, "rb").read() + b"\0")
+    return h.hexdigest()
 
 
 def counters(paths, kernel: str) -> None:

@@ -1,7 +1,13 @@
 """The rocprofv3 CSV summariser on small hand-made CSV files (CPU only)."""
 import json
+import os
+import shutil
 import subprocess
 import sys
+
+import pytest
+
+from paper_2512_07350_amd import profile_summary
 
 HEAD = '"Correlation_Id","Dispatch_Id","Agent_Id","Queue_Id","Process_Id","Thread_Id","Grid_Size","Kernel_Id","Kernel_Name","Workgroup_Size","LDS_Block_Size","Scratch_Size","VGPR_Count","Accum_VGPR_Count","SGPR_Count","Counter_Name","Counter_Value","Start_Timestamp","End_Timestamp"\n'
 
@@ -60,3 +66,24 @@ def test_stats_table(tmp_path):
                          capture_output=True, text=True, check=True)
     lines = [l for l in res.stdout.splitlines() if l.startswith("| `")]
     assert lines == ["| `attention_kernel<128,1>` | 4 | 0.400 | 100.00 | 80.00 | 90.00 | 110.00 |"]
+
+
+CSRC = os.path.join(os.path.dirname(profile_summary.__file__), "csrc")
+
+
+@pytest.mark.parametrize("name", ["lp_attention.hip", "lp_attention.h", "lp_attention_kernel.h", "lp_attention_64.hip", "lp_attention_128.hip",
+                                  "lp_attention_short.hip", "lp_device.h", "lp_internal.h"])
+def test_a_traffic_record_is_stale_once_a_source_of_attention_changes(tmp_path, name):
+    """Prices and dealing are in the dispatch: they move a call to other tiles, or add or drop the merge, with the kernels as they were."""
+    import bench
+    csrc = shutil.copytree(CSRC, tmp_path / "csrc")
+    assert profile_summary.source_sha256(str(csrc)) == profile_summary.source_sha256()
+    record = tmp_path / "t.json"
+    record.write_text(json.dumps({"records": [{"workload": "w", "attention_source_sha256": profile_summary.source_sha256(), "attention_bytes_per_launch": 7}]}))
+    assert bench.traffic_record(str(record), "w", False) == 7 and bench.traffic_record(str(record), "w", True) is None
+    with open(csrc / name, "a") as fh:
+        fh.write("// \n")
+    changed = profile_summary.source_sha256(str(csrc))
+    assert changed != profile_summary.source_sha256()
+    record.write_text(json.dumps({"records": [{"workload": "w", "attention_source_sha256": changed, "attention_bytes_per_launch": 7}]}))
+    assert bench.traffic_record(str(record), "w", False) is None
