@@ -40,8 +40,8 @@
 //    it and no look at the scores at all: exp2 of a score 100 log2 units above that maximum is
 //    still an ordinary binary32 / bf16 number, and numerator and denominator of the final
 //    division carry the same power of two.  Only if a row sum or an accumulator comes out
-//    non-finite (a score about 2^7 log2 units above the first round's) does the workgroup run
-//    the segment again, this time raising the maximum lazily: when some score exceeds it by
+//    non-finite (a score about 2^7 log2 units above the first round's), or a row sum vanishes (nothing but -inf
+//    in the first round), does the workgroup run the segment again, this time raising the maximum lazily: when some score exceeds it by
 //    more than kRescaleThreshold, in a rarely taken, wave-uniform branch that rescales the
 //    output accumulators.
 //  * The score product of round r+1, the softmax of round r and the PV product of round
@@ -256,23 +256,29 @@ __device__ __forceinline__ void settle_acc(f32x4 (&acc)[D / 16][QB], f32x4 (&l_a
 // exceeds kRescaleThreshold, raise the maximum by delta and rescale what was accumulated
 // under the old one: these scores, the output accumulators, the row sums, and the
 // probabilities p_pending that have been computed but not yet multiplied into either.
+// A query that has seen nothing but scores of -inf has no maximum yet, which neg_m = -0 says (no_maximum): the first
+// score above -inf sets it, wherever that lies, and nothing has been accumulated that would have to be rescaled.
+constexpr uint32_t kNoMaximum = 0x80000000u;                                   // -0; 0 - m and x - x are never that
+__device__ __forceinline__ bool no_maximum(const f32x4 &neg_m) { return __float_as_uint(neg_m[0]) == kNoMaximum; }
 template <int D, int QB>
 __device__ __forceinline__ void raise_maximum(const float (&lane_max)[QB], f32x4 (&s)[2][QB], f32x4 (&neg_m)[QB],
                                               bf16x8 (&p_pending)[QB], f32x4 (&acc)[D / 16][QB], f32x4 (&l_acc)[QB]) {
     bool raise = false;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) raise = raise || (lane_max[qb] > kRescaleThreshold);
+    for (int qb = 0; qb < QB; ++qb) raise = raise || (lane_max[qb] > (no_maximum(neg_m[qb]) ? -INFINITY : kRescaleThreshold));
     if (__builtin_expect(__any(raise) != 0, 0)) {     // the branch body is laid out away from the loop
         settle_acc<D, QB>(acc, l_acc, false);
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            const float delta = fmaxf(quad_max(lane_max[qb]), 0.0f);           // the maximum never goes down
-            const float alpha = __builtin_amdgcn_exp2f(-delta);
+            const float top = quad_max(lane_max[qb]);
+            const bool none = no_maximum(neg_m[qb]), sets = none && top != -INFINITY;
+            const float delta = sets ? top : none ? 0.0f : fmaxf(top, 0.0f);   // a maximum never goes down
+            const float alpha = none ? 0.0f : __builtin_amdgcn_exp2f(-delta);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 s[0][qb][i] -= delta;
                 s[1][qb][i] -= delta;
-                neg_m[qb][i] -= delta;
+                neg_m[qb][i] = sets ? 0.0f - top : neg_m[qb][i] - delta;
                 l_acc[qb][i] *= alpha;
             }
 #pragma unroll
@@ -722,7 +728,7 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
         // score is above that, and as long as nothing overflows binary32 / bf16 (2^127) the result
         // is the same sum of the same terms, only scaled by another power of two on both sides of
         // the final division.  If a row sum or an accumulator does come out non-finite -- some
-        // score exceeded the first round's maximum by about 2^7 in log2 units -- the workgroup
+        // score exceeded the first round's maximum by about 2^7 in log2 units -- or a row sum as good as 0, the workgroup
         // runs the segment again with the check (CHECK = true), which raises the maximum as it goes.
         auto run_segment = [&](auto checked_c) {
         constexpr bool CHECK = decltype(checked_c)::value;
@@ -783,11 +789,13 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
 #pragma unroll
             for (int e = 1; e < 8; ++e) tmax = fmaxf(tmax, s_a[e / 4][qb][e % 4]);
             tmax = quad_max(tmax);
+            // a round of nothing but -inf: scores are taken as they are, see no_maximum
+            const float neg = tmax == -INFINITY ? __uint_as_float(kNoMaximum) : 0.0f - tmax;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                w.neg_m[qb][e] = -tmax;
-                s_a[0][qb][e] -= tmax;
-                s_a[1][qb][e] -= tmax;
+                w.neg_m[qb][e] = neg;
+                s_a[0][qb][e] += neg;
+                s_a[1][qb][e] += neg;
             }
             s_b[0][qb] = s_a[0][qb];
             s_b[1][qb] = s_a[1][qb];
@@ -834,11 +842,16 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
         {
             // anything in this lane's row sums or accumulators that is not finite, or within 2^7 of
             // not being so (partial rows are stored as bf16)?  As integers, the largest positive and the largest negative
-            // magnitude (an infinity and any NaN lie above every number): half an instruction each per register
+            // magnitude (an infinity and any NaN lie above every number): half an instruction each per register.
+            // And a row sum far below 1, which the key of the maximum alone adds: no score of the first round was above -inf, and
+            // those that followed lie too far below 0, what they were taken relative to.
             settle_acc<D, QB>(w.acc, w.l_acc, false);
             constexpr uint32_t kTooLarge = (127 + 121) << 23;          // 2^121
             int32_t pos = 0;
             uint32_t neg = 0;
+            int32_t smallest = kTooLarge;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) smallest = min(smallest, int32_t(__float_as_uint(w.l_acc[qb][0])));
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -851,9 +864,10 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
                         neg = max(max(y0, y1), neg);
                     }
                 }
-            const bool too_large = pos >= int32_t(kTooLarge) || neg >= (0x80000000u | kTooLarge);
+            constexpr int32_t kTooSmall = (127 - 60) << 23;            // 2^-60
+            const bool out_of_range = pos >= int32_t(kTooLarge) || neg >= (0x80000000u | kTooLarge) || smallest < kTooSmall;
             // the barrier also makes sure that every wave has left the segment's tiles
-            if (__syncthreads_or(too_large)) {
+            if (__syncthreads_or(out_of_range)) {
                 start_tiles<D>(lds0, a, seg, c, n, stride_tok);
                 run_segment(std::true_type{});
             }
@@ -885,7 +899,7 @@ __device__ __forceinline__ void run_units(uint32_t lds0, const AttnParams &a, La
             } else {
                 float *slot = a.ws + (size_t(2) * sharer + (first_segment ? 0 : 1)) * slot_floats<D>();
                 if (quad == 0) {
-                    slot[row0 + col] = -w.neg_m[qb][0];
+                    slot[row0 + col] = l_tot == 0.0f ? -INFINITY : -w.neg_m[qb][0];        // 0: every key of this part at -inf
                     slot[kBM + row0 + col] = l_tot;
                 }
                 store_rows<D, QB>(out_lds, w.acc, qb, 1.0f, reinterpret_cast<__bf16 *>(slot + 2 * kBM) + row0 * D, D, 16, lane);

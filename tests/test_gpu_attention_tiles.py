@@ -102,3 +102,30 @@ def test_tiles_on_strided_layouts(layout, n, rows, last, hd):
         g.assert_attention_close(got[b][picked], orc.attention(q, k, v, rows=picked), "%s item %d hd=%d" % (layout, b, hd))
     out[where] = np.nan
     assert np.all(np.isnan(out)), "wrote outside its rows"
+
+
+def dead_keys(n, heads, hd, dead, far, seed):
+    """q, k, v whose keys dead[0] .. dead[1] - 1 have score -inf; the scores of the first `far` of them all lie 4096 hd^-1/2 / ln 2 (522 or
+    738) log2 units lower."""
+    q, k, v = synth.qkv_bf16(seed, n, heads, hd)
+    q[:, :, 3:5] = 0x3f80                                # 1.0
+    k[dead[0]:dead[1], :, 3] = 0xff80                    # -inf
+    k[:far, :, 4] = 0xc580                               # -4096
+    return q, k, v
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("far", [0, 0.7, 1], ids=["scores near 0", "far below, then near 0", "scores far below"])
+@pytest.mark.parametrize("n,heads,rows,last,cut,dead", [
+    (1000, 24, 128, 0, False, (0, 32)), (1000, 24, 128, 0, False, (0, 999)), (700, 40, 128, 0, False, (5, 640)), (1001, 40, 192, 0, False, (0, 500)),
+    (1500, 40, 256, 0, False, (0, 64)), (1500, 40, 256, 0, False, (64, 1000)), (2500, 40, 256, 192, False, (0, 33)), (2500, 40, 256, 192, False, (0, 2499)),
+    (5000, 2, 256, 0, True, (0, 32)), (5000, 2, 256, 0, True, (0, 2600)), (5000, 2, 256, 0, True, (900, 4999)), (2000, 70, 256, 0, True, (0, 1100))])
+def test_tiles_whose_first_keys_have_score_minus_infinity(n, heads, rows, last, cut, dead, far, hd):
+    """Keys whose score is -inf count for nothing, also where they are all of the first round, of a part of a cut tile, or all but one."""
+    from tests import gpu_util as g
+    runs(n, heads, hd, rows, last, cut)
+    q, k, v = dead_keys(n, heads, hd, dead, int(far * n), 6900 + n)
+    got = g.hip_attention(q, k, v)
+    picked = synth.sample_rows(n, 32, seed=3, tile=rows)
+    g.assert_attention_close(got[picked], orc.attention(q, k, v, rows=picked), "n=%d dead %s" % (n, dead))
+    assert np.all(np.isfinite(got))
