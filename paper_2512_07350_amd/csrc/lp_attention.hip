@@ -137,7 +137,9 @@ struct Route {
 Route pick_route(int head_dim, int64_t n, int all_heads, int cus, bool scratch, bool split) {
     Route r;
     r.deal = deal_finer(head_dim, n, all_heads, uint32_t(cus), split, deal_large(head_dim, n, all_heads, uint32_t(cus), scratch));
-    r.short_kernel = lp::attention_short_launchable(n, all_heads) && lp::attention_short_us(n, all_heads, head_dim, cus, split) < r.deal.us;
+    // up to 32 tokens are the short kernel's whatever the prices say: they may lie so far apart that the 64 rows of a tile, most of
+    // them past the end, reach past 2^32 bytes, which attention_kernel's offsets do not hold
+    r.short_kernel = lp::attention_short_launchable(n, all_heads) && (n <= 32 || lp::attention_short_us(n, all_heads, head_dim, cus, split) < r.deal.us);
     r.cut = !r.short_kernel && r.deal.sharers != r.deal.shared;
     return r;
 }

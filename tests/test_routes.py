@@ -19,6 +19,15 @@ def test_attention_never_takes_a_grid_that_cannot_be_launched(n, heads, scratch,
     assert threads <= MAX_THREADS or routes.attention_tiles(n, heads, hd, scratch, CUS).rows > 0
 
 
+@pytest.mark.parametrize("hd", [64, 128])
+def test_calls_of_up_to_32_tokens_stay_with_the_short_kernel(hd):
+    """The one whose offsets hold tokens 2^27 elements apart; its grid can be launched for any number of heads then."""
+    for n in (1, 2, 15, 31, 32):
+        for heads in (1, 40, 5000, 1 << 20, (1 << 24) - 1):
+            for scratch, split, cus in ((True, False, CUS), (False, True, CUS), (True, True, 8), (False, False, 304)):
+                assert routes.attention_tiles(n, heads, hd, scratch, cus, split).rows == 0
+
+
 @pytest.mark.parametrize("head_dim", [0, 64, 128])
 @pytest.mark.parametrize("d_in", [64, 128, 512, 5120])
 def test_gemm_never_takes_a_grid_that_cannot_be_launched(d_in, head_dim):
